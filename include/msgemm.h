@@ -68,6 +68,11 @@ typedef enum {
 
 /* How phase 1 and phase 2 are scheduled on the GPU. */
 typedef enum {
+    /* The library's choice.  With the paper's encoding of 4-bit codes, d = 2, scale blocks of whole runs of 128 columns
+     * (or none) and up to 16 columns, msgemm_run then takes the matrix form: the codes are decoded in registers and the
+     * sum of Section 3.2 is formed by the matrix cores without tabulating its terms first (fp32 sums of exact products,
+     * int32 for int8 X); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
+     * A value map installed later is served by the table kernels below, and so is every other AUTO problem. */
     MSGEMM_VARIANT_AUTO = 0,
     /* Two launches: L is written to device memory once and shared by all rows
      * (the arrangement of Section 4: one L, kept in cache between the phases); any d in 1..4. */
@@ -96,9 +101,10 @@ typedef enum {
      * (msgemm_plan_set_codebook, msgemm_plan_codes8) with a value beyond +-65504
      * are refused on such a plan; values that fp16 cannot hold exactly are rounded
      * to nearest.  Accumulation is fp32.  scale_group % 32 == 0.  Not available
-     * for fp32 X.  AUTO picks it for b > 2 unless the problem is small (columns
-     * times code bytes up to 64 MiB, scale blocks of whole k-tiles): then
-     * FUSED_LDS runs one pass per column, which is faster there. */
+     * for fp32 X.  Among the table kernels AUTO picks it for b > 2 unless the
+     * problem is small (columns times code bytes up to 64 MiB, scale blocks of
+     * whole k-tiles): then FUSED_LDS runs one pass per column, which is faster
+     * there. */
     MSGEMM_VARIANT_FUSED_LDS16 = 3,
     /* GLOBAL_LUT with half of every table (the optimisation sketched in Section
      * 4.1): only the combinations whose last code has its top bit clear are
@@ -122,7 +128,7 @@ typedef struct {
     int tile_rows;       /* rows per workgroup (fused variant), else 0 */
     int tile_groups;     /* table groups of a k-tile (one table in LDS), else 0 */
     int split_k;         /* partial sums reduced per output: k-tiles, or runs of k-tiles (long k, batches; with the
-                            k-tiles of a batched plan dealt evenly: the most any output has) */
+                            k-tiles of a batched plan dealt evenly: the most any output has; matrix form: wavefronts) */
     int col_chunk;       /* batch columns handled per pass over the codes */
     int64_t workspace_bytes; /* device memory the plan owns besides the codes in its kernels' order */
 } msgemm_plan_info_t;
@@ -150,8 +156,11 @@ typedef struct {
     int rows_per_lane;           /* single-column kernel: 16 (default) or 8 (its 16-wavefront form);
                                     batched kernel: 8 (default) or 4 */
     int no_xcd_map;              /* 1: workgroup ids in k-tile-major order instead of grouped per L2 */
-    int batched_form;            /* batched kernel: 0 = library's choice, 1 = build phase per k-tile, 2 = pipelined */
-    int batched_segments;        /* batched kernel: k-segments (partial sums per output); 0 = library's choice */
+    int batched_form;            /* batched kernel: 0 = library's choice, 1 = build phase per k-tile, 2 = pipelined;
+                                    3 with AUTO = the matrix form wherever it can serve the problem (panels_per_workgroup:
+                                    1, 2 or 4 tiles of 16 rows per workgroup; batched_segments).  Any other request in this
+                                    structure that names a form of the table kernels keeps AUTO from the matrix form */
+    int batched_segments;        /* batched kernel, matrix form: k-segments (partial sums per output); 0 = library's choice */
     int global_plain_consumer;   /* two-launch variant: 1 = the one-thread-per-output consumer */
     int global_chunk_kib;        /* two-launch variant: table KiB per chunk; 0 = 1024 */
     int global_segments;         /* two-launch variant: runs of chunks; 0 = library's choice */

@@ -1,0 +1,694 @@
+// The matrix form of msgemm_run: Y = M x X with the codes decoded in registers and the sums done by the matrix cores.
+//
+// The two phases of the method add, for every row, the table entries L(codes, j) = sum_r b(i_r) x(jd + r) that its
+// codes address (Section 3.2, second line of the y(i) equation).  Where the matrix cores are the adders, the entries
+// need not be tabulated first: sum_j sum_r b(i_r) x(jd + r) is the first line of the same equation, and one
+// v_mfma_f32_16x16x32 forms and adds the entries of 16 rows x 16 groups of two codes x 16 columns at once.  Nothing is
+// built per workgroup, so a workgroup can own its rows for all of k: there are no partial sums between workgroups, no
+// second launch and no table start-up, and the kernel is bound by the code stream.  Values, products and sums are those
+// of the full-width tables: the integers -8..7 are exact in fp16 / bf16 / int8, products are exact, sums are fp32
+// (int32 for int8 activations).
+//
+// The plan's rule (matrix_choose_shape) gives this form what the library chooses itself for the paper's encoding at
+// d = 2; tables in LDS remain for every request for a variant, another value map, 8-bit weights and scale blocks that
+// are not whole runs of 128 columns.
+//
+// Layout of the codes: [row group of 16 R rows][run of 128 columns][row tile r < R][lane][16 bytes].  Lane (n, q) =
+// (lane & 15, lane >> 4) holds columns 32 q + 0..31 of row n of its tile, dword w of its 16 bytes the 8 from 8 w on, with
+// the nibbles in the order the decoder yields them; MFMA step t takes dword t of every lane (int8: dwords 2 t, 2 t + 1).
+// One 16-byte load of a wavefront is 1 KiB of consecutive memory and one row tile's share of a run.
+// Scales: [row group][scale block][n][r] fp16, so a lane's scales for its R tiles are one load.
+#include "device_types.h"
+#include "fused_common.h"
+#include "msgemm_internal.h"
+
+#include <type_traits>
+
+namespace msgemm {
+namespace {
+
+constexpr int kRun = 128;          // columns of k per step: one 16-byte load per lane and row tile
+constexpr uint32_t kPastEnd = 0x7fff0000u;  // a buffer offset past any plan's codes: the load returns zero and reads nothing
+constexpr int kAuxNt = 2;          // buffer cache policy bit: non-temporal (every code is used once)
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// 16 bytes at any alignment the element type allows (columns of X may start anywhere)
+template <int kAlign> struct __attribute__((packed, aligned(kAlign))) Any16 { uint32_t a, b, c, d; };
+
+template <int kAlign> __device__ __forceinline__ v4u load_any16(const void* p)
+{
+    const Any16<kAlign> v = *(const Any16<kAlign>*)p;
+    return v4u{v.a, v.b, v.c, v.d};
+}
+template <int kAlign> struct __attribute__((packed, aligned(kAlign))) Any4 { uint32_t a; };
+struct __attribute__((packed, aligned(1))) Any2 { uint16_t a; };
+
+// What differs between the activation types.
+//   kFrags  operand registers (16 bytes) of X per run of 128 columns and tile of 16 columns of X; one MFMA each
+//   kRaw    16-byte loads per run as X is stored
+//   decode  the codes of one MFMA step -> its weight operand
+template <typename XT> struct Policy;
+
+// (x & mask) | bits in one instruction (with two constants the compiler takes two)
+__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t bits)
+{
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(mask), "v"(bits));
+    return r;
+}
+
+template <> struct Policy<__half> {
+    using acc_t = v4f;
+    using out_t = __half;
+    static constexpr int kFrags = 4, kRaw = 4;
+    static __device__ __forceinline__ void decode(const v4u& c, int t, v4u& w)
+    {
+        // offset-binary nibbles: 0x6400 | u is 1024 + u in fp16 (and 1024 + 16 u with the nibble one place up); the
+        // offset is taken off exactly
+        const uint32_t x = c[t], y = x >> 8;
+        const v2h off0 = {(_Float16)-1032.0f, (_Float16)-1032.0f}, off1 = {(_Float16)-72.0f, (_Float16)-72.0f};
+        const v2h sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
+        const v2h a = __builtin_bit_cast(v2h, and_or(x, 0x000f000fu, 0x64006400u)) + off0;
+        const v2h b = __builtin_bit_cast(v2h, and_or(x, 0x00f000f0u, 0x64006400u)) * sixteenth + off1;
+        const v2h d = __builtin_bit_cast(v2h, and_or(y, 0x000f000fu, 0x64006400u)) + off0;
+        const v2h e = __builtin_bit_cast(v2h, and_or(y, 0x00f000f0u, 0x64006400u)) * sixteenth + off1;
+        w = v4u{__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, d),
+                __builtin_bit_cast(uint32_t, e)};
+    }
+    static __device__ __forceinline__ v4f mma(const v4u& x, const v4u& w, const v4f& c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, x), __builtin_bit_cast(v8h, w), c, 0, 0, 0);
+    }
+};
+
+struct Bf16Weights {
+    static __device__ __forceinline__ void decode(const v4u& c, int t, v4u& w)
+    {
+        // two's-complement nibbles: v_cvt_off_f32_i4 gives value / 16 in fp32, whose upper half is its bf16; the factor
+        // is a power of two and is put back with the sums
+        const uint32_t x = c[t], y = x >> 4;
+        const float f0 = __builtin_amdgcn_cvt_off_f32_i4((int)x), f1 = __builtin_amdgcn_cvt_off_f32_i4((int)((x >> 8) & 0xff));
+        const float f2 = __builtin_amdgcn_cvt_off_f32_i4((int)((x >> 16) & 0xff)), f3 = __builtin_amdgcn_cvt_off_f32_i4((int)(x >> 24));
+        const float f4 = __builtin_amdgcn_cvt_off_f32_i4((int)y), f5 = __builtin_amdgcn_cvt_off_f32_i4((int)((y >> 8) & 0xff));
+        const float f6 = __builtin_amdgcn_cvt_off_f32_i4((int)((y >> 16) & 0xff)), f7 = __builtin_amdgcn_cvt_off_f32_i4((int)(y >> 24));
+        w = v4u{__builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u),
+                __builtin_amdgcn_perm(__float_as_uint(f3), __float_as_uint(f2), 0x07060302u),
+                __builtin_amdgcn_perm(__float_as_uint(f5), __float_as_uint(f4), 0x07060302u),
+                __builtin_amdgcn_perm(__float_as_uint(f7), __float_as_uint(f6), 0x07060302u)};
+    }
+    static __device__ __forceinline__ v4f mma(const v4u& x, const v4u& w, const v4f& c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x), __builtin_bit_cast(v8bf, w), c, 0, 0, 0);
+    }
+};
+
+template <> struct Policy<bf16_t> : Bf16Weights {
+    using acc_t = v4f;
+    using out_t = bf16_t;
+    static constexpr int kFrags = 4, kRaw = 4;
+};
+
+// fp32 activations: x = h + m + l in three bf16 pieces of eight bits each (by truncation, exact), three MFMAs per step.
+template <> struct Policy<float> : Bf16Weights {
+    using acc_t = v4f;
+    using out_t = float;
+    static constexpr int kFrags = 4, kRaw = 8;
+};
+
+template <> struct Policy<int8_t> {
+    using acc_t = v4i;
+    using out_t = int;
+    static constexpr int kFrags = 2, kRaw = 2;
+    static __device__ __forceinline__ void decode(const v4u& c, int t, v4u& w)
+    {
+        // two's-complement nibbles in the upper half of a byte are 16 x the value; the sums are shifted back
+        w = v4u{(c[2 * t] << 4) & 0xf0f0f0f0u, c[2 * t] & 0xf0f0f0f0u, (c[2 * t + 1] << 4) & 0xf0f0f0f0u,
+                c[2 * t + 1] & 0xf0f0f0f0u};
+    }
+    static __device__ __forceinline__ v4i mma(const v4u& x, const v4u& w, const v4i& c)
+    {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(v4i, x), __builtin_bit_cast(v4i, w), c, 0, 0, 0);
+    }
+};
+
+// Which nibble of a code dword holds the e-th of its 8 columns, and what is stored there for a two's-complement code.
+enum Encoding { kEncF16, kEncBf16, kEncI8 };
+__host__ __device__ __forceinline__ int nibble_of(int enc, int e)
+{
+    if (enc == kEncF16) return (e >> 1 & 1) | (e >> 2 & 1) << 1 | (e & 1) << 2;  // pairs (0,4) (1,5) (2,6) (3,7)
+    return e < 4 ? 2 * e : 2 * (e - 4) + 1;                                     // low nibbles of the bytes, then high ones
+}
+__host__ __device__ __forceinline__ uint32_t stored_code(int enc, uint32_t code) { return enc == kEncF16 ? code ^ 8u : code; }
+inline int encoding_of(int x_dtype)
+{
+    return x_dtype == MSGEMM_F16 ? kEncF16 : x_dtype == MSGEMM_I8 ? kEncI8 : kEncBf16;
+}
+
+struct MatrixArgs {
+    const uint8_t* codes;
+    const __half* scales;
+    const void* X;
+    int64_t ldx;
+    void* Y;
+    int64_t ldy;
+    int64_t m, k;
+    int b;                 // columns of X
+    int runs;              // ceil(k / 128)
+    int full_runs;         // k / 128
+    int nblocks;           // scale blocks per row
+    FastDiv div_block;     // runs per scale block
+    uint32_t* partials;    // several k-segments: [segment][column][row of m_pad] fp32 / int32, else nullptr
+    int64_t m_pad;
+    int seg_runs;          // full runs per segment
+};
+
+// fp32 activations: four elements as the three bf16 parts x = h + m + l (8 bits each by truncation, exact).  The
+// differences are taken from the element clamped to the finite range: an infinite activation is infinite in its first
+// part and adds finite numbers in the others (as it does in a fp32 product), a NaN stays one.
+template <typename XT> constexpr int kOperands = sizeof(XT) == 4 ? 3 : 1;
+struct Split { v2u part[3]; };
+__device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+__device__ __forceinline__ void split(const v4u& x, Split& s)
+{
+    uint32_t m[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float v = __builtin_amdgcn_fmed3f(__uint_as_float(x[e]), -3.402823466e38f, 3.402823466e38f);
+        const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+        m[e] = __float_as_uint(r);
+        l[e] = __float_as_uint(r - __uint_as_float(m[e] & 0xffff0000u));
+    }
+    s.part[0] = v2u{upper_halves(x[0], x[1]), upper_halves(x[2], x[3])};
+    s.part[1] = v2u{upper_halves(m[0], m[1]), upper_halves(m[2], m[3])};
+    s.part[2] = v2u{upper_halves(l[0], l[1]), upper_halves(l[2], l[3])};
+}
+
+// LDS only: the loads in flight to registers are not waited for
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Streaming kernel.  A workgroup owns 16 R rows for all of k; its W wavefronts take the runs of 128 columns in turn, each
+// with D runs of codes and activations in flight, and add their sums through LDS.  Bound by the code stream.  Wavefronts
+// share nothing until the end, so there is no barrier in the loop; activations come straight from the L2.
+//
+// kCols4 > 0, up to 4 kCols4 columns of X: consecutive lanes load consecutive 16-byte pieces of a column (a lane holding
+// the operand of a column of its own instead would touch 64 cache lines per load, which the L1 takes one by one), and the
+// wavefront passes them through an LDS buffer of its own into operand order: lane (n, q) then has column n.
+// kCols4 == 0, up to four columns (int8: eight): lane n loads column n / T for step n % T of a run only (T steps) -- one
+// load, nothing to transpose -- and every step has accumulators of its own, of which the rows of that step are the ones
+// that count.  They end up in the same lane: y(column q) is the sum over t of register t of accumulator t of lane group q.
+template <typename XT, int R, int kCols4, int W, int D, bool kScaled>
+__global__ void __launch_bounds__(W * 64)
+matrix_stream_kernel(MatrixArgs a)
+{
+    using P = Policy<XT>;
+    using acc_t = typename P::acc_t;
+    using YT = typename P::out_t;
+    constexpr bool kInt = sizeof(XT) == 1;
+    constexpr bool kCompact = kCols4 == 0;
+    constexpr int T = P::kFrags;
+    constexpr int kOps = kOperands<XT>;
+    constexpr int kPiece = 16 / (int)sizeof(XT);       // elements of a 16-byte piece
+    constexpr int kLanesPerCol = kRun / kPiece;        // pieces of a column's run
+    constexpr int kColsPerLoad = 64 / kLanesPerCol;
+    constexpr int kRaw = kCompact ? P::kRaw / T : (4 * kCols4 + kColsPerLoad - 1) / kColsPerLoad;
+    constexpr int kAcc = kCompact ? T : 1;             // accumulators per row tile
+    constexpr int kRows = 16 * R;
+    constexpr int kPitch = kRows + 4;                  // LDS: the four lane groups' columns fall on different banks
+    constexpr int kCols = kCompact ? 16 / T : 4 * kCols4; // columns of X the kernel holds
+    constexpr int kXWords = kCompact ? 0 : kOps * T * 256; // a wavefront's operands of one run
+    constexpr int kRedWords = W * kCols * kPitch;
+    __shared__ __align__(16) uint32_t lds[W * kXWords > kRedWords ? W * kXWords : kRedWords];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, q = lane >> 4;
+    const int rg = blockIdx.x;
+
+    const uint32_t run_bytes = R * 1024u;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.scales + (int64_t)rg * a.nblocks * kRows), 0, kScaled ? (int)(a.nblocks * kRows * 2) : 0, 0x00020000);
+
+    // where this lane's pieces of a run of X start (columns past the last one repeat it: their sums are not used), and
+    // which column of the run the first element is
+    const int first = kCompact ? 32 * q + (n % T) * (kInt ? 16 : 8) : lane % kLanesPerCol * kPiece;
+    const XT* xcol[kCompact ? 1 : kRaw];
+#pragma unroll
+    for (int i = 0; i < (kCompact ? 1 : kRaw); ++i) {
+        int c = kCompact ? n / T : i * kColsPerLoad + lane / kLanesPerCol;
+        c = c < a.b ? c : a.b - 1;
+        xcol[i] = (const XT*)a.X + (int64_t)c * a.ldx + first;
+    }
+
+    struct Stage {
+        v4u codes[R];
+        v4u x[kRaw];
+        uint32_t q[(R + 1) / 2];
+    };
+
+    auto load_codes_of = [&](Stage& st, int run, bool ok) {
+        const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + lane * 16u;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            st.codes[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + r * 1024u), 0, kAuxNt);
+        if constexpr (kScaled) {
+            const uint32_t so = fast_div((uint32_t)(ok ? run : 0), a.div_block) * (uint32_t)(kRows * 2) + n * (uint32_t)(R * 2);
+            if constexpr (R == 4) {
+                const v2u v = __builtin_amdgcn_raw_buffer_load_b64(srsrc, (int)so, 0, 0);
+                st.q[0] = v.x; st.q[1] = v.y;
+            } else if constexpr (R == 2) {
+                st.q[0] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, (int)so, 0, 0);
+            } else {
+                st.q[0] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(srsrc, (int)so, 0, 0);
+            }
+        }
+    };
+    auto piece_of = [&](int i) { return kCompact ? xcol[0] + i * kPiece : xcol[kCompact ? 0 : i]; };
+    auto load_x = [&](Stage& st, int run) {
+#pragma unroll
+        for (int i = 0; i < kRaw; ++i) st.x[i] = load_any16<sizeof(XT)>(piece_of(i) + (int64_t)run * kRun);
+    };
+    // the run that k ends in: elements past k are zero whatever lies behind them (k is even: pairs are whole)
+    auto load_x_tail = [&](Stage& st) {
+        const int64_t k0 = (int64_t)a.full_runs * kRun;
+        const int left = (int)(a.k - k0) - first;
+#pragma unroll
+        for (int i = 0; i < kRaw; ++i)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int e = w * (4 / (int)sizeof(XT)), at = e + (kCompact ? i * kPiece : 0);
+                uint32_t v = 0;
+                if constexpr (kInt) {
+                    const Any2* p = (const Any2*)(piece_of(i) + k0 + e);
+                    if (at < left) v = p[0].a;
+                    if (at + 2 < left) v |= (uint32_t)p[1].a << 16;
+                } else {
+                    if (at < left) v = ((const Any4<sizeof(XT)>*)(piece_of(i) + k0 + e))->a;
+                }
+                st.x[i][w] = v;
+            }
+    };
+
+    // Operand slots of a wavefront: 16 bytes per (operand, step t, lane group q, column), the column rotated by the piece
+    // so that the pieces of a column, written side by side, fall on different banks (and so do the columns of a read).
+    uint32_t* const xs = lds + wave * kXWords;
+    auto slot = [](int op, int t, int qq, int col) { return ((op * T + t) * 64 + qq * 16 + (col ^ (qq * T + t))) * 4; };
+    auto put_x = [&](const Stage& st) {
+        const int j = lane % kLanesPerCol;
+#pragma unroll
+        for (int i = 0; i < kRaw; ++i) {
+            const int col = i * kColsPerLoad + lane / kLanesPerCol;
+            if constexpr (sizeof(XT) == 4) {
+                // half a slot: elements 4 (j & 1) .. + 3 of the 8 of step (j / 2) % 4
+                Split s;
+                split(st.x[i], s);
+#pragma unroll
+                for (int op = 0; op < 3; ++op) *(v2u*)&xs[slot(op, (j >> 1) & 3, j >> 3, col) + 2 * (j & 1)] = s.part[op];
+            } else {
+                *(v4u*)&xs[slot(0, j % T, j / T, col)] = st.x[i];
+            }
+        }
+    };
+
+    // The MFMAs add to the running sums themselves, except where a run's sum is scaled first, and for fp32: there a run's
+    // three products are summed on their own and added once (adding them one by one to the running sum would round it
+    // three times as often).
+    constexpr bool kDirect = !kScaled && sizeof(XT) != 4;
+    acc_t acc[R][kAcc];
+    float sum[R];                                      // (scaled, compact) one column per lane
+    acc_t total[R][kAcc];                              // int8: sums already shifted back
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int v = 0; v < kAcc; ++v) acc[r][v] = total[r][v] = acc_t{0, 0, 0, 0};
+        sum[r] = 0.0f;
+    }
+
+    auto consume = [&](const Stage& st) {
+        acc_t blk[R][kAcc];
+        v4u x[kOps];
+        if constexpr (kCompact && sizeof(XT) == 4) {
+            Split s0, s1;
+            split(st.x[0], s0);
+            split(st.x[kRaw - 1], s1);
+#pragma unroll
+            for (int op = 0; op < kOps; ++op) x[op] = v4u{s0.part[op].x, s0.part[op].y, s1.part[op].x, s1.part[op].y};
+        } else if constexpr (kCompact) {
+            x[0] = st.x[0];
+        } else {
+            put_x(st);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            v4u w[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) P::decode(st.codes[r], t, w[r]);
+#pragma unroll
+            for (int op = kOps - 1; op >= 0; --op) {   // (the smallest part first)
+                if constexpr (!kCompact) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    acc_t& to = kDirect ? acc[r][kCompact ? t : 0] : blk[r][kCompact ? t : 0];
+                    const bool fresh = !kDirect && op == kOps - 1 && (kCompact || t == 0);
+                    to = P::mma(x[op], w[r], fresh ? acc_t{0, 0, 0, 0} : to);
+                }
+            }
+        }
+        if constexpr (!kDirect) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float s = kScaled ? __half2float(__ushort_as_half((uint16_t)(st.q[r / 2] >> (16 * (r & 1))))) : 1.0f;
+                if constexpr (kCompact) {
+                    sum[r] = fmaf(s, (blk[r][0][0] + blk[r][1 % kAcc][1]) + (blk[r][2 % kAcc][2] + blk[r][3 % kAcc][3]), sum[r]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[r][0][i] = fmaf(s, blk[r][0][i], acc[r][0][i]);
+                }
+            }
+        }
+    };
+
+    // Wavefront `wave` takes runs wave, wave + W, ... of the segment's full ones; the ragged one goes to the next in turn,
+    // loaded first and added last.  The loop's loads are never skipped by a branch (a load that some paths leave out makes the
+    // compiler wait for all of them): past the last run the codes come from past the end of the buffer, which reads no
+    // memory, and the activations are those of the first run again.
+    const int run0 = blockIdx.y * a.seg_runs, left_runs = a.full_runs - run0;
+    const int here = left_runs <= 0 ? 0 : left_runs < a.seg_runs ? left_runs : a.seg_runs;
+    const int mine = (here - wave + W - 1) / W;
+    const bool tail = a.runs > a.full_runs && blockIdx.y == gridDim.y - 1 && wave == here % W;
+    Stage tail_stage;
+    if (tail) {
+        load_codes_of(tail_stage, a.full_runs, true);
+        load_x_tail(tail_stage);
+    }
+    auto shift_back = [&] {
+        if constexpr (kInt) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int v = 0; v < kAcc; ++v)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { total[r][v][i] += acc[r][v][i] >> 4; acc[r][v][i] = 0; }
+        }
+    };
+    if (mine > 0) {
+        Stage ring[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int run = run0 + wave + d * W;
+            load_codes_of(ring[d], run, d < mine);
+            load_x(ring[d], d < mine ? run : run0 + wave);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int it = 0;
+        for (; it + D <= mine; it += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                consume(ring[d]);
+                const int next = it + d + D;
+                const int run = run0 + wave + next * W;
+                load_codes_of(ring[d], run, next < mine);
+                load_x(ring[d], next < mine ? run : run0 + wave);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // int8: 16 x the sum of a run stays under 2^21: shift back before 1024 runs can have overflowed
+            if constexpr (kInt) if ((it / D & 63) == 63) shift_back();
+        }
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (it + d < mine) consume(ring[d]);
+    }
+    if (tail) consume(tail_stage);
+    shift_back();
+
+    // the wavefronts' sums, [wavefront][column][row]
+    if constexpr (!kCompact) lds_barrier();            // (every wavefront has left its operands)
+    auto bits = [](auto v) { uint32_t u; __builtin_memcpy(&u, &v, 4); return u; };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint32_t* out = lds + wave * kCols * kPitch + r * 16 + n;
+        if constexpr (kCompact && kInt) {
+            out[(2 * q) * kPitch] = bits(total[r][0][0] + total[r][1 % kAcc][1]);
+            out[(2 * q + 1) * kPitch] = bits(total[r][0][2] + total[r][1 % kAcc][3]);
+        } else if constexpr (kCompact && !kDirect) {
+            out[q * kPitch] = bits(sum[r]);
+        } else if constexpr (kCompact) {
+            out[q * kPitch] = bits((acc[r][0][0] + acc[r][1 % kAcc][1]) + (acc[r][2 % kAcc][2] + acc[r][3 % kAcc][3]));
+        } else if (4 * q < kCols) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[(4 * q + i) * kPitch] = kInt ? bits(total[r][0][i]) : bits(acc[r][0][i]);
+        }
+    }
+    __syncthreads();
+    const int outs = kRows * a.b;
+    for (int o = threadIdx.x; o < outs; o += W * 64) {
+        const int c = o / kRows, row = o % kRows;
+        const int64_t grow = (int64_t)rg * kRows + row;
+        if (grow >= a.m) continue;
+        using S = typename std::conditional<kInt, int, float>::type;
+        S s = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            S v;
+            __builtin_memcpy(&v, &lds[(w * kCols + c) * kPitch + row], 4);
+            s += v;
+        }
+        if (a.partials) {
+            a.partials[((int64_t)blockIdx.y * a.b + c) * a.m_pad + grow] = bits(s);
+            continue;
+        }
+        if constexpr (!kInt && !__is_same(XT, __half)) s *= 16.0f;  // (bf16 weights are value / 16)
+        ((YT*)a.Y)[(int64_t)c * a.ldy + grow] = to_output<YT, S>(s);
+    }
+}
+
+// The segments' sums, in order.
+template <typename XT>
+__global__ void __launch_bounds__(256)
+matrix_reduce_kernel(MatrixArgs a, int segments)
+{
+    using YT = typename Policy<XT>::out_t;
+    using S = typename std::conditional<sizeof(XT) == 1, int, float>::type;
+    const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (row >= a.m) return;
+    const int c = blockIdx.y;
+    S s = 0;
+    for (int seg = 0; seg < segments; ++seg) {
+        S v;
+        __builtin_memcpy(&v, &a.partials[((int64_t)seg * a.b + c) * a.m_pad + row], 4);
+        s += v;
+    }
+    if constexpr (sizeof(XT) != 1 && !__is_same(XT, __half)) s *= 16.0f;
+    ((YT*)a.Y)[(int64_t)c * a.ldy + row] = to_output<YT, S>(s);
+}
+
+// Row-major codes -> the order above (inverse: back again).
+template <bool kInverse>
+__global__ void __launch_bounds__(256)
+matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs, int R,
+                     int enc, int64_t dwords)
+{
+    const int64_t kbytes = k / 2;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
+        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63;
+        const int64_t tile = i >> 8;                       // (row group, run, r)
+        const int r = (int)(tile % R);
+        const int64_t rest = tile / R;
+        const int64_t run = rest % runs, rg = rest / runs;
+        const int64_t row = (rg * R + r) * 16 + (lane & 15);
+        const int64_t byte0 = (run * kRun + 32 * (lane >> 4) + 8 * w) / 2;
+        uint8_t* src = rows + row * kbytes + byte0;
+        uint32_t v = kInverse ? ((const uint32_t*)tiled)[i] : 0;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const bool ok = row < m && byte0 + e / 2 < kbytes;
+            const int p0 = 4 * nibble_of(enc, e), p1 = 4 * nibble_of(enc, e + 1);
+            if constexpr (kInverse) {
+                if (ok) src[e / 2] = (uint8_t)(stored_code(enc, (v >> p0) & 15u) | stored_code(enc, (v >> p1) & 15u) << 4);
+            } else {
+                const uint32_t byte = ok ? src[e / 2] : 0u;
+                v |= stored_code(enc, byte & 15u) << p0 | stored_code(enc, byte >> 4) << p1;
+            }
+        }
+        if constexpr (!kInverse) ((uint32_t*)tiled)[i] = v;
+    }
+}
+
+// scales [m][nblocks] -> [row group][scale block][n][r]; rows past m get zero
+__global__ void __launch_bounds__(256)
+matrix_repack_scales_kernel(const __half* __restrict__ scales, __half* __restrict__ ordered, int64_t m, int64_t nblocks,
+                            int R, int64_t total)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        const int r = (int)(i % R), n = (int)(i / R) & 15;
+        const int64_t rest = i / (16 * R);
+        const int64_t block = rest % nblocks, rg = rest / nblocks;
+        const int64_t row = (rg * R + r) * 16 + n;
+        ordered[i] = row < m ? scales[row * nblocks + block] : __float2half(0.0f);
+    }
+}
+
+template <typename XT, int R, int kCols4, int W, int D>
+int launch_stream(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)p.row_blocks, (unsigned)p.mx_segments), block(W * 64);
+    if (sizeof(XT) != 1 && a.scales)
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, sizeof(XT) != 1>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, false>), grid, block, 0, s, a);
+    MSGEMM_HIP_TRY(hipGetLastError());
+    if (p.mx_segments > 1) {
+        hipLaunchKernelGGL(matrix_reduce_kernel<XT>, dim3((unsigned)((a.m + 255) / 256), (unsigned)a.b), dim3(256), 0, s, a,
+                           p.mx_segments);
+        MSGEMM_HIP_TRY(hipGetLastError());
+    }
+    return MSGEMM_OK;
+}
+
+template <typename XT>
+int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+#define MSGEMM_CASE(RR, CC, WW, DD) \
+    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW) return launch_stream<XT, RR, CC, WW, DD>(p, a, s);
+    MSGEMM_CASE(4, 0, 4, 4)
+    MSGEMM_CASE(2, 0, 4, 4)
+    MSGEMM_CASE(1, 0, 4, 8)
+    MSGEMM_CASE(4, 2, 4, 4)
+    MSGEMM_CASE(2, 2, 4, 4)
+    MSGEMM_CASE(1, 2, 4, 4)
+    MSGEMM_CASE(4, 4, 8, 2)
+    MSGEMM_CASE(2, 4, 4, 4)
+    MSGEMM_CASE(1, 4, 4, 4)
+#undef MSGEMM_CASE
+    return MSGEMM_ERR_UNSUPPORTED;
+}
+
+}  // namespace
+
+// Whether the library's own choice for a plan is the matrix form, and its shape.
+bool matrix_choose_shape(Plan& p, int requested_variant)
+{
+    const msgemm_plan_options_t& o = p.opt;
+    p.matrix = false;
+    if (requested_variant != MSGEMM_VARIANT_AUTO || p.d != 2 || p.codes8) return false;
+    if (p.scale_group % kRun != 0) return false;
+    const bool asked = o.batched_form == 3;
+    // a request for a form of the table kernels keeps them
+    if (!asked && (o.panels_per_workgroup || o.k_tiles_per_workgroup || o.reduce_mode || o.rows_per_lane || o.no_xcd_map ||
+                   o.batched_form == 1 || o.batched_form == 2 || o.batched_segments || o.batched_deal || o.poll_limit || o.skip_publish))
+        return false;
+    const int64_t runs = (p.k + kRun - 1) / kRun;
+    if (p.b > 16) return false;
+    if (runs * 4096 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
+    // One fp32 column: three products per weight where the table kernels add once per pair.
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && p.m * p.k > ((int64_t)32 << 20) && !asked) return false;
+    // A short k under very many rows: a workgroup lives for one or two loads per wavefront, and the table kernels' larger
+    // workgroups go through such a matrix faster (300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; at 100000
+    // rows and 512 columns the matrix form is ahead, 17.2 against 20.5 with eight columns of X).
+    if (p.k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
+
+    // Row tiles per wavefront: the work of the busiest compute unit in row tiles, weighted by what a row tile costs -- the
+    // fewer tiles share a load of activations, the more of it each carries (measured with 1, 4 / 8 and 16 columns).
+    const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
+    const auto groups = [&](int tiles) { return (p.m + 16 * tiles - 1) / (16 * tiles); };
+    const double cost[3][3] = {{1.25, 1.0, 1.03}, {1.2, 1.0, 1.0}, {1.55, 1.2, 1.0}};
+    const int width = compact ? 0 : p.b <= 8 ? 1 : 2;
+    double best = 0;
+    int R = 1;
+    for (int i = 0; i < 3; ++i) {
+        const int r = 1 << i;
+        const double c = (double)((groups(r) + p.cus - 1) / p.cus) * r * cost[width][i];
+        if (i == 0 || c < best) { best = c; R = r; }
+    }
+    if (asked && (o.panels_per_workgroup == 1 || o.panels_per_workgroup == 2 || o.panels_per_workgroup == 4)) R = o.panels_per_workgroup;
+    const int W = width == 2 && R == 4 ? 8 : 4;
+    // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a
+    // wavefront keeps 16 runs.
+    int64_t segments = 1;
+    while (groups(R) * segments * 2 <= p.cus && runs >= 2 * segments * W * 16) segments *= 2;
+    if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
+    p.mx_r = R;
+    p.mx_waves = W;
+    p.mx_segments = (int)segments;
+    p.mx_cols = 2 * width;
+    p.matrix = true;
+    p.row_blocks = groups(R);
+    p.m_pad = p.row_blocks * 16 * R;
+    p.ktiles = runs;
+    p.fs.groups = kRun / 2;
+    p.fs.cols = 1;
+    p.fs.entry_bytes = 4;
+    p.fs.tile_rows = 16 * R;
+    const int64_t sums = (int64_t)W * segments;
+    p.segments = (int)(runs < sums ? runs : sums);  // partial sums per output: one per wavefront with a run
+    p.partial_bytes = segments > 1 ? (size_t)segments * (size_t)p.b * (size_t)p.m_pad * 4u : 0;
+    return true;
+}
+
+size_t matrix_scale_bytes(const Plan& p) { return (size_t)p.nblocks * (size_t)p.m_pad * 2u; }
+
+static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStream_t s)
+{
+    const int64_t dwords = p.ktiles * p.m_pad * 16;
+    int64_t blocks = (dwords + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    const int enc = encoding_of(p.x_dtype);
+    if (inverse)
+        hipLaunchKernelGGL((matrix_repack_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
+                           p.m, p.k, p.ktiles, p.mx_r, enc, dwords);
+    else
+        hipLaunchKernelGGL((matrix_repack_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
+                           p.m, p.k, p.ktiles, p.mx_r, enc, dwords);
+    MSGEMM_HIP_TRY(hipGetLastError());
+    return MSGEMM_OK;
+}
+
+size_t matrix_code_bytes(const Plan& p) { return (size_t)p.ktiles * (size_t)p.m_pad * 64u; }
+
+int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
+{
+    if (p.scales) {
+        const int64_t total = (int64_t)(matrix_scale_bytes(p) / 2);
+        int64_t blocks = (total + 255) / 256;
+        if (blocks > 65536) blocks = 65536;
+        hipLaunchKernelGGL(matrix_repack_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const __half*)p.scales,
+                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, total);
+        MSGEMM_HIP_TRY(hipGetLastError());
+    }
+    return matrix_repack(p, (uint8_t*)W_codes, false, s);  // (read only in this direction)
+}
+
+int matrix_unpack(const Plan& p, uint8_t* row_major, hipStream_t s) { return matrix_repack(p, row_major, true, s); }
+
+int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ldy, hipStream_t s)
+{
+    MatrixArgs a;
+    a.codes = p.codes_tiled;
+    a.scales = (const __half*)p.scales_ordered;
+    a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
+    a.m = p.m; a.k = p.k; a.b = (int)p.b;
+    a.runs = (int)p.ktiles;
+    a.full_runs = (int)(p.k / kRun);
+    a.nblocks = (int)p.nblocks;
+    a.partials = p.mx_segments > 1 ? (uint32_t*)p.partials : nullptr;
+    a.m_pad = p.m_pad;
+    a.seg_runs = (a.full_runs + p.mx_segments - 1) / p.mx_segments;
+    a.div_block = make_fastdiv(p.scale_group > 0 ? (uint32_t)(p.scale_group / kRun) : 1u);
+    switch (p.x_dtype) {
+    case MSGEMM_F16: return launch_for_type<__half>(p, a, s);
+    case MSGEMM_BF16: return launch_for_type<bf16_t>(p, a, s);
+    case MSGEMM_F32: return launch_for_type<float>(p, a, s);
+    case MSGEMM_I8: return launch_for_type<int8_t>(p, a, s);
+    default: return MSGEMM_ERR_UNSUPPORTED;
+    }
+}
+
+}  // namespace msgemm

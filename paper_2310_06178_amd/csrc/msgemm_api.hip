@@ -33,6 +33,8 @@ void free_plan(Plan* p)
     if (p->partials) (void)hipFree(p->partials);
     if (p->flags) (void)hipFree(p->flags);
     if (p->epochs) (void)hipFree(p->epochs);
+    if (p->ready) (void)hipEventDestroy(p->ready);
+    free_plan(p->tables);
     delete p;
 }
 
@@ -59,7 +61,9 @@ static int ensure_row_major(const Plan& cp, hipStream_t s)
     uint8_t* buf = nullptr;
     hipError_t e = hipMalloc((void**)&buf, code_bytes);
     if (e != hipSuccess) { msgemm::set_hip_error(e); return MSGEMM_ERR_ALLOC; }
-    const int rc = p.d3 ? msgemm::launch_repack3(p, buf, true, s) : msgemm::launch_unpack(p, buf, s);
+    const int rc = p.d3       ? msgemm::launch_repack3(p, buf, true, s)
+                   : p.matrix ? msgemm::matrix_unpack(p, buf, s)
+                              : msgemm::launch_unpack(p, buf, s);
     if (rc != MSGEMM_OK) { (void)hipFree(buf); return rc; }
     p.codes = buf;
     p.workspace_bytes += code_bytes;
@@ -69,9 +73,10 @@ static int ensure_row_major(const Plan& cp, hipStream_t s)
 // values256 != nullptr: 8-bit weights.  k and scale_group then count two per code
 // byte (the kernels see a code byte as the pair of 4-bit codes it would be for
 // int4 weights; only the table build knows better), d is 2, the variant FUSED_LDS.
+// tables_only: never the matrix form.
 static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x_dtype, int y_dtype, int d,
                      int scale_group, const void* W_codes, const void* scales, int variant, void* stream,
-                     const float* values256, const msgemm_plan_options_t* options)
+                     const float* values256, const msgemm_plan_options_t* options, bool tables_only = false)
 {
     if (!out) return MSGEMM_ERR_INVALID_ARG;
     *out = nullptr;
@@ -120,7 +125,11 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
 
     // variant
     p->variant = MSGEMM_VARIANT_GLOBAL_LUT;
-    if (variant != MSGEMM_VARIANT_GLOBAL_LUT) {
+    p->cus = 256;
+    (void)hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
+    if (!tables_only && msgemm::matrix_choose_shape(*p, variant)) {
+        p->variant = MSGEMM_VARIANT_FUSED_LDS;
+    } else if (variant != MSGEMM_VARIANT_GLOBAL_LUT) {
         rc = msgemm::fused_choose_shape(*p, variant);
         if (rc == MSGEMM_OK) {
             p->variant = p->fs.entry_bytes == 2 ? MSGEMM_VARIANT_FUSED_LDS16 : MSGEMM_VARIANT_FUSED_LDS;
@@ -175,6 +184,28 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
         p->workspace_bytes = p->lut_ws_bytes;
         rc = msgemm::global_plan_setup(*p, s);
         if (rc != MSGEMM_OK) return fail(rc);
+    } else if (p->matrix) {
+        // the codes and scales in its own order; partial sums only where a few rows' k is cut into segments
+        const size_t tiled = msgemm::matrix_code_bytes(*p);
+        e = hipMalloc((void**)&p->codes_tiled, tiled);
+        if (e != hipSuccess) { msgemm::set_hip_error(e); return fail(MSGEMM_ERR_ALLOC); }
+        p->workspace_bytes = tiled + p->partial_bytes;
+        if (p->partial_bytes) {
+            e = hipMalloc((void**)&p->partials, p->partial_bytes);
+            if (e != hipSuccess) { msgemm::set_hip_error(e); return fail(MSGEMM_ERR_ALLOC); }
+        }
+        if (p->scales) {
+            const size_t so = msgemm::matrix_scale_bytes(*p);
+            e = hipMalloc((void**)&p->scales_ordered, so);
+            if (e != hipSuccess) { msgemm::set_hip_error(e); return fail(MSGEMM_ERR_ALLOC); }
+            p->workspace_bytes += so;
+        }
+        rc = msgemm::matrix_repack(*p, W_codes, s);
+        if (rc != MSGEMM_OK) return fail(rc);
+        e = hipEventCreateWithFlags(&p->ready, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e);
+        e = hipEventRecord(p->ready, s);
+        if (e != hipSuccess) return hip_fail(e);
     } else if (p->d3) {
         // depth-3 tables in LDS: the rotated code runs and one partial sum per (segment, column, row)
         const size_t tiled = (size_t)p->ktiles * (size_t)(p->fs.groups / 8) * (size_t)p->m_pad * 12u;
@@ -247,6 +278,42 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     return MSGEMM_OK;
 }
 
+// The plan that serves a matrix-form plan's calls while another value map is installed: the same problem with its
+// tables in LDS (full-width entries hold any value), made from the repacked codes on the null stream.  The matrix form's
+// buffers stay: launches already enqueued or captured keep the old map.
+static int ensure_tables(Plan& p)
+{
+    if (p.tables) return MSGEMM_OK;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream of the program may be capturing)
+    MSGEMM_HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+    // (no stream of its own: with a second queue the device no longer deals workgroup ids over its XCDs from the first
+    // one on, which the XCD-local reduction of other plans relies on)
+    hipStream_t s = nullptr;
+    uint8_t* rows = nullptr;
+    msgemm_plan_t* made = nullptr;
+    int rc = MSGEMM_ERR_HIP;
+    hipError_t e = hipStreamWaitEvent(s, p.ready, 0);
+    if (e == hipSuccess) {
+        e = hipMalloc((void**)&rows, (size_t)p.m * (size_t)(p.k / 2));
+        rc = e == hipSuccess ? msgemm::matrix_unpack(p, rows, s) : MSGEMM_ERR_ALLOC;
+        if (rc == MSGEMM_OK)
+            rc = plan_impl(&made, p.m, p.k, p.b, p.x_dtype, p.y_dtype, p.d, p.scale_group, rows, p.scales,
+                           MSGEMM_VARIANT_AUTO, s, nullptr, nullptr, true);
+        const hipError_t es = hipStreamSynchronize(s);
+        if (rc == MSGEMM_OK && es != hipSuccess) { e = es; rc = MSGEMM_ERR_HIP; }
+    }
+    if (e != hipSuccess) msgemm::set_hip_error(e);
+    if (rows) (void)hipFree(rows);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (rc != MSGEMM_OK) {
+        msgemm::free_plan(reinterpret_cast<Plan*>(made));
+        return rc;
+    }
+    p.tables = reinterpret_cast<Plan*>(made);
+    p.workspace_bytes += p.tables->workspace_bytes;
+    return MSGEMM_OK;
+}
+
 extern "C" {
 
 int msgemm_plan(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x_dtype, int y_dtype, int d,
@@ -303,6 +370,11 @@ int msgemm_plan_set_codebook(msgemm_plan_t* plan, const float* values16)
     if (p.variant == MSGEMM_VARIANT_FUSED_LDS16)
         for (int i = 0; i < 16; ++i)
             if (v[i] > 65504.0f || v[i] < -65504.0f) return MSGEMM_ERR_UNSUPPORTED;
+    if (p.matrix && values16) {
+        int rc = ensure_tables(p);
+        if (rc == MSGEMM_OK) rc = msgemm_plan_set_codebook(reinterpret_cast<msgemm_plan_t*>(p.tables), values16);
+        if (rc != MSGEMM_OK) return rc;
+    }
     for (int i = 0; i < 16; ++i) p.values[i] = v[i];  // travels in the arguments of every later launch
     p.custom_values = values16 != nullptr;
     return MSGEMM_OK;
@@ -357,6 +429,8 @@ int msgemm_run(const msgemm_plan_t* plan, const void* X, int64_t ldx, void* Y, i
     const Plan& p = *reinterpret_cast<const Plan*>(plan);
     if (ldx < (p.codes8 ? p.k / 2 : p.k) || ldy < p.m) return MSGEMM_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
+    if (p.matrix && !p.custom_values) return msgemm::launch_matrix(p, X, ldx, Y, ldy, s);
+    if (p.matrix) return msgemm_run(reinterpret_cast<const msgemm_plan_t*>(p.tables), X, ldx, Y, ldy, stream);
     if (p.variant != MSGEMM_VARIANT_GLOBAL_LUT) return msgemm::launch_fused(p, X, ldx, Y, ldy, s);
     int rc = msgemm::launch_build_lut(p, X, ldx, p.lut_ws, s);
     if (rc != MSGEMM_OK) return rc;
@@ -400,6 +474,7 @@ int msgemm_run_static(const msgemm_plan_t* plan, const void* X, int64_t ldx, voi
     int device = -1;
     MSGEMM_HIP_TRY(hipGetDevice(&device));
     if (device != p.device) return MSGEMM_ERR_INVALID_ARG;
+    if (p.matrix && p.custom_values) return msgemm_run_static(reinterpret_cast<const msgemm_plan_t*>(p.tables), X, ldx, Y, ldy, stream);
     // the partial sums over the k-tiles (or k-segments) are the only memory the fused kernels need besides the
     // plan's weights, X and Y when those sums are added by a second launch: no flag, count or table outlives a call
     if (p.partial_bytes > kScratchBytes) return MSGEMM_ERR_UNSUPPORTED;
@@ -411,6 +486,7 @@ int msgemm_run_static(const msgemm_plan_t* plan, const void* X, int64_t ldx, voi
     q.flags = nullptr;
     q.epochs = nullptr;
     q.error_word = nullptr;
+    if (p.matrix) return msgemm::launch_matrix(q, X, ldx, Y, ldy, (hipStream_t)stream);
     return msgemm::launch_fused(q, X, ldx, Y, ldy, (hipStream_t)stream);
 }
 
@@ -418,6 +494,7 @@ int msgemm_plan_check(const msgemm_plan_t* plan, void* stream)
 {
     if (!plan) return MSGEMM_ERR_INVALID_ARG;
     const Plan& p = *reinterpret_cast<const Plan*>(plan);
+    if (p.tables) return msgemm_plan_check(reinterpret_cast<const msgemm_plan_t*>(p.tables), stream);
     if (!p.flags) return MSGEMM_OK;  // no in-launch reduction in this plan's variant
     hipStream_t s = (hipStream_t)stream;
     unsigned err = 0;

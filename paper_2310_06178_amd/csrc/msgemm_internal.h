@@ -82,6 +82,14 @@ struct Plan {
     bool d3;              // depth-3 tables in LDS (kernels_depth3.hip): codes_tiled holds its rotated 96-bit runs
     bool d3_half;         // ... with half tables (Section 4.1)
     int d3_sub;           // ... sub-panels of 64 rows per wavefront
+    // matrix form (kernels_matrix.hip): codes_tiled and scales_ordered hold its own orders
+    bool matrix;
+    int mx_r;             // row tiles of 16 per wavefront
+    int mx_waves;         // wavefronts per workgroup
+    int mx_cols;          // columns of X held, in fours (0: the compact form)
+    int mx_segments;      // k-segments (workgroups along k), added by a second launch if more than one
+    Plan* tables;         // the same problem with tables in LDS, made when another value map is installed; or nullptr
+    hipEvent_t ready;     // recorded behind the repack (matrix form): `tables` is made from the repacked codes
     int wide_tables;      // single-column kernel, wide form: tables a workgroup holds (1 or 2); 0 = another form
     size_t workspace_bytes;
 };
@@ -127,6 +135,14 @@ int batched_phase_form_panels(int64_t panels, int64_t ktiles, int64_t scale_grou
 int launch_repack_scales_batched(const Plan& p, hipStream_t s);
 bool xcd_round_robin(int device, hipStream_t s);
 int launch_batched(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ldy, hipStream_t s);
+
+// kernels_matrix.hip (codes decoded in registers, sums on the matrix cores: the library's own choice where it applies)
+bool matrix_choose_shape(Plan& p, int requested_variant);  // fills the mx_* fields, row_blocks, m_pad, ...; false if not applicable
+size_t matrix_code_bytes(const Plan& p);
+size_t matrix_scale_bytes(const Plan& p);
+int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s);
+int matrix_unpack(const Plan& p, uint8_t* row_major, hipStream_t s);
+int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ldy, hipStream_t s);
 
 // calibration.hip
 int launch_calib_stream_read(const void* src, size_t bytes, void* sink, hipStream_t s);

@@ -1,0 +1,113 @@
+"""The matrix form of msgemm_run (codes decoded in registers, sums on the matrix cores), against the CPU oracle at the
+sizes where its kernels can go wrong: edges of the 16-row tiles and of the 128-column runs, ragged last runs of a few
+columns, every operand width (compact, 8 and 16 columns), k cut into segments, unaligned activations, infinities."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2310_06178_amd import binding as B
+from paper_2310_06178_amd import inputs, torch_io
+from test_gpu_parity import NONUNIFORM, Y_OF_X, check, elem_bound, oracle_y, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # m, k, b, xd, sg, options
+    (1, 2, 1, "f32", 0, {}),
+    (17, 126, 3, "f16", 0, {}),                 # no full run at all
+    (15, 128, 4, "bf16", 128, {}),
+    (65, 130, 2, "i8", 0, {}),
+    (33, 258, 5, "f16", 0, {}),                 # a ragged run of two columns
+    (64, 1152, 8, "bf16", 128, {}),             # nine runs over four wavefronts
+    (129, 642, 9, "i8", 0, {}),
+    (200, 1410, 16, "f32", 0, {}),
+    (47, 384, 12, "f32", 384, {}),              # one scale per row
+    (100, 2304, 1, "f32", 256, {}),
+    (77, 5000, 7, "f32", 0, {}),
+    (513, 4096, 16, "bf16", 256, {}),
+    (300, 4098, 11, "f16", 0, {}),
+] + [(m, k, b, xd, sg, {"panels_per_workgroup": r}) for r in (1, 2, 4) for m, k, b, xd, sg in [
+    (131, 1666, 1, "f16", 0), (131, 1666, 8, "i8", 0), (131, 1666, 16, "i8", 0), (260, 1280, 6, "bf16", 128),
+    (260, 1280, 4, "f32", 128), (100, 900, 14, "f16", 0)]
+] + [(m, k, b, xd, sg, {"batched_segments": s}) for s in (2, 7) for m, k, b, xd, sg in [
+    (131, 1154, 3, "f16", 0), (131, 1154, 16, "i8", 0), (70, 2560, 9, "bf16", 128), (70, 2050, 2, "f32", 0)]]
+
+
+@pytest.mark.parametrize("m,k,b,xd,sg,options", CASES)
+def test_matrix_form_against_oracle(m, k, b, xd, sg, options):
+    codes = inputs.make_codes(m, k, seed=m + 3 * k + b)
+    X = inputs.make_x(k, b, xd, seed=k + b)
+    scales = inputs.make_scales(m, k, sg, seed=6) if sg else None
+    out, info = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO, ldx_pad=3, ldy_pad=5,
+                        options=dict(options, batched_form=3))
+    assert info["variant"] == B.VARIANT_FUSED_LDS and info["tile_groups"] == 64
+    # full-width arithmetic: exact weights and products, fp32 sums
+    check(out, oracle_y(codes, X, xd, scales, sg), xd, f"matrix form {options}", elem_bound(codes, X, xd, scales, sg))
+
+
+def test_matrix_form_int8_sums_outgrow_the_shifted_accumulators():
+    """The int8 kernel adds 16 x the products: over 2^31 / (16 * 1024) columns of the largest products it must have
+    shifted back in between.  One segment of k = 300000 under one row tile, every sum at its largest."""
+    m, k, b = 5, 300000, 2
+    codes = np.full((m, k // 2), 0x88, dtype=np.uint8)
+    X = np.full((b, k), -128, dtype=np.int8)
+    X[1] = 127
+    out, _ = run_gpu(codes, X, "i8", None, 0, 2, B.VARIANT_AUTO, options={"batched_form": 3, "batched_segments": 1})
+    assert np.all(out[0] == 1024 * k) and np.all(out[1] == -8 * 127 * k)
+
+
+@pytest.mark.parametrize("xd", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("b", [1, 6, 13])
+def test_matrix_form_infinite_activations(xd, b):
+    """0 x inf is NaN and every other code gives an infinity of its sign, in the column that holds the infinity only."""
+    m, k = 64, 512
+    codes = inputs.make_codes(m, k, seed=4)
+    X = inputs.make_x(k, b, "f32", seed=5)
+    X[b - 1, 77] = np.inf
+    Xh = {"f32": X, "f16": X.astype(np.float16), "bf16": inputs.f32_to_bf16_bits(X)}[xd]
+    out, _ = run_gpu(codes, Xh, xd, None, 0, 2, B.VARIANT_AUTO, options={"batched_form": 3})
+    y = torch_io.to_f64(out)
+    v = np.array([oracle.decode(int(c)) for c in codes[:, 77 // 2] >> 4], dtype=np.float64)
+    assert np.all(np.isnan(y[b - 1][v == 0])) and np.all(y[b - 1][v != 0] == np.inf * v[v != 0])
+    assert np.all(np.isfinite(y[: b - 1]))
+
+
+@pytest.mark.parametrize("xd,b,sg", [("f16", 1, 128), ("bf16", 5, 0), ("f32", 2, 0), ("i8", 16, 0)])
+def test_other_entry_points_on_a_matrix_form_plan(xd, b, sg):
+    """The library's own choice for this problem is the matrix form: phase 2 alone, the entry point that allocates
+    nothing and another value map (served by the table kernels until the paper's map is restored) work on its plan."""
+    m, k, yd = 300, 1154 if not sg else 1152, Y_OF_X[xd]
+    codes = inputs.make_codes(m, k, seed=1)
+    X = inputs.make_x(k, b, xd, seed=2)
+    scales = inputs.make_scales(m, k, sg, seed=3) if sg else None
+    ref, bound = oracle_y(codes, X, xd, scales, sg), elem_bound(codes, X, xd, scales, sg)
+    dX = torch_io.to_device(X, xd)
+    plan = B.msgemm_plan(m, k, b, xd, yd, 2, sg, torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"))
+    try:
+        def run(call):
+            Y = torch_io.empty_output(b, m, yd)
+            Y.fill_(-3)
+            call(Y)
+            torch.cuda.synchronize()
+            return torch_io.to_host(Y)
+
+        assert B.msgemm_plan_get_info(plan)["tile_groups"] == 64
+        first = run(lambda Y: B.msgemm_run(plan, dX, k, Y, m))
+        check(first, ref, xd, "matrix form", bound)
+        assert np.array_equal(run(lambda Y: B.msgemm_run_static(plan, dX, k, Y, m)), first)
+        L = torch.empty(B.msgemm_lut_bytes(plan) // 4, dtype=torch.int32, device="cuda:0")
+        B.msgemm_build_lut(plan, dX, k, L)
+        check(run(lambda Y: B.msgemm_consume_lut(plan, L, Y, m)), ref, xd, "two phases", bound)
+        if xd != "i8":
+            B.msgemm_plan_set_codebook(plan, NONUNIFORM)
+            want = oracle.gemm_f64(codes, oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64), scales, sg,
+                                   codebook=NONUNIFORM)
+            cb = elem_bound(codes, X, xd, scales, sg, table16=True, codebook=NONUNIFORM)
+            check(run(lambda Y: B.msgemm_run(plan, dX, k, Y, m)), want, xd, "value map", cb)
+            check(run(lambda Y: B.msgemm_run_static(plan, dX, k, Y, m)), want, xd, "value map, static", cb)
+            B.msgemm_plan_set_codebook(plan, None)
+            assert np.array_equal(run(lambda Y: B.msgemm_run(plan, dX, k, Y, m)), first)
+        assert B.msgemm_plan_check(plan) == B.OK
+    finally:
+        B.msgemm_destroy(plan)
