@@ -69,7 +69,7 @@ typedef enum {
 /* How phase 1 and phase 2 are scheduled on the GPU. */
 typedef enum {
     /* The library's choice.  With the paper's encoding of 4-bit codes, d = 2, scale blocks of whole runs of 128 columns
-     * (or none) and up to 16 columns, msgemm_run then takes the matrix form: the codes are decoded in registers and the
+     * (or none), msgemm_run then takes the matrix form: the codes are decoded in registers and the
      * sum of Section 3.2 is formed by the matrix cores without tabulating its terms first (fp32 sums of exact products,
      * int32 for int8 X); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
      * A value map installed later is served by the table kernels below, and so is every other AUTO problem. */
@@ -157,9 +157,11 @@ typedef struct {
                                     batched kernel: 8 (default) or 4 */
     int no_xcd_map;              /* 1: workgroup ids in k-tile-major order instead of grouped per L2 */
     int batched_form;            /* batched kernel: 0 = library's choice, 1 = build phase per k-tile, 2 = pipelined;
-                                    3 with AUTO = the matrix form wherever it can serve the problem (panels_per_workgroup:
-                                    1, 2 or 4 tiles of 16 rows per workgroup; batched_segments).  Any other request in this
-                                    structure that names a form of the table kernels keeps AUTO from the matrix form */
+                                    3 with AUTO = the matrix form wherever it can serve the problem (then
+                                    panels_per_workgroup = 1, 2 or 4 tiles of 16 rows per wavefront, 3 for the tile kernel;
+                                    rows_per_lane = 4 the tile kernel, 8 the streaming kernel for more than 16 columns;
+                                    batched_segments).  Any other request in this structure that names a form of the table
+                                    kernels keeps AUTO from the matrix form */
     int batched_segments;        /* batched kernel, matrix form: k-segments (partial sums per output); 0 = library's choice */
     int global_plain_consumer;   /* two-launch variant: 1 = the one-thread-per-output consumer */
     int global_chunk_kib;        /* two-launch variant: table KiB per chunk; 0 = 1024 */

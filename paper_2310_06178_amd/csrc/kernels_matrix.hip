@@ -164,7 +164,9 @@ struct MatrixArgs {
     FastDiv div_block;     // runs per scale block
     uint32_t* partials;    // several k-segments: [segment][column][row of m_pad] fp32 / int32, else nullptr
     int64_t m_pad;
-    int seg_runs;          // full runs per segment
+    int seg_runs;          // full runs per segment (tile kernel: runs)
+    int row_groups;
+    int passes;            // passes over the columns of X
 };
 
 // fp32 activations: four elements as the three bf16 parts x = h + m + l (8 bits each by truncation, exact).  The
@@ -230,6 +232,8 @@ matrix_stream_kernel(MatrixArgs a)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, q = lane >> 4;
     const int rg = blockIdx.x;
+    const int col0 = blockIdx.z * kCols;               // passes of kCols columns
+    const int ncols = a.b - col0 < kCols ? a.b - col0 : kCols;
 
     const uint32_t run_bytes = R * 1024u;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -244,8 +248,8 @@ matrix_stream_kernel(MatrixArgs a)
 #pragma unroll
     for (int i = 0; i < (kCompact ? 1 : kRaw); ++i) {
         int c = kCompact ? n / T : i * kColsPerLoad + lane / kLanesPerCol;
-        c = c < a.b ? c : a.b - 1;
-        xcol[i] = (const XT*)a.X + (int64_t)c * a.ldx + first;
+        c = c < ncols ? c : ncols - 1;
+        xcol[i] = (const XT*)a.X + (int64_t)(col0 + c) * a.ldx + first;
     }
 
     struct Stage {
@@ -448,7 +452,7 @@ matrix_stream_kernel(MatrixArgs a)
         }
     }
     __syncthreads();
-    const int outs = kRows * a.b;
+    const int outs = kRows * ncols;
     for (int o = threadIdx.x; o < outs; o += W * 64) {
         const int c = o / kRows, row = o % kRows;
         const int64_t grow = (int64_t)rg * kRows + row;
@@ -462,11 +466,256 @@ matrix_stream_kernel(MatrixArgs a)
             s += v;
         }
         if (a.partials) {
-            a.partials[((int64_t)blockIdx.y * a.b + c) * a.m_pad + grow] = bits(s);
+            a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(s);
             continue;
         }
         if constexpr (!kInt && !__is_same(XT, __half)) s *= 16.0f;  // (bf16 weights are value / 16)
-        ((YT*)a.Y)[(int64_t)c * a.ldy + grow] = to_output<YT, S>(s);
+        ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(s);
+    }
+}
+
+// Tile kernel, more columns than the streaming kernel holds.  A workgroup owns 64 R rows (four wavefronts of R row tiles)
+// for all of k, or a segment of it, and up to 16 NT columns: two groups of four wavefronts take alternate runs, and the
+// wavefronts of a group share the run's activations, staged in LDS in the streaming kernel's operand slots.
+//
+// Bound by the code stream and the matrix cores; what it takes to get near either:
+//   * Loads return in order, so a wait for activations is a wait for every code requested before them, and the codes take
+//     the trip to memory.  Both are therefore requested five to six steps ahead (registers; three more steps in LDS).
+//   * One barrier per step.  The operands of an MFMA step are read and decoded under the MFMAs of the one before it, also
+//     across the barrier: the two wavefronts of a SIMD leave it together, and what each did alone before its first MFMA
+//     would be a third of a step.
+template <typename XT, int R, int NT, bool kScaled>
+__global__ void __launch_bounds__(512)
+matrix_tile_kernel(MatrixArgs a)
+{
+    using P = Policy<XT>;
+    using acc_t = typename P::acc_t;
+    using YT = typename P::out_t;
+    constexpr bool kInt = sizeof(XT) == 1;
+    constexpr int Wr = 4, Wk = 2;                      // wavefronts side by side in rows, groups of them along k
+    constexpr int T = P::kFrags;
+    constexpr int kPiece = 16 / (int)sizeof(XT);       // elements of a 16-byte piece
+    constexpr int kLanesPerCol = kRun / kPiece, kColsPerLoad = 64 / kLanesPerCol;
+    constexpr int kLoads = T * NT;                     // loads of a run's activations
+    constexpr int kMine = (kLoads + Wr - 1) / Wr;      // of them a wavefront's
+    constexpr int kCodesAhead = 6, kXAhead = 3, kBuffers = 3;
+    constexpr int kRows = 16 * R * Wr;
+    constexpr int kPitch = kRows + 4;
+    constexpr int Rp = R == 3 ? 4 : R;                 // scales per lane and block, padded to a power of two
+    static_assert(sizeof(XT) != 4, "fp32 activations have three parts");
+    constexpr int kXWords = Wk * kBuffers * kLoads * 256, kRedWords = 2 * Wk * 16 * kPitch;
+    __shared__ __align__(16) uint32_t lds[kXWords > kRedWords ? kXWords : kRedWords];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave % Wr, g = wave / Wr;
+    const int n = lane & 15, q = lane >> 4;
+    // the column passes of one row group follow each other on one XCD: they stream the same codes
+    const int unit = blockIdx.x / kXcds, pass = unit % a.passes;
+    const int rg = unit / a.passes * kXcds + blockIdx.x % kXcds;
+    if (rg >= a.row_groups) return;
+    const int col0 = pass * NT * 16, ncols = a.b - col0 < NT * 16 ? a.b - col0 : NT * 16;
+    // this segment's runs (the last one may be ragged)
+    const int run0 = blockIdx.y * a.seg_runs;
+    const int run1 = run0 + a.seg_runs < a.runs ? run0 + a.seg_runs : a.runs;
+
+    constexpr uint32_t run_bytes = R * Wr * 1024u;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
+    constexpr int kScaleRow = Wr * 16 * Rp;
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.scales + (int64_t)rg * a.nblocks * kScaleRow), 0, kScaled ? (int)(a.nblocks * kScaleRow * 2) : 0, 0x00020000);
+
+    struct Codes {
+        v4u c[R];
+        uint32_t q[(Rp + 1) / 2];
+    };
+    auto load_codes_of = [&](Codes& st, int run) {
+        const bool ok = run < run1;
+        const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + wr * R * 1024u + lane * 16u;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            st.c[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + r * 1024u), 0, kAuxNt);
+        if constexpr (kScaled) {
+            const uint32_t so = (ok ? fast_div((uint32_t)run, a.div_block) * (uint32_t)(kScaleRow * 2) : kPastEnd) + (wr * 16 + n) * (uint32_t)(Rp * 2);
+            if constexpr (Rp == 4) {
+                const v2u v = __builtin_amdgcn_raw_buffer_load_b64(srsrc, (int)so, 0, 0);
+                st.q[0] = v.x; st.q[1] = v.y;
+            } else if constexpr (Rp == 2) {
+                st.q[0] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, (int)so, 0, 0);
+            } else {
+                st.q[0] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(srsrc, (int)so, 0, 0);
+            }
+        }
+    };
+
+    // Staging: load f = wr + i Wr of a run takes kColsPerLoad columns, consecutive lanes consecutive pieces.  The address
+    // stops at the last whole piece of the column; what that moves is shifted back when the piece is put into LDS (only
+    // from the run that k ends in on), zeros coming in: elements past k are zero whatever lies behind them.
+    const XT* xcol[kMine];
+    uint32_t xslot[kMine];
+    const int xoff = lane % kLanesPerCol * kPiece;
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        int c = (wr + i * Wr) * kColsPerLoad + lane / kLanesPerCol;
+        const int j = lane % kLanesPerCol;
+        xslot[i] = ((c / 16 * T + j % T) * 64 + j / T * 16 + ((c & 15) ^ j)) * 4;
+        c = c < ncols ? c : ncols - 1;
+        xcol[i] = (const XT*)a.X + (int64_t)(col0 + c) * a.ldx;
+    }
+    const int last = (int)a.k - kPiece, whole = run1 < a.full_runs ? run1 : a.full_runs;
+    auto load_x = [&](v4u (&x)[kMine], int run) {
+        const int kk = run * kRun + xoff;
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) x[i] = load_any16<sizeof(XT)>(xcol[i] + (kk < last ? kk : last));
+    };
+    auto put_x = [&](v4u (&x)[kMine], int run, int buf) {
+        if (run >= whole) {
+            const int sh = run < run1 ? run * kRun + xoff - last : kPiece;  // elements, even (past the segment: all)
+            const int h = sh > 0 ? sh * (int)sizeof(XT) / 2 : 0;            // halfwords
+#pragma unroll
+            for (int i = 0; i < kMine; ++i) {
+                v4u v = x[i];
+                if (h & 1) v = v4u{v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16, v[2] >> 16 | v[3] << 16, v[3] >> 16};
+                if (h & 2) v = v4u{v[1], v[2], v[3], 0};
+                if (h & 4) v = v4u{v[2], v[3], 0, 0};
+                if (h & ~7) v = v4u{0, 0, 0, 0};
+                x[i] = v;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kMine; ++i)
+            if (kLoads % Wr == 0 || wr + i * Wr < kLoads) *(v4u*)&lds[(g * kBuffers + buf) * kLoads * 256 + xslot[i]] = x[i];
+    };
+
+    acc_t acc[R][NT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[r][nt] = acc_t{0, 0, 0, 0};
+    auto read_x = [&](int buf, int t, int nt) {
+        return *(const v4u*)&lds[((g * kBuffers + buf) * kLoads + nt * T + t) * 256 + q * 64 + (n ^ (q * T + t)) * 4];
+    };
+    auto decode = [&](v4u (&w)[R], const Codes& st, int t) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) P::decode(st.c[r], t, w[r]);
+    };
+
+    // Step s: group g's run is run0 + g + s Wk (past the segment: codes from past the end, scale zero); all groups make the
+    // same number of steps, rounded up to the unrolling.  At its start the activations of step s + 2 go to LDS and those of
+    // s + 5 are requested, at its end the codes of s + 6.
+    const int steps = (run1 - run0 + Wk - 1) / Wk;
+    const auto run_of = [&](int s) { return run0 + g + s * Wk; };
+    v4u xr[kXAhead][kMine], x[NT], w[2][R];
+    Codes ring[kCodesAhead];
+    load_codes_of(ring[0], run_of(0));
+    load_x(xr[0], run_of(0));
+    __builtin_amdgcn_sched_barrier(0);
+    load_codes_of(ring[1], run_of(1));
+    load_x(xr[1], run_of(1));
+    __builtin_amdgcn_sched_barrier(0);
+    load_codes_of(ring[2], run_of(2));
+    load_x(xr[2], run_of(2));
+    __builtin_amdgcn_sched_barrier(0);
+    put_x(xr[0], run_of(0), 0);
+    load_codes_of(ring[3], run_of(3));
+    load_x(xr[0], run_of(3));
+    __builtin_amdgcn_sched_barrier(0);
+    put_x(xr[1], run_of(1), 1);
+    load_codes_of(ring[4], run_of(4));
+    load_x(xr[1], run_of(4));
+    __builtin_amdgcn_sched_barrier(0);
+    load_codes_of(ring[5], run_of(5));
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) x[nt] = read_x(0, 0, nt);
+    decode(w[0], ring[0], 0);
+    for (int s = 0; s < steps; s += kCodesAhead) {
+#pragma unroll
+        for (int d = 0; d < kCodesAhead; ++d) {
+            Codes& mine = ring[d];
+            acc_t blk[R][NT];
+            put_x(xr[(d + 2) % kXAhead], run_of(s + d + 2), (d + 2) % kBuffers);
+            load_x(xr[(d + 2) % kXAhead], run_of(s + d + 2 + kXAhead));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int now = (d * T + t) & 1, then = now ^ 1;
+                const bool over = t + 1 == T;          // what is read ahead belongs to the next step
+                decode(w[then], over ? ring[(d + 1) % kCodesAhead] : mine, over ? 0 : t + 1);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if constexpr (kScaled) {
+                            blk[r][nt] = P::mma(x[nt], w[now][r], t == 0 ? acc_t{0, 0, 0, 0} : blk[r][nt]);
+                        } else {
+                            acc[r][nt] = P::mma(x[nt], w[now][r], acc[r][nt]);
+                        }
+                    }
+                    x[nt] = read_x(over ? (d + 1) % kBuffers : d % kBuffers, over ? 0 : t + 1, nt);
+                }
+                constexpr int kDecode = kInt ? 6 : __is_same(XT, __half) ? 9 : 13;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                  // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x002, kDecode / NT + 1, 0);   // its share of the decoding
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // the tile's next operand
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (kScaled) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float q = __half2float(__ushort_as_half((uint16_t)(mine.q[r / 2] >> (16 * (r & 1)))));
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[r][nt][i] = fmaf(q, blk[r][nt][i], acc[r][nt][i]);
+                        asm volatile("" : "+v"(acc[r][nt]));   // (here and now: the compiler would keep all steps' sums until the end of the loop)
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_codes_of(mine, run_of(s + d + kCodesAhead));
+            lds_barrier();
+        }
+    }
+    // the groups' sums, a column tile at a time, [group][column][row] in alternating halves of the LDS
+    auto bits = [](auto v) { uint32_t u; __builtin_memcpy(&u, &v, 4); return u; };
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        uint32_t* red = lds + (nt & 1) * Wk * 16 * kPitch;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (kInt) acc[r][nt][i] >>= 4;
+                red[(g * 16 + 4 * q + i) * kPitch + (wr * R + r) * 16 + n] = bits(acc[r][nt][i]);
+            }
+        lds_barrier();
+        for (int o = threadIdx.x; o < kRows * 16; o += Wr * Wk * 64) {
+            const int c = nt * 16 + o / kRows, row = o % kRows;
+            const int64_t grow = (int64_t)rg * kRows + row;
+            if (grow >= a.m || c >= ncols) continue;
+            using S = typename std::conditional<kInt, int, float>::type;
+            S sum = 0;
+#pragma unroll
+            for (int k = 0; k < Wk; ++k) {
+                S v;
+                __builtin_memcpy(&v, &red[(k * 16 + c % 16) * kPitch + row], 4);
+                sum += v;
+            }
+            if (a.partials) {
+                a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(sum);
+                continue;
+            }
+            if constexpr (!kInt && !__is_same(XT, __half)) sum *= 16.0f;  // (bf16 weights are value / 16)
+            ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(sum);
+        }
     }
 }
 
@@ -522,35 +771,64 @@ matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, in
     }
 }
 
-// scales [m][nblocks] -> [row group][scale block][n][r]; rows past m get zero
+// scales [m][nblocks] -> [row group][scale block][row wavefront][n][its row tiles, padded to Rp]; rows past m get zero
 __global__ void __launch_bounds__(256)
 matrix_repack_scales_kernel(const __half* __restrict__ scales, __half* __restrict__ ordered, int64_t m, int64_t nblocks,
-                            int R, int64_t total)
+                            int R, int Wr, int Rp, int64_t total)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(i % R), n = (int)(i / R) & 15;
-        const int64_t rest = i / (16 * R);
+        const int r = (int)(i % Rp), n = (int)(i / Rp) & 15, wr = (int)(i / (16 * Rp) % Wr);
+        const int64_t rest = i / (16 * Rp * Wr);
         const int64_t block = rest % nblocks, rg = rest / nblocks;
-        const int64_t row = (rg * R + r) * 16 + n;
-        ordered[i] = row < m ? scales[row * nblocks + block] : __float2half(0.0f);
+        const int64_t row = ((rg * Wr + wr) * R + r) * 16 + n;
+        ordered[i] = r < R && row < m ? scales[row * nblocks + block] : __float2half(0.0f);
     }
 }
 
-template <typename XT, int R, int kCols4, int W, int D>
-int launch_stream(const Plan& p, const MatrixArgs& a, hipStream_t s)
+template <typename XT> int reduce_segments(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
-    const dim3 grid((unsigned)p.row_blocks, (unsigned)p.mx_segments), block(W * 64);
-    if (sizeof(XT) != 1 && a.scales)
-        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, sizeof(XT) != 1>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, false>), grid, block, 0, s, a);
-    MSGEMM_HIP_TRY(hipGetLastError());
     if (p.mx_segments > 1) {
         hipLaunchKernelGGL(matrix_reduce_kernel<XT>, dim3((unsigned)((a.m + 255) / 256), (unsigned)a.b), dim3(256), 0, s, a,
                            p.mx_segments);
         MSGEMM_HIP_TRY(hipGetLastError());
     }
     return MSGEMM_OK;
+}
+
+template <typename XT, int R, int kCols4, int W, int D>
+int launch_stream(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)p.row_blocks, (unsigned)p.mx_segments, (unsigned)a.passes), block(W * 64);
+    if (sizeof(XT) != 1 && a.scales)
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, sizeof(XT) != 1>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, false>), grid, block, 0, s, a);
+    MSGEMM_HIP_TRY(hipGetLastError());
+    return reduce_segments<XT>(p, a, s);
+}
+
+template <typename XT, int R, int NT>
+int launch_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)(kXcds * a.passes * ((a.row_groups + kXcds - 1) / kXcds)), (unsigned)p.mx_segments);
+    if (sizeof(XT) != 1 && a.scales)
+        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, sizeof(XT) != 1>), grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false>), grid, dim3(512), 0, s, a);
+    MSGEMM_HIP_TRY(hipGetLastError());
+    return reduce_segments<XT>(p, a, s);
+}
+
+template <typename XT>
+int launch_tile_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+#define MSGEMM_CASE(RR, NN) \
+    if (p.mx_r == RR && p.mx_cols == NN) return launch_tile<XT, RR, NN>(p, a, s);
+    MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2)
+    MSGEMM_CASE(1, 3) MSGEMM_CASE(2, 3) MSGEMM_CASE(3, 3)
+    MSGEMM_CASE(1, 4) MSGEMM_CASE(2, 4) MSGEMM_CASE(3, 4)
+#undef MSGEMM_CASE
+    return MSGEMM_ERR_UNSUPPORTED;
 }
 
 template <typename XT>
@@ -586,54 +864,83 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
                    o.batched_form == 1 || o.batched_form == 2 || o.batched_segments || o.batched_deal || o.poll_limit || o.skip_publish))
         return false;
     const int64_t runs = (p.k + kRun - 1) / kRun;
-    if (p.b > 16) return false;
-    if (runs * 4096 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
+    if (runs * 16384 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
+    // More than 16 columns: passes of the streaming kernel over 16 at a time while the codes of all passes are few (they
+    // stay in the caches, and the passes run side by side), and for fp32; from there on the tile kernel, which decodes a
+    // code once for 64 columns.  us, passes against tile: 1024 x 1024 x 64 3.3 / 10.5, 8192 x 4096 x 64 15.5 / 19.1,
+    // 4096 x 14336 x 64 (112 MiB in four passes) 20.6 / 28.3; level at 8192 x 8192 x 64 (128 MiB), 28672 x 8192 x 32 57 / 38;
+    // with a short k, 49152 x 768 x 64 (72 MiB), 37 / 19.
+    const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && p.k >= kRun &&
+                          !(p.x_dtype == MSGEMM_I8 && p.k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
+    const bool tile = tile_can && (asked && o.rows_per_lane ? o.rows_per_lane == 4
+                                                            : (p.b + 15) / 16 * p.m * (p.k / 2) > ((int64_t)(runs >= 8 ? 112 : 32) << 20));
     // One fp32 column: three products per weight where the table kernels add once per pair.
     if (p.x_dtype == MSGEMM_F32 && p.b == 1 && p.m * p.k > ((int64_t)32 << 20) && !asked) return false;
     // A short k under very many rows: a workgroup lives for one or two loads per wavefront, and the table kernels' larger
     // workgroups go through such a matrix faster (300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; at 100000
     // rows and 512 columns the matrix form is ahead, 17.2 against 20.5 with eight columns of X).
-    if (p.k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
+    if (!tile && p.k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
 
-    // Row tiles per wavefront: the work of the busiest compute unit in row tiles, weighted by what a row tile costs -- the
-    // fewer tiles share a load of activations, the more of it each carries (measured with 1, 4 / 8 and 16 columns).
     const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
-    const auto groups = [&](int tiles) { return (p.m + 16 * tiles - 1) / (16 * tiles); };
-    const double cost[3][3] = {{1.25, 1.0, 1.03}, {1.2, 1.0, 1.0}, {1.55, 1.2, 1.0}};
-    const int width = compact ? 0 : p.b <= 8 ? 1 : 2;
+    const bool scaled = p.scale_group > 0;
+    const int Wr = tile ? 4 : 1;
+    const int width = tile ? 3 : compact ? 0 : p.b <= 8 ? 1 : 2;
+    p.mx_cols = tile ? (p.b <= 32 ? 2 : p.b <= 48 ? 3 : 4) : 2 * width;
+    const int64_t passes = tile ? (p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols) : (p.b + 15) / 16;
+    if (passes > 65535) return false;
+    const auto groups = [&](int r) { return (p.m + 16 * Wr * r - 1) / (16 * Wr * r); };
+    const auto waves = [&](int r) { return tile ? 8 : width == 2 && r == 4 ? 8 : 4; };
+    // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a wavefront
+    // keeps 16 runs (tile kernel: four steps; 12288 x 49152 x 64, 64 row groups: 228 us in one segment, 95 in four).
+    const auto segments_of = [&](int r) {
+        int64_t n = 1;
+        while (groups(r) * passes * n * 2 <= p.cus && runs >= 2 * n * (tile ? 8 : waves(r) * 16)) n *= 2;
+        return n;
+    };
+    // Row tiles per wavefront: the work of the busiest compute unit, in row tiles for the streaming kernel, weighted by
+    // what a row tile costs -- the fewer tiles share a load of activations, the more of it each carries (measured with
+    // 1, 4 / 8 and 16 columns) -- and in workgroups of 1, 2 and 3 tiles for the tile kernel (28672 x 8192 x 64 scaled: two
+    // rounds of one tile 73 us, one of two 53; 49152 x 12288 x 64: 135, 110 and 87; three scaled tiles do not fit the
+    // registers).
+    const int tiles[2][3] = {{1, 2, 4}, {1, 2, 3}};
+    const double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 4.0}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
     double best = 0;
     int R = 1;
-    for (int i = 0; i < 3; ++i) {
-        const int r = 1 << i;
-        const double c = (double)((groups(r) + p.cus - 1) / p.cus) * r * cost[width][i];
+    for (int i = 0; i < (tile && scaled ? 2 : 3); ++i) {
+        const int r = tiles[tile][i];
+        const int64_t n = tile ? segments_of(r) : 1;
+        const double c = (double)((groups(r) * passes * n + p.cus - 1) / p.cus) * cost[width][i] / (double)n;
         if (i == 0 || c < best) { best = c; R = r; }
     }
-    if (asked && (o.panels_per_workgroup == 1 || o.panels_per_workgroup == 2 || o.panels_per_workgroup == 4)) R = o.panels_per_workgroup;
-    const int W = width == 2 && R == 4 ? 8 : 4;
-    // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a
-    // wavefront keeps 16 runs.
-    int64_t segments = 1;
-    while (groups(R) * segments * 2 <= p.cus && runs >= 2 * segments * W * 16) segments *= 2;
+    for (int i = 0; i < 3; ++i)
+        if (asked && o.panels_per_workgroup == tiles[tile][i]) R = o.panels_per_workgroup;
+    const int W = waves(R);
+    int64_t segments = segments_of(R);
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
+    p.mx_tile_kernel = tile;
     p.mx_r = R;
+    p.mx_row_waves = Wr;
     p.mx_waves = W;
     p.mx_segments = (int)segments;
-    p.mx_cols = 2 * width;
     p.matrix = true;
     p.row_blocks = groups(R);
-    p.m_pad = p.row_blocks * 16 * R;
+    p.m_pad = p.row_blocks * 16 * Wr * R;
     p.ktiles = runs;
     p.fs.groups = kRun / 2;
     p.fs.cols = 1;
     p.fs.entry_bytes = 4;
-    p.fs.tile_rows = 16 * R;
-    const int64_t sums = (int64_t)W * segments;
-    p.segments = (int)(runs < sums ? runs : sums);  // partial sums per output: one per wavefront with a run
+    p.fs.tile_rows = 16 * Wr * R;
+    const int64_t sums = (int64_t)(W / Wr) * segments;
+    p.segments = (int)(runs < sums ? runs : sums);  // partial sums per output: one per wavefront (or group) with a run
     p.partial_bytes = segments > 1 ? (size_t)segments * (size_t)p.b * (size_t)p.m_pad * 4u : 0;
     return true;
 }
 
-size_t matrix_scale_bytes(const Plan& p) { return (size_t)p.nblocks * (size_t)p.m_pad * 2u; }
+static int scale_slots(const Plan& p) { return p.mx_r == 3 ? 4 : p.mx_r; }
+size_t matrix_scale_bytes(const Plan& p)
+{
+    return (size_t)p.nblocks * (size_t)p.row_blocks * (size_t)(p.mx_row_waves * 16 * scale_slots(p)) * 2u;
+}
 
 static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStream_t s)
 {
@@ -643,10 +950,10 @@ static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStr
     const int enc = encoding_of(p.x_dtype);
     if (inverse)
         hipLaunchKernelGGL((matrix_repack_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r, enc, dwords);
+                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, dwords);
     else
         hipLaunchKernelGGL((matrix_repack_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r, enc, dwords);
+                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, dwords);
     MSGEMM_HIP_TRY(hipGetLastError());
     return MSGEMM_OK;
 }
@@ -660,7 +967,7 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         int64_t blocks = (total + 255) / 256;
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(matrix_repack_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const __half*)p.scales,
-                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, total);
+                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), total);
         MSGEMM_HIP_TRY(hipGetLastError());
     }
     return matrix_repack(p, (uint8_t*)W_codes, false, s);  // (read only in this direction)
@@ -680,8 +987,18 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
     a.nblocks = (int)p.nblocks;
     a.partials = p.mx_segments > 1 ? (uint32_t*)p.partials : nullptr;
     a.m_pad = p.m_pad;
-    a.seg_runs = (a.full_runs + p.mx_segments - 1) / p.mx_segments;
+    a.seg_runs = ((p.mx_tile_kernel ? a.runs : a.full_runs) + p.mx_segments - 1) / p.mx_segments;
+    a.row_groups = (int)p.row_blocks;
+    a.passes = p.mx_tile_kernel ? (int)((p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols)) : (int)((p.b + 15) / 16);
     a.div_block = make_fastdiv(p.scale_group > 0 ? (uint32_t)(p.scale_group / kRun) : 1u);
+    if (p.mx_tile_kernel) {
+        switch (p.x_dtype) {
+        case MSGEMM_F16: return launch_tile_for_type<__half>(p, a, s);
+        case MSGEMM_BF16: return launch_tile_for_type<bf16_t>(p, a, s);
+        case MSGEMM_I8: return launch_tile_for_type<int8_t>(p, a, s);
+        default: return MSGEMM_ERR_UNSUPPORTED;
+        }
+    }
     switch (p.x_dtype) {
     case MSGEMM_F16: return launch_for_type<__half>(p, a, s);
     case MSGEMM_BF16: return launch_for_type<bf16_t>(p, a, s);

@@ -84,9 +84,11 @@ struct Plan {
     int d3_sub;           // ... sub-panels of 64 rows per wavefront
     // matrix form (kernels_matrix.hip): codes_tiled and scales_ordered hold its own orders
     bool matrix;
+    bool mx_tile_kernel;  // the tile kernel (more than 16 columns), else the streaming kernel
     int mx_r;             // row tiles of 16 per wavefront
+    int mx_row_waves;     // wavefronts side by side in rows
     int mx_waves;         // wavefronts per workgroup
-    int mx_cols;          // columns of X held, in fours (0: the compact form)
+    int mx_cols;          // columns of X held: streaming kernel in fours (0: the compact form), tile kernel in sixteens
     int mx_segments;      // k-segments (workgroups along k), added by a second launch if more than one
     Plan* tables;         // the same problem with tables in LDS, made when another value map is installed; or nullptr
     hipEvent_t ready;     // recorded behind the repack (matrix form): `tables` is made from the repacked codes

@@ -1,6 +1,7 @@
 """The matrix form of msgemm_run (codes decoded in registers, sums on the matrix cores), against the CPU oracle at the
 sizes where its kernels can go wrong: edges of the 16-row tiles and of the 128-column runs, ragged last runs of a few
-columns, every operand width (compact, 8 and 16 columns), k cut into segments, unaligned activations, infinities."""
+columns, every operand width (compact, 8, 16 and up to 64 columns, column passes), k cut into segments, unaligned activations,
+infinities."""
 import numpy as np
 import pytest
 import torch
@@ -34,6 +35,20 @@ CASES = [
     (131, 1154, 3, "f16", 0), (131, 1154, 16, "i8", 0), (70, 2560, 9, "bf16", 128), (70, 2050, 2, "f32", 0)]]
 
 
+# more than 16 columns: the tile kernel (rows_per_lane 4) and passes of the streaming kernel (8)
+CASES += [(m, k, b, xd, sg, {"rows_per_lane": 4, "panels_per_workgroup": r}) for r in (1, 2, 3) for m, k, b, xd, sg in [
+    (1, 128, 17, "f16", 0),                     # one full run: padded steps only
+    (63, 130, 32, "bf16", 0),                   # a ragged run of two columns after it
+    (193, 1666, 33, "f16", 0), (193, 1666, 47, "i8", 0), (257, 898, 64, "i8", 0), (130, 1536, 20, "bf16", 128),
+    (385, 1664, 65, "f16", 128),                # two column passes, the second of one column; 13 runs: 6.5 steps a group
+    (65, 1792, 48, "bf16", 256)]
+] + [(m, k, b, xd, sg, {"rows_per_lane": 4, "batched_segments": s}) for s in (2, 5) for m, k, b, xd, sg in [
+    (131, 1154, 33, "f16", 0), (131, 1154, 64, "i8", 0), (70, 2560, 90, "bf16", 128)]
+] + [(m, k, b, xd, sg, {"rows_per_lane": 8}) for m, k, b, xd, sg in [
+    (131, 1154, 17, "f16", 0), (65, 1154, 35, "i8", 0), (70, 2560, 32, "bf16", 128), (100, 770, 50, "f32", 0)]
+] + [(131, 1154, 33, "f16", 0, {"rows_per_lane": 8, "batched_segments": 3})]
+
+
 @pytest.mark.parametrize("m,k,b,xd,sg,options", CASES)
 def test_matrix_form_against_oracle(m, k, b, xd, sg, options):
     codes = inputs.make_codes(m, k, seed=m + 3 * k + b)
@@ -58,7 +73,7 @@ def test_matrix_form_int8_sums_outgrow_the_shifted_accumulators():
 
 
 @pytest.mark.parametrize("xd", ["f32", "f16", "bf16"])
-@pytest.mark.parametrize("b", [1, 6, 13])
+@pytest.mark.parametrize("b", [1, 6, 13, 20])
 def test_matrix_form_infinite_activations(xd, b):
     """0 x inf is NaN and every other code gives an infinity of its sign, in the column that holds the infinity only."""
     m, k = 64, 512
@@ -66,7 +81,7 @@ def test_matrix_form_infinite_activations(xd, b):
     X = inputs.make_x(k, b, "f32", seed=5)
     X[b - 1, 77] = np.inf
     Xh = {"f32": X, "f16": X.astype(np.float16), "bf16": inputs.f32_to_bf16_bits(X)}[xd]
-    out, _ = run_gpu(codes, Xh, xd, None, 0, 2, B.VARIANT_AUTO, options={"batched_form": 3})
+    out, _ = run_gpu(codes, Xh, xd, None, 0, 2, B.VARIANT_AUTO, options={"batched_form": 3, "rows_per_lane": 4})
     y = torch_io.to_f64(out)
     v = np.array([oracle.decode(int(c)) for c in codes[:, 77 // 2] >> 4], dtype=np.float64)
     assert np.all(np.isnan(y[b - 1][v == 0])) and np.all(y[b - 1][v != 0] == np.inf * v[v != 0])
