@@ -219,7 +219,11 @@ int msgemm_plan_with_options(msgemm_plan_t** out, int64_t m, int64_t k, int64_t 
  * multiple of 64 that divides k; 32 for fp16 / bf16 activations with b > 2)
  * and scales as in msgemm_plan.  Runs with the tables in LDS, full-width
  * entries for b <= 2 and for fp32 activations, fp16 entries (values256[code] *
- * x rounded to fp16) for wider fp16 / bf16 batches; floating-point activations
+ * x rounded to fp16) for wider fp16 / bf16 batches; a map that is E4M3 or E5M2
+ * times a power of two (patterns without a number in the format: any value
+ * that another pattern has), with k even and scale_group 0 or a multiple of
+ * 128, runs in the matrix form of AUTO instead (full-width results; the variant
+ * reported is the one it takes the place of); floating-point activations
  * only (MSGEMM_ERR_UNSUPPORTED for int8).  The plan works with msgemm_run,
  * msgemm_plan_get_info (d reads 1, lut_groups k) and msgemm_destroy; the
  * other entry points refuse it.  options: as for msgemm_plan_with_options, NULL = none.

@@ -10,8 +10,8 @@
 // (int32 for int8 activations).
 //
 // The plan's rule (matrix_choose_shape) gives this form what the library chooses itself for the paper's encoding at
-// d = 2; tables in LDS remain for every request for a variant, another value map, 8-bit weights and scale blocks that
-// are not whole runs of 128 columns.
+// d = 2, and 8-bit weights whose value map is a format the device converts (E4M3, E5M2, times a power of two); tables in
+// LDS remain for every request for a variant, other value maps and scale blocks that are not whole runs of 128 columns.
 //
 // Layout of the codes: [row group of 16 R rows][run of 128 columns][row tile r < R][lane][16 bytes].  Lane (n, q) =
 // (lane & 15, lane >> 4) holds columns 32 q + 0..31 of row n of its tile, dword w of its 16 bytes the 8 from 8 w on, with
@@ -22,6 +22,7 @@
 #include "fused_common.h"
 #include "msgemm_internal.h"
 
+#include <math.h>
 #include <type_traits>
 
 namespace msgemm {
@@ -136,6 +137,24 @@ template <> struct Policy<int8_t> {
     }
 };
 
+// 8-bit codes of a floating-point format the device converts (every finite pattern exact in fp16 and bf16): two dwords of
+// four codes -> the weight operand of one MFMA step.
+enum Format { kInt4, kE4M3, kE5M2 };
+template <int F, typename XT, bool kHigh> __device__ __forceinline__ uint32_t convert_pair(uint32_t x)
+{
+    if constexpr (__is_same(XT, __half)) {
+        if constexpr (F == kE4M3) return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x, 1.0f, kHigh));
+        else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_bf8((int)x, 1.0f, kHigh));
+    } else {
+        if constexpr (F == kE4M3) return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)x, 1.0f, kHigh));
+        else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((int)x, 1.0f, kHigh));
+    }
+}
+template <int F, typename XT> __device__ __forceinline__ v4u convert(uint32_t lo, uint32_t hi)
+{
+    return v4u{convert_pair<F, XT, false>(lo), convert_pair<F, XT, true>(lo), convert_pair<F, XT, false>(hi), convert_pair<F, XT, true>(hi)};
+}
+
 // Which nibble of a code dword holds the e-th of its 8 columns, and what is stored there for a two's-complement code.
 enum Encoding { kEncF16, kEncBf16, kEncI8 };
 __host__ __device__ __forceinline__ int nibble_of(int enc, int e)
@@ -167,6 +186,7 @@ struct MatrixArgs {
     int seg_runs;          // full runs per segment (tile kernel: runs)
     int row_groups;
     int passes;            // passes over the columns of X
+    float factor;          // a power of two that the weight operands leave out (bf16 from 4-bit codes: value / 16)
 };
 
 // fp32 activations: four elements as the three bf16 parts x = h + m + l (8 bits each by truncation, exact).  The
@@ -206,7 +226,7 @@ __device__ __forceinline__ void lds_barrier()
 // kCols4 == 0, up to four columns (int8: eight): lane n loads column n / T for step n % T of a run only (T steps) -- one
 // load, nothing to transpose -- and every step has accumulators of its own, of which the rows of that step are the ones
 // that count.  They end up in the same lane: y(column q) is the sum over t of register t of accumulator t of lane group q.
-template <typename XT, int R, int kCols4, int W, int D, bool kScaled>
+template <typename XT, int R, int kCols4, int W, int D, bool kScaled, int F>
 __global__ void __launch_bounds__(W * 64)
 matrix_stream_kernel(MatrixArgs a)
 {
@@ -235,7 +255,8 @@ matrix_stream_kernel(MatrixArgs a)
     const int col0 = blockIdx.z * kCols;               // passes of kCols columns
     const int ncols = a.b - col0 < kCols ? a.b - col0 : kCols;
 
-    const uint32_t run_bytes = R * 1024u;
+    constexpr int kVecs = F == kInt4 ? 1 : 2;          // 16-byte loads of codes per lane, row tile and run
+    constexpr uint32_t run_bytes = R * kVecs * 1024u;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -253,7 +274,7 @@ matrix_stream_kernel(MatrixArgs a)
     }
 
     struct Stage {
-        v4u codes[R];
+        v4u codes[R * kVecs];
         v4u x[kRaw];
         uint32_t q[(R + 1) / 2];
     };
@@ -261,7 +282,7 @@ matrix_stream_kernel(MatrixArgs a)
     auto load_codes_of = [&](Stage& st, int run, bool ok) {
         const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + lane * 16u;
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R * kVecs; ++r)
             st.codes[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + r * 1024u), 0, kAuxNt);
         if constexpr (kScaled) {
             const uint32_t so = fast_div((uint32_t)(ok ? run : 0), a.div_block) * (uint32_t)(kRows * 2) + n * (uint32_t)(R * 2);
@@ -354,7 +375,10 @@ matrix_stream_kernel(MatrixArgs a)
         for (int t = 0; t < T; ++t) {
             v4u w[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) P::decode(st.codes[r], t, w[r]);
+            for (int r = 0; r < R; ++r) {
+                if constexpr (F == kInt4) P::decode(st.codes[r], t, w[r]);
+                else w[r] = convert<F, XT>(st.codes[2 * r + t / 2][2 * (t & 1)], st.codes[2 * r + t / 2][2 * (t & 1) + 1]);
+            }
 #pragma unroll
             for (int op = kOps - 1; op >= 0; --op) {   // (the smallest part first)
                 if constexpr (!kCompact) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
@@ -469,7 +493,7 @@ matrix_stream_kernel(MatrixArgs a)
             a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(s);
             continue;
         }
-        if constexpr (!kInt && !__is_same(XT, __half)) s *= 16.0f;  // (bf16 weights are value / 16)
+        if constexpr (!kInt && !(F == kInt4 && __is_same(XT, __half))) s *= a.factor;
         ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(s);
     }
 }
@@ -713,7 +737,7 @@ matrix_tile_kernel(MatrixArgs a)
                 a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(sum);
                 continue;
             }
-            if constexpr (!kInt && !__is_same(XT, __half)) sum *= 16.0f;  // (bf16 weights are value / 16)
+            if constexpr (!kInt && !__is_same(XT, __half)) sum *= a.factor;
             ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(sum);
         }
     }
@@ -735,7 +759,7 @@ matrix_reduce_kernel(MatrixArgs a, int segments)
         __builtin_memcpy(&v, &a.partials[((int64_t)seg * a.b + c) * a.m_pad + row], 4);
         s += v;
     }
-    if constexpr (sizeof(XT) != 1 && !__is_same(XT, __half)) s *= 16.0f;
+    if constexpr (sizeof(XT) != 1) s *= a.factor;
     ((YT*)a.Y)[(int64_t)c * a.ldy + row] = to_output<YT, S>(s);
 }
 
@@ -771,6 +795,29 @@ matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, in
     }
 }
 
+// Row-major 8-bit codes -> the order above; a pattern that the format does not read as its value is replaced by one it does.
+struct Remap { uint8_t to[256]; };
+__global__ void __launch_bounds__(256)
+matrix_repack8_kernel(const uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs,
+                      int R, Remap remap, int64_t dwords)
+{
+    __shared__ uint8_t to[256];
+    to[threadIdx.x] = remap.to[threadIdx.x];
+    __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
+        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63, half = (int)(i >> 8) & 1;
+        const int64_t tile = i >> 9;                       // (row group, run, r)
+        const int64_t run = tile / R % runs, rg = tile / R / runs;
+        const int64_t row = (rg * R + tile % R) * 16 + (lane & 15);
+        const int64_t col = run * kRun + 32 * (lane >> 4) + 16 * half + 4 * w;
+        uint32_t v = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (row < m && col + e < k) v |= (uint32_t)to[rows[row * k + col + e]] << (8 * e);
+        ((uint32_t*)tiled)[i] = v;
+    }
+}
+
 // scales [m][nblocks] -> [row group][scale block][row wavefront][n][its row tiles, padded to Rp]; rows past m get zero
 __global__ void __launch_bounds__(256)
 matrix_repack_scales_kernel(const __half* __restrict__ scales, __half* __restrict__ ordered, int64_t m, int64_t nblocks,
@@ -795,14 +842,14 @@ template <typename XT> int reduce_segments(const Plan& p, const MatrixArgs& a, h
     return MSGEMM_OK;
 }
 
-template <typename XT, int R, int kCols4, int W, int D>
+template <typename XT, int R, int kCols4, int W, int D, int F>
 int launch_stream(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
     const dim3 grid((unsigned)p.row_blocks, (unsigned)p.mx_segments, (unsigned)a.passes), block(W * 64);
     if (sizeof(XT) != 1 && a.scales)
-        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, sizeof(XT) != 1>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, sizeof(XT) != 1, F>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((matrix_stream_kernel<XT, R, kCols4, W, D, false, F>), grid, block, 0, s, a);
     MSGEMM_HIP_TRY(hipGetLastError());
     return reduce_segments<XT>(p, a, s);
 }
@@ -811,8 +858,10 @@ template <typename XT, int R, int NT>
 int launch_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
     const dim3 grid((unsigned)(kXcds * a.passes * ((a.row_groups + kXcds - 1) / kXcds)), (unsigned)p.mx_segments);
-    if (sizeof(XT) != 1 && a.scales)
-        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, sizeof(XT) != 1>), grid, dim3(512), 0, s, a);
+    constexpr bool kCanScale = sizeof(XT) != 1 && R < 3;
+    if (sizeof(XT) != 1 && !kCanScale && a.scales) return MSGEMM_ERR_UNSUPPORTED;
+    if (kCanScale && a.scales)
+        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale>), grid, dim3(512), 0, s, a);
     else
         hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false>), grid, dim3(512), 0, s, a);
     MSGEMM_HIP_TRY(hipGetLastError());
@@ -835,51 +884,112 @@ template <typename XT>
 int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
 #define MSGEMM_CASE(RR, CC, WW, DD) \
-    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW) return launch_stream<XT, RR, CC, WW, DD>(p, a, s);
+    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW) return launch_stream<XT, RR, CC, WW, DD, kInt4>(p, a, s);
     MSGEMM_CASE(4, 0, 4, 4)
     MSGEMM_CASE(2, 0, 4, 4)
     MSGEMM_CASE(1, 0, 4, 8)
-    MSGEMM_CASE(4, 2, 4, 4)
-    MSGEMM_CASE(2, 2, 4, 4)
-    MSGEMM_CASE(1, 2, 4, 4)
+    MSGEMM_CASE(4, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+    MSGEMM_CASE(2, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+    MSGEMM_CASE(1, 2, 4, sizeof(XT) == 4 ? 2 : 4)
     MSGEMM_CASE(4, 4, 8, 2)
-    MSGEMM_CASE(2, 4, 4, 4)
-    MSGEMM_CASE(1, 4, 4, 4)
+    MSGEMM_CASE(2, 4, 4, sizeof(XT) == 4 ? 2 : 4)
+    MSGEMM_CASE(1, 4, 4, sizeof(XT) == 4 ? 2 : 4)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
 
+template <typename XT, int F>
+int launch_for_codes8(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+#define MSGEMM_CASE(RR, CC, DD) \
+    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == 4) return launch_stream<XT, RR, CC, 4, DD, F>(p, a, s);
+    MSGEMM_CASE(2, 0, 4)
+    MSGEMM_CASE(1, 0, 4)
+    MSGEMM_CASE(2, 2, 2)
+    MSGEMM_CASE(1, 2, 4)
+    MSGEMM_CASE(2, 4, 2)
+    MSGEMM_CASE(1, 4, 2)
+#undef MSGEMM_CASE
+    return MSGEMM_ERR_UNSUPPORTED;
+}
+
+template <typename XT> int launch_for_format(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+    return p.mx_format == kE4M3 ? launch_for_codes8<XT, kE4M3>(p, a, s) : launch_for_codes8<XT, kE5M2>(p, a, s);
+}
+
+// Finite value of a pattern of a format (OCP 8-bit formats: bias 7 and 15; E4M3 has no infinities and one NaN a sign).
+bool format_value(int format, int pattern, double& v)
+{
+    const int mb = format == kE4M3 ? 3 : 2, bias = format == kE4M3 ? 7 : 15;
+    const int e = (pattern & 0x7f) >> mb, f = pattern & ((1 << mb) - 1);
+    if (format == kE4M3 ? (pattern & 0x7f) == 0x7f : e == 31) return false;
+    v = e == 0 ? ldexp((double)f, 1 - bias - mb) : ldexp(1.0 + ldexp((double)f, -mb), e - bias);
+    if (pattern & 0x80) v = -v;
+    return true;
+}
+
 }  // namespace
+
+// Whether a map of 256 values is one of the formats the device converts, times a power of two; a pattern that stands for
+// no number in the format must have a value that another pattern has.
+void matrix_find_format(Plan& p, const float* values)
+{
+    p.mx_format = kInt4;
+    for (int format : {kE4M3, kE5M2}) {
+        const float one = values[format == kE4M3 ? 0x38 : 0x3c];
+        int exponent = 0;
+        if (!(one > 0.0f) || frexpf(one, &exponent) != 0.5f || exponent < -20 || exponent > 20) continue;
+        bool ok = true;
+        for (int i = 0; i < 256 && ok; ++i) {
+            double v;
+            p.mx_remap[i] = (uint8_t)i;
+            if (format_value(format, i, v)) { ok = (double)values[i] == v * one; continue; }
+            ok = false;
+            for (int j = 0; j < 256 && !ok; ++j)
+                if (format_value(format, j, v) && (double)values[i] == v * one) { p.mx_remap[i] = (uint8_t)j; ok = true; }
+        }
+        if (!ok) continue;
+        p.mx_format = format;
+        p.mx_factor = one;
+        return;
+    }
+}
 
 // Whether the library's own choice for a plan is the matrix form, and its shape.
 bool matrix_choose_shape(Plan& p, int requested_variant)
 {
     const msgemm_plan_options_t& o = p.opt;
     p.matrix = false;
-    if (requested_variant != MSGEMM_VARIANT_AUTO || p.d != 2 || p.codes8) return false;
-    if (p.scale_group % kRun != 0) return false;
+    // 8-bit codes: of a format the device converts, and an even number of columns (internally two count for one)
+    const bool bytes = p.codes8;
+    if (bytes ? p.mx_format == kInt4 || p.k % 4 : requested_variant != MSGEMM_VARIANT_AUTO || p.d != 2) return false;
+    const int64_t k = bytes ? p.k / 2 : p.k, code_bytes = p.m * (p.k / 2);
+    if ((bytes ? p.scale_group / 2 : p.scale_group) % kRun != 0) return false;
     const bool asked = o.batched_form == 3;
     // a request for a form of the table kernels keeps them
     if (!asked && (o.panels_per_workgroup || o.k_tiles_per_workgroup || o.reduce_mode || o.rows_per_lane || o.no_xcd_map ||
                    o.batched_form == 1 || o.batched_form == 2 || o.batched_segments || o.batched_deal || o.poll_limit || o.skip_publish))
         return false;
-    const int64_t runs = (p.k + kRun - 1) / kRun;
+    const int64_t runs = (k + kRun - 1) / kRun;
     if (runs * 16384 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
     // More than 16 columns: passes of the streaming kernel over 16 at a time while the codes of all passes are few (they
     // stay in the caches, and the passes run side by side), and for fp32; from there on the tile kernel, which decodes a
     // code once for 64 columns.  us, passes against tile: 1024 x 1024 x 64 3.3 / 10.5, 8192 x 4096 x 64 15.5 / 19.1,
     // 4096 x 14336 x 64 (112 MiB in four passes) 20.6 / 28.3; level at 8192 x 8192 x 64 (128 MiB), 28672 x 8192 x 32 57 / 38;
     // with a short k, 49152 x 768 x 64 (72 MiB), 37 / 19.
-    const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && p.k >= kRun &&
-                          !(p.x_dtype == MSGEMM_I8 && p.k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
+    const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun && !bytes &&
+                          !(p.x_dtype == MSGEMM_I8 && k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
     const bool tile = tile_can && (asked && o.rows_per_lane ? o.rows_per_lane == 4
-                                                            : (p.b + 15) / 16 * p.m * (p.k / 2) > ((int64_t)(runs >= 8 ? 112 : 32) << 20));
-    // One fp32 column: three products per weight where the table kernels add once per pair.
-    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && p.m * p.k > ((int64_t)32 << 20) && !asked) return false;
+                                                            : (p.b + 15) / 16 * code_bytes > ((int64_t)(runs >= 8 ? 112 : 32) << 20));
+    // One fp32 column of 4-bit codes: decoding and three products per weight where the table kernels add once per pair
+    // (4096 x 4096 5.5 us against 6.9, 8192 x 8192 11.0 against 10.3, 49152 x 12288 74 against 52; 8-bit codes, one
+    // conversion for two, 12.5 against 17.0 at 8192 x 8192).
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && p.m * k > ((int64_t)32 << 20) && !asked) return false;
     // A short k under very many rows: a workgroup lives for one or two loads per wavefront, and the table kernels' larger
     // workgroups go through such a matrix faster (300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; at 100000
     // rows and 512 columns the matrix form is ahead, 17.2 against 20.5 with eight columns of X).
-    if (!tile && p.k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
+    if (!tile && k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
 
     const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
     const bool scaled = p.scale_group > 0;
@@ -906,13 +1016,13 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     const double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 4.0}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
     double best = 0;
     int R = 1;
-    for (int i = 0; i < (tile && scaled ? 2 : 3); ++i) {
+    for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i) {
         const int r = tiles[tile][i];
         const int64_t n = tile ? segments_of(r) : 1;
         const double c = (double)((groups(r) * passes * n + p.cus - 1) / p.cus) * cost[width][i] / (double)n;
         if (i == 0 || c < best) { best = c; R = r; }
     }
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i)
         if (asked && o.panels_per_workgroup == tiles[tile][i]) R = o.panels_per_workgroup;
     const int W = waves(R);
     int64_t segments = segments_of(R);
@@ -926,7 +1036,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     p.row_blocks = groups(R);
     p.m_pad = p.row_blocks * 16 * Wr * R;
     p.ktiles = runs;
-    p.fs.groups = kRun / 2;
+    p.fs.groups = bytes ? kRun : kRun / 2;
     p.fs.cols = 1;
     p.fs.entry_bytes = 4;
     p.fs.tile_rows = 16 * Wr * R;
@@ -958,7 +1068,7 @@ static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStr
     return MSGEMM_OK;
 }
 
-size_t matrix_code_bytes(const Plan& p) { return (size_t)p.ktiles * (size_t)p.m_pad * 64u; }
+size_t matrix_code_bytes(const Plan& p) { return (size_t)p.ktiles * (size_t)p.m_pad * (p.codes8 ? 128u : 64u); }
 
 int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
 {
@@ -969,6 +1079,17 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         hipLaunchKernelGGL(matrix_repack_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const __half*)p.scales,
                            (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), total);
         MSGEMM_HIP_TRY(hipGetLastError());
+    }
+    if (p.codes8) {
+        const int64_t dwords = (int64_t)(matrix_code_bytes(p) / 4);
+        int64_t blocks = (dwords + 255) / 256;
+        if (blocks > 65536) blocks = 65536;
+        Remap remap;
+        for (int i = 0; i < 256; ++i) remap.to[i] = p.mx_remap[i];
+        hipLaunchKernelGGL(matrix_repack8_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const uint8_t*)W_codes,
+                           p.codes_tiled, p.m, p.k / 2, p.ktiles, p.mx_r, remap, dwords);
+        MSGEMM_HIP_TRY(hipGetLastError());
+        return MSGEMM_OK;
     }
     return matrix_repack(p, (uint8_t*)W_codes, false, s);  // (read only in this direction)
 }
@@ -981,16 +1102,26 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
     a.codes = p.codes_tiled;
     a.scales = (const __half*)p.scales_ordered;
     a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
-    a.m = p.m; a.k = p.k; a.b = (int)p.b;
+    const int64_t k = p.codes8 ? p.k / 2 : p.k, group = p.codes8 ? p.scale_group / 2 : p.scale_group;
+    a.m = p.m; a.k = k; a.b = (int)p.b;
     a.runs = (int)p.ktiles;
-    a.full_runs = (int)(p.k / kRun);
+    a.full_runs = (int)(k / kRun);
     a.nblocks = (int)p.nblocks;
     a.partials = p.mx_segments > 1 ? (uint32_t*)p.partials : nullptr;
     a.m_pad = p.m_pad;
     a.seg_runs = ((p.mx_tile_kernel ? a.runs : a.full_runs) + p.mx_segments - 1) / p.mx_segments;
     a.row_groups = (int)p.row_blocks;
     a.passes = p.mx_tile_kernel ? (int)((p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols)) : (int)((p.b + 15) / 16);
-    a.div_block = make_fastdiv(p.scale_group > 0 ? (uint32_t)(p.scale_group / kRun) : 1u);
+    a.div_block = make_fastdiv(group > 0 ? (uint32_t)(group / kRun) : 1u);
+    a.factor = p.codes8 ? p.mx_factor : p.x_dtype == MSGEMM_F16 ? 1.0f : 16.0f;
+    if (p.codes8) {
+        switch (p.x_dtype) {
+        case MSGEMM_F16: return launch_for_format<__half>(p, a, s);
+        case MSGEMM_BF16: return launch_for_format<bf16_t>(p, a, s);
+        case MSGEMM_F32: return launch_for_format<float>(p, a, s);
+        default: return MSGEMM_ERR_UNSUPPORTED;
+        }
+    }
     if (p.mx_tile_kernel) {
         switch (p.x_dtype) {
         case MSGEMM_F16: return launch_tile_for_type<__half>(p, a, s);

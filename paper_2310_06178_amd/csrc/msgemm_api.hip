@@ -127,8 +127,9 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     p->variant = MSGEMM_VARIANT_GLOBAL_LUT;
     p->cus = 256;
     (void)hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
+    if (values256) msgemm::matrix_find_format(*p, values256);
     if (!tables_only && msgemm::matrix_choose_shape(*p, variant)) {
-        p->variant = MSGEMM_VARIANT_FUSED_LDS;
+        p->variant = values256 ? variant : (int)MSGEMM_VARIANT_FUSED_LDS;  // (8-bit codes: the one it takes the place of)
     } else if (variant != MSGEMM_VARIANT_GLOBAL_LUT) {
         rc = msgemm::fused_choose_shape(*p, variant);
         if (rc == MSGEMM_OK) {
@@ -141,7 +142,7 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     if (p->codes8) {
         // the kernels that have a table build for it: one column with 16 rows per lane,
         // four fp32 columns, eight fp16 columns with 8 rows per lane
-        const bool ok = (p->variant == MSGEMM_VARIANT_FUSED_LDS && p->fs.cols == 1 && p->fs.lane_bytes == 16) ||
+        const bool ok = p->matrix || (p->variant == MSGEMM_VARIANT_FUSED_LDS && p->fs.cols == 1 && p->fs.lane_bytes == 16) ||
                         (p->variant == MSGEMM_VARIANT_FUSED_LDS && p->fs.cols == 4) ||
                         (p->variant == MSGEMM_VARIANT_FUSED_LDS16 && (p->fs.lane_bytes == 8 || p->fs.groups == 16));
         if (!ok) return fail(MSGEMM_ERR_UNSUPPORTED);

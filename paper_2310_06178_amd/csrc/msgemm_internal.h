@@ -90,6 +90,9 @@ struct Plan {
     int mx_waves;         // wavefronts per workgroup
     int mx_cols;          // columns of X held: streaming kernel in fours (0: the compact form), tile kernel in sixteens
     int mx_segments;      // k-segments (workgroups along k), added by a second launch if more than one
+    int mx_format;        // 8-bit codes: the format the device converts (kernels_matrix.hip), 0 = none
+    float mx_factor;      // ... times this power of two
+    uint8_t mx_remap[256]; // ... and the pattern that stands for each
     Plan* tables;         // the same problem with tables in LDS, made when another value map is installed; or nullptr
     hipEvent_t ready;     // recorded behind the repack (matrix form): `tables` is made from the repacked codes
     int wide_tables;      // single-column kernel, wide form: tables a workgroup holds (1 or 2); 0 = another form
@@ -139,6 +142,7 @@ bool xcd_round_robin(int device, hipStream_t s);
 int launch_batched(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ldy, hipStream_t s);
 
 // kernels_matrix.hip (codes decoded in registers, sums on the matrix cores: the library's own choice where it applies)
+void matrix_find_format(Plan& p, const float* values256);   // fills mx_format, mx_factor, mx_remap
 bool matrix_choose_shape(Plan& p, int requested_variant);  // fills the mx_* fields, row_blocks, m_pad, ...; false if not applicable
 size_t matrix_code_bytes(const Plan& p);
 size_t matrix_scale_bytes(const Plan& p);

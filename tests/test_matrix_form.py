@@ -126,3 +126,48 @@ def test_other_entry_points_on_a_matrix_form_plan(xd, b, sg):
         assert B.msgemm_plan_check(plan) == B.OK
     finally:
         B.msgemm_destroy(plan)
+
+
+def e5m2_values():
+    """OCP E5M2 patterns (1 sign, 5 exponent bits with bias 15, 2 mantissa bits); infinities and NaNs are given numbers."""
+    v = np.empty(256)
+    for p in range(256):
+        e, f = (p >> 2) & 31, p & 3
+        v[p] = f * 2.0 ** -16 if e == 0 else (1 + f / 4) * 2.0 ** (e - 15)
+        if e == 31:
+            v[p] = [0.0, 1.5, 3.0, 57344.0][f]
+        if p & 0x80:
+            v[p] = -v[p]
+    return v
+
+
+@pytest.mark.parametrize("m,k,b,xd,sg,options", [
+    (131, 1666, 1, "f16", 0, {}), (131, 1666, 4, "bf16", 0, {"panels_per_workgroup": 2}), (100, 640, 8, "f16", 128, {}),
+    (100, 640, 16, "bf16", 128, {"panels_per_workgroup": 2}), (47, 130, 3, "f32", 0, {}), (47, 1154, 12, "f32", 0, {}),
+    (64, 256, 20, "f16", 256, {}), (33, 126, 2, "f32", 0, {}), (70, 2560, 2, "f16", 128, {"batched_segments": 3})])
+@pytest.mark.parametrize("table", ["e4m3", "e5m2", "other"])
+def test_codes8_of_a_device_format(table, m, k, b, xd, sg, options):
+    """8-bit weights whose value map is an 8-bit floating-point format times a power of two run in the matrix form; every
+    pattern occurs, those without a number in the format with the values the map gives them.  Any other map keeps the tables."""
+    values = {"e4m3": np.nan_to_num(inputs.fp8_e4m3_values(), nan=-0.5) / 16, "e5m2": e5m2_values() * 2.0 ** -12,
+              "other": np.nan_to_num(inputs.fp8_e4m3_values(), nan=0.3) / 16}[table]
+    codes = np.random.default_rng(m + k + b).integers(0, 256, size=(m, k), dtype=np.uint8)
+    codes[0, :126] = np.arange(126) + 130   # (patterns up to 255, the specials among them)
+    X = inputs.make_x(k, b, xd, seed=k + 1)
+    scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
+    Xd = oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64)
+    ref = oracle.gemm_f64_codes8(codes, Xd, values, scales, sg)
+    plan = B.msgemm_plan_codes8(m, k, b, xd, Y_OF_X[xd], sg, torch_io.to_device(codes, "codes"),
+                                torch_io.to_device(scales, "scales"), values, options=dict(options, batched_form=3))
+    try:
+        matrix = B.msgemm_plan_get_info(plan)["tile_groups"] == 128
+        assert matrix == (table != "other")
+        Y = torch_io.empty_output(b, m, Y_OF_X[xd], ldy=m + 1)
+        Y.fill_(-3)
+        B.msgemm_run(plan, torch_io.to_device(X, xd), k, Y, m + 1)
+        torch.cuda.synchronize()
+        out = torch_io.to_host(Y)
+    finally:
+        B.msgemm_destroy(plan)
+    check(np.ascontiguousarray(out[:, :m]), ref, xd, f"8-bit weights {table}",
+          elem_bound(codes, X, xd, scales, sg, table16=not matrix and b > 2 and xd != "f32", values256=values))
