@@ -137,25 +137,36 @@ def load():
 
 
 def _ptr(t):
-    """Device address of a torch tensor / raw int / None."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
+    """Device address of a torch tensor / raw int / None (what a c_void_p argument takes)."""
+    if t is None or isinstance(t, int):
+        return t
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_raw_stream = None   # (device index) -> handle of torch's current stream there, once torch has initialised the device
 
 
 def _stream(stream):
+    """The handle of a stream: torch's current one for None.  A decoding step makes this call for every weight matrix, so
+    the handle is asked for directly where torch offers that, without a Stream object around it."""
+    global _raw_stream
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream[0](_raw_stream[1]())
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        handle = torch.cuda.current_stream().cuda_stream   # (initialises the device)
+        of_device = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if of_device is not None and device is not None and of_device(device()) == handle:
+            _raw_stream = (of_device, device)
+        return handle
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def status_string(status: int) -> str:
@@ -250,7 +261,7 @@ def msgemm_consume_lut(plan, L, Y, ldy, stream=None):
 
 
 def msgemm_run(plan, X, ldx, Y, ldy, stream=None):
-    rc = load().msgemm_run(ctypes.c_void_p(plan), _ptr(X), int(ldx), _ptr(Y), int(ldy), _stream(stream))
+    rc = (_lib or load()).msgemm_run(plan, _ptr(X), int(ldx), _ptr(Y), int(ldy), _stream(stream))
     if rc != OK:
         raise MsgemmError(rc, "msgemm_run")
 
