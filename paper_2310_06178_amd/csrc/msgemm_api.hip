@@ -279,17 +279,29 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     return MSGEMM_OK;
 }
 
-// The plan that serves a matrix-form plan's calls while another value map is installed: the same problem with its
-// tables in LDS (full-width entries hold any value), made from the repacked codes on the null stream.  The matrix form's
-// buffers stay: launches already enqueued or captured keep the old map.
+// The plan that serves a matrix-form plan's calls while another value map is installed: the same problem by the table
+// kernels the library would choose, made from the repacked codes on the null stream.  The matrix form's buffers stay:
+// launches already enqueued or captured keep the old map.
 static int ensure_tables(Plan& p)
 {
     if (p.tables) return MSGEMM_OK;
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream of the program may be capturing)
     MSGEMM_HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
     // (no stream of its own: with a second queue the device no longer deals workgroup ids over its XCDs from the first
-    // one on, which the XCD-local reduction of other plans relies on)
-    hipStream_t s = nullptr;
+    // one on, which the XCD-local reduction of other plans relies on; only while a stream that waits for the null stream
+    // is being captured, which work on the null stream would break, one is made)
+    hipStream_t s = nullptr, own = nullptr;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(nullptr, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        const hipError_t ec = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
+        if (ec != hipSuccess) {
+            msgemm::set_hip_error(ec);
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            return MSGEMM_ERR_HIP;
+        }
+        s = own;
+    }
     uint8_t* rows = nullptr;
     msgemm_plan_t* made = nullptr;
     int rc = MSGEMM_ERR_HIP;
@@ -305,6 +317,7 @@ static int ensure_tables(Plan& p)
     }
     if (e != hipSuccess) msgemm::set_hip_error(e);
     if (rows) (void)hipFree(rows);
+    if (own) (void)hipStreamDestroy(own);
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (rc != MSGEMM_OK) {
         msgemm::free_plan(reinterpret_cast<Plan*>(made));

@@ -2,6 +2,8 @@
 sizes where its kernels can go wrong: edges of the 16-row tiles and of the 128-column runs, ragged last runs of a few
 columns, every operand width (compact, 8, 16 and up to 64 columns, column passes), k cut into segments, unaligned activations,
 infinities."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -171,3 +173,32 @@ def test_codes8_of_a_device_format(table, m, k, b, xd, sg, options):
         B.msgemm_destroy(plan)
     check(np.ascontiguousarray(out[:, :m]), ref, xd, f"8-bit weights {table}",
           elem_bound(codes, X, xd, scales, sg, table16=not matrix and b > 2 and xd != "f32", values256=values))
+
+
+@pytest.mark.parametrize("non_blocking", [1, 0])
+def test_first_value_map_while_a_stream_is_captured(non_blocking):
+    # the table kernels' plan is made at that point, outside the capture; the captured launch keeps the map it was given
+    lib = B.load()  # (its symbols and those of the runtime it is linked to)
+    m, k = 96, 512
+    codes, X = inputs.make_codes(m, k, seed=21), inputs.make_x(k, 1, "f32", seed=22)
+    dX, Y = torch_io.to_device(X, "f32"), torch.zeros((1, m), dtype=torch.float32, device="cuda:0")
+    plan = B.msgemm_plan(m, k, 1, "f32", "f32", 2, 0, torch_io.to_device(codes, "codes"))
+    B.msgemm_run(plan, dX, k, Y, m)
+    torch.cuda.synchronize()
+    stream, graph, instance = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
+    assert lib.hipStreamCreateWithFlags(ctypes.byref(stream), non_blocking) == 0
+    assert lib.hipStreamBeginCapture(stream, 0) == 0  # (global mode)
+    B.msgemm_plan_set_codebook(plan, NONUNIFORM)
+    B.msgemm_run(plan, dX, k, Y, m, stream.value)
+    assert lib.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0 and graph.value
+    B.msgemm_plan_set_codebook(plan, None)
+    assert lib.hipGraphInstantiate(ctypes.byref(instance), graph, None, None, ctypes.c_size_t(0)) == 0
+    want = oracle.gemm_f64(codes, X.astype(np.float64), None, 0, codebook=NONUNIFORM)
+    for _ in range(3):
+        Y.zero_()
+        torch.cuda.synchronize()
+        assert lib.hipGraphLaunch(instance, stream) == 0 and lib.hipStreamSynchronize(stream) == 0
+        assert oracle.rel_l2(torch_io.to_f64(torch_io.to_host(Y)), want) < 1e-5
+    assert lib.hipGraphExecDestroy(instance) == 0 and lib.hipGraphDestroy(graph) == 0
+    assert lib.hipStreamDestroy(stream) == 0
+    B.msgemm_destroy(plan)
