@@ -72,7 +72,8 @@ typedef enum {
      * (or none), msgemm_run then takes the matrix form: the codes are decoded in registers and the
      * sum of Section 3.2 is formed by the matrix cores without tabulating its terms first (fp32 sums of exact products,
      * int32 for int8 X); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
-     * A value map installed later is served by the table kernels below, and so is every other AUTO problem. */
+     * A value map installed later is served by the table kernels below, and so is every other AUTO problem (above all a
+     * single fp32 column on a matrix of more than 32 Mi weights, and k <= 512 under very many rows, where they are faster). */
     MSGEMM_VARIANT_AUTO = 0,
     /* Two launches: L is written to device memory once and shared by all rows
      * (the arrangement of Section 4: one L, kept in cache between the phases); any d in 1..4. */
@@ -245,6 +246,10 @@ int msgemm_plan_codes8(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b,
  * entries the values are rounded to fp16.  The comparison entry point
  * msgemm_dequant_mfma_run refuses a plan with a custom map.  The map travels
  * in the arguments of each launch: launches already enqueued keep the old one.
+ * On a plan in the matrix form (AUTO) the first map other than the paper's
+ * allocates the table kernels' copy of the codes and workspace and fills them
+ * from the plan's codes (MSGEMM_ERR_ALLOC if that fails, and the plan stays as
+ * it was); the call returns when that is done.
  */
 int msgemm_plan_set_codebook(msgemm_plan_t* plan, const float* values16);
 
@@ -293,7 +298,9 @@ int msgemm_run(const msgemm_plan_t* plan, const void* X, int64_t ldx,
  * nothing.  Plans of the fused variants only (MSGEMM_ERR_UNSUPPORTED for
  * GLOBAL_LUT / GLOBAL_LUT_HALF) whose partial sums fit the array
  * (split_k * b * m rounded up to whole panels * 4 bytes <= 16 MiB, else
- * MSGEMM_ERR_UNSUPPORTED); the plan's device must be current
+ * MSGEMM_ERR_UNSUPPORTED; the matrix form adds its wavefronts' sums in LDS and
+ * needs the array only where k is cut into segments, at most 12.6 MB by the
+ * library's own choice); the plan's device must be current
  * (MSGEMM_ERR_INVALID_ARG).  All calls on one device share the array: calls
  * that overlap on a device -- different streams, different plans -- race.
  * Nothing in the array needs a particular value when a call starts.

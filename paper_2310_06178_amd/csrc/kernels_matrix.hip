@@ -226,6 +226,12 @@ __device__ __forceinline__ void lds_barrier()
 // kCols4 == 0, up to four columns (int8: eight): lane n loads column n / T for step n % T of a run only (T steps) -- one
 // load, nothing to transpose -- and every step has accumulators of its own, of which the rows of that step are the ones
 // that count.  They end up in the same lane: y(column q) is the sum over t of register t of accumulator t of lane group q.
+//
+// Measured (one launch in a graph, cold codes; in brackets the table kernels with their second launch where they have
+// one): 16384 x 4096 x 1 fp16 7.4 us = 4.5 TB/s (9.5; a launch that only reads the codes 6.7), 49152 x 12288 x 1 45.2 us =
+// 6.7 TB/s (51.7), 14336 x 4096 x 16 fp16 with scales 9.5 us (30), 8192 x 8192 x 16 int8 8.6 us (30), 4096 x 4096 x 4 fp32
+// 6.0 us (8.9), 8192 x 8192 E4M3 codes, one column, 13.0 us (18.0).  What is left at sixteen columns is the decoding: two
+// to three vector instructions per pair of weights against one MFMA for sixteen columns.
 template <typename XT, int R, int kCols4, int W, int D, bool kScaled, int F>
 __global__ void __launch_bounds__(W * 64)
 matrix_stream_kernel(MatrixArgs a)
@@ -508,6 +514,10 @@ matrix_stream_kernel(MatrixArgs a)
 //   * One barrier per step.  The operands of an MFMA step are read and decoded under the MFMAs of the one before it, also
 //     across the barrier: the two wavefronts of a SIMD leave it together, and what each did alone before its first MFMA
 //     would be a third of a step.
+// Measured: 28672 x 8192 x 64 bf16 with scales 52 us (table kernels 228-235), 49152 x 12288 x 64 fp16 87 us = 890 Tflop/s
+// (536-550).  The matrix cores are in use for 0.47 of the cycles there, the vector units for 0.34, at a clock of 1.8 GHz
+// (power; 2.3 under light loads).  Without its loads from memory the kernel takes 61 us.  Slower: twelve wavefronts of two
+// row tiles (119 us: registers, and the barrier gets longer); level: the operand slots turned by the step alone.
 template <typename XT, int R, int NT, bool kScaled>
 __global__ void __launch_bounds__(512)
 matrix_tile_kernel(MatrixArgs a)
@@ -743,7 +753,8 @@ matrix_tile_kernel(MatrixArgs a)
     }
 }
 
-// The segments' sums, in order.
+// The segments' sums, in order.  Bound by the trip to memory of a handful of loads (about 3 us with its launch), which a
+// segment has to win back: see segments_of in matrix_choose_shape.
 template <typename XT>
 __global__ void __launch_bounds__(256)
 matrix_reduce_kernel(MatrixArgs a, int segments)
@@ -763,7 +774,8 @@ matrix_reduce_kernel(MatrixArgs a, int segments)
     ((YT*)a.Y)[(int64_t)c * a.ldy + row] = to_output<YT, S>(s);
 }
 
-// Row-major codes -> the order above (inverse: back again).
+// Row-major codes -> the order above (inverse: back again).  Once per plan; 32 MiB in 65 us, bound by the row-major side,
+// where neighbouring lanes are a row apart.
 template <bool kInverse>
 __global__ void __launch_bounds__(256)
 matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs, int R,
