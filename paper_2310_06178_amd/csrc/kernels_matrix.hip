@@ -1013,10 +1013,12 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     const auto groups = [&](int r) { return (p.m + 16 * Wr * r - 1) / (16 * Wr * r); };
     const auto waves = [&](int r) { return tile ? 8 : width == 2 && r == 4 ? 8 : 4; };
     // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a wavefront
-    // keeps 16 runs (tile kernel: four steps; 12288 x 49152 x 64, 64 row groups: 228 us in one segment, 95 in four).
+    // keeps 16 runs (tile kernel: a workgroup 20, since the second launch and the sums' trip to memory and back take 10 to
+    // 15 us; 12288 x 49152 x 64, 64 row groups: 228 us in one segment, 95 in four; 8192 x 10240 x 64 in segments of 20 runs
+    // 27 us, of 40 29; but 16384 x 4096 x 64 28 in segments of 16, 21 uncut, int8 21 against 14.5).
     const auto segments_of = [&](int r) {
         int64_t n = 1;
-        while (groups(r) * passes * n * 2 <= p.cus && runs >= 2 * n * (tile ? 8 : waves(r) * 16)) n *= 2;
+        while (groups(r) * passes * n * 2 <= p.cus && runs >= 2 * n * (tile ? 20 : waves(r) * 16)) n *= 2;
         return n;
     };
     // Row tiles per wavefront: the work of the busiest compute unit, in row tiles for the streaming kernel, weighted by
