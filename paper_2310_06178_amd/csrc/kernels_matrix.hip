@@ -987,13 +987,21 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     if (runs * 16384 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
     // More than 16 columns: passes of the streaming kernel over 16 at a time while the codes of all passes are few (they
     // stay in the caches, and the passes run side by side), and for fp32; from there on the tile kernel, which decodes a
-    // code once for 64 columns.  us, passes against tile: 1024 x 1024 x 64 3.3 / 10.5, 8192 x 4096 x 64 15.5 / 19.1,
-    // 4096 x 14336 x 64 (112 MiB in four passes) 20.6 / 28.3; level at 8192 x 8192 x 64 (128 MiB), 28672 x 8192 x 32 57 / 38;
-    // with a short k, 49152 x 768 x 64 (72 MiB), 37 / 19.
+    // code once for 64 columns.  us, passes against tile: 1024 x 1024 x 64 3.3 / 10.5, 8192 x 4096 x 64 15.7 / 20,
+    // 4096 x 14336 x 64 (112 MiB in four passes) 19.6 / 25.6; level at 8192 x 8192 x 64 (128 MiB), 28672 x 8192 x 32 57 / 38;
+    // with a short k, 49152 x 768 x 64 (72 MiB), 37 / 19.  The line is lower where the tile kernel's row groups fill the
+    // device uncut and its column tiles are not mostly padding: 12288 x 2048 x 64 (48 MiB) 15.5 / 16.3, 14336 x 4096 x 24
+    // (56) 15.5 / 13.5, 16384 x 2048 x 64 (64) 20.7 / 16.6, 14336 x 4096 x 48 (84) 23.5 / 17.6, 12288 x 4096 x 64 (96) 26.5 / 21.1,
+    // 28672 x 4096 x 32 (112) 36 / 24; of columns five eighths are enough: 8192 x 4096 x 80 (two tiles of 64) 24.1 / 20.1,
+    // 16384 x 4096 x 20 (one of 32) 19.0 / 16.1; fewer were not measured.
     const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun && !bytes &&
                           !(p.x_dtype == MSGEMM_I8 && k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
-    const bool tile = tile_can && (asked && o.rows_per_lane ? o.rows_per_lane == 4
-                                                            : (p.b + 15) / 16 * code_bytes > ((int64_t)(runs >= 8 ? 112 : 32) << 20));
+    const int tile_tiles = p.b <= 32 ? 2 : p.b <= 48 ? 3 : 4;
+    const int64_t tile_passes = (p.b + 16 * tile_tiles - 1) / (16 * tile_tiles);
+    const bool fills = (p.m + 63) / 64 * tile_passes * 8 > (int64_t)5 * p.cus && p.b >= 10 * tile_tiles * tile_passes;
+    const bool tile = tile_can && (asked && o.rows_per_lane
+                                       ? o.rows_per_lane == 4
+                                       : (p.b + 15) / 16 * code_bytes > ((int64_t)(runs < 8 ? 32 : fills ? 48 : 112) << 20));
     // One fp32 column of 4-bit codes: decoding and three products per weight where the table kernels add once per pair
     // (4096 x 4096 5.5 us against 6.9, 8192 x 8192 11.0 against 10.3, 49152 x 12288 74 against 52; 8-bit codes, one
     // conversion for two, 12.5 against 17.0 at 8192 x 8192).
@@ -1007,8 +1015,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     const bool scaled = p.scale_group > 0;
     const int Wr = tile ? 4 : 1;
     const int width = tile ? 3 : compact ? 0 : p.b <= 8 ? 1 : 2;
-    p.mx_cols = tile ? (p.b <= 32 ? 2 : p.b <= 48 ? 3 : 4) : 2 * width;
-    const int64_t passes = tile ? (p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols) : (p.b + 15) / 16;
+    p.mx_cols = tile ? tile_tiles : 2 * width;
+    const int64_t passes = tile ? tile_passes : (p.b + 15) / 16;
     if (passes > 65535) return false;
     const auto groups = [&](int r) { return (p.m + 16 * Wr * r - 1) / (16 * Wr * r); };
     const auto waves = [&](int r) { return tile ? 8 : width == 2 && r == 4 ? 8 : 4; };
