@@ -191,15 +191,17 @@ struct MatrixArgs {
 
 // fp32 activations: four elements as the three bf16 parts x = h + m + l (8 bits each by truncation, exact).  The
 // differences are taken from the element clamped to the finite range: an infinite activation is infinite in its first
-// part and adds finite numbers in the others (as it does in a fp32 product), a NaN stays one.
+// part and adds finite numbers in the others (as it does in a fp32 product).  A NaN is made quiet first: the upper half of
+// one whose payload lies in the lower sixteen bits only would be that of an infinity.
 template <typename XT> constexpr int kOperands = sizeof(XT) == 4 ? 3 : 1;
 struct Split { v2u part[3]; };
 __device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
-__device__ __forceinline__ void split(const v4u& x, Split& s)
+__device__ __forceinline__ void split(v4u x, Split& s)
 {
     uint32_t m[4], l[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
+        x[e] = __float_as_uint(__builtin_canonicalizef(__uint_as_float(x[e])));
         const float v = __builtin_amdgcn_fmed3f(__uint_as_float(x[e]), -3.402823466e38f, 3.402823466e38f);
         const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
         m[e] = __float_as_uint(r);

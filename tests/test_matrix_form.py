@@ -90,6 +90,51 @@ def test_matrix_form_infinite_activations(xd, b):
     assert np.all(np.isfinite(y[: b - 1]))
 
 
+# an operand width of each kind (compact, 8, 16 columns, the tile kernel, passes of the streaming kernel), with and
+# without scales, in one segment and in several
+SPECIAL = [(b, sg, dict(o, batched_form=3)) for sg in (0, 128) for b, o in [
+    (1, {}), (6, {}), (13, {}), (13, {"batched_segments": 2}), (2, {"batched_segments": 3}), (20, {"rows_per_lane": 4}),
+    (37, {"rows_per_lane": 4, "batched_segments": 2}), (20, {"rows_per_lane": 8})]]
+
+
+@pytest.mark.parametrize("xd,bits", [("f32", 0x7f800001), ("f32", 0xff80ffff), ("f32", 0x7fc00000), ("f32", 0x7f810000),
+                                     ("f16", 0x7c01), ("f16", 0xfe00), ("bf16", 0xff81), ("bf16", 0x7fc0)])
+@pytest.mark.parametrize("b,sg,options", SPECIAL)
+def test_matrix_form_nan_activations(b, sg, options, xd, bits):
+    """A NaN, quiet or signalling, its payload in any bit, makes every output of its column a NaN (0 x NaN too), in a full
+    run of columns and in a ragged one, and no other column's."""
+    m, k = 70, 640 if sg else 642
+    codes = inputs.make_codes(m, k, seed=4)
+    scales = inputs.make_scales(m, k, sg, seed=6) if sg else None
+    for c, j in ((b - 1, k - 1), (0, 300)):
+        X = inputs.make_x(k, b, xd, seed=5)
+        X.view(np.uint32 if xd == "f32" else np.uint16)[c, j] = bits
+        out, _ = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO, options=options)
+        y = torch_io.to_f64(out)
+        assert np.all(np.isnan(y[c])) and np.all(np.isfinite(np.delete(y, c, axis=0)))
+
+
+@pytest.mark.parametrize("xd", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("b,sg,options", [s for s in SPECIAL if s[1] or "batched_segments" in s[2]])
+def test_matrix_form_infinite_activations_scaled_or_in_segments(b, sg, options, xd):
+    m, k = 70, 640 if sg else 642
+    codes = inputs.make_codes(m, k, seed=4)
+    scales = inputs.make_scales(m, k, sg, seed=6) if sg else None   # (positive)
+    X = inputs.make_x(k, b, "f32", seed=5)
+    X[b - 1, k - 2], X[0, 77] = -np.inf, np.inf
+    Xh = {"f32": X, "f16": X.astype(np.float16), "bf16": inputs.f32_to_bf16_bits(X)}[xd]
+    out, _ = run_gpu(codes, Xh, xd, scales, sg, 2, B.VARIANT_AUTO, options=options)
+    y = torch_io.to_f64(out)
+    terms = np.zeros((b, m))
+    for c, j in ((0, 77), (b - 1, k - 2)):
+        v = np.array([oracle.decode(int(c)) for c in codes[:, j // 2] >> (4 * (j & 1)) & 15], dtype=np.float64)
+        with np.errstate(invalid="ignore"):
+            terms[c] += X[c, j].astype(np.float64) * v
+    assert np.array_equal(np.isnan(y), np.isnan(terms))
+    hit = np.isinf(terms)
+    assert np.array_equal(y[hit], terms[hit]) and np.all(np.isfinite(y[terms == 0]))
+
+
 @pytest.mark.parametrize("xd,b,sg", [("f16", 1, 128), ("bf16", 5, 0), ("f32", 2, 0), ("i8", 16, 0)])
 def test_other_entry_points_on_a_matrix_form_plan(xd, b, sg):
     """The library's own choice for this problem is the matrix form: phase 2 alone, the entry point that allocates
