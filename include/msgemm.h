@@ -71,7 +71,8 @@ typedef enum {
     /* The library's choice.  With the paper's encoding of 4-bit codes, d = 2, scale blocks of whole runs of 128 columns
      * (or none), msgemm_run then takes the matrix form: the codes are decoded in registers and the
      * sum of Section 3.2 is formed by the matrix cores without tabulating its terms first (fp32 sums of exact products,
-     * int32 for int8 X); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
+     * int32 for int8 X; fp32 X of every magnitude exactly, but with elements under 2^-109, or with infinities or NaNs, up
+     * to three times slower); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
      * A value map installed later is served by the table kernels below, and so is every other AUTO problem (above all a
      * single fp32 column on a matrix of more than 32 Mi weights, and k <= 512 under very many rows, where they are faster). */
     MSGEMM_VARIANT_AUTO = 0,

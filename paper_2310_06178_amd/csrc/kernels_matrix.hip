@@ -114,7 +114,7 @@ template <> struct Policy<bf16_t> : Bf16Weights {
     static constexpr int kFrags = 4, kRaw = 4;
 };
 
-// fp32 activations: x = h + m + l in three bf16 pieces of eight bits each (by truncation, exact), three MFMAs per step.
+// fp32 activations: x = h + m + l in three bf16 pieces of eight bits each (see Split), three MFMAs per step.
 template <> struct Policy<float> : Bf16Weights {
     using acc_t = v4f;
     using out_t = float;
@@ -186,30 +186,58 @@ struct MatrixArgs {
     int seg_runs;          // full runs per segment (tile kernel: runs)
     int row_groups;
     int passes;            // passes over the columns of X
-    float factor;          // a power of two that the weight operands leave out (bf16 from 4-bit codes: value / 16)
+    float factor;          // a power of two that the weight operands leave out (bf16 activations, 4-bit codes: value / 16)
 };
 
-// fp32 activations: four elements as the three bf16 parts x = h + m + l (8 bits each by truncation, exact).  The
-// differences are taken from the element clamped to the finite range: an infinite activation is infinite in its first
-// part and adds finite numbers in the others (as it does in a fp32 product).  A NaN is made quiet first: the upper half of
-// one whose payload lies in the lower sixteen bits only would be that of an infinity.
+// fp32 activations: four elements as the three bf16 parts x = h + m + l, eight bits each by truncation.  Exact but for two
+// kinds of elements, which the kernel makes up for after its loop (`split` costs six instructions an element there):
+//   * bf16 ends at 2^-133, so the last part of an element under 2^-109 may lose bits.  The lower half of `lost` tells whether
+//     one did; split_lost gives those bits, 2^64 times as large, in the same form.
+//   * An infinity leaves a NaN in the second part, and so in every sum of its column.  split_any takes the differences from
+//     the element clamped to the finite range: an infinite activation is then infinite in its first part and adds finite
+//     numbers in the others (as it does in a fp32 product), and a NaN is made quiet first (the upper half of one whose
+//     payload lies in the lower sixteen bits only would be that of an infinity).
 template <typename XT> constexpr int kOperands = sizeof(XT) == 4 ? 3 : 1;
 struct Split { v2u part[3]; };
+constexpr float kLostUp = 0x1p64f, kLostUnit = 0x1p-64f;
 __device__ __forceinline__ uint32_t upper_halves(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
-__device__ __forceinline__ void split(v4u x, Split& s)
+__device__ __forceinline__ float upper_half(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
+__device__ __forceinline__ void split_finite(const v4u& x, const v4u& first, Split& s, uint32_t (&l)[4])
 {
-    uint32_t m[4], l[4];
+    uint32_t m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        m[e] = __float_as_uint(__uint_as_float(x[e]) - upper_half(x[e]));
+        l[e] = __float_as_uint(__uint_as_float(m[e]) - upper_half(m[e]));
+    }
+    s.part[0] = v2u{upper_halves(first[0], first[1]), upper_halves(first[2], first[3])};
+    s.part[1] = v2u{upper_halves(m[0], m[1]), upper_halves(m[2], m[3])};
+    s.part[2] = v2u{upper_halves(l[0], l[1]), upper_halves(l[2], l[3])};
+}
+__device__ __forceinline__ void split(const v4u& x, Split& s, uint32_t& lost)
+{
+    uint32_t l[4];
+    split_finite(x, x, s, l);
+    lost |= l[0] | l[1] | l[2] | l[3];
+}
+__device__ __forceinline__ void split_any(v4u x, Split& s, uint32_t (&l)[4])
+{
+    v4u v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         x[e] = __float_as_uint(__builtin_canonicalizef(__uint_as_float(x[e])));
-        const float v = __builtin_amdgcn_fmed3f(__uint_as_float(x[e]), -3.402823466e38f, 3.402823466e38f);
-        const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
-        m[e] = __float_as_uint(r);
-        l[e] = __float_as_uint(r - __uint_as_float(m[e] & 0xffff0000u));
+        v[e] = __float_as_uint(__builtin_amdgcn_fmed3f(__uint_as_float(x[e]), -3.402823466e38f, 3.402823466e38f));
     }
-    s.part[0] = v2u{upper_halves(x[0], x[1]), upper_halves(x[2], x[3])};
-    s.part[1] = v2u{upper_halves(m[0], m[1]), upper_halves(m[2], m[3])};
-    s.part[2] = v2u{upper_halves(l[0], l[1]), upper_halves(l[2], l[3])};
+    split_finite(v, x, s, l);
+}
+__device__ __forceinline__ void split_lost(const v4u& x, Split& s)
+{
+    uint32_t l[4], none[4];
+    split_any(x, s, l);
+    v4u y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = __float_as_uint((__uint_as_float(l[e]) - upper_half(l[e])) * kLostUp);
+    split_finite(y, y, s, none);
 }
 
 // LDS only: the loads in flight to registers are not waited for
@@ -257,7 +285,8 @@ matrix_stream_kernel(MatrixArgs a)
     constexpr int kRedWords = W * kCols * kPitch;
     __shared__ __align__(16) uint32_t lds[W * kXWords > kRedWords ? W * kXWords : kRedWords];
 
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, q = lane >> 4;
     const int rg = blockIdx.x;
     const int col0 = blockIdx.z * kCols;               // passes of kCols columns
@@ -272,14 +301,18 @@ matrix_stream_kernel(MatrixArgs a)
 
     // where this lane's pieces of a run of X start (columns past the last one repeat it: their sums are not used), and
     // which column of the run the first element is
-    const int first = kCompact ? 32 * q + (n % T) * (kInt ? 16 : 8) : lane % kLanesPerCol * kPiece;
+    int first;
     const XT* xcol[kCompact ? 1 : kRaw];
+    auto locate = [&] {
+        first = kCompact ? 32 * (lane >> 4) + (lane & 15) % T * (kInt ? 16 : 8) : lane % kLanesPerCol * kPiece;
 #pragma unroll
-    for (int i = 0; i < (kCompact ? 1 : kRaw); ++i) {
-        int c = kCompact ? n / T : i * kColsPerLoad + lane / kLanesPerCol;
-        c = c < ncols ? c : ncols - 1;
-        xcol[i] = (const XT*)a.X + (int64_t)(col0 + c) * a.ldx + first;
-    }
+        for (int i = 0; i < (kCompact ? 1 : kRaw); ++i) {
+            int c = kCompact ? (lane & 15) / T : i * kColsPerLoad + lane / kLanesPerCol;
+            c = c < ncols ? c : ncols - 1;
+            xcol[i] = (const XT*)a.X + (int64_t)(col0 + c) * a.ldx + first;
+        }
+    };
+    locate();
 
     struct Stage {
         v4u codes[R * kVecs];
@@ -334,7 +367,7 @@ matrix_stream_kernel(MatrixArgs a)
     // so that the pieces of a column, written side by side, fall on different banks (and so do the columns of a read).
     uint32_t* const xs = lds + wave * kXWords;
     auto slot = [](int op, int t, int qq, int col) { return ((op * T + t) * 64 + qq * 16 + (col ^ (qq * T + t))) * 4; };
-    auto put_x = [&](const Stage& st) {
+    auto put_x = [&](const Stage& st, auto split_one) {
         const int j = lane % kLanesPerCol;
 #pragma unroll
         for (int i = 0; i < kRaw; ++i) {
@@ -342,7 +375,7 @@ matrix_stream_kernel(MatrixArgs a)
             if constexpr (sizeof(XT) == 4) {
                 // half a slot: elements 4 (j & 1) .. + 3 of the 8 of step (j / 2) % 4
                 Split s;
-                split(st.x[i], s);
+                split_one(st.x[i], s);
 #pragma unroll
                 for (int op = 0; op < 3; ++op) *(v2u*)&xs[slot(op, (j >> 1) & 3, j >> 3, col) + 2 * (j & 1)] = s.part[op];
             } else {
@@ -365,22 +398,35 @@ matrix_stream_kernel(MatrixArgs a)
         sum[r] = 0.0f;
     }
 
-    auto consume = [&](const Stage& st) {
-        acc_t blk[R][kAcc];
-        v4u x[kOps];
+    // a run's activations in operand order: in registers (compact) or in the wavefront's LDS buffer
+    v4u x[kOps];
+    auto operands = [&](const Stage& st, auto split_one) {
         if constexpr (kCompact && sizeof(XT) == 4) {
             Split s0, s1;
-            split(st.x[0], s0);
-            split(st.x[kRaw - 1], s1);
+            split_one(st.x[0], s0);
+            split_one(st.x[kRaw - 1], s1);
 #pragma unroll
             for (int op = 0; op < kOps; ++op) x[op] = v4u{s0.part[op].x, s0.part[op].y, s1.part[op].x, s1.part[op].y};
         } else if constexpr (kCompact) {
             x[0] = st.x[0];
         } else {
-            put_x(st);
+            put_x(st, split_one);
         }
+    };
+    // ... times its weights, `unit` times added to the sums (fp32 only; 1 for the others)
+    auto multiply = [&](const Stage& st, float unit) {
+        acc_t blk[R][kAcc];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
+            // (fp32: a step's operands are read together, ahead of its decoding; one by one, which the compiler does to save
+            // registers, 4096 x 4096 x 8 takes 9.4 us instead of 7.5.  The widest instance has two wavefronts a SIMD and none
+            // to spare: 14336 x 4096 x 16 15.4 one by one, 16.5 together.)
+            constexpr bool kTogether = !kCompact && kOps > 1 && R * kCols4 < 16;
+            if constexpr (kTogether) {
+#pragma unroll
+                for (int op = 0; op < kOps; ++op) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
+                __builtin_amdgcn_sched_barrier(0);
+            }
             v4u w[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -389,7 +435,7 @@ matrix_stream_kernel(MatrixArgs a)
             }
 #pragma unroll
             for (int op = kOps - 1; op >= 0; --op) {   // (the smallest part first)
-                if constexpr (!kCompact) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
+                if constexpr (!kCompact && !kTogether) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     acc_t& to = kDirect ? acc[r][kCompact ? t : 0] : blk[r][kCompact ? t : 0];
@@ -401,7 +447,8 @@ matrix_stream_kernel(MatrixArgs a)
         if constexpr (!kDirect) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const float s = kScaled ? __half2float(__ushort_as_half((uint16_t)(st.q[r / 2] >> (16 * (r & 1))))) : 1.0f;
+                float s = kScaled ? __half2float(__ushort_as_half((uint16_t)(st.q[r / 2] >> (16 * (r & 1))))) : 1.0f;
+                if constexpr (sizeof(XT) == 4) s *= unit;
                 if constexpr (kCompact) {
                     sum[r] = fmaf(s, (blk[r][0][0] + blk[r][1 % kAcc][1]) + (blk[r][2 % kAcc][2] + blk[r][3 % kAcc][3]), sum[r]);
                 } else {
@@ -410,6 +457,14 @@ matrix_stream_kernel(MatrixArgs a)
                 }
             }
         }
+    };
+    // fp32: the weight operands' factor goes in with each run, so that the sums are held at their own magnitude
+    constexpr float kUnit = sizeof(XT) == 4 && F == kInt4 ? 16.0f : 1.0f;
+    uint32_t lost = 0;                                 // bits that split has left out
+    auto consume = [&](const Stage& st) {
+        if constexpr (sizeof(XT) == 4) operands(st, [&](const v4u& v, Split& s) { split(v, s, lost); });
+        else operands(st, 0);
+        multiply(st, kUnit);
     };
 
     // Wavefront `wave` takes runs wave, wave + W, ... of the segment's full ones; the ragged one goes to the next in turn,
@@ -463,6 +518,56 @@ matrix_stream_kernel(MatrixArgs a)
             if (it + d < mine) consume(ring[d]);
     }
     if (tail) consume(tail_stage);
+    if constexpr (sizeof(XT) == 4) {
+        // Infinities or NaNs (both have left NaNs in the sums): all over again.  Then what very small activations have lost.
+        // Nothing of this is in the way otherwise: a look per run instead would cost 2 to 8 percent.
+        bool nan = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (kCompact) nan |= sum[r] != sum[r];
+            else
+#pragma unroll
+                for (int i = 0; i < 4; ++i) nan |= 4 * q < kCols && acc[r][0][i] != acc[r][0][i];
+        }
+        const bool again = __builtin_amdgcn_ballot_w64(nan) != 0;
+        const bool some = __builtin_amdgcn_ballot_w64(nan || (lost & 0xffffu) != 0) != 0;
+        if (again) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                sum[r] = 0.0f;
+                acc[r][0] = acc_t{0, 0, 0, 0};
+            }
+        }
+        const int last = run0 + wave + (mine - 1 + (tail ? 1 : 0)) * W;
+        if (some) {
+            asm volatile("" : "+v"(lane));             // (the addresses are worked out again rather than kept through the loop)
+            locate();
+        }
+        constexpr int kAtOnce = kCompact ? 4 : 2;      // runs requested together
+        for (int pass = again ? 0 : 1; some && pass < 2; ++pass) {
+#pragma unroll 1
+            for (int run = run0 + wave; run <= last; run += kAtOnce * W) {
+                Stage st[kAtOnce];
+#pragma unroll
+                for (int d = 0; d < kAtOnce; ++d) {
+                    const int r = run + d * W <= last ? run + d * W : last;
+                    load_codes_of(st[d], r, true);
+                    if (r < a.full_runs) load_x(st[d], r);
+                    else load_x_tail(st[d]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int d = 0; d < kAtOnce; ++d) {
+                    if (run + d * W > last) break;
+                    if (pass == 0) operands(st[d], [](const v4u& v, Split& s) { uint32_t l[4]; split_any(v, s, l); });
+                    else operands(st[d], [](const v4u& v, Split& s) { split_lost(v, s); });
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(st[d], pass == 0 ? kUnit : kUnit * kLostUnit);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
     shift_back();
 
     // the wavefronts' sums, [wavefront][column][row]
@@ -501,7 +606,7 @@ matrix_stream_kernel(MatrixArgs a)
             a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(s);
             continue;
         }
-        if constexpr (!kInt && !(F == kInt4 && __is_same(XT, __half))) s *= a.factor;
+        if constexpr (!kInt && !(F == kInt4 && !__is_same(XT, bf16_t))) s *= a.factor;
         ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(s);
     }
 }
@@ -1137,7 +1242,7 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
     a.row_groups = (int)p.row_blocks;
     a.passes = p.mx_tile_kernel ? (int)((p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols)) : (int)((p.b + 15) / 16);
     a.div_block = make_fastdiv(group > 0 ? (uint32_t)(group / kRun) : 1u);
-    a.factor = p.codes8 ? p.mx_factor : p.x_dtype == MSGEMM_F16 ? 1.0f : 16.0f;
+    a.factor = p.codes8 ? p.mx_factor : p.x_dtype == MSGEMM_BF16 ? 16.0f : 1.0f;
     if (p.codes8) {
         switch (p.x_dtype) {
         case MSGEMM_F16: return launch_for_format<__half>(p, a, s);

@@ -1,7 +1,7 @@
 """The matrix form of msgemm_run (codes decoded in registers, sums on the matrix cores), against the CPU oracle at the
 sizes where its kernels can go wrong: edges of the 16-row tiles and of the 128-column runs, ragged last runs of a few
 columns, every operand width (compact, 8, 16 and up to 64 columns, column passes), k cut into segments, unaligned activations,
-infinities."""
+infinities, NaNs, activations near the ends of their range."""
 import ctypes
 
 import numpy as np
@@ -11,7 +11,7 @@ import torch
 import oracle
 from paper_2310_06178_amd import binding as B
 from paper_2310_06178_amd import inputs, torch_io
-from test_gpu_parity import NONUNIFORM, Y_OF_X, check, elem_bound, oracle_y, run_gpu
+from test_gpu_parity import ABS_FLOOR, NONUNIFORM, TOL, U_OUT, Y_OF_X, check, elem_bound, oracle_y, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -88,6 +88,76 @@ def test_matrix_form_infinite_activations(xd, b):
     v = np.array([oracle.decode(int(c)) for c in codes[:, 77 // 2] >> 4], dtype=np.float64)
     assert np.all(np.isnan(y[b - 1][v == 0])) and np.all(y[b - 1][v != 0] == np.inf * v[v != 0])
     assert np.all(np.isfinite(y[: b - 1]))
+
+
+WIDTHS_F32 = [(b, sg, dict(o, batched_form=3)) for sg in (0, 128) for b, o in [
+    (1, {}), (6, {}), (13, {}), (13, {"batched_segments": 2}), (2, {"batched_segments": 3}), (20, {}),
+    (4, {"panels_per_workgroup": 2}), (4, {"panels_per_workgroup": 4}), (16, {"panels_per_workgroup": 2}),
+    (16, {"panels_per_workgroup": 4})]]
+
+
+@pytest.mark.parametrize("xd,magnitude", [("f32", 1e-30), ("f32", 1e-34), ("f32", 1e-36), ("f32", 3e-38), ("f32", 1e-40),
+                                          ("f32", 1e37), ("bf16", 1e-37), ("bf16", 1e37)])
+@pytest.mark.parametrize("b,sg,options", WIDTHS_F32)
+def test_matrix_form_activations_of_any_magnitude(b, sg, options, xd, magnitude):
+    """Activations near the ends of the range, subnormal ones among them: the bounds are those of ordinary ones (fp32: the
+    products of the three parts are exact wherever the element is)."""
+    m, k = 70, 1280 if sg else 1282
+    codes = inputs.make_codes(m, k, seed=4)
+    scales = inputs.make_scales(m, k, sg, seed=6) if sg else None
+    X = (inputs.make_x(k, b, "f32", seed=5) * np.float32(magnitude if magnitude < 1 else magnitude / 64)).astype(np.float32)
+    if xd == "bf16":
+        X = inputs.f32_to_bf16_bits(X)
+    out, _ = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO, options=options, ldx_pad=3)
+    ref, bound = oracle_y(codes, X, xd, scales, sg), elem_bound(codes, X, xd, scales, sg)
+    if magnitude < 1e-30:
+        # results that are subnormal themselves: every rounding of a sum may be half a step of the format, with k / 32 + 8
+        # of them per output (one per run and wavefront, and those inside an instruction)
+        bound = bound + (k // 32 + 8) * 2.0 ** -150
+        y = torch_io.to_f64(out)
+        assert np.all(np.abs(y - ref) <= bound + U_OUT[xd] * 1.01 * np.abs(ref) + ABS_FLOOR[xd])
+        if magnitude > 1e-39 and not sg:
+            assert oracle.rel_l2(y, ref) <= TOL[xd]
+    else:
+        check(out, ref, xd, f"magnitude {magnitude}", bound)
+
+
+@pytest.mark.parametrize("b,sg,options", [w for w in WIDTHS_F32 if w[0] > 1])
+def test_matrix_form_infinity_beside_very_small_activations(b, sg, options):
+    m, k = 70, 1280 if sg else 1282
+    codes = inputs.make_codes(m, k, seed=4)
+    scales = inputs.make_scales(m, k, sg, seed=6) if sg else None
+    X = (inputs.make_x(k, b, "f32", seed=5) * np.float32(1e-35)).astype(np.float32)
+    ref, bound = oracle_y(codes, X, "f32", scales, sg), elem_bound(codes, X, "f32", scales, sg)
+    X[b - 1, 500] = np.inf
+    out, _ = run_gpu(codes, X, "f32", scales, sg, 2, B.VARIANT_AUTO, options=options)
+    check(np.ascontiguousarray(out[:-1]), ref[:-1], "f32", "other columns", bound[:-1])
+    v = np.array([oracle.decode(int(c)) for c in codes[:, 250] & 15], dtype=np.float64)
+    assert np.array_equal(np.isnan(out[-1]), v == 0) and np.all(out[-1][v != 0] == np.inf * v[v != 0])
+
+
+@pytest.mark.parametrize("b,sg,options", WIDTHS_F32)
+def test_matrix_form_fp32_single_activations_are_exact(b, sg, options):
+    """One activation at a time among zeros, from the smallest subnormal to the largest numbers, with patterns that fill
+    all three parts: a product with a code is exact where fp32 can hold it, else within the step that two roundings can
+    make.  A large one among codes of zero and other magnitudes in the other columns of X do not change that."""
+    m, k = 16, 256
+    codes = np.zeros((m, k // 2), dtype=np.uint8)
+    codes[:, 36] = np.arange(16) | np.arange(16) << 4        # columns 72 and 73
+    scales = np.full((m, k // sg), 0.5, dtype=np.float16) if sg else None
+    patterns = [1 << i for i in (0, 1, 7, 8, 15, 16, 22)] + [0x00000fff, 0x000abcde, 0x007fffff, 0x00891a29, 0x00ffffff, 0x01fedcbb,
+                                                            0x08abcdef, 0x0bffffff, 0x1f765432, 0x3f800001, 0x7cabcdef]
+    value = np.array([oracle.decode(i) for i in range(16)], dtype=np.float64)
+    for n in range(0, len(patterns), 1 if b == 1 else b):
+        X = np.zeros((b, k), dtype=np.uint32)
+        mine = (patterns + patterns)[n:n + b]
+        X[:, 72], X[:, 200] = mine, 0x7cffffff               # (the second meets codes of zero)
+        X = X.view(np.float32)
+        out, _ = run_gpu(codes, X, "f32", scales, sg, 2, B.VARIANT_AUTO, options=options)
+        ref = X[:, 72].astype(np.float64)[:, None] * value[None, :] * (0.5 if sg else 1.0)
+        held = ref.astype(np.float32).astype(np.float64) == ref
+        step = np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
+        assert np.all(np.abs(out - ref) <= np.where(held, 0.0, step)), [hex(p) for p in mine]
 
 
 # an operand width of each kind (compact, 8, 16 columns, the tile kernel, passes of the streaming kernel), with and
