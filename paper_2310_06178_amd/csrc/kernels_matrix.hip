@@ -190,7 +190,7 @@ struct MatrixArgs {
 };
 
 // fp32 activations: four elements as the three bf16 parts x = h + m + l, eight bits each by truncation.  Exact but for two
-// kinds of elements, which the kernel makes up for after its loop (`split` costs six instructions an element there):
+// kinds of elements, which the kernel makes up for after its loop (`split` takes six instructions an element in it):
 //   * bf16 ends at 2^-133, so the last part of an element under 2^-109 may lose bits.  The lower half of `lost` tells whether
 //     one did; split_lost gives those bits, 2^64 times as large, in the same form.
 //   * An infinity leaves a NaN in the second part, and so in every sum of its column.  split_any takes the differences from
@@ -219,6 +219,7 @@ __device__ __forceinline__ void split(const v4u& x, Split& s, uint32_t& lost)
     uint32_t l[4];
     split_finite(x, x, s, l);
     lost |= l[0] | l[1] | l[2] | l[3];
+    asm volatile("" : "+v"(lost));   // (here and now: the compiler would keep all these until the end of the loop)
 }
 __device__ __forceinline__ void split_any(v4u x, Split& s, uint32_t (&l)[4])
 {
@@ -414,7 +415,7 @@ matrix_stream_kernel(MatrixArgs a)
         }
     };
     // ... times its weights, `unit` times added to the sums (fp32 only; 1 for the others)
-    auto multiply = [&](const Stage& st, float unit) {
+    auto multiply = [&](const Stage& st, float unit, auto in_steps) {
         acc_t blk[R][kAcc];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -427,6 +428,7 @@ matrix_stream_kernel(MatrixArgs a)
                 for (int op = 0; op < kOps; ++op) x[op] = *(const v4u*)&xs[slot(op, t, q, n)];
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (decltype(in_steps)::value) __builtin_amdgcn_sched_barrier(0);
             v4u w[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -461,10 +463,18 @@ matrix_stream_kernel(MatrixArgs a)
     // fp32: the weight operands' factor goes in with each run, so that the sums are held at their own magnitude
     constexpr float kUnit = sizeof(XT) == 4 && F == kInt4 ? 16.0f : 1.0f;
     uint32_t lost = 0;                                 // bits that split has left out
-    auto consume = [&](const Stage& st) {
-        if constexpr (sizeof(XT) == 4) operands(st, [&](const v4u& v, Split& s) { split(v, s, lost); });
-        else operands(st, 0);
-        multiply(st, kUnit);
+    // (outside the loop the widest fp32 instance would run out of registers if the compiler did all steps at once)
+    constexpr std::bool_constant<sizeof(XT) == 4 && kScaled && R * kCols4 >= 16> kInSteps;
+    auto consume = [&](const Stage& st, auto in_steps) {
+        if constexpr (sizeof(XT) == 4) {
+            operands(st, [&](const v4u& v, Split& s) {
+                split(v, s, lost);
+                if constexpr (decltype(in_steps)::value) __builtin_amdgcn_sched_barrier(0);
+            });
+        } else {
+            operands(st, 0);
+        }
+        multiply(st, kUnit, in_steps);
     };
 
     // Wavefront `wave` takes runs wave, wave + W, ... of the segment's full ones; the ragged one goes to the next in turn,
@@ -503,7 +513,7 @@ matrix_stream_kernel(MatrixArgs a)
         for (; it + D <= mine; it += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                consume(ring[d]);
+                consume(ring[d], std::false_type{});
                 const int next = it + d + D;
                 const int run = run0 + wave + next * W;
                 load_codes_of(ring[d], run, next < mine);
@@ -515,55 +525,53 @@ matrix_stream_kernel(MatrixArgs a)
         }
 #pragma unroll
         for (int d = 0; d < D - 1; ++d)
-            if (it + d < mine) consume(ring[d]);
+            if (it + d < mine) consume(ring[d], kInSteps);
     }
-    if (tail) consume(tail_stage);
+    if (tail) consume(tail_stage, kInSteps);
     if constexpr (sizeof(XT) == 4) {
         // Infinities or NaNs (both have left NaNs in the sums): all over again.  Then what very small activations have lost.
         // Nothing of this is in the way otherwise: a look per run instead would cost 2 to 8 percent.
-        bool nan = false;
+        float all = 0.0f;                              // (not a number if one of the sums is not)
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if constexpr (kCompact) nan |= sum[r] != sum[r];
-            else
-#pragma unroll
-                for (int i = 0; i < 4; ++i) nan |= 4 * q < kCols && acc[r][0][i] != acc[r][0][i];
+            if constexpr (kCompact) all += sum[r];
+            else all += (acc[r][0][0] + acc[r][0][1]) + (acc[r][0][2] + acc[r][0][3]);
         }
-        const bool again = __builtin_amdgcn_ballot_w64(nan) != 0;
-        const bool some = __builtin_amdgcn_ballot_w64(nan || (lost & 0xffffu) != 0) != 0;
-        if (again) {
+        const bool nan = (kCompact || 4 * q < kCols) && all != all;
+        if (__builtin_amdgcn_ballot_w64(nan || (lost & 0xffffu) != 0)) {
+            const bool again = __builtin_amdgcn_ballot_w64(nan) != 0;
+            if (again) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                sum[r] = 0.0f;
-                acc[r][0] = acc_t{0, 0, 0, 0};
-            }
-        }
-        const int last = run0 + wave + (mine - 1 + (tail ? 1 : 0)) * W;
-        if (some) {
-            asm volatile("" : "+v"(lane));             // (the addresses are worked out again rather than kept through the loop)
-            locate();
-        }
-        constexpr int kAtOnce = kCompact ? 4 : 2;      // runs requested together
-        for (int pass = again ? 0 : 1; some && pass < 2; ++pass) {
-#pragma unroll 1
-            for (int run = run0 + wave; run <= last; run += kAtOnce * W) {
-                Stage st[kAtOnce];
-#pragma unroll
-                for (int d = 0; d < kAtOnce; ++d) {
-                    const int r = run + d * W <= last ? run + d * W : last;
-                    load_codes_of(st[d], r, true);
-                    if (r < a.full_runs) load_x(st[d], r);
-                    else load_x_tail(st[d]);
+                for (int r = 0; r < R; ++r) {
+                    sum[r] = 0.0f;
+                    acc[r][0] = acc_t{0, 0, 0, 0};
                 }
-                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int last = run0 + wave + (mine - 1 + (tail ? 1 : 0)) * W;
+            asm volatile("" : "+v"(lane));                 // (the addresses are worked out again rather than kept through the loop)
+            locate();
+            constexpr int kAtOnce = kCompact ? 4 : 1;      // runs requested together
+            for (int pass = again ? 0 : 1; pass < 2; ++pass) {
+#pragma unroll 1
+                for (int run = run0 + wave; run <= last; run += kAtOnce * W) {
+                    Stage st[kAtOnce];
 #pragma unroll
-                for (int d = 0; d < kAtOnce; ++d) {
-                    if (run + d * W > last) break;
-                    if (pass == 0) operands(st[d], [](const v4u& v, Split& s) { uint32_t l[4]; split_any(v, s, l); });
-                    else operands(st[d], [](const v4u& v, Split& s) { split_lost(v, s); });
+                    for (int d = 0; d < kAtOnce; ++d) {
+                        const int r = run + d * W <= last ? run + d * W : last;
+                        load_codes_of(st[d], r, true);
+                        if (r < a.full_runs) load_x(st[d], r);
+                        else load_x_tail(st[d]);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
-                    multiply(st[d], pass == 0 ? kUnit : kUnit * kLostUnit);
-                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int d = 0; d < kAtOnce; ++d) {
+                        if (run + d * W > last) break;
+                        if (pass == 0) operands(st[d], [](const v4u& v, Split& s) { uint32_t l[4]; split_any(v, s, l); });
+                        else operands(st[d], [](const v4u& v, Split& s) { split_lost(v, s); });
+                        __builtin_amdgcn_sched_barrier(0);
+                        multiply(st[d], pass == 0 ? kUnit : kUnit * kLostUnit, std::true_type{});
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
         }
