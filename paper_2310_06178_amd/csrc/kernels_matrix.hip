@@ -23,6 +23,9 @@
 #include "msgemm_internal.h"
 
 #include <math.h>
+
+#include <algorithm>
+#include <iterator>
 #include <type_traits>
 
 namespace msgemm {
@@ -1083,6 +1086,55 @@ void matrix_find_format(Plan& p, const float* values)
     }
 }
 
+namespace {
+
+// A short k under many rows: a workgroup of the matrix form lives for a run or two per wavefront, and the table kernels'
+// larger workgroups go through such a matrix faster.  The lines beyond which they do, in rows (times passes over 16 columns
+// of X) per compute unit; each lies between shapes measured on its two sides.  us, tables / matrix form: one fp16 column,
+// 49152 x 128 4.9 / 4.1, 65536 x 128 5.0 / 5.2, 300000 x 128 6.3 / 18; 65536 x 256 8.1 / 6.1, 100000 x 256 6.5 / 8.4; 180000 x
+// 640 level, 300000 x 640 25 / 29, 600000 x 1024 level, 1000003 x 1024 78 / 102.  Eight columns: 49152 x 128 6.5 / 5.3, 65536 x
+// 128 6.6 / 7.3; 180000 x 640 1.14 : 1, 600000 x 640 71 / 92.  More columns: 24576 x 128 x 33 1.9 : 1, 57000 x 128 x 48 12.9 / 22.6;
+// 49152 x 64 x 33 1.5 : 1, 57000 x 64 x 48 10.2 / 23.2; 40000 x 256 x 48 1.2 : 1, 80000 x 256 x 48 21.8 / 34.4; 100000 x 384 x 32 30 / 39.
+// A k that is no whole number of runs adds loads of single elements and counts for more: 156556 x 754 15.8 / 17.3, int8
+// 180000 x 640 1.3 : 1 but 182415 x 692 19.2 / 23.0.
+enum { kHalf = 1, kFloat = 2, kBytes = 4, kAny = 7, kRagged = 8 };  // types of X: fp16 and bf16, fp32, int8; k % 128 != 0 only
+struct ShortLine { int k_from, k_to, b_from, b_to, types, rows; };
+constexpr int kAllColumns = 1 << 30;
+constexpr ShortLine kShort4[] = {
+    // k up to a run, two runs
+    {1, 128, 1, 1, kAny, 240},            {1, 128, 2, 2, kBytes, 384},          {1, 256, 1, 1, kBytes, 384},
+    {1, 256, 1, 2, kHalf | kFloat, 288},  {1, 256, 2, 4, kFloat, 240},          {1, 128, 3, 4, kHalf, 352},
+    {1, 128, 5, 8, kHalf, 248},           {1, 64, 5, 8, kFloat, 240},           {1, 128, 9, 16, kHalf, 352},
+    {1, 128, 9, 16, kBytes, 400},         {1, 32, 9, 32, kFloat, 100},          {1, 64, 9, kAllColumns, kFloat, 184},
+    {1, 128, 9, 16, kFloat, 192},         {65, 128, 17, 32, kFloat, 150},       {1, 64, 17, 32, kBytes, 432},
+    {1, 64, 17, kAllColumns, kAny, 600},  {65, 128, 17, kAllColumns, kAny, 352},
+    {129, 192, 17, kAllColumns, kAny, 432},  {193, 256, 17, kAllColumns, kAny, 600},
+    // up to eight
+    {257, 320, 17, 48, kAny, 640},        {321, 384, 17, 32, kAny, 640},        {385, 512, 17, 32, kHalf, 2048},
+    {513, 768, 1, 1, kHalf | kRagged, 600},  {513, 768, 1, 1, kBytes | kRagged, 416},  {513, 768, 2, 8, kBytes | kRagged, 640},
+    {513, 768, 1, 1, kHalf | kFloat, 1024},  {513, 768, 1, 1, kBytes, 3072},    {769, 1024, 1, 1, kHalf | kFloat, 3072},
+    {513, 1024, 2, 2, kFloat, 3072},      {513, 768, 2, 4, kHalf, 3072},        {513, 768, 5, 8, kHalf, 900}, 
+    {769, 1024, 5, 8, kHalf, 3072},       {513, 768, 9, 32, kAny | kRagged, 1536},  {513, 640, 9, 16, kHalf | kBytes, 3072},
+};
+constexpr ShortLine kShort8[] = {  // 8-bit codes
+    {1, 64, 1, 1, kAny, 184},    {65, 128, 1, 1, kAny, 288},    {129, 256, 1, 1, kAny, 448},  {257, 512, 1, 1, kAny, 288},
+    {513, 768, 1, 1, kAny, 320}, {769, 1024, 1, 1, kAny, 3072}, {1, 32, 5, 16, kFloat, 320},  {1, 64, 2, 2, kAny, 288},
+    {1, 64, 17, kAllColumns, kAny, 640}, {65, 96, 33, kAllColumns, kAny, 900},
+};
+bool short_k(const Plan& p, int64_t k)
+{
+    const int type = p.x_dtype == MSGEMM_F32 ? kFloat : p.x_dtype == MSGEMM_I8 ? kBytes : kHalf;
+    const int64_t rows = p.m * ((p.b + 15) / 16);
+    const auto beyond = [&](const ShortLine& l) {
+        return k >= l.k_from && k <= l.k_to && p.b >= l.b_from && p.b <= l.b_to && (type & l.types) && rows > (int64_t)l.rows * p.cus &&
+               (!(l.types & kRagged) || k % kRun != 0);
+    };
+    if (p.codes8) return std::any_of(std::begin(kShort8), std::end(kShort8), beyond);
+    return std::any_of(std::begin(kShort4), std::end(kShort4), beyond);
+}
+
+}  // namespace
+
 // Whether the library's own choice for a plan is the matrix form, and its shape.
 bool matrix_choose_shape(Plan& p, int requested_variant)
 {
@@ -1121,10 +1173,10 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     // (4096 x 4096 5.5 us against 6.9, 8192 x 8192 11.0 against 10.3, 49152 x 12288 74 against 52; 8-bit codes, one
     // conversion for two, 12.5 against 17.0 at 8192 x 8192).
     if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && p.m * k > ((int64_t)32 << 20) && !asked) return false;
-    // A short k under very many rows: a workgroup lives for one or two loads per wavefront, and the table kernels' larger
-    // workgroups go through such a matrix faster (300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; at 100000
-    // rows and 512 columns the matrix form is ahead, 17.2 against 20.5 with eight columns of X).
+    // (streaming kernel, 300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; ahead at 100000 rows and 512 columns,
+    // 17.2 against 20.5 with eight columns of X)
     if (!tile && k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
+    if (short_k(p, k) && !asked) return false;
 
     const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
     const bool scaled = p.scale_group > 0;

@@ -245,6 +245,44 @@ def test_other_entry_points_on_a_matrix_form_plan(xd, b, sg):
         B.msgemm_destroy(plan)
 
 
+CUS = 256
+CHOICES = [
+    # m, k, b, xd, matrix form: the two sides of some of the lines of the library's own choice
+    (32768, 1024, 1, "f32", True), (32896, 1024, 1, "f32", False),      # one fp32 column: 32 Mi weights
+    (32896, 1024, 2, "f32", True),
+    (240 * CUS, 128, 1, "f16", True), (240 * CUS + 1, 128, 1, "f16", False), (240 * CUS + 1, 258, 1, "f16", True),
+    (512 * CUS, 512, 5, "f16", True), (512 * CUS + 1, 512, 5, "f16", False), (512 * CUS + 1, 514, 5, "f16", True),
+    (200 * CUS, 64, 48, "f16", True), (200 * CUS + 1, 64, 48, "f16", False),    # (three passes over 16 columns)
+    (117 * CUS + 1, 66, 48, "f16", True), (118 * CUS, 66, 48, "f16", False),
+    (600 * CUS, 514, 1, "bf16", True), (600 * CUS + 1, 514, 1, "bf16", False), (600 * CUS + 1, 640, 1, "bf16", True),
+    (1024 * CUS, 640, 1, "f16", True), (1024 * CUS + 1, 640, 1, "f16", False),
+    (64, 256, 3, "f16", True),
+]
+
+
+@pytest.mark.parametrize("m,k,b,xd,matrix", CHOICES)
+def test_where_the_matrix_form_is_the_librarys_own_choice(m, k, b, xd, matrix):
+    if torch.cuda.get_device_properties(0).multi_processor_count != CUS:
+        pytest.skip("the lines are in rows per compute unit")
+    codes = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(m + k))
+    X = inputs.make_x(k, b, xd, seed=3)
+    plan = B.msgemm_plan(m, k, b, xd, Y_OF_X[xd], 2, 0, codes)
+    try:
+        info = B.msgemm_plan_get_info(plan)
+        assert (info["tile_groups"] == 64 and info["tile_rows"] <= 192) == matrix
+        Y = torch_io.empty_output(b, m, Y_OF_X[xd])
+        Y.fill_(-3)
+        B.msgemm_run(plan, torch_io.to_device(X, xd), k, Y, m)
+        torch.cuda.synchronize()
+        out = torch_io.to_host(Y)
+    finally:
+        B.msgemm_destroy(plan)
+    rows = np.unique(np.concatenate([np.arange(min(m, 70)), np.arange(m - min(m, 70), m), np.random.default_rng(m).integers(0, m, 60)]))
+    some = np.ascontiguousarray(codes.cpu().numpy()[rows])
+    check(np.ascontiguousarray(out[:, rows]), oracle_y(some, X, xd, None, 0), xd, "own choice",
+          elem_bound(some, X, xd, None, 0, table16=info["variant"] == B.VARIANT_FUSED_LDS16))
+
+
 def e5m2_values():
     """OCP E5M2 patterns (1 sign, 5 exponent bits with bias 15, 2 mantissa bits); infinities and NaNs are given numbers."""
     v = np.empty(256)
