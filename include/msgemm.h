@@ -72,9 +72,11 @@ typedef enum {
      * (or none), msgemm_run then takes the matrix form: the codes are decoded in registers and the
      * sum of Section 3.2 is formed by the matrix cores without tabulating its terms first (fp32 sums of exact products,
      * int32 for int8 X; fp32 X of every magnitude exactly, but with elements under 2^-109, or with infinities or NaNs, up
-     * to three times slower); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64 and col_chunk 1.
-     * A value map installed later is served by the table kernels below, and so is every other AUTO problem (above all a
-     * single fp32 column on a matrix of more than 32 Mi weights, and k <= 512 under very many rows, where they are faster). */
+     * to three times slower); reported as FUSED_LDS, whose full-width results it has, with tile_groups 64, col_chunk 1 and
+     * tile_rows up to 192 (256 or more where the library's own choice is a table kernel).  A value map installed later is
+     * served by the table kernels below (msgemm_plan_get_info then reports the one that does, until the paper's map is back),
+     * and so is every other AUTO problem: above all a single fp32 column on a matrix of more than 32 Mi weights, and a short
+     * k under very many rows, where they are faster. */
     MSGEMM_VARIANT_AUTO = 0,
     /* Two launches: L is written to device memory once and shared by all rows
      * (the arrangement of Section 4: one L, kept in cache between the phases); any d in 1..4. */
@@ -125,7 +127,7 @@ typedef struct {
     int x_dtype, y_dtype, lut_dtype;
     int d;
     int scale_group;
-    int variant;         /* the variant actually chosen */
+    int variant;         /* the variant actually chosen; it and the four fields of the kernel's shape: what msgemm_run would use now */
     int64_t lut_groups;  /* last dimension of L */
     int tile_rows;       /* rows per workgroup (fused variant), else 0 */
     int tile_groups;     /* table groups of a k-tile (one table in LDS), else 0 */

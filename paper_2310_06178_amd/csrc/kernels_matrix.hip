@@ -1113,7 +1113,7 @@ constexpr ShortLine kShort4[] = {
     {257, 320, 17, 48, kAny, 640},        {321, 384, 17, 32, kAny, 640},        {385, 512, 17, 32, kHalf, 2048},
     {513, 768, 1, 1, kHalf | kRagged, 600},  {513, 768, 1, 1, kBytes | kRagged, 416},  {513, 768, 2, 8, kBytes | kRagged, 640},
     {513, 768, 1, 1, kHalf | kFloat, 1024},  {513, 768, 1, 1, kBytes, 3072},    {769, 1024, 1, 1, kHalf | kFloat, 3072},
-    {513, 1024, 2, 2, kFloat, 3072},      {513, 768, 2, 4, kHalf, 3072},        {513, 768, 5, 8, kHalf, 900}, 
+    {513, 1024, 2, 2, kFloat, 3072},      {513, 768, 2, 4, kHalf, 3072},        {513, 768, 5, 8, kHalf, 900},
     {769, 1024, 5, 8, kHalf, 3072},       {513, 768, 9, 32, kAny | kRagged, 1536},  {513, 640, 9, 16, kHalf | kBytes, 3072},
 };
 constexpr ShortLine kShort8[] = {  // 8-bit codes

@@ -400,13 +400,15 @@ int msgemm_plan_get_info(const msgemm_plan_t* plan, msgemm_plan_info_t* info)
     const Plan& p = *reinterpret_cast<const Plan*>(plan);
     info->m = p.m; info->k = p.codes8 ? p.k / 2 : p.k; info->b = p.b;
     info->x_dtype = p.x_dtype; info->y_dtype = p.y_dtype; info->lut_dtype = p.lut_dtype;
-    info->d = p.codes8 ? 1 : p.d; info->scale_group = p.codes8 ? p.scale_group / 2 : p.scale_group; info->variant = p.half_table ? (int)MSGEMM_VARIANT_GLOBAL_LUT_HALF : p.variant;
+    info->d = p.codes8 ? 1 : p.d; info->scale_group = p.codes8 ? p.scale_group / 2 : p.scale_group;
     info->lut_groups = p.codes8 ? p.k / 2 : p.lut_groups;
-    const bool fused = p.variant != MSGEMM_VARIANT_GLOBAL_LUT;
-    info->tile_rows = fused ? p.fs.tile_rows : 0;
-    info->tile_groups = fused ? p.fs.groups : 0;
-    info->split_k = fused ? (p.segments > 0 ? p.segments : (int)p.ktiles) : 1;
-    info->col_chunk = fused ? p.fs.cols : (int)p.b;
+    const Plan& runs = p.matrix && p.custom_values ? *p.tables : p;  // what msgemm_run would use now
+    const bool fused = runs.variant != MSGEMM_VARIANT_GLOBAL_LUT;
+    info->variant = runs.half_table ? (int)MSGEMM_VARIANT_GLOBAL_LUT_HALF : runs.variant;
+    info->tile_rows = fused ? runs.fs.tile_rows : 0;
+    info->tile_groups = fused ? runs.fs.groups : 0;
+    info->split_k = fused ? (runs.segments > 0 ? runs.segments : (int)runs.ktiles) : 1;
+    info->col_chunk = fused ? runs.fs.cols : (int)p.b;
     info->workspace_bytes = (int64_t)p.workspace_bytes;
     return MSGEMM_OK;
 }

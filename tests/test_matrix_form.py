@@ -235,12 +235,45 @@ def test_other_entry_points_on_a_matrix_form_plan(xd, b, sg):
             B.msgemm_plan_set_codebook(plan, NONUNIFORM)
             want = oracle.gemm_f64(codes, oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64), scales, sg,
                                    codebook=NONUNIFORM)
-            cb = elem_bound(codes, X, xd, scales, sg, table16=True, codebook=NONUNIFORM)
+            cb = elem_bound(codes, X, xd, scales, sg, codebook=NONUNIFORM,   # (a problem this small: full-width tables)
+                            table16=B.msgemm_plan_get_info(plan)["variant"] == B.VARIANT_FUSED_LDS16)
             check(run(lambda Y: B.msgemm_run(plan, dX, k, Y, m)), want, xd, "value map", cb)
             check(run(lambda Y: B.msgemm_run_static(plan, dX, k, Y, m)), want, xd, "value map, static", cb)
             B.msgemm_plan_set_codebook(plan, None)
             assert np.array_equal(run(lambda Y: B.msgemm_run(plan, dX, k, Y, m)), first)
         assert B.msgemm_plan_check(plan) == B.OK
+    finally:
+        B.msgemm_destroy(plan)
+
+
+def test_plan_info_names_the_kernels_that_serve_a_value_map():
+    """Nine columns and 8 MiB of codes: the table kernels for it have 16-bit entries.  With a value map installed the plan
+    reports them, with their limits, and the matrix form again when the paper's map is back."""
+    m, k, b = 4096, 4096, 9
+    codes, X = inputs.make_codes(m, k, seed=31), inputs.make_x(k, b, "f16", seed=32)
+    dX, Y = torch_io.to_device(X, "f16"), torch_io.empty_output(b, m, "f16")
+    plan = B.msgemm_plan(m, k, b, "f16", "f16", 2, 0, torch_io.to_device(codes, "codes"))
+    try:
+        shape = ("variant", "tile_rows", "tile_groups", "split_k", "col_chunk")
+        at_first = B.msgemm_plan_get_info(plan)
+        assert at_first["variant"] == B.VARIANT_FUSED_LDS and at_first["tile_groups"] == 64 and at_first["tile_rows"] <= 192
+        beyond = list(NONUNIFORM)
+        beyond[3] = 70000.0
+        assert B.msgemm_plan_set_codebook(plan, beyond, check=False) == B.ERR_UNSUPPORTED
+        assert [B.msgemm_plan_get_info(plan)[f] for f in shape] == [at_first[f] for f in shape]   # (nothing was installed)
+        B.msgemm_plan_set_codebook(plan, NONUNIFORM)
+        info = B.msgemm_plan_get_info(plan)
+        assert info["variant"] == B.VARIANT_FUSED_LDS16 and info["col_chunk"] == 8 and info["tile_groups"] in (16, 32)
+        B.msgemm_run(plan, dX, k, Y, m)
+        torch.cuda.synchronize()
+        check(torch_io.to_host(Y), oracle.gemm_f64(codes, X.astype(np.float64), codebook=NONUNIFORM), "f16", "value map",
+              elem_bound(codes, X, "f16", None, 0, table16=True, codebook=NONUNIFORM))
+        big = dX.clone()
+        big[2, 5] = 60000.0                              # times a value of 6: outside the 16-bit entries
+        B.msgemm_run(plan, big, k, Y, m)
+        assert B.msgemm_plan_check(plan) == B.ERR_RANGE
+        B.msgemm_plan_set_codebook(plan, None)
+        assert [B.msgemm_plan_get_info(plan)[f] for f in shape] == [at_first[f] for f in shape]
     finally:
         B.msgemm_destroy(plan)
 
