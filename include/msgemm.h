@@ -15,8 +15,11 @@
  * call only enqueues work on that stream and never synchronises it, except
  * msgemm_plan (which returns after its one-off weight repack has been
  * enqueued; the caller may free W_codes / scales once the stream has been
- * synchronised) and msgemm_destroy (which synchronises the device before it
- * frees).  No exception or abort crosses this boundary: every entry point
+ * synchronised), the first msgemm_plan_set_codebook on a plan in the matrix form
+ * (which makes the table kernels' plan on the null stream of the plan's device,
+ * whichever device is current, and returns when that is done), msgemm_plan_check
+ * (which waits for the stream) and msgemm_destroy (which synchronises the device
+ * before it frees).  No exception or abort crosses this boundary: every entry point
  * returns MSGEMM_OK (0) or a negative msgemm_status_t.
  *
  * Storage conventions (the paper fixes none; Section 4 only requires that the

@@ -279,12 +279,36 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     return MSGEMM_OK;
 }
 
+// Makes a device the current one for as long as it lives (the caller's is current again afterwards).
+namespace {
+class CurrentDevice {
+public:
+    explicit CurrentDevice(int device) : status_(hipGetDevice(&before_))
+    {
+        if (status_ != hipSuccess || before_ == device) return;
+        status_ = hipSetDevice(device);
+        changed_ = status_ == hipSuccess;
+    }
+    ~CurrentDevice() { if (changed_) (void)hipSetDevice(before_); }
+    CurrentDevice(const CurrentDevice&) = delete;
+    CurrentDevice& operator=(const CurrentDevice&) = delete;
+    hipError_t status() const { return status_; }
+
+private:
+    int before_ = 0;
+    bool changed_ = false;
+    hipError_t status_;
+};
+}  // namespace
+
 // The plan that serves a matrix-form plan's calls while another value map is installed: the same problem by the table
-// kernels the library would choose, made from the repacked codes on the null stream.  The matrix form's buffers stay:
-// launches already enqueued or captured keep the old map.
+// kernels the library would choose, made from the repacked codes on the null stream of the plan's device.  The matrix form's
+// buffers stay: launches already enqueued or captured keep the old map.
 static int ensure_tables(Plan& p)
 {
     if (p.tables) return MSGEMM_OK;
+    const CurrentDevice device(p.device);
+    MSGEMM_HIP_TRY(device.status());
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another stream of the program may be capturing)
     MSGEMM_HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
     // (no stream of its own: with a second queue the device no longer deals workgroup ids over its XCDs from the first

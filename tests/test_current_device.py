@@ -1,0 +1,63 @@
+"""Which device and stream the host side of the library uses, on the CPU: libmsgemm.so over a stand-in for the HIP runtime
+(recording_hip_runtime.c) that knows several devices and computes nothing.  Each case runs in a process of its own."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ALLOC, LAUNCH, WORK, EVENT = 1, 2, 3, 4
+
+PRELUDE = """
+import ctypes, sys
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+from paper_2310_06178_amd import binding as B
+lib = B.load()
+device = ctypes.c_int()
+def current():
+    rec.hipGetDevice(ctypes.byref(device))
+    return device.value
+def calls(since):
+    return [(rec.rec_kind(i), rec.rec_device(i), rec.rec_own_stream(i)) for i in range(since, rec.rec_count())]
+ADDRESS = 0x10000
+MAP = [0.0, 0.5] + [0.25 * i for i in range(14)]
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "librecording_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wall", "-Wextra", "-Werror", "-o", out,
+                    os.path.join(ROOT, "tests", "recording_hip_runtime.c")], check=True)
+    return out
+
+
+def run(runtime, body):
+    p = subprocess.run([sys.executable, "-c", PRELUDE + body, runtime], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, p.stderr[-3000:]
+    return p.stdout
+
+
+def test_first_value_map_works_on_the_plans_device(runtime):
+    """The table kernels' plan is allocated and filled on the device of the plan, whatever device is current, and the
+    current device is the caller's again afterwards."""
+    out = run(runtime, """
+rec.hipSetDevice(2)
+plan = B.msgemm_plan(96, 512, 1, "f16", "f16", 2, 128, ADDRESS, ADDRESS, stream=0)
+made = calls(0)
+assert made and all(d == 2 for _, d, _ in made)
+rec.hipSetDevice(1)
+since = rec.rec_count()
+B.msgemm_plan_set_codebook(plan, MAP)
+used = calls(since)
+assert [k for k, _, _ in used].count(1) >= 3 and [k for k, _, _ in used].count(2) >= 2, used   # allocations and launches
+assert all(d == 2 for _, d, _ in used), used
+assert current() == 1
+since = rec.rec_count()
+B.msgemm_plan_set_codebook(plan, MAP[::-1])             # the next map: host only
+B.msgemm_plan_set_codebook(plan, None)
+assert rec.rec_count() == since and current() == 1
+print("ok")
+""")
+    assert out.strip().endswith("ok")
