@@ -249,7 +249,9 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
                 p->epoch_words = (size_t)msgemm::kXcds * (size_t)p->col_passes *
                                  (((size_t)p->segments * (size_t)p->row_blocks + msgemm::kXcds - 1) / msgemm::kXcds);
                 p->epoch_words += (size_t)p->row_blocks * (size_t)p->col_passes;  // arrival counts (XCD-local reduction)
-                p->xcd_round_robin = msgemm::xcd_round_robin(p->device, s) ? 1 : 0;
+                // (what is seen is kept for the process: not looked at on behalf of a plan that cannot ask for that
+                // reduction, and whose stream may be a second queue, which is dealt differently)
+                p->xcd_round_robin = !tables_only && msgemm::xcd_round_robin(p->device, s) ? 1 : 0;
             }
             else {
                 // one word per workgroup id of the grid, in either order of the ids (row groups or units dealt over the XCDs)

@@ -74,12 +74,21 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int bloc
 }
 int hipGetSymbolAddress(void** p, const void* symbol) { *p = (void*)symbol; return 0; }
 struct dim { unsigned x, y, z; };
-int __hipPushCallConfiguration(struct dim g, struct dim b, size_t lds, void* stream) { (void)g; (void)b; (void)lds; (void)stream; return 0; }
+static struct { struct dim grid, block; size_t lds; void* stream; } pushed;
+int __hipPushCallConfiguration(struct dim g, struct dim b, size_t lds, void* stream)
+{
+    pushed.grid = g;
+    pushed.block = b;
+    pushed.lds = lds;
+    pushed.stream = stream;
+    return 0;
+}
 int __hipPopCallConfiguration(struct dim* g, struct dim* b, size_t* lds, void** stream)
 {
-    (void)g; (void)b;
-    *lds = 0;
-    *stream = 0;
+    *g = pushed.grid;
+    *b = pushed.block;
+    *lds = pushed.lds;
+    *stream = pushed.stream;
     return 0;
 }
 int hipLaunchKernel(const void* f, struct dim g, struct dim b, void** args, size_t lds, void* stream)

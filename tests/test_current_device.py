@@ -61,3 +61,27 @@ assert rec.rec_count() == since and current() == 1
 print("ok")
 """)
     assert out.strip().endswith("ok")
+
+
+def test_dispatch_order_is_not_looked_at_from_a_temporary_stream(runtime):
+    """While a stream that waits for the null stream is captured, the table kernels' plan is made on a stream of its own; the
+    look at how the device deals workgroups over its dies, made once per process, waits for a plan on the caller's stream."""
+    out = run(runtime, """
+m, k, b = 4096, 4096, 9                                  # (served by the batched table kernels)
+plan = B.msgemm_plan(m, k, b, "f16", "f16", 2, 0, ADDRESS, stream=0)
+rec.rec_capture(1)
+since = rec.rec_count()
+B.msgemm_plan_set_codebook(plan, MAP)
+rec.rec_capture(0)
+used = calls(since)
+on_own = [kind for kind, _, own in used if own]
+assert 2 in on_own and not [1 for kind, _, own in used if kind in (2, 3) and not own], used
+since = rec.rec_count()
+B.msgemm_plan(m, k, b, "f16", "f16", 2, 0, ADDRESS, None, B.VARIANT_FUSED_LDS16, stream=0)
+first = calls(since)
+since = rec.rec_count()
+B.msgemm_plan(m, k, b, "f16", "f16", 2, 0, ADDRESS, None, B.VARIANT_FUSED_LDS16, stream=0)
+assert len(first) > len(calls(since)), (first, calls(since))   # the look itself: here, and once
+print("ok")
+""")
+    assert out.strip().endswith("ok")
