@@ -143,19 +143,21 @@ template <> struct Policy<int8_t> {
 // 8-bit codes of a floating-point format the device converts (every finite pattern exact in fp16 and bf16): two dwords of
 // four codes -> the weight operand of one MFMA step.
 enum Format { kInt4, kE4M3, kE5M2 };
-template <int F, typename XT, bool kHigh> __device__ __forceinline__ uint32_t convert_pair(uint32_t x)
+// times a power of two (bf16 only, whose range has room for it: the products are then those of the map's own values)
+template <int F, typename XT, bool kHigh> __device__ __forceinline__ uint32_t convert_pair(uint32_t x, float times)
 {
     if constexpr (__is_same(XT, __half)) {
         if constexpr (F == kE4M3) return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x, 1.0f, kHigh));
         else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_bf8((int)x, 1.0f, kHigh));
     } else {
-        if constexpr (F == kE4M3) return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)x, 1.0f, kHigh));
-        else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((int)x, 1.0f, kHigh));
+        if constexpr (F == kE4M3) return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((int)x, times, kHigh));
+        else return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((int)x, times, kHigh));
     }
 }
-template <int F, typename XT> __device__ __forceinline__ v4u convert(uint32_t lo, uint32_t hi)
+template <int F, typename XT> __device__ __forceinline__ v4u convert(uint32_t lo, uint32_t hi, float times)
 {
-    return v4u{convert_pair<F, XT, false>(lo), convert_pair<F, XT, true>(lo), convert_pair<F, XT, false>(hi), convert_pair<F, XT, true>(hi)};
+    return v4u{convert_pair<F, XT, false>(lo, times), convert_pair<F, XT, true>(lo, times),
+               convert_pair<F, XT, false>(hi, times), convert_pair<F, XT, true>(hi, times)};
 }
 
 // Which nibble of a code dword holds the e-th of its 8 columns, and what is stored there for a two's-complement code.
@@ -189,7 +191,9 @@ struct MatrixArgs {
     int seg_runs;          // full runs per segment (tile kernel: runs)
     int row_groups;
     int passes;            // passes over the columns of X
-    float factor;          // a power of two that the weight operands leave out (bf16 activations, 4-bit codes: value / 16)
+    float factor;          // a power of two that the weight operands leave out (bf16 activations, 4-bit codes: value / 16;
+                           // fp16 activations, 8-bit codes: the map's, which could take the weights out of fp16's range)
+    float times;           // a power of two that the weight operands have in them (8-bit codes, bf16 and fp32 activations)
 };
 
 // fp32 activations: four elements as the three bf16 parts x = h + m + l, eight bits each by truncation.  Exact but for two
@@ -436,7 +440,7 @@ matrix_stream_kernel(MatrixArgs a)
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if constexpr (F == kInt4) P::decode(st.codes[r], t, w[r]);
-                else w[r] = convert<F, XT>(st.codes[2 * r + t / 2][2 * (t & 1)], st.codes[2 * r + t / 2][2 * (t & 1) + 1]);
+                else w[r] = convert<F, XT>(st.codes[2 * r + t / 2][2 * (t & 1)], st.codes[2 * r + t / 2][2 * (t & 1) + 1], a.times);
             }
 #pragma unroll
             for (int op = kOps - 1; op >= 0; --op) {   // (the smallest part first)
@@ -1302,7 +1306,8 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
     a.row_groups = (int)p.row_blocks;
     a.passes = p.mx_tile_kernel ? (int)((p.b + 16 * p.mx_cols - 1) / (16 * p.mx_cols)) : (int)((p.b + 15) / 16);
     a.div_block = make_fastdiv(group > 0 ? (uint32_t)(group / kRun) : 1u);
-    a.factor = p.codes8 ? p.mx_factor : p.x_dtype == MSGEMM_BF16 ? 16.0f : 1.0f;
+    a.factor = p.codes8 ? (p.x_dtype == MSGEMM_F16 ? p.mx_factor : 1.0f) : p.x_dtype == MSGEMM_BF16 ? 16.0f : 1.0f;
+    a.times = p.codes8 ? p.mx_factor : 1.0f;
     if (p.codes8) {
         switch (p.x_dtype) {
         case MSGEMM_F16: return launch_for_format<__half>(p, a, s);

@@ -361,6 +361,42 @@ def test_codes8_of_a_device_format(table, m, k, b, xd, sg, options):
           elem_bound(codes, X, xd, scales, sg, table16=not matrix and b > 2 and xd != "f32", values256=values))
 
 
+@pytest.mark.parametrize("xd,magnitude", [("bf16", 1e35), ("f32", 1e35), ("bf16", 1e-36), ("f32", 1e-36), ("f16", 1e4)])
+@pytest.mark.parametrize("power", [-20, -12, 12, 19])
+@pytest.mark.parametrize("b,sg,options", [(1, 0, {}), (12, 128, {}), (20, 0, {}), (2, 0, {"batched_segments": 3})])
+def test_codes8_power_of_two_of_the_map_at_the_ends_of_the_range(b, sg, options, power, xd, magnitude):
+    """The products are those of the map's own values: neither the format's (up to 57344 times as large) nor the power of two
+    takes a sum out of the range of fp32 when the result is inside it, or under its smallest normal number."""
+    if xd != "f16" and (power > 0) == (magnitude > 1):
+        pytest.skip("results outside the range of fp32, or near its end")
+    if power > 0 and b > 2 and xd != "f32":
+        pytest.skip("refused: values over 65504 where the table kernels have 16-bit entries")
+    m, k, two = 64, 1280 if sg else 1282, 2.0 ** power
+    values = e5m2_values() * two
+    codes = np.random.default_rng(m + b).integers(0, 256, size=(m, k), dtype=np.uint8)
+    X = (inputs.make_x(k, b, "f32", seed=k + 1) * np.float32(magnitude)).astype(np.float32)
+    X = {"f32": X, "bf16": inputs.f32_to_bf16_bits(X), "f16": np.clip(X, -6e4, 6e4).astype(np.float16)}[xd]
+    scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
+    Xd = oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64)
+    ref = oracle.gemm_f64_codes8(codes, Xd, values, scales, sg)
+    plan = B.msgemm_plan_codes8(m, k, b, xd, Y_OF_X[xd], sg, torch_io.to_device(codes, "codes"),
+                                torch_io.to_device(scales, "scales"), values, options=dict(options, batched_form=3))
+    try:
+        assert B.msgemm_plan_get_info(plan)["tile_groups"] == 128
+        Y = torch_io.empty_output(b, m, Y_OF_X[xd])
+        Y.fill_(-3)
+        B.msgemm_run(plan, torch_io.to_device(X, xd), k, Y, m)
+        torch.cuda.synchronize()
+        out = torch_io.to_host(Y)
+    finally:
+        B.msgemm_destroy(plan)
+    if xd == "f16" and np.abs(ref).max() > 6e4:
+        over = np.abs(ref) > 65600                       # (outputs outside fp16: infinities of the right sign)
+        assert np.array_equal(torch_io.to_f64(out)[over], np.inf * np.sign(ref[over]))
+        return
+    check(out, ref, xd, f"E5M2 times 2^{power}", elem_bound(codes, X, xd, scales, sg, values256=values))
+
+
 @pytest.mark.parametrize("non_blocking", [1, 0])
 def test_first_value_map_while_a_stream_is_captured(non_blocking):
     # the table kernels' plan is made at that point, outside the capture; the captured launch keeps the map it was given
