@@ -203,10 +203,12 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
         }
         rc = msgemm::matrix_repack(*p, W_codes, s);
         if (rc != MSGEMM_OK) return fail(rc);
-        e = hipEventCreateWithFlags(&p->ready, hipEventDisableTiming);
-        if (e != hipSuccess) return hip_fail(e);
-        e = hipEventRecord(p->ready, s);
-        if (e != hipSuccess) return hip_fail(e);
+        if (!p->codes8) {  // (a plan of 8-bit codes takes no other value map)
+            e = hipEventCreateWithFlags(&p->ready, hipEventDisableTiming);
+            if (e != hipSuccess) return hip_fail(e);
+            e = hipEventRecord(p->ready, s);
+            if (e != hipSuccess) return hip_fail(e);
+        }
     } else if (p->d3) {
         // depth-3 tables in LDS: the rotated code runs and one partial sum per (segment, column, row)
         const size_t tiled = (size_t)p->ktiles * (size_t)(p->fs.groups / 8) * (size_t)p->m_pad * 12u;

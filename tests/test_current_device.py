@@ -85,3 +85,18 @@ assert len(first) > len(calls(since)), (first, calls(since))   # the look itself
 print("ok")
 """)
     assert out.strip().endswith("ok")
+
+
+def test_plans_of_8_bit_codes_make_no_event(runtime):
+    """The event orders the making of the table kernels' plan behind the repack; 8-bit codes keep their map."""
+    out = run(runtime, """
+from paper_2310_06178_amd import inputs
+values = [0.0 if v != v else float(v) for v in inputs.fp8_e4m3_values()]
+eight = B.msgemm_plan_codes8(96, 512, 1, "f16", "f16", 0, ADDRESS, None, values, stream=0)
+assert B.msgemm_plan_get_info(eight)["tile_groups"] == 128   # (the matrix form)
+assert 4 not in [k for k, _, _ in calls(0)]
+B.msgemm_plan(96, 512, 1, "f16", "f16", 2, 0, ADDRESS, stream=0)
+assert [k for k, _, _ in calls(0)].count(4) == 1
+print("ok")
+""")
+    assert out.strip().endswith("ok")
