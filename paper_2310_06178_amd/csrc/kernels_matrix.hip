@@ -1022,9 +1022,11 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
     MSGEMM_CASE(4, 0, 4, 4)
     MSGEMM_CASE(2, 0, 4, 4)
     MSGEMM_CASE(1, 0, 4, 8)
-    MSGEMM_CASE(4, 2, 4, sizeof(XT) == 4 ? 2 : 4)
-    MSGEMM_CASE(2, 2, 4, sizeof(XT) == 4 ? 2 : 4)
-    MSGEMM_CASE(1, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+    if constexpr (sizeof(XT) != 1) {  // (int8: the compact form holds eight columns)
+        MSGEMM_CASE(4, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+        MSGEMM_CASE(2, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+        MSGEMM_CASE(1, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+    }
     MSGEMM_CASE(4, 4, 8, 2)
     MSGEMM_CASE(2, 4, 4, sizeof(XT) == 4 ? 2 : 4)
     MSGEMM_CASE(1, 4, 4, sizeof(XT) == 4 ? 2 : 4)
