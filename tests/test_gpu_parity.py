@@ -900,26 +900,34 @@ def test_column_passes_of_the_single_column_kernels(m, k, b, xd, sg, options):
         B.msgemm_destroy(plan)
 
 
-def test_two_columns_at_full_size():
-    """The paper's 12288 x 49152 GeMM (Section 5) with two activation vectors: two column passes through the long-k
-    form, 234 units over 8 XCDs, every row against the oracle."""
+def matrix_form(info):
+    """The library's own choice where the codes are decoded in registers; its table kernels' panels have 256 rows or more."""
+    return info["variant"] == B.VARIANT_FUSED_LDS and info["tile_groups"] == 64 and info["tile_rows"] <= 192
+
+
+@pytest.mark.parametrize("variant", [B.VARIANT_AUTO, B.VARIANT_FUSED_LDS])
+def test_two_columns_at_full_size(variant):
+    """The paper's 12288 x 49152 GeMM (Section 5) with two activation vectors: by tables, two column passes through the
+    long-k form, 234 units over 8 XCDs; in the matrix form, which is the library's own choice; every row against the oracle."""
     m, k, b, xd = 12288, 49152, 2, "f16"
     codes = inputs.make_codes(m, k, seed=41)
     X = inputs.make_x(k, b, xd, seed=42)
-    out, info = run_gpu(codes, X, xd, None, 0, 2, B.VARIANT_AUTO)
-    assert info["variant"] == B.VARIANT_FUSED_LDS and info["col_chunk"] == 1
+    out, info = run_gpu(codes, X, xd, None, 0, 2, variant)
+    assert info["variant"] == B.VARIANT_FUSED_LDS and info["col_chunk"] == 1 and matrix_form(info) == (variant == B.VARIANT_AUTO)
     check(out, oracle_y(codes, X, xd, None, 0), xd, "mlp1 shape, b = 2", elem_bound(codes, X, xd, None, 0))
 
 
 # ---------------------------------------------------------------------------
-# the benchmark configurations at full size, library's own choice of variant
+# the benchmark configurations at full size: the library's own choice, and the table kernels it would choose
 
+@pytest.mark.parametrize("tables", [0, 1])
 @pytest.mark.parametrize("name", ["cfg1", "cfg2", "cfg3a", "cfg3b", "cfg4", "cfg5", "mlp1", "mlp2", "mlp2_b16", "big1"])
-def test_config_full_size(name):
+def test_config_full_size(name, tables):
     cfg, codes, X, scales = inputs.make_config(name)
     m, k, b, xd, sg = cfg["m"], cfg["k"], cfg["b"], cfg["x"], cfg["scale_group"]
-    out, info = run_gpu(codes, X, xd, scales, sg, cfg["d"], B.VARIANT_AUTO)
-    assert info["variant"] in (B.VARIANT_FUSED_LDS, B.VARIANT_FUSED_LDS16)
+    variant = B.VARIANT_AUTO if not tables else B.VARIANT_FUSED_LDS if b <= 2 or xd == "f32" else B.VARIANT_FUSED_LDS16
+    out, info = run_gpu(codes, X, xd, scales, sg, cfg["d"], variant)
+    assert matrix_form(info) != tables and info["variant"] == (variant if tables else B.VARIANT_FUSED_LDS)
     # every row of every configuration goes through the oracle (the largest, cfg5, is 15e9 multiply-adds:
     # a few seconds on the host cores), and through it once more with magnitudes for the per-element bound
     rows = np.arange(m)
@@ -935,18 +943,20 @@ def test_config_full_size(name):
     print(f"{name}: rows checked {len(rows)}/{m}, rel L2 {err:.3e}")
 
 
+@pytest.mark.parametrize("variant,options", [(B.VARIANT_FUSED_LDS, None), (B.VARIANT_AUTO, {"batched_form": 3})])
 @pytest.mark.parametrize("m,k,xd,sg", [
+    # (matrix form: 16385 row groups; chains of 512 and 256 runs a wavefront, k in segments)
     ((1 << 20) + 3, 1024, "f16", 128),   # a million rows: 4097 panels, offsets of the partial buffer near their range
     (515, 1 << 18, "f16", 0),            # 2048 k-tiles: the long-k form at scale
     (259, 1 << 17, "i8", 0),             # the same with integer tables
 ])
-def test_extreme_aspect_ratios(m, k, xd, sg):
-    """Very tall and very wide problems (b = 1), every row against the oracle."""
+def test_extreme_aspect_ratios(m, k, xd, sg, variant, options):
+    """Very tall and very wide problems (b = 1), by tables and in the matrix form, every row against the oracle."""
     codes = inputs.make_codes(m, k, seed=17)
     X = inputs.make_x(k, 1, xd, seed=18)
     scales = inputs.make_scales(m, k, sg, seed=19) if sg else None
-    out, info = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO)
-    assert info["variant"] == B.VARIANT_FUSED_LDS
+    out, info = run_gpu(codes, X, xd, scales, sg, 2, variant, options=options)
+    assert info["variant"] == B.VARIANT_FUSED_LDS and matrix_form(info) == (options is not None)
     check(out, oracle_y(codes, X, xd, scales, sg), xd, f"{m}x{k}", elem_bound(codes, X, xd, scales, sg))
 
 
@@ -1234,12 +1244,16 @@ CODES8_CASES = [
 ]
 
 
+# E4M3 runs in the matrix form where no request and no scale block is against it; with one value moved, always by tables
+@pytest.mark.parametrize("moved", [0, 1])
 @pytest.mark.parametrize("m,k,b,xd,sg,options", CODES8_CASES)
-def test_codes8_against_oracle(m, k, b, xd, sg, options):
+def test_codes8_against_oracle(m, k, b, xd, sg, options, moved):
     codes = inputs.make_codes8(m, k, seed=m + k)
     X = inputs.make_x(k, b, xd, seed=k + 1)
     scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
     values = e4m3_finite() / 16.0   # keeps fp16 outputs in range
+    if moved:
+        values[0x2b] *= 1.25
     ref = oracle.gemm_f64_codes8(codes, x_to_f64(X, xd), values, scales, sg)
     dC, dS, dX = torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"), torch_io.to_device(X, xd)
     plan = B.msgemm_plan_codes8(m, k, b, xd, Y_OF_X[xd], sg, dC, dS, values, options=options or None)
@@ -1247,6 +1261,8 @@ def test_codes8_against_oracle(m, k, b, xd, sg, options):
         info = B.msgemm_plan_get_info(plan)
         assert (info["k"], info["d"], info["lut_groups"], info["scale_group"]) == (k, 1, k, sg)
         assert info["variant"] == (B.VARIANT_FUSED_LDS if b <= 2 or xd == "f32" else B.VARIANT_FUSED_LDS16)
+        matrix = info["tile_groups"] == 128
+        assert matrix == (not moved and not options and sg % 128 == 0)
         for rep in range(2):
             Y = torch_io.empty_output(b, m, Y_OF_X[xd], ldy=m + 1)
             Y.fill_(-3)
@@ -1254,7 +1270,8 @@ def test_codes8_against_oracle(m, k, b, xd, sg, options):
             torch.cuda.synchronize()
             out = torch_io.to_host(Y)
             check(np.ascontiguousarray(out[:, :m]), ref, xd, f"8-bit weights call {rep}",
-                  elem_bound(codes, X, xd, scales, sg, table16=info["variant"] == B.VARIANT_FUSED_LDS16, values256=values))
+                  elem_bound(codes, X, xd, scales, sg, table16=info["variant"] == B.VARIANT_FUSED_LDS16 and not matrix,
+                             values256=values))
     finally:
         B.msgemm_destroy(plan)
 

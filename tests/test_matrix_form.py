@@ -11,7 +11,7 @@ import torch
 import oracle
 from paper_2310_06178_amd import binding as B
 from paper_2310_06178_amd import inputs, torch_io
-from test_gpu_parity import ABS_FLOOR, NONUNIFORM, TOL, U_OUT, Y_OF_X, check, elem_bound, oracle_y, run_gpu
+from test_gpu_parity import ABS_FLOOR, NONUNIFORM, TOL, U_OUT, Y_OF_X, check, elem_bound, matrix_form, oracle_y, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -256,7 +256,7 @@ def test_plan_info_names_the_kernels_that_serve_a_value_map():
     try:
         shape = ("variant", "tile_rows", "tile_groups", "split_k", "col_chunk")
         at_first = B.msgemm_plan_get_info(plan)
-        assert at_first["variant"] == B.VARIANT_FUSED_LDS and at_first["tile_groups"] == 64 and at_first["tile_rows"] <= 192
+        assert matrix_form(at_first)
         beyond = list(NONUNIFORM)
         beyond[3] = 70000.0
         assert B.msgemm_plan_set_codebook(plan, beyond, check=False) == B.ERR_UNSUPPORTED
@@ -302,7 +302,7 @@ def test_where_the_matrix_form_is_the_librarys_own_choice(m, k, b, xd, matrix):
     plan = B.msgemm_plan(m, k, b, xd, Y_OF_X[xd], 2, 0, codes)
     try:
         info = B.msgemm_plan_get_info(plan)
-        assert (info["tile_groups"] == 64 and info["tile_rows"] <= 192) == matrix
+        assert matrix_form(info) == matrix
         Y = torch_io.empty_output(b, m, Y_OF_X[xd])
         Y.fill_(-3)
         B.msgemm_run(plan, torch_io.to_device(X, xd), k, Y, m)
@@ -424,3 +424,32 @@ def test_first_value_map_while_a_stream_is_captured(non_blocking):
     assert lib.hipGraphExecDestroy(instance) == 0 and lib.hipGraphDestroy(graph) == 0
     assert lib.hipStreamDestroy(stream) == 0
     B.msgemm_destroy(plan)
+
+
+def _random_cases(count, seed):
+    rng = np.random.default_rng(seed)
+    cases = []
+    while len(cases) < count:
+        xd = ["f32", "f16", "bf16", "i8"][rng.integers(4)]
+        m, k = int(rng.integers(1, 1500)), 2 * int(rng.integers(1, 1400))
+        sg = 0 if xd == "i8" else int([0, 0, 128, 256, 384][rng.integers(5)])
+        if sg:
+            k = max(sg, (k // sg) * sg)
+        b = int([1, 1, 2, 3, 4, 5, 8, 9, 13, 16, 17, 24, 32, 40, 48, 64, 70, 130][rng.integers(18)])
+        options = [None, {"batched_form": 3}, {"batched_form": 3, "rows_per_lane": int([4, 8][rng.integers(2)])},
+                   {"batched_form": 3, "panels_per_workgroup": int(rng.integers(1, 5))},
+                   {"batched_form": 3, "batched_segments": int(rng.integers(2, 6)), "rows_per_lane": int([4, 8][rng.integers(2)])}]
+        cases.append((m, k, b, xd, sg, options[rng.integers(5)]))
+    return cases
+
+
+@pytest.mark.parametrize("m,k,b,xd,sg,options", _random_cases(160, seed=23100617))
+def test_random_shapes_in_the_matrix_form(m, k, b, xd, sg, options):
+    """Seeded random problems by the library's own choice, which is the matrix form for all of them, and with requests for
+    its kernels and shapes (those that do not fit the problem fall back to its choice)."""
+    codes = inputs.make_codes(m, k, seed=m * 31 + k)
+    X = inputs.make_x(k, b, xd, seed=k * 7 + b)
+    scales = inputs.make_scales(m, k, sg, seed=m + b) if sg else None
+    out, info = run_gpu(codes, X, xd, scales, sg, 0, B.VARIANT_AUTO, ldx_pad=2, ldy_pad=1, options=options)
+    assert matrix_form(info)
+    check(out, oracle_y(codes, X, xd, scales, sg), xd, f"{m}x{k}x{b} {xd} sg={sg} {options}", elem_bound(codes, X, xd, scales, sg))
