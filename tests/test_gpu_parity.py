@@ -117,6 +117,11 @@ def run_gpu(codes, X, xd, scales, sg, d, variant, ldx_pad=0, ldy_pad=0, use_phas
     return out, info
 
 
+def matrix_form(info):
+    """The library's own choice where the codes are decoded in registers; its table kernels' panels have 256 rows or more."""
+    return info["variant"] == B.VARIANT_FUSED_LDS and info["tile_groups"] == 64 and info["tile_rows"] <= 192
+
+
 # ---------------------------------------------------------------------------
 # two-launch variant: every d, dtype, ragged shapes, scale block sizes
 
@@ -317,15 +322,18 @@ def test_fused_variant_batched(m, k, b, xd, sg, variant):
     check(out, ref, xd, "fused batched", elem_bound(codes, X, xd, scales, sg, table16=variant == B.VARIANT_FUSED_LDS16))
     if variant == B.VARIANT_FUSED_LDS16:
         assert info["col_chunk"] == 8
-        # the library's own choice for a batch this small: a pass of the single-column kernels per column
-        # (full-width entries), where the scale blocks allow it (whole k-tiles of 128 columns)
-        out_auto, info_auto = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO)
-        if sg % 128 == 0:
-            assert info_auto["variant"] == B.VARIANT_FUSED_LDS and info_auto["col_chunk"] == 1
-            check(out_auto, ref, xd, "fused batched, library's choice", elem_bound(codes, X, xd, scales, sg))
-        else:
-            assert info_auto["variant"] == B.VARIANT_FUSED_LDS16
-            assert np.array_equal(out_auto, out)
+        # the library's own choice: the matrix form where scale blocks are whole runs of 128 columns; among the table
+        # kernels (a request for one of their forms keeps it to them) a pass of the single-column kernels per column for a
+        # batch this small (full-width entries), where the scale blocks allow that
+        for options in (None, {"no_xcd_map": 1}):
+            out_auto, info_auto = run_gpu(codes, X, xd, scales, sg, 2, B.VARIANT_AUTO, options=options)
+            if sg % 128 == 0:
+                assert info_auto["variant"] == B.VARIANT_FUSED_LDS and info_auto["col_chunk"] == 1
+                assert matrix_form(info_auto) == (options is None)
+                check(out_auto, ref, xd, f"fused batched, library's choice {options}", elem_bound(codes, X, xd, scales, sg))
+            else:
+                assert info_auto["variant"] == B.VARIANT_FUSED_LDS16
+                assert np.array_equal(out_auto, out)
 
 
 PIPELINED_CASES = [
@@ -824,6 +832,8 @@ BACK_TO_BACK_CASES = [
     (4100, 1280, 2, "bf16", 128, B.VARIANT_FUSED_LDS, {"k_tiles_per_workgroup": 4, "reduce_mode": 3, "panels_per_workgroup": 16}),  # long-k form, parity-tagged sums
     (2300, 768, 2, "i8", 0, B.VARIANT_FUSED_LDS, {"k_tiles_per_workgroup": 1, "reduce_mode": 2}),         # plain form, flags, two column passes
     (2100, 512, 8, "bf16", 128, B.VARIANT_FUSED_LDS16, {"batched_form": 1, "reduce_mode": 3}),            # batched, sums added in the launch
+    (300, 4098, 1, "f16", 0, B.VARIANT_AUTO, {"batched_form": 3, "batched_segments": 3}),                  # matrix form, sums added by a second launch
+    (300, 2560, 33, "bf16", 128, B.VARIANT_AUTO, {"batched_form": 3, "rows_per_lane": 4, "batched_segments": 2}),
 ]
 
 
@@ -898,11 +908,6 @@ def test_column_passes_of_the_single_column_kernels(m, k, b, xd, sg, options):
         assert B.msgemm_plan_check(plan) == B.OK
     finally:
         B.msgemm_destroy(plan)
-
-
-def matrix_form(info):
-    """The library's own choice where the codes are decoded in registers; its table kernels' panels have 256 rows or more."""
-    return info["variant"] == B.VARIANT_FUSED_LDS and info["tile_groups"] == 64 and info["tile_rows"] <= 192
 
 
 @pytest.mark.parametrize("variant", [B.VARIANT_AUTO, B.VARIANT_FUSED_LDS])
@@ -1327,13 +1332,14 @@ def test_codes8_refusals():
     (513, 384, 70, "bf16", 128),     # two column tiles, ragged rows
     (64, 1024, 16, "bf16", 256),
 ])
-def test_dequant_mfma_comparison_kernel(m, k, b, xd, sg):
+@pytest.mark.parametrize("variant", [B.VARIANT_AUTO, B.VARIANT_FUSED_LDS, B.VARIANT_GLOBAL_LUT])   # (three orders of the codes)
+def test_dequant_mfma_comparison_kernel(m, k, b, xd, sg, variant):
     codes = inputs.make_codes(m, k, seed=m + k)
     X = inputs.make_x(k, b, xd, seed=b)
     scales = inputs.make_scales(m, k, sg, seed=4) if sg else None
     ref = oracle_y(codes, X, xd, scales, sg)
     dC, dS, dX = torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"), torch_io.to_device(X, xd)
-    plan = B.msgemm_plan(m, k, b, xd, Y_OF_X[xd], 2, sg, dC, dS)
+    plan = B.msgemm_plan(m, k, b, xd, Y_OF_X[xd], 2, sg, dC, dS, variant)
     try:
         Y = torch_io.empty_output(b, m, Y_OF_X[xd], ldy=m + 3)
         Y.fill_(-3)

@@ -13,13 +13,13 @@ pytestmark = pytest.mark.gpu
 TOL = {"f16": 2e-3, "i8": 0.0}
 
 
-def _both_ways(m, k, b, xd, sg, seed):
+def _both_ways(m, k, b, xd, sg, seed, variant, options):
     yd = {"f16": "f16", "i8": "i32"}[xd]
     codes = inputs.make_codes(m, k, seed=seed)
     X = inputs.make_x(k, b, xd, seed=seed + 1)
     scales = inputs.make_scales(m, k, sg, seed=seed + 2) if sg else None
     dC, dS, dX = torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"), torch_io.to_device(X, xd)
-    plan = B.msgemm_plan(m, k, b, xd, yd, 2, sg, dC, dS)
+    plan = B.msgemm_plan(m, k, b, xd, yd, 2, sg, dC, dS, variant, options=options)
     try:
         info = B.msgemm_plan_get_info(plan)
         assert info["variant"] in (B.VARIANT_FUSED_LDS, B.VARIANT_FUSED_LDS16) and info["split_k"] > 1
@@ -50,10 +50,21 @@ def _both_ways(m, k, b, xd, sg, seed):
 
 
 def test_static_scratch_entry_point_matches_msgemm_run_twice_in_a_row():
-    _both_ways(4100, 2048, 1, "f16", 128, seed=50)     # single column, 16 k-tiles, 17 panels: 1.1 MB of partial sums
-    _both_ways(700, 512, 1, "f16", 0, seed=60)         # then a smaller one over the same array
-    _both_ways(1500, 1024, 9, "i8", 0, seed=70)        # a batched plan (two column passes), bit-exact
-    _both_ways(300, 256, 1, "f16", 128, seed=80)
+    one, wide = (B.VARIANT_FUSED_LDS, None), (B.VARIANT_FUSED_LDS16, None)
+    _both_ways(4100, 2048, 1, "f16", 128, 50, *one)    # single column, 16 k-tiles, 17 panels: 1.1 MB of partial sums
+    _both_ways(700, 512, 1, "f16", 0, 60, *one)        # then a smaller one over the same array
+    _both_ways(1500, 1024, 9, "i8", 0, 70, *wide)      # a batched plan (two column passes), bit-exact
+    _both_ways(300, 256, 1, "f16", 128, 80, *one)
+
+
+def test_static_scratch_entry_point_on_plans_in_the_matrix_form():
+    own = (B.VARIANT_AUTO, None)                       # the library's own choice: no partial sums between workgroups
+    _both_ways(4100, 2048, 1, "f16", 128, 50, *own)
+    _both_ways(1500, 1024, 9, "i8", 0, 70, *own)
+    segments = {"batched_form": 3, "batched_segments": 4}   # sums in the array, added by a second launch
+    _both_ways(4100, 2048, 3, "f16", 128, 50, B.VARIANT_AUTO, segments)
+    _both_ways(1500, 1024, 9, "i8", 0, 70, B.VARIANT_AUTO, segments)
+    _both_ways(300, 4096, 40, "f16", 128, 80, B.VARIANT_AUTO, dict(segments, rows_per_lane=4))
 
 
 def test_static_scratch_entry_point_refusals():
