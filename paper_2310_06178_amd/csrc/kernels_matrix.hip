@@ -875,8 +875,9 @@ matrix_tile_kernel(MatrixArgs a)
     }
 }
 
-// The segments' sums, in order.  Bound by the trip to memory of a handful of loads (about 3 us with its launch), which a
-// segment has to win back: see segments_of in matrix_choose_shape.
+// The segments' sums, in order.  Bound by the trip to memory of a handful of loads: 2.6 us for 256 rows of three columns, 4.6 to
+// 6 for 64 columns of 4096 to 12288 rows.  What a cut has to win back is more, the writing of the sums and the launch with it: see
+// segments_of in matrix_choose_shape.
 template <typename XT>
 __global__ void __launch_bounds__(256)
 matrix_reduce_kernel(MatrixArgs a, int segments)
@@ -1196,10 +1197,14 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a wavefront
     // keeps 16 runs (tile kernel: a workgroup 20, since the second launch and the sums' trip to memory and back take 10 to
     // 15 us; 12288 x 49152 x 64, 64 row groups: 228 us in one segment, 95 in four; 8192 x 10240 x 64 in segments of 20 runs
-    // 27 us, of 40 29; but 16384 x 4096 x 64 28 in segments of 16, 21 uncut, int8 21 against 14.5).
+    // 27 us, of 40 29; but 16384 x 4096 x 64 28 in segments of 16, 21 uncut, int8 21 against 14.5).  With fp32 activations a
+    // run takes three products and as much splitting, and fewer are enough: 448 x 12288 x 1 9.6 us uncut, 8.0 in two, 7.2 in four
+    // segments of 6 runs a wavefront, 448 x 4096 x 1 4.9 uncut, 6.1 in two; 448 x 8192 x 16 16.0, 12.0 and 9.4, 448 x 4096 x 16 9.6,
+    // 8.7 and 7.5, x 8 6.8, 7.1 and 6.6.
+    const int keep = tile ? 20 : p.x_dtype != MSGEMM_F32 ? 16 : compact ? 6 : p.b <= 8 ? 5 : 4;
     const auto segments_of = [&](int r) {
         int64_t n = 1;
-        while (groups(r) * passes * n * 2 <= p.cus && runs >= 2 * n * (tile ? 20 : waves(r) * 16)) n *= 2;
+        while (groups(r) * passes * n * 2 <= p.cus && runs >= 2 * n * (tile ? keep : waves(r) * keep)) n *= 2;
         return n;
     };
     // Row tiles per wavefront: the work of the busiest compute unit, in row tiles for the streaming kernel, weighted by
@@ -1221,6 +1226,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
         if (asked && o.panels_per_workgroup == tiles[tile][i]) R = o.panels_per_workgroup;
     const int W = waves(R);
     int64_t segments = segments_of(R);
+    // (a single fp32 column whose chains stay long although they are cut: 2048 x 16084 10.2 us in two segments, tables 8.7;
+    // level at 2048 x 12288, 12 runs a wavefront)
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * W * 12 && !asked) return false;
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
     p.mx_tile_kernel = tile;
     p.mx_r = R;

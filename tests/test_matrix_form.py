@@ -283,6 +283,8 @@ CHOICES = [
     # m, k, b, xd, matrix form: the two sides of some of the lines of the library's own choice
     (32768, 1024, 1, "f32", True), (32896, 1024, 1, "f32", False),      # one fp32 column: 32 Mi weights
     (32896, 1024, 2, "f32", True),
+    (2048, 12288, 1, "f32", True), (2048, 16084, 1, "f32", False),      # ... and long chains although k is cut
+    (448, 8192, 1, "f32", True), (448, 12288, 16, "f32", True),         # (two and four segments)
     (240 * CUS, 128, 1, "f16", True), (240 * CUS + 1, 128, 1, "f16", False), (240 * CUS + 1, 258, 1, "f16", True),
     (512 * CUS, 512, 5, "f16", True), (512 * CUS + 1, 512, 5, "f16", False), (512 * CUS + 1, 514, 5, "f16", True),
     (200 * CUS, 64, 48, "f16", True), (200 * CUS + 1, 64, 48, "f16", False),    # (three passes over 16 columns)
