@@ -1025,7 +1025,9 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
     MSGEMM_CASE(2, 0, 4, 4)
     MSGEMM_CASE(1, 0, 4, 8)
     if constexpr (sizeof(XT) != 1) {  // (int8: the compact form holds eight columns)
-        MSGEMM_CASE(4, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+        // (four row tiles: rings of four leave one wavefront a SIMD.  us, depth four / three / two: 50000 x 1024 x 8 fp16 15.0 / 9.7 /
+        // 8.7, 28672 x 8192 x 8 fp16 24.5 / 22.4 / 22.1, bf16 27.8 / 25.4 / 24.1, 12288 x 49152 x 8 fp16 55.9 / 56.0 / 59.3, bf16 64.6 / 64.6 / 63.3)
+        MSGEMM_CASE(4, 2, 4, __is_same(XT, __half) ? 3 : 2)
         MSGEMM_CASE(2, 2, 4, sizeof(XT) == 4 ? 2 : 4)
         MSGEMM_CASE(1, 2, 4, sizeof(XT) == 4 ? 2 : 4)
     }
