@@ -1150,8 +1150,9 @@ bool short_k(const Plan& p, int64_t k)
 
 }  // namespace
 
-// Whether the library's own choice for a plan is the matrix form, and its shape.
-bool matrix_choose_shape(Plan& p, int requested_variant)
+// Whether the library's own choice for a plan is the matrix form, and its shape.  anyway: also where the table kernels are the
+// faster ones.
+bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
 {
     const msgemm_plan_options_t& o = p.opt;
     p.matrix = false;
@@ -1187,11 +1188,11 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     // One fp32 column of 4-bit codes: decoding and three products per weight where the table kernels add once per pair
     // (4096 x 4096 5.5 us against 6.9, 8192 x 8192 11.0 against 10.3, 49152 x 12288 74 against 52; 8-bit codes, one
     // conversion for two, 12.5 against 17.0 at 8192 x 8192).
-    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && p.m * k > ((int64_t)32 << 20) && !asked) return false;
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && p.m * k > ((int64_t)32 << 20) && !asked && !anyway) return false;
     // (streaming kernel, 300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; ahead at 100000 rows and 512 columns,
     // 17.2 against 20.5 with eight columns of X)
-    if (!tile && k <= 512 && p.m > (int64_t)512 * p.cus && !asked) return false;
-    if (short_k(p, k) && !asked) return false;
+    if (!tile && k <= 512 && p.m > (int64_t)512 * p.cus && !asked && !anyway) return false;
+    if (short_k(p, k) && !asked && !anyway) return false;
 
     const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
     const bool scaled = p.scale_group > 0;
@@ -1236,7 +1237,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant)
     int64_t segments = segments_of(R);
     // (a single fp32 column whose chains stay long although they are cut: 2048 x 16084 10.2 us in two segments, tables 8.7;
     // level at 2048 x 12288, 12 runs a wavefront)
-    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * W * 12 && !asked) return false;
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * W * 12 && !asked && !anyway) return false;
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
     p.mx_tile_kernel = tile;
     p.mx_r = R;

@@ -128,12 +128,15 @@ static int plan_impl(msgemm_plan_t** out, int64_t m, int64_t k, int64_t b, int x
     p->cus = 256;
     (void)hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, p->device);
     if (values256) msgemm::matrix_find_format(*p, values256);
+    const int matrix_variant = values256 ? variant : (int)MSGEMM_VARIANT_FUSED_LDS;  // (8-bit codes: the one it takes the place of)
     if (!tables_only && msgemm::matrix_choose_shape(*p, variant)) {
-        p->variant = values256 ? variant : (int)MSGEMM_VARIANT_FUSED_LDS;  // (8-bit codes: the one it takes the place of)
+        p->variant = matrix_variant;
     } else if (variant != MSGEMM_VARIANT_GLOBAL_LUT) {
         rc = msgemm::fused_choose_shape(*p, variant);
         if (rc == MSGEMM_OK) {
             p->variant = p->fs.entry_bytes == 2 ? MSGEMM_VARIANT_FUSED_LDS16 : MSGEMM_VARIANT_FUSED_LDS;
+        } else if (rc == MSGEMM_ERR_UNSUPPORTED && !tables_only && msgemm::matrix_choose_shape(*p, variant, true)) {
+            p->variant = matrix_variant;  // (the tables would be the faster ones, but cannot serve it)
         } else if (variant != MSGEMM_VARIANT_AUTO || rc != MSGEMM_ERR_UNSUPPORTED) {
             return fail(rc);
         }

@@ -143,7 +143,7 @@ int launch_batched(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t l
 
 // kernels_matrix.hip (codes decoded in registers, sums on the matrix cores: the library's own choice where it applies)
 void matrix_find_format(Plan& p, const float* values256);   // fills mx_format, mx_factor, mx_remap
-bool matrix_choose_shape(Plan& p, int requested_variant);  // fills the mx_* fields, row_blocks, m_pad, ...; false if not applicable
+bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway = false);  // fills the mx_* fields, row_blocks, m_pad, ...; false if not applicable
 size_t matrix_code_bytes(const Plan& p);
 size_t matrix_scale_bytes(const Plan& p);
 int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s);

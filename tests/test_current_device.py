@@ -1,4 +1,4 @@
-"""Which device and stream the host side of the library uses, on the CPU: libmsgemm.so over a stand-in for the HIP runtime
+"""Which device and stream the host side of the library uses, and what it chooses, on the CPU: libmsgemm.so over a stand-in for the HIP runtime
 (recording_hip_runtime.c) that knows several devices and computes nothing.  Each case runs in a process of its own."""
 import os
 import subprocess
@@ -97,6 +97,22 @@ assert B.msgemm_plan_get_info(eight)["tile_groups"] == 128   # (the matrix form)
 assert 4 not in [k for k, _, _ in calls(0)]
 B.msgemm_plan(96, 512, 1, "f16", "f16", 2, 0, ADDRESS, stream=0)
 assert [k for k, _, _ in calls(0)].count(4) == 1
+print("ok")
+""")
+    assert out.strip().endswith("ok")
+
+
+def test_the_matrix_form_serves_what_the_table_kernels_refuse(runtime):
+    """Where a short k under many rows belongs to the tables but their partial sums would pass 2 GiB."""
+    out = run(runtime, """
+from paper_2310_06178_amd import inputs
+values = [0.0 if v != v else float(v) for v in inputs.fp8_e4m3_values()]
+for m, matrix in ((1 << 20, False), (1 << 22, True)):
+    plan = B.msgemm_plan(m, 64, 200, "f16", "f16", 2, 0, ADDRESS, stream=0)
+    info = B.msgemm_plan_get_info(plan)
+    assert (info["variant"] == B.VARIANT_FUSED_LDS and info["tile_groups"] == 64) == matrix, info
+    plan = B.msgemm_plan_codes8(m, 64, 200, "f16", "f16", 0, ADDRESS, None, values, stream=0)
+    assert (B.msgemm_plan_get_info(plan)["tile_groups"] == 128) == matrix
 print("ok")
 """)
     assert out.strip().endswith("ok")
