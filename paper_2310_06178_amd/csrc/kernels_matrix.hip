@@ -58,12 +58,13 @@ struct __attribute__((packed, aligned(1))) Any2 { uint16_t a; };
 //   decode  the codes of one MFMA step -> its weight operand
 template <typename XT> struct Policy;
 
-// (x & mask) | bits in one instruction (with two constants the compiler takes two)
+// (x & mask) | bits in one instruction: with `bits` as a constant the compiler takes two, so its value is hidden from it.  (The
+// instruction itself is left to the compiler.  Written as inline asm it is not looked at when the wait states behind a matrix
+// instruction are counted, and its result may take a register that the matrix instruction has yet to write.)
 __device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t mask, uint32_t bits)
 {
-    uint32_t r;
-    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "s"(mask), "v"(bits));
-    return r;
+    asm("" : "+v"(bits));
+    return (x & mask) | bits;
 }
 
 template <> struct Policy<__half> {
