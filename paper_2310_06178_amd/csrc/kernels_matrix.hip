@@ -1021,20 +1021,15 @@ template <typename XT>
 int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
 #define MSGEMM_CASE(RR, CC, WW, DD) \
-    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW) return launch_stream<XT, RR, CC, WW, DD, kInt4>(p, a, s);
-    MSGEMM_CASE(4, 0, 4, 4)
-    MSGEMM_CASE(2, 0, 4, 4)
-    MSGEMM_CASE(1, 0, 4, 8)
+    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW && p.mx_depth == DD) return launch_stream<XT, RR, CC, WW, DD, kInt4>(p, a, s);
+    MSGEMM_CASE(4, 0, 4, 2)
+    MSGEMM_CASE(2, 0, 4, 2) MSGEMM_CASE(2, 0, 4, 4)
+    MSGEMM_CASE(1, 0, 4, 2) MSGEMM_CASE(1, 0, 4, 4) MSGEMM_CASE(1, 0, 4, 8) MSGEMM_CASE(1, 0, 16, 2)
     if constexpr (sizeof(XT) != 1) {  // (int8: the compact form holds eight columns)
-        // (four row tiles: rings of four leave one wavefront a SIMD.  us, depth four / three / two: 50000 x 1024 x 8 fp16 15.0 / 9.7 /
-        // 8.7, 28672 x 8192 x 8 fp16 24.5 / 22.4 / 22.1, bf16 27.8 / 25.4 / 24.1, 12288 x 49152 x 8 fp16 55.9 / 56.0 / 59.3, bf16 64.6 / 64.6 / 63.3)
-        MSGEMM_CASE(4, 2, 4, __is_same(XT, __half) ? 3 : 2)
-        MSGEMM_CASE(2, 2, 4, sizeof(XT) == 4 ? 2 : 4)
-        MSGEMM_CASE(1, 2, 4, sizeof(XT) == 4 ? 2 : 4)
+        MSGEMM_CASE(4, 2, 8, 2) MSGEMM_CASE(2, 2, 8, 2) MSGEMM_CASE(1, 2, 8, 2)
     }
-    MSGEMM_CASE(4, 4, 8, 2)
-    MSGEMM_CASE(2, 4, 4, sizeof(XT) == 4 ? 2 : 4)
-    MSGEMM_CASE(1, 4, 4, sizeof(XT) == 4 ? 2 : 4)
+    constexpr int kWidest = sizeof(XT) == 4 ? 8 : 4;
+    MSGEMM_CASE(4, 4, kWidest, 2) MSGEMM_CASE(2, 4, 8, 2) MSGEMM_CASE(1, 4, 8, 2)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
@@ -1043,12 +1038,13 @@ template <typename XT, int F>
 int launch_for_codes8(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
 #define MSGEMM_CASE(RR, CC, DD) \
-    if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == 4) return launch_stream<XT, RR, CC, 4, DD, F>(p, a, s);
+    if (p.mx_r == RR && p.mx_cols == CC && p.mx_depth == DD) return launch_stream<XT, RR, CC, 4, DD, F>(p, a, s);
     MSGEMM_CASE(2, 0, 4)
     MSGEMM_CASE(1, 0, 4)
     MSGEMM_CASE(2, 2, 2)
     // (fp32: rings of four take all registers of a SIMD for one wavefront; 4096 x 4096 x 8 8.4 us, in twos 7.5, 20000 x 512 x 8 15.4 / 7.4)
-    MSGEMM_CASE(1, 2, sizeof(XT) == 4 ? 2 : 4)
+    constexpr int kDeep = sizeof(XT) == 4 ? 2 : 4;
+    MSGEMM_CASE(1, 2, kDeep)
     MSGEMM_CASE(2, 4, 2)
     MSGEMM_CASE(1, 4, 2)
 #undef MSGEMM_CASE
@@ -1203,6 +1199,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     const int64_t passes = tile ? tile_passes : (p.b + 15) / 16;
     if (passes > 65535) return false;
     const auto groups = [&](int r) { return (p.m + 16 * Wr * r - 1) / (16 * Wr * r); };
+    // (wavefronts that the rule for segments counts with; the streaming kernel's workgroups may have more)
     const auto waves = [&](int r) { return tile ? 8 : width == 2 && r == 4 ? 8 : 4; };
     // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a wavefront
     // keeps 16 runs (tile kernel: a workgroup 20, since the second launch and the sums' trip to memory and back take 10 to
@@ -1223,7 +1220,14 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // rounds of one tile 73 us, one of two 53; 49152 x 12288 x 64: 135, 110 and 87; three scaled tiles do not fit the
     // registers).
     const int tiles[2][3] = {{1, 2, 4}, {1, 2, 3}};
-    const double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 4.0}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
+    double cost[4][3] = {{1.25, 2.0, 3.95}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
+    // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, a little more
+    // where two workgroups of one tile would do the work of one of two.  us, one tile / two: 28672 x 4096 x 1 fp16 with scales 12.1 / 12.9,
+    // 11008 x 4096 x 4 bf16 7.1 / 8.0, 8192 x 8192 x 1 bf16 8.4 / 8.7, 8192 x 4096 x 1 5.1 / 5.0, 16384 x 16384 x 1 23.7 / 23.1)
+    if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && p.x_dtype != MSGEMM_I8) {
+        if (runs < 96) cost[0][0] = runs < 64 && groups(1) <= 2 * p.cus ? 1.05 : 0.98;
+        cost[0][2] = 4.12;
+    }
     double best = 0;
     int R = 1;
     for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i) {
@@ -1234,12 +1238,37 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     }
     for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i)
         if (asked && o.panels_per_workgroup == tiles[tile][i]) R = o.panels_per_workgroup;
-    const int W = waves(R);
     int64_t segments = segments_of(R);
     // (a single fp32 column whose chains stay long although they are cut: 2048 x 16084 10.2 us in two segments, tables 8.7;
     // level at 2048 x 12288, 12 runs a wavefront)
-    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * W * 12 && !asked && !anyway) return false;
+    if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * waves(R) * 12 && !asked && !anyway) return false;
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
+    // Streaming kernel, wavefronts and depth of their rings: what keeps the memory busy is some 32 KiB of codes in flight per compute
+    // unit (its share of 6.3 TB/s times a microsecond's trip); more only queues, and an unrolled loop that is gone through once or twice
+    // is fetched for nothing.  us, one column or a few, one row tile, "wavefronts x depth":
+    //   a workgroup per compute unit: 4096 x 14336 x 1 fp16 4 x 8 7.1, 16 x 2 7.0, 4 x 4 7.9; 4096 x 4096 x 1 fp32 5.6, 5.0, 5.1; a short k
+    //   in fours, 2048 x 1024 x 1 fp16 4 x 8 2.8, 16 x 2 2.7, 4 x 2 2.5
+    //   two: 8192 x 8192 x 1 bf16 4 x 8 9.1, 4 x 4 8.4; 8192 x 14336 x 1 fp16 11.8, 11.4
+    //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; but 12288 x 49152 x 1 45.8, 4 x 2 47.5
+    // Two row tiles: 6144 x 6144 x 3 4 x 4 5.6; 14336 x 8192 x 4 fp32 in two workgroups per compute unit 4 x 4 20.4, 4 x 2 19.2.
+    // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 4096 x 4096 x 8 fp32 4 x 2 7.2, 8 x 2 6.4; 28672 x 4096 x 6 fp16 (four row tiles)
+    // 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16 columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15.
+    const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
+    int W = 4, D = 2;
+    if (tile) {
+        W = 8;
+    } else if (bytes) {
+        D = compact ? 4 : width == 1 && R == 1 && p.x_dtype != MSGEMM_F32 ? 4 : 2;
+    } else if (!compact) {
+        W = width == 2 && R == 4 && p.x_dtype != MSGEMM_F32 ? 4 : 8;
+    } else if (R == 2) {
+        D = per_cu == 1 ? 4 : 2;
+    } else if (R == 1) {
+        if (seg_runs >= 32 && per_cu == 1) W = 16;
+        else if (seg_runs >= 256) D = 8;
+        else if (seg_runs >= 16 && per_cu <= 2) D = 4;
+    }
+    p.mx_depth = D;
     p.mx_tile_kernel = tile;
     p.mx_r = R;
     p.mx_row_waves = Wr;

@@ -88,6 +88,7 @@ struct Plan {
     int mx_r;             // row tiles of 16 per wavefront
     int mx_row_waves;     // wavefronts side by side in rows
     int mx_waves;         // wavefronts per workgroup
+    int mx_depth;         // streaming kernel: runs that a wavefront has in flight
     int mx_cols;          // columns of X held: streaming kernel in fours (0: the compact form), tile kernel in sixteens
     int mx_segments;      // k-segments (workgroups along k), added by a second launch if more than one
     int mx_format;        // 8-bit codes: the format the device converts (kernels_matrix.hip), 0 = none
