@@ -18,6 +18,8 @@
 // the nibbles in the order the decoder yields them; MFMA step t takes dword t of every lane (int8: dwords 2 t, 2 t + 1).
 // One 16-byte load of a wavefront is 1 KiB of consecutive memory and one row tile's share of a run.
 // Scales: [row group][scale block][n][r] fp16, so a lane's scales for its R tiles are one load.
+// The tile kernel's tiles have 32 rows: lane (n, h) = (lane & 31, lane >> 5) holds columns 64 h + 0..63 of row n in two such loads, one behind the
+// other; its steps take 8 columns of each half (int8: 16).
 #include "device_types.h"
 #include "fused_common.h"
 #include "msgemm_internal.h"
@@ -33,6 +35,7 @@ namespace {
 
 constexpr int kRun = 128;          // columns of k per step: one 16-byte load per lane and row tile
 constexpr uint32_t kPastEnd = 0x7fff0000u;  // a buffer offset past any plan's codes: the load returns zero and reads nothing
+constexpr int kTileRowWaves = 2;   // tile kernel: wavefronts side by side in rows
 constexpr int kAuxNt = 2;          // buffer cache policy bit: non-temporal (every code is used once)
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
@@ -40,6 +43,8 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v16i __attribute__((ext_vector_type(16)));
 
 // 16 bytes at any alignment the element type allows (columns of X may start anywhere)
 template <int kAlign> struct __attribute__((packed, aligned(kAlign))) Any16 { uint32_t a, b, c, d; };
@@ -628,28 +633,19 @@ matrix_stream_kernel(MatrixArgs a)
     }
 }
 
-// Tile kernel, more columns than the streaming kernel holds.  A workgroup owns 64 R rows (four wavefronts of R row tiles)
-// for all of k, or a segment of it, and up to 16 NT columns: two groups of four wavefronts take alternate runs, and the
-// wavefronts of a group share the run's activations, staged in LDS in the streaming kernel's operand slots.
-//
-// Bound by the code stream and the matrix cores; what it takes to get near either:
-//   * Loads return in order, so a wait for activations is a wait for every code requested before them, and the codes take
-//     the trip to memory.  Both are therefore requested five to six steps ahead (registers; three more steps in LDS).
-//   * One barrier per step.  The operands of an MFMA step are read and decoded under the MFMAs of the one before it, also
-//     across the barrier: the two wavefronts of a SIMD leave it together, and what each did alone before its first MFMA
-//     would be a third of a step.
-// Measured: 28672 x 8192 x 64 bf16 with scales 52 us (table kernels 228-235), 49152 x 12288 x 64 fp16 87 us = 890 Tflop/s
-// (536-550).  The matrix cores are in use for 0.47 of the cycles there, the vector units for 0.34, at a clock of 1.8 GHz
-// (power; 2.3 under light loads).  Without its loads from memory the kernel takes 61 us.  Slower: twelve wavefronts of two
-// row tiles (119 us: registers, and the barrier gets longer); level: the operand slots turned by the step alone.
-template <typename XT, int R, int NT, bool kScaled>
+// Tile kernel for int8 activations, a long k and up to 48 columns: the larger tiles of the kernel below have too little to do between its
+// meetings there (8 steps of a microsecond and a half, 28672 x 4096 x 24: 15.6 us against 14.6).  A workgroup owns 64 R rows (four wavefronts of
+// R row tiles) for all of k, or a segment of it, and up to 16 NT columns: two groups of four wavefronts take alternate runs, and the wavefronts
+// of a group share the run's activations, staged in LDS in the streaming kernel's operand slots.  Activations and codes are requested five
+// to six steps ahead (registers; three more steps in LDS): loads return in order, so a wait for activations is a wait for every code requested
+// before them.  The operands of an MFMA step are read and decoded under the MFMAs of the one before it, also across the barrier.
+template <typename XT, int R, int NT>
 __global__ void __launch_bounds__(512)
-matrix_tile_kernel(MatrixArgs a)
+matrix_small_tile_kernel(MatrixArgs a)
 {
     using P = Policy<XT>;
     using acc_t = typename P::acc_t;
     using YT = typename P::out_t;
-    constexpr bool kInt = sizeof(XT) == 1;
     constexpr int Wr = 4, Wk = 2;                      // wavefronts side by side in rows, groups of them along k
     constexpr int T = P::kFrags;
     constexpr int kPiece = 16 / (int)sizeof(XT);       // elements of a 16-byte piece
@@ -659,8 +655,6 @@ matrix_tile_kernel(MatrixArgs a)
     constexpr int kCodesAhead = 6, kXAhead = 3, kBuffers = 3;
     constexpr int kRows = 16 * R * Wr;
     constexpr int kPitch = kRows + 4;
-    constexpr int Rp = R == 3 ? 4 : R;                 // scales per lane and block, padded to a power of two
-    static_assert(sizeof(XT) != 4, "fp32 activations have three parts");
     constexpr int kXWords = Wk * kBuffers * kLoads * 256, kRedWords = 2 * Wk * 16 * kPitch;
     __shared__ __align__(16) uint32_t lds[kXWords > kRedWords ? kXWords : kRedWords];
 
@@ -679,13 +673,9 @@ matrix_tile_kernel(MatrixArgs a)
     constexpr uint32_t run_bytes = R * Wr * 1024u;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
-    constexpr int kScaleRow = Wr * 16 * Rp;
-    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.scales + (int64_t)rg * a.nblocks * kScaleRow), 0, kScaled ? (int)(a.nblocks * kScaleRow * 2) : 0, 0x00020000);
-
     struct Codes {
         v4u c[R];
-        uint32_t q[(Rp + 1) / 2];
+        uint32_t unused;                               // (without it the compiler makes branches of the shifts below: 28672 x 4096 x 24 15.0 us, 14.6)
     };
     auto load_codes_of = [&](Codes& st, int run) {
         const bool ok = run < run1;
@@ -693,17 +683,6 @@ matrix_tile_kernel(MatrixArgs a)
 #pragma unroll
         for (int r = 0; r < R; ++r)
             st.c[r] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + r * 1024u), 0, kAuxNt);
-        if constexpr (kScaled) {
-            const uint32_t so = (ok ? fast_div((uint32_t)run, a.div_block) * (uint32_t)(kScaleRow * 2) : kPastEnd) + (wr * 16 + n) * (uint32_t)(Rp * 2);
-            if constexpr (Rp == 4) {
-                const v2u v = __builtin_amdgcn_raw_buffer_load_b64(srsrc, (int)so, 0, 0);
-                st.q[0] = v.x; st.q[1] = v.y;
-            } else if constexpr (Rp == 2) {
-                st.q[0] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, (int)so, 0, 0);
-            } else {
-                st.q[0] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(srsrc, (int)so, 0, 0);
-            }
-        }
     };
 
     // Staging: load f = wr + i Wr of a run takes kColsPerLoad columns, consecutive lanes consecutive pieces.  The address
@@ -792,7 +771,6 @@ matrix_tile_kernel(MatrixArgs a)
 #pragma unroll
         for (int d = 0; d < kCodesAhead; ++d) {
             Codes& mine = ring[d];
-            acc_t blk[R][NT];
             put_x(xr[(d + 2) % kXAhead], run_of(s + d + 2), (d + 2) % kBuffers);
             load_x(xr[(d + 2) % kXAhead], run_of(s + d + 2 + kXAhead));
             __builtin_amdgcn_sched_barrier(0);
@@ -804,16 +782,10 @@ matrix_tile_kernel(MatrixArgs a)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        if constexpr (kScaled) {
-                            blk[r][nt] = P::mma(x[nt], w[now][r], t == 0 ? acc_t{0, 0, 0, 0} : blk[r][nt]);
-                        } else {
-                            acc[r][nt] = P::mma(x[nt], w[now][r], acc[r][nt]);
-                        }
-                    }
+                    for (int r = 0; r < R; ++r) acc[r][nt] = P::mma(x[nt], w[now][r], acc[r][nt]);
                     x[nt] = read_x(over ? (d + 1) % kBuffers : d % kBuffers, over ? 0 : t + 1, nt);
                 }
-                constexpr int kDecode = kInt ? 6 : __is_same(XT, __half) ? 9 : 13;
+                constexpr int kDecode = 6;
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
@@ -822,19 +794,6 @@ matrix_tile_kernel(MatrixArgs a)
                         __builtin_amdgcn_sched_group_barrier(0x002, kDecode / NT + 1, 0);   // its share of the decoding
                     }
                     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // the tile's next operand
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (kScaled) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const float q = __half2float(__ushort_as_half((uint16_t)(mine.q[r / 2] >> (16 * (r & 1)))));
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[r][nt][i] = fmaf(q, blk[r][nt][i], acc[r][nt][i]);
-                        asm volatile("" : "+v"(acc[r][nt]));   // (here and now: the compiler would keep all steps' sums until the end of the loop)
-                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -851,7 +810,7 @@ matrix_tile_kernel(MatrixArgs a)
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (kInt) acc[r][nt][i] >>= 4;
+                acc[r][nt][i] >>= 4;
                 red[(g * 16 + 4 * q + i) * kPitch + (wr * R + r) * 16 + n] = bits(acc[r][nt][i]);
             }
         lds_barrier();
@@ -859,11 +818,10 @@ matrix_tile_kernel(MatrixArgs a)
             const int c = nt * 16 + o / kRows, row = o % kRows;
             const int64_t grow = (int64_t)rg * kRows + row;
             if (grow >= a.m || c >= ncols) continue;
-            using S = typename std::conditional<kInt, int, float>::type;
-            S sum = 0;
+            int sum = 0;
 #pragma unroll
             for (int k = 0; k < Wk; ++k) {
-                S v;
+                int v;
                 __builtin_memcpy(&v, &red[(k * 16 + c % 16) * kPitch + row], 4);
                 sum += v;
             }
@@ -871,8 +829,337 @@ matrix_tile_kernel(MatrixArgs a)
                 a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(sum);
                 continue;
             }
-            if constexpr (!kInt && !__is_same(XT, __half)) sum *= a.factor;
-            ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = to_output<YT, S>(sum);
+            ((YT*)a.Y)[(int64_t)(col0 + c) * a.ldy + grow] = sum;
+        }
+    }
+}
+
+// Tile kernel, more columns than the streaming kernel holds.  A workgroup owns 64 R rows for all of k, or a segment of it, and up
+// to 32 NT columns.  Four pairs of wavefronts take alternate runs of 128 columns of k; each wavefront of a pair has R tiles of 32 rows, and the
+// pair shares the run's activations, staged in LDS.
+//
+// What bounds it, and what the shape is for (49152 x 12288 x 64 fp16, 28672 x 8192 x 64 bf16 with scales):
+//   * Issue of vector and matrix instructions, and power.  A SIMD issues a matrix instruction in 8 clocks and a vector instruction in 4.7, whichever
+//     of its two wavefronts they come from: products of 32 x 32 need half as many as products of 16 x 16.  With them 2.3 (4.3 with scales) vector
+//     instructions per 16 x 16 x 32 products fit beside the matrix cores' own 16 clocks.  The clock falls to 1.5 GHz under 49152 x 12288 x 64;
+//     with activations of zero it takes 65 us.
+//   * LDS: two wavefronts read a run's activations, where four did in tiles of 16 rows.
+//   * Vector memory: 112 KiB of codes and activations a step and compute unit, 1800 of its 4300 clocks.  Activations go straight to the LDS (through
+//     registers 91 us instead of 79), and no wavefront asks for much at once: the next step's activations in the first half of a step, then
+//     the codes of the step after it, which come from memory and have a step more to arrive.
+//   * One meeting of the wavefronts a step, behind it.  Ahead of the last products of a step: level.
+// Measured, us: 49152 x 12288 x 64 fp16 77 to 82 = 0.94 to 1.0 Pflop/s (tiles of 16 rows with activations through registers 87 to 89), 28672 x 8192 x 64 bf16 with
+// scales 41 to 44 (51 to 52), 16384 x 4096 x 64 15.6 (21), 14336 x 4096 x 32 12.6 (14.3), 28672 x 4096 x 64 int8 18.6 (20.9).  Level or slower: wavefronts of
+// different priority, an interleaving of products and decoding laid down by hand.
+// 32 x 32 products, sixteen (int8: 32) columns of k at a time
+template <typename XT> struct Big {
+    using acc_t = v16f;
+    static constexpr int kSteps = 8, kVecSteps = 4;    // per run; per 16-byte load of codes
+    static __device__ __forceinline__ v16f mma(const v4u& x, const v4u& w, const v16f& c)
+    {
+        if constexpr (__is_same(XT, __half))
+            return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, x), __builtin_bit_cast(v8h, w), c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, x), __builtin_bit_cast(v8bf, w), c, 0, 0, 0);
+    }
+};
+template <> struct Big<int8_t> {
+    using acc_t = v16i;
+    static constexpr int kSteps = 4, kVecSteps = 2;
+    static __device__ __forceinline__ v16i mma(const v4u& x, const v4u& w, const v16i& c)
+    {
+        return __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(v4i, x), __builtin_bit_cast(v4i, w), c, 0, 0, 0);
+    }
+};
+
+template <typename XT, int R, int NT, bool kScaled, bool kDirect>
+__global__ void __launch_bounds__(512)
+matrix_tile_kernel(MatrixArgs a)
+{
+    using P = Policy<XT>;
+    using G = Big<XT>;
+    using acc_t = typename G::acc_t;
+    using YT = typename P::out_t;
+    static_assert(sizeof(XT) != 4 && !(kScaled && R > 2));
+    constexpr bool kInt = sizeof(XT) == 1;
+    constexpr int Wr = kTileRowWaves, Wk = 8 / Wr;
+    constexpr int T = G::kSteps;
+    constexpr int kPiece = 16 / (int)sizeof(XT);       // elements of a 16-byte piece
+    constexpr int kPieces = kRun / kPiece;             // pieces of a column's run
+    constexpr int kColsPerLoad = 64 / kPieces;         // a wavefront's load: 1 KiB of LDS
+    constexpr int kMine = 32 * NT / kColsPerLoad / Wr; // of a run's loads a wavefront's
+    constexpr uint32_t kTileBytes = 32 * NT * kRun * sizeof(XT), kStageBytes = Wk * kTileBytes;
+    constexpr int kRows = 32 * R * Wr;
+    // the final sum: column tiles at a time, and words from row to row (16 rows' pieces of 16 bytes fall on different banks)
+    constexpr int kAtOnce = R < 3 ? NT : 1, kPitch = 32 * kAtOnce + 4;
+    constexpr int Rp = R == 3 ? 4 : R;                 // scales per lane and block, padded to a power of two
+    constexpr uint32_t kRedBytes = Wk * kRows * kPitch * 4;
+    __shared__ __align__(1024) uint8_t lds[2 * kStageBytes > kRedBytes ? 2 * kStageBytes : kRedBytes];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave % Wr, g = wave / Wr;
+    const int n = lane & 31, h = lane >> 5;
+    // the column passes of one row group follow each other on one XCD: they stream the same codes
+    const int unit = blockIdx.x / kXcds, pass = unit % a.passes;
+    const int rg = unit / a.passes * kXcds + blockIdx.x % kXcds;
+    if (rg >= a.row_groups) return;
+    const int col0 = pass * NT * 32, ncols = a.b - col0 < NT * 32 ? a.b - col0 : NT * 32;
+    // what the end needs is fetched now: there the trip of the scalar loads would be in the way
+    YT* Y = (YT*)a.Y;
+    uint32_t* partials = a.partials;
+    int64_t ldy = a.ldy, m = a.m;
+    float factor = a.factor;
+    asm volatile("" : "+s"(Y), "+s"(partials), "+s"(ldy), "+s"(m), "+s"(factor));
+    // this segment's runs; a ragged one (the last of k) goes first, so that what it takes is part of the start
+    const int run0 = blockIdx.y * a.seg_runs;
+    const int run1 = run0 + a.seg_runs < a.runs ? run0 + a.seg_runs : a.runs;
+    const int nruns = run1 - run0, ragged = run1 > a.full_runs ? 1 : 0;
+    const int steps = (nruns + Wk - 1) / Wk;
+
+    constexpr uint32_t run_bytes = R * Wr * 2048u;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
+    constexpr int kScaleRow = Wr * 32 * Rp;
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.scales + (int64_t)rg * a.nblocks * kScaleRow), 0, kScaled ? (int)(a.nblocks * kScaleRow * 2) : 0, 0x00020000);
+
+    // Activations.  Load i of a run takes kColsPerLoad columns, a lane 16 bytes, which go to 16 bytes of LDS in the lanes' order; which
+    // piece of its column a lane takes is turned by the column, so that the lanes that read one piece of 16 columns find them on
+    // different banks while every load still covers whole runs of columns.
+    const auto turn = [](int col) { return kInt ? (col >> 1) & 7 : col & 15; };
+    const uint8_t* const xbase = (const uint8_t*)((const XT*)a.X + (int64_t)col0 * a.ldx);
+    using off_t = typename std::conditional<kDirect, uint32_t, int64_t>::type;   // (direct: the host has seen that 32 bits are enough)
+    off_t xoff[kMine];                                 // bytes from xbase, at the first run
+    int xpiece[kMine];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const int slot = (wr + i * Wr) * kColsPerLoad + lane / kPieces;
+        xpiece[i] = (lane % kPieces ^ turn(slot)) * kPiece;
+        xoff[i] = (off_t)((slot < ncols ? slot : ncols - 1) * a.ldx * (int64_t)sizeof(XT)) + xpiece[i] * (int)sizeof(XT);
+    }
+    const uint64_t xaddr = (uint64_t)xbase;
+    const v4i xrsrc = {(int)(uint32_t)xaddr, (int)((uint32_t)(xaddr >> 32) & 0xffffu), (int)0x7fffffff, 0x00020000};
+    uint8_t* const mine = lds + g * kTileBytes;
+
+    struct Codes {
+        v4u c[R][2];
+        uint32_t q[1];
+    };
+    v4u xr[kDirect ? 1 : kMine];
+    const auto run_at = [&](int i) { return ragged ? (i == 0 ? run1 - 1 : run0 + i - 1) : run0 + i; };
+    // (a step past the last run: the codes come from past the end of the buffer, the activations are those of the first run again)
+    const auto load_code = [&](Codes& st, bool ok, int run, int j) {
+        const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + wr * R * 2048u + lane * 16u;
+        st.c[j / 2][j % 2] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + j * 1024u), 0, kAuxNt);
+    };
+    const auto load_scales = [&](Codes& st, bool ok, int run) {
+        if constexpr (kScaled) {
+            const uint32_t so = (ok ? fast_div((uint32_t)run, a.div_block) * (uint32_t)(kScaleRow * 2) : kPastEnd) + (wr * 32 + n) * (uint32_t)(Rp * 2);
+            if constexpr (Rp == 2) st.q[0] = __builtin_amdgcn_raw_buffer_load_b32(srsrc, (int)so, 0, 0);
+            else st.q[0] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(srsrc, (int)so, 0, 0);
+        }
+    };
+    const auto load_x = [&](uint32_t buf, int run, int j) {
+        if constexpr (kDirect) {
+            const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)mine + buf + (wr + j * Wr) * 1024u;
+            // (the wait states are those behind a vector instruction that writes a scalar operand, which the compiler does not count into asm)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                         :: "s"(to), "v"(xoff[j]), "s"(xrsrc), "s"(run * (int)(kRun * sizeof(XT))));
+        } else {
+            xr[j] = load_any16<sizeof(XT)>(xbase + xoff[j] + (int64_t)run * (int)(kRun * sizeof(XT)));
+        }
+    };
+    const auto put = [&](int i, uint32_t buf, const v4u& v) { *(v4u*)&mine[buf + (wr + i * Wr) * 1024 + lane * 16] = v; };
+    // The ragged run: the address stops at the last whole piece of the column, what that moves is shifted back, zeros coming in
+    // (elements past k are zero whatever lies behind them).
+    const auto stage_ragged = [&] {
+        const int last = (int)a.k - kPiece;
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const int kk = a.full_runs * kRun + xpiece[i], at = kk < last ? kk : last;
+            v4u v = load_any16<sizeof(XT)>(xbase + xoff[i] + (int64_t)(at - xpiece[i]) * (int)sizeof(XT));
+            const int h2 = (kk - at) * (int)sizeof(XT) / 2;   // halfwords
+            if (h2 & 1) v = v4u{v[0] >> 16 | v[1] << 16, v[1] >> 16 | v[2] << 16, v[2] >> 16 | v[3] << 16, v[3] >> 16};
+            if (h2 & 2) v = v4u{v[1], v[2], v[3], 0};
+            if (h2 & 4) v = v4u{v[2], v[3], 0, 0};
+            if (h2 & ~7) v = v4u{0, 0, 0, 0};
+            put(i, 0, v);
+        }
+    };
+    // the first step's, requested at once
+    const auto request = [&](Codes& st) {
+        if (g >= nruns) return;
+        const int run = run_at(g);
+        if (run < a.full_runs) {
+#pragma unroll
+            for (int j = 0; j < kMine; ++j) load_x(0, run, j);
+            if constexpr (!kDirect) {
+#pragma unroll
+                for (int j = 0; j < kMine; ++j) put(j, 0, xr[j]);
+            }
+        } else {
+            stage_ragged();
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) load_code(st, true, run, j);
+        load_scales(st, true, run);
+    };
+    // The next step's activations are in LDS for every wavefront when this returns, its codes in registers; the codes of the one after it are
+    // still on their way: `later` loads, the last that were asked for.
+    const auto arrive = [&](auto later) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(decltype(later)::value) : "memory");
+    };
+
+    acc_t acc[R][NT];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][nt][i] = 0;
+    const uint32_t xread = g * kTileBytes + (uint32_t)n * (kPieces * 16u) + (uint32_t)((h * T) ^ turn(n)) * 16u;
+    // A step, and the requests behind it, spread over it: asked for at once they queue up in front of the vector memory unit, and the
+    // wavefront with them.  The activations of the next step go first (they come from the L2), then the codes of the one after it, which
+    // have a step more to arrive.
+    v4u w[2][R], x[2][NT];
+    constexpr int kHalf = T / 2;
+    constexpr int kLater = 2 * R + (kScaled ? 1 : 0);
+    const auto compute = [&](const Codes& st, const Codes& next, Codes& later, int s, uint32_t buf) {
+        const bool ok1 = (s + 1) * Wk + g < nruns, ok2 = (s + 2) * Wk + g < nruns;
+        const int run1 = ok1 ? run_at((s + 1) * Wk + g) : 0, run2 = ok2 ? run_at((s + 2) * Wk + g) : 0;
+        acc_t blk[kScaled ? R : 1][kScaled ? NT : 1];
+        const uint32_t from = xread + buf;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) x[0][nt] = *(const v4u*)&lds[from + nt * 32 * kPieces * 16];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int now = t & 1, then = now ^ 1;
+            if (t < kHalf) {
+#pragma unroll
+                for (int j = t * kMine / kHalf; j < (t + 1) * kMine / kHalf; ++j) load_x(buf ^ kStageBytes, run1, j);
+            } else {
+#pragma unroll
+                for (int j = (t - kHalf) * 2 * R / kHalf; j < (t + 1 - kHalf) * 2 * R / kHalf; ++j) load_code(later, ok2, run2, j);
+                if (t == kHalf) load_scales(later, ok2, run2);
+            }
+            if (t + 1 < T) {
+                const uint32_t at = from ^ (uint32_t)((t + 1) * 16);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) x[then][nt] = *(const v4u*)&lds[at + nt * 32 * kPieces * 16];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (t + 1 < T) P::decode(st.c[r][(t + 1) / G::kVecSteps], (t + 1) % G::kVecSteps, w[then][r]);
+                else P::decode(next.c[r][0], 0, w[then][r]);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if constexpr (kScaled) {
+                        if (t == 0)
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) blk[r][nt][i] = 0;
+                        blk[r][nt] = G::mma(x[now][nt], w[now][r], blk[r][nt]);
+                    } else {
+                        acc[r][nt] = G::mma(x[now][nt], w[now][r], acc[r][nt]);
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (kScaled) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float q = __half2float(__ushort_as_half((uint16_t)(st.q[r / 2] >> (16 * (r & 1)))));
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[r][nt][i] = fmaf(q, blk[r][nt][i], acc[r][nt][i]);
+                    asm volatile("" : "+v"(acc[r][nt]));   // (here and now: the compiler would keep all steps' sums until the end of the loop)
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    Codes ring[3];
+    request(ring[0]);
+    {
+        const bool ok = Wk + g < nruns;
+        const int run = ok ? run_at(Wk + g) : 0;
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) load_code(ring[1], ok, run, j);
+        load_scales(ring[1], ok, run);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) P::decode(ring[0].c[r][0], 0, w[0][r]);
+    arrive(std::integral_constant<int, kLater>{});
+    uint32_t buf = 0;
+    for (int s = 0; s < steps; s += 3) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            if (s + d < steps) {
+                if ((s + d) * Wk + g < nruns) {
+                    compute(ring[d], ring[(d + 1) % 3], ring[(d + 2) % 3], s + d, buf);
+                    if constexpr (!kDirect) {
+#pragma unroll
+                        for (int j = 0; j < kMine; ++j) put(j, buf ^ kStageBytes, xr[j]);
+                    }
+                }
+                arrive(std::integral_constant<int, kLater>{});
+                buf ^= kStageBytes;
+            }
+        }
+    }
+    arrive(std::integral_constant<int, 0>{});
+    // the pairs' sums, [pair][row][column], four columns of a row at a time
+    auto bits = [](auto v) { uint32_t u; __builtin_memcpy(&u, &v, 4); return u; };
+    uint32_t* const red = (uint32_t*)lds;
+    using S = typename std::conditional<kInt, int, float>::type;
+#pragma unroll
+    for (int n0 = 0; n0 < NT; n0 += kAtOnce) {
+        if (n0) lds_barrier();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int nt = n0; nt < n0 + kAtOnce; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v4u v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (kInt) acc[r][nt][4 * i + e] >>= 4;
+                        v[e] = bits(acc[r][nt][4 * i + e]);
+                    }
+                    *(v4u*)&red[(g * kRows + (wr * R + r) * 32 + n) * kPitch + (nt - n0) * 32 + 8 * i + 4 * h] = v;
+                }
+        lds_barrier();
+#pragma unroll
+        for (int o = 0; o < R * kAtOnce; ++o) {
+            const int at = o * 512 + threadIdx.x, row = at % kRows, c = at / kRows * 4;
+            const int64_t grow = (int64_t)rg * kRows + row;
+            S sum[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < Wk; ++k) {
+                S v[4];
+                __builtin_memcpy(v, &red[(k * kRows + row) * kPitch + c], 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += v[e];
+            }
+            const int col = n0 * 32 + c, left = grow < m ? ncols - col : 0;
+            if (partials) {
+                uint32_t* const to = partials + ((int64_t)blockIdx.y * a.b + col0 + col) * a.m_pad + grow;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < left) to[e * a.m_pad] = bits(sum[e]);
+            } else {
+                YT* const to = Y + (int64_t)(col0 + col) * ldy + grow;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (!kInt && !__is_same(XT, __half)) sum[e] *= factor;
+                    if (e < left) to[e * ldy] = to_output<YT, S>(sum[e]);
+                }
+            }
         }
     }
 }
@@ -904,17 +1191,17 @@ matrix_reduce_kernel(MatrixArgs a, int segments)
 template <bool kInverse>
 __global__ void __launch_bounds__(256)
 matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs, int R,
-                     int enc, int64_t dwords)
+                     int enc, int tall, int64_t dwords)
 {
     const int64_t kbytes = k / 2;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
         const int w = (int)(i & 3), lane = (int)(i >> 2) & 63;
-        const int64_t tile = i >> 8;                       // (row group, run, r)
+        const int64_t tile = i >> (tall ? 9 : 8);          // (row group, run, r)
         const int r = (int)(tile % R);
         const int64_t rest = tile / R;
         const int64_t run = rest % runs, rg = rest / runs;
-        const int64_t row = (rg * R + r) * 16 + (lane & 15);
-        const int64_t byte0 = (run * kRun + 32 * (lane >> 4) + 8 * w) / 2;
+        const int64_t row = tall ? (rg * R + r) * 32 + (lane & 31) : (rg * R + r) * 16 + (lane & 15);
+        const int64_t byte0 = (run * kRun + (tall ? 64 * (lane >> 5) + 32 * ((int)(i >> 8) & 1) : 32 * (lane >> 4)) + 8 * w) / 2;
         uint8_t* src = rows + row * kbytes + byte0;
         uint32_t v = kInverse ? ((const uint32_t*)tiled)[i] : 0;
 #pragma unroll
@@ -958,13 +1245,13 @@ matrix_repack8_kernel(const uint8_t* __restrict__ rows, uint8_t* __restrict__ ti
 // scales [m][nblocks] -> [row group][scale block][row wavefront][n][its row tiles, padded to Rp]; rows past m get zero
 __global__ void __launch_bounds__(256)
 matrix_repack_scales_kernel(const __half* __restrict__ scales, __half* __restrict__ ordered, int64_t m, int64_t nblocks,
-                            int R, int Wr, int Rp, int64_t total)
+                            int R, int Wr, int Rp, int height, int64_t total)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(i % Rp), n = (int)(i / Rp) & 15, wr = (int)(i / (16 * Rp) % Wr);
-        const int64_t rest = i / (16 * Rp * Wr);
+        const int r = (int)(i % Rp), n = (int)(i / Rp) % height, wr = (int)(i / (height * Rp) % Wr);
+        const int64_t rest = i / (height * Rp * Wr);
         const int64_t block = rest % nblocks, rg = rest / nblocks;
-        const int64_t row = ((rg * Wr + wr) * R + r) * 16 + n;
+        const int64_t row = ((rg * Wr + wr) * R + r) * height + n;
         ordered[i] = r < R && row < m ? scales[row * nblocks + block] : __float2half(0.0f);
     }
 }
@@ -997,10 +1284,13 @@ int launch_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
     const dim3 grid((unsigned)(kXcds * a.passes * ((a.row_groups + kXcds - 1) / kXcds)), (unsigned)p.mx_segments);
     constexpr bool kCanScale = sizeof(XT) != 1 && R < 3;
     if (sizeof(XT) != 1 && !kCanScale && a.scales) return MSGEMM_ERR_UNSUPPORTED;
-    if (kCanScale && a.scales)
-        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale>), grid, dim3(512), 0, s, a);
-    else
-        hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false>), grid, dim3(512), 0, s, a);
+    // straight into the LDS (at any alignment) where 32 bits reach every piece
+    const bool direct = (32 * NT + 1) * a.ldx * (int64_t)sizeof(XT) < (1ll << 31);
+    const bool scaled = kCanScale && a.scales;
+    if (scaled && direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale, true>), grid, dim3(512), 0, s, a);
+    else if (scaled) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale, false>), grid, dim3(512), 0, s, a);
+    else if (direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false, true>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false, false>), grid, dim3(512), 0, s, a);
     MSGEMM_HIP_TRY(hipGetLastError());
     return reduce_segments<XT>(p, a, s);
 }
@@ -1009,10 +1299,27 @@ template <typename XT>
 int launch_tile_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
 #define MSGEMM_CASE(RR, NN) \
-    if (p.mx_r == RR && p.mx_cols == NN) return launch_tile<XT, RR, NN>(p, a, s);
+    if (p.mx_r == RR && p.mx_cols == 2 * NN) return launch_tile<XT, RR, NN>(p, a, s);
+    MSGEMM_CASE(1, 1) MSGEMM_CASE(2, 1) MSGEMM_CASE(3, 1)
     MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2)
-    MSGEMM_CASE(1, 3) MSGEMM_CASE(2, 3) MSGEMM_CASE(3, 3)
-    MSGEMM_CASE(1, 4) MSGEMM_CASE(2, 4) MSGEMM_CASE(3, 4)
+#undef MSGEMM_CASE
+    return MSGEMM_ERR_UNSUPPORTED;
+}
+
+template <int R, int NT>
+int launch_small(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)(kXcds * a.passes * ((a.row_groups + kXcds - 1) / kXcds)), (unsigned)p.mx_segments);
+    hipLaunchKernelGGL((matrix_small_tile_kernel<int8_t, R, NT>), grid, dim3(512), 0, s, a);
+    MSGEMM_HIP_TRY(hipGetLastError());
+    return reduce_segments<int8_t>(p, a, s);
+}
+
+int launch_small_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+#define MSGEMM_CASE(RR, NN) \
+    if (p.mx_r == RR && p.mx_cols == NN) return launch_small<RR, NN>(p, a, s);
+    MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2) MSGEMM_CASE(1, 3) MSGEMM_CASE(2, 3) MSGEMM_CASE(3, 3)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
@@ -1165,23 +1472,27 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         return false;
     const int64_t runs = (k + kRun - 1) / kRun;
     if (runs * 16384 >= (int64_t)kPastEnd - 65536) return false;  // 32-bit offsets within a row group
-    // More than 16 columns: passes of the streaming kernel over 16 at a time while the codes of all passes are few (they
-    // stay in the caches, and the passes run side by side), and for fp32; from there on the tile kernel, which decodes a
-    // code once for 64 columns.  us, passes against tile: 1024 x 1024 x 64 3.3 / 10.5, 8192 x 4096 x 64 15.7 / 20,
-    // 4096 x 14336 x 64 (112 MiB in four passes) 19.6 / 25.6; level at 8192 x 8192 x 64 (128 MiB), 28672 x 8192 x 32 57 / 38;
-    // with a short k, 49152 x 768 x 64 (72 MiB), 37 / 19.  The line is lower where the tile kernel's row groups fill the
-    // device uncut and its column tiles are not mostly padding: 12288 x 2048 x 64 (48 MiB) 15.5 / 16.3, 14336 x 4096 x 24
-    // (56) 15.5 / 13.5, 16384 x 2048 x 64 (64) 20.7 / 16.6, 14336 x 4096 x 48 (84) 23.5 / 17.6, 12288 x 4096 x 64 (96) 26.5 / 21.1,
-    // 28672 x 4096 x 32 (112) 36 / 24; of columns five eighths are enough: 8192 x 4096 x 80 (two tiles of 64) 24.1 / 20.1,
-    // 16384 x 4096 x 20 (one of 32) 19.0 / 16.1; fewer were not measured.
+    // More than 16 columns (fp32: never, its activations have three parts): the tile kernel, which decodes a code once for 64 columns,
+    // where its row groups and column tiles fill five eighths of the device; passes of the streaming kernel over 16 columns at a time
+    // where they do not, until the codes of all passes are many.  us, passes / tile.  Filling: 16384 x 128 x 20 fp16 3.9 / 3.9, x 64 5.8 / 4.6;
+    // 11008 x 512 x 20 4.7 / 4.5, x 64 7.1 / 5.5; 14336 x 4096 x 17 13.7 / 12.6; 8192 x 4096 x 72 24.7 / 15.0; 28672 x 4096 x 64 45.9 / 22.1.  Not: 4096 x 4096 x
+    // 64 (32 MiB) 8.0 / 13.7, 8192 x 4096 x 64 (64) 13.2 / 14.2, 4096 x 14336 x 48 (84) 19.1 / 18.0, 8192 x 8192 x 48 (96) 26.2 / 19.0; int8 4096 x 14336 x 64
+    // (112) 15.4 / 15.7, 8192 x 8192 x 64 (128) 17.9 / 16.9.
+    // int8 up to 48 columns: a long k keeps the kernel of smaller tiles (28672 x 4096 x 24 14.6 / 15.6, 14000 x 3006 x 33 10.8 / 11.7; 20 runs and more were
+    // compared) by its own lines; a short one under few rows does well with passes (16384 x 512 x 20 4.2 / 4.3, 16384 x 1024 x 20 5.3 / 5.1).
     const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun && !bytes &&
                           !(p.x_dtype == MSGEMM_I8 && k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
-    const int tile_tiles = p.b <= 32 ? 2 : p.b <= 48 ? 3 : 4;
+    const bool int8 = p.x_dtype == MSGEMM_I8, narrow8 = int8 && p.b <= 48;
+    const int64_t pass_mib = ((p.b + 15) / 16 * code_bytes) >> 20, row_groups = (p.m + 63) / 64;
+    const int small_tiles = p.b <= 32 ? 2 : 3;
+    const bool small = tile_can && narrow8 && (asked && o.rows_per_lane ? o.rows_per_lane == 4 :
+        runs >= 20 && pass_mib >= (row_groups * 8 > (int64_t)5 * p.cus && p.b >= 10 * small_tiles ? 48 : 112));
+    const int64_t tall_passes = p.b <= 32 ? 1 : (p.b + 63) / 64;
+    const bool tall = tile_can && !small && (asked && o.rows_per_lane ? o.rows_per_lane == 4 :
+        row_groups * tall_passes * 8 > (int64_t)5 * p.cus ? !narrow8 || runs >= 8 || row_groups > 2 * p.cus : !narrow8 && pass_mib >= (int8 ? 113 : 80));
+    const bool tile = small || tall;
+    const int tile_tiles = small ? small_tiles : p.b <= 32 ? 2 : 4;
     const int64_t tile_passes = (p.b + 16 * tile_tiles - 1) / (16 * tile_tiles);
-    const bool fills = (p.m + 63) / 64 * tile_passes * 8 > (int64_t)5 * p.cus && p.b >= 10 * tile_tiles * tile_passes;
-    const bool tile = tile_can && (asked && o.rows_per_lane
-                                       ? o.rows_per_lane == 4
-                                       : (p.b + 15) / 16 * code_bytes > ((int64_t)(runs < 8 ? 32 : fills ? 48 : 112) << 20));
     // One fp32 column of 4-bit codes: decoding and three products per weight where the table kernels add once per pair
     // (4096 x 4096 5.5 us against 6.9, 8192 x 8192 11.0 against 10.3, 49152 x 12288 74 against 52; 8-bit codes, one
     // conversion for two, 12.5 against 17.0 at 8192 x 8192).
@@ -1189,11 +1500,13 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // (streaming kernel, 300001 x 512: 19 us against 27, 300001 x 64: 6.3 against 17; ahead at 100000 rows and 512 columns,
     // 17.2 against 20.5 with eight columns of X)
     if (!tile && k <= 512 && p.m > (int64_t)512 * p.cus && !asked && !anyway) return false;
-    if (short_k(p, k) && !asked && !anyway) return false;
+    // (tile kernel: short k is no matter to it until there are very many workgroups of one run; us, tables / tile: 49152 x 128 x 20 fp16 17.0 /
+    // 5.0, 80000 x 256 x 64 31.4 / 13.5, 300000 x 128 x 64 60 / 42, bf16 with scales 67 / 55; 1000000 x 128 x 17 61 / 81, x 33 105 / 115)
+    if ((tall ? runs == 1 && p.m > (int64_t)2400 * p.cus : short_k(p, k)) && !asked && !anyway) return false;
 
     const bool compact = p.b <= (p.x_dtype == MSGEMM_I8 ? 8 : 4);
     const bool scaled = p.scale_group > 0;
-    const int Wr = tile ? 4 : 1;
+    const int Wr = tile ? 4 : 1;   // (wavefronts of 16 R rows, or half as many of 32 R)
     const int width = tile ? 3 : compact ? 0 : p.b <= 8 ? 1 : 2;
     p.mx_cols = tile ? tile_tiles : 2 * width;
     const int64_t passes = tile ? tile_passes : (p.b + 15) / 16;
@@ -1271,7 +1584,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     p.mx_depth = D;
     p.mx_tile_kernel = tile;
     p.mx_r = R;
-    p.mx_row_waves = Wr;
+    p.mx_tall = tall;
+    p.mx_row_waves = p.mx_tall ? kTileRowWaves : Wr;
     p.mx_waves = W;
     p.mx_segments = (int)segments;
     p.matrix = true;
@@ -1282,7 +1596,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     p.fs.cols = 1;
     p.fs.entry_bytes = 4;
     p.fs.tile_rows = 16 * Wr * R;
-    const int64_t sums = (int64_t)(W / Wr) * segments;
+    const int64_t sums = (int64_t)(W / p.mx_row_waves) * segments;
     p.segments = (int)(runs < sums ? runs : sums);  // partial sums per output: one per wavefront (or group) with a run
     p.partial_bytes = segments > 1 ? (size_t)segments * (size_t)p.b * (size_t)p.m_pad * 4u : 0;
     return true;
@@ -1291,7 +1605,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
 static int scale_slots(const Plan& p) { return p.mx_r == 3 ? 4 : p.mx_r; }
 size_t matrix_scale_bytes(const Plan& p)
 {
-    return (size_t)p.nblocks * (size_t)p.row_blocks * (size_t)(p.mx_row_waves * 16 * scale_slots(p)) * 2u;
+    return (size_t)p.nblocks * (size_t)p.row_blocks * (size_t)(p.mx_row_waves * (p.mx_tall ? 32 : 16) * scale_slots(p)) * 2u;
 }
 
 static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStream_t s)
@@ -1302,10 +1616,10 @@ static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStr
     const int enc = encoding_of(p.x_dtype);
     if (inverse)
         hipLaunchKernelGGL((matrix_repack_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, dwords);
+                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, p.mx_tall ? 1 : 0, dwords);
     else
         hipLaunchKernelGGL((matrix_repack_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, dwords);
+                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, p.mx_tall ? 1 : 0, dwords);
     MSGEMM_HIP_TRY(hipGetLastError());
     return MSGEMM_OK;
 }
@@ -1319,7 +1633,7 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         int64_t blocks = (total + 255) / 256;
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(matrix_repack_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const __half*)p.scales,
-                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), total);
+                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), p.mx_tall ? 32 : 16, total);
         MSGEMM_HIP_TRY(hipGetLastError());
     }
     if (p.codes8) {
@@ -1365,7 +1679,7 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
         default: return MSGEMM_ERR_UNSUPPORTED;
         }
     }
-    if (p.mx_tile_kernel) {
+    if (p.mx_tall) {
         switch (p.x_dtype) {
         case MSGEMM_F16: return launch_tile_for_type<__half>(p, a, s);
         case MSGEMM_BF16: return launch_tile_for_type<bf16_t>(p, a, s);
@@ -1373,6 +1687,7 @@ int launch_matrix(const Plan& p, const void* X, int64_t ldx, void* Y, int64_t ld
         default: return MSGEMM_ERR_UNSUPPORTED;
         }
     }
+    if (p.mx_tile_kernel) return p.x_dtype == MSGEMM_I8 ? launch_small_tile(p, a, s) : MSGEMM_ERR_UNSUPPORTED;
     switch (p.x_dtype) {
     case MSGEMM_F16: return launch_for_type<__half>(p, a, s);
     case MSGEMM_BF16: return launch_for_type<bf16_t>(p, a, s);
