@@ -617,13 +617,14 @@ matrix_stream_kernel(MatrixArgs a)
         const int64_t grow = (int64_t)rg * kRows + row;
         if (grow >= a.m) continue;
         using S = typename std::conditional<kInt, int, float>::type;
-        S s = 0;
+        S v[W];                                        // (in pairs: sixteen sums one after the other would round more than four did)
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            S v;
-            __builtin_memcpy(&v, &lds[(w * kCols + c) * kPitch + row], 4);
-            s += v;
-        }
+        for (int w = 0; w < W; ++w) __builtin_memcpy(&v[w], &lds[(w * kCols + c) * kPitch + row], 4);
+#pragma unroll
+        for (int step = 1; step < W; step *= 2)
+#pragma unroll
+            for (int w = 0; w < W; w += 2 * step) v[w] += v[w + step];
+        S s = v[0];
         if (a.partials) {
             a.partials[((int64_t)blockIdx.y * a.b + col0 + c) * a.m_pad + grow] = bits(s);
             continue;
@@ -1331,12 +1332,17 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
     if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW && p.mx_depth == DD) return launch_stream<XT, RR, CC, WW, DD, kInt4>(p, a, s);
     MSGEMM_CASE(4, 0, 4, 2)
     MSGEMM_CASE(2, 0, 4, 2) MSGEMM_CASE(2, 0, 4, 4)
-    MSGEMM_CASE(1, 0, 4, 2) MSGEMM_CASE(1, 0, 4, 4) MSGEMM_CASE(1, 0, 4, 8) MSGEMM_CASE(1, 0, 16, 2)
+    MSGEMM_CASE(1, 0, 4, 2) MSGEMM_CASE(1, 0, 4, 4) MSGEMM_CASE(1, 0, 16, 2)
+    if constexpr (sizeof(XT) != 4) {
+        MSGEMM_CASE(2, 0, 8, 2) MSGEMM_CASE(1, 0, 4, 8)
+    } else {
+        MSGEMM_CASE(4, 2, 4, 2) MSGEMM_CASE(2, 2, 4, 2) MSGEMM_CASE(1, 2, 4, 2)
+        MSGEMM_CASE(2, 4, 4, 2) MSGEMM_CASE(1, 4, 4, 2)
+    }
     if constexpr (sizeof(XT) != 1) {  // (int8: the compact form holds eight columns)
         MSGEMM_CASE(4, 2, 8, 2) MSGEMM_CASE(2, 2, 8, 2) MSGEMM_CASE(1, 2, 8, 2)
     }
-    constexpr int kWidest = sizeof(XT) == 4 ? 8 : 4;
-    MSGEMM_CASE(4, 4, kWidest, 2) MSGEMM_CASE(2, 4, 8, 2) MSGEMM_CASE(1, 4, 8, 2)
+    MSGEMM_CASE(4, 4, 8, 2) MSGEMM_CASE(4, 4, 4, 2) MSGEMM_CASE(2, 4, 8, 2) MSGEMM_CASE(1, 4, 8, 2)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
@@ -1533,14 +1539,14 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // rounds of one tile 73 us, one of two 53; 49152 x 12288 x 64: 135, 110 and 87; three scaled tiles do not fit the
     // registers).
     const int tiles[2][3] = {{1, 2, 4}, {1, 2, 3}};
-    double cost[4][3] = {{1.25, 2.0, 3.95}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
-    // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, a little more
-    // where two workgroups of one tile would do the work of one of two.  us, one tile / two: 28672 x 4096 x 1 fp16 with scales 12.1 / 12.9,
-    // 11008 x 4096 x 4 bf16 7.1 / 8.0, 8192 x 8192 x 1 bf16 8.4 / 8.7, 8192 x 4096 x 1 5.1 / 5.0, 16384 x 16384 x 1 23.7 / 23.1)
-    if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && p.x_dtype != MSGEMM_I8) {
-        if (runs < 96) cost[0][0] = runs < 64 && groups(1) <= 2 * p.cus ? 1.05 : 0.98;
-        cost[0][2] = 4.12;
-    }
+    double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
+    // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, a little more where two
+    // workgroups of one tile would do the work of one of two, or very many have theirs to start.  us, one tile / two: 28672 x 4096 x 1 fp16 with
+    // scales 12.1 / 12.4, 11008 x 4096 x 4 bf16 7.1 / 8.0, 20480 x 8192 x 1 fp16 15.7 / 16.9, 8192 x 8192 x 1 bf16 8.4 / 8.7, 8192 x 4096 x 1 5.1 / 5.0, 42240 x 6912 x
+    // 4 28.8 / 27.5, 16384 x 16384 x 1 23.7 / 23.1.  fp32, two tiles / four: 16384 x 8192 x 4 19.2 / 18.6, 33280 x 4096 x 16 38.0 / 34.3)
+    if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && !int8 && runs < 96)
+        cost[0][0] = runs < 64 && groups(1) <= 2 * p.cus ? 1.05 : runs >= 48 && groups(1) > 8 * p.cus ? 1.12 : 0.98;
+    if (p.x_dtype == MSGEMM_F32 && !bytes) cost[0][2] = 3.95, cost[2][2] = 3.8;
     double best = 0;
     int R = 1;
     for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i) {
@@ -1558,28 +1564,34 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
     // Streaming kernel, wavefronts and depth of their rings: what keeps the memory busy is some 32 KiB of codes in flight per compute
     // unit (its share of 6.3 TB/s times a microsecond's trip); more only queues, and an unrolled loop that is gone through once or twice
-    // is fetched for nothing.  us, one column or a few, one row tile, "wavefronts x depth":
+    // is fetched for nothing.  us, "wavefronts x depth", one column or a few and one row tile:
     //   a workgroup per compute unit: 4096 x 14336 x 1 fp16 4 x 8 7.1, 16 x 2 7.0, 4 x 4 7.9; 4096 x 4096 x 1 fp32 5.6, 5.0, 5.1; a short k
     //   in fours, 2048 x 1024 x 1 fp16 4 x 8 2.8, 16 x 2 2.7, 4 x 2 2.5
     //   two: 8192 x 8192 x 1 bf16 4 x 8 9.1, 4 x 4 8.4; 8192 x 14336 x 1 fp16 11.8, 11.4
-    //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; but 12288 x 49152 x 1 45.8, 4 x 2 47.5
-    // Two row tiles: 6144 x 6144 x 3 4 x 4 5.6; 14336 x 8192 x 4 fp32 in two workgroups per compute unit 4 x 4 20.4, 4 x 2 19.2.
-    // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 4096 x 4096 x 8 fp32 4 x 2 7.2, 8 x 2 6.4; 28672 x 4096 x 6 fp16 (four row tiles)
-    // 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16 columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15.
+    //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
+    //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3
+    // Two row tiles: 6144 x 6144 x 3 fp16 4 x 4 5.6; in more workgroups 42240 x 6912 x 4 fp16 4 x 4 27.9, 8 x 2 27.5, 13160 x 24704 x 1 bf16 31.7, 30.8, 33792 x
+    // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 37725 x 3640 x 1 int8 4 x 4 14.9, 4 x 2 17.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.
+    // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
+    // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15, but
+    // 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; fp32, whose operands of eight
+    // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
+    const bool f32 = p.x_dtype == MSGEMM_F32;
     int W = 4, D = 2;
     if (tile) {
         W = 8;
     } else if (bytes) {
-        D = compact ? 4 : width == 1 && R == 1 && p.x_dtype != MSGEMM_F32 ? 4 : 2;
+        D = compact ? 4 : width == 1 && R == 1 && !f32 ? 4 : 2;
     } else if (!compact) {
-        W = width == 2 && R == 4 && p.x_dtype != MSGEMM_F32 ? 4 : 8;
+        W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : width == 2 && R == 4 && seg_runs >= 16 && groups(R) * passes * 4 >= 3 * p.cus ? 4 : 8;
     } else if (R == 2) {
-        D = per_cu == 1 ? 4 : 2;
+        if (per_cu == 1 || (int8 && seg_runs < 48)) D = 4;
+        else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
-        if (seg_runs >= 32 && per_cu == 1) W = 16;
-        else if (seg_runs >= 256) D = 8;
-        else if (seg_runs >= 16 && per_cu <= 2) D = 4;
+        if (per_cu == 1 && seg_runs >= 32) W = 16;
+        else if (per_cu > 1 && seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
+        else if (seg_runs >= (per_cu > 2 ? 48 : int8 ? 12 : 16)) D = 4;
     }
     p.mx_depth = D;
     p.mx_tile_kernel = tile;
