@@ -19,7 +19,7 @@
 // One 16-byte load of a wavefront is 1 KiB of consecutive memory and one row tile's share of a run.
 // Scales: [row group][scale block][n][r] fp16, so a lane's scales for its R tiles are one load.
 // The tile kernel's tiles have 32 rows: lane (n, h) = (lane & 31, lane >> 5) holds columns 64 h + 0..63 of row n in two such loads, one behind the
-// other; its steps take 8 columns of each half (int8: 16).
+// other (8-bit codes: four); its steps take 8 columns of each half (int8: 16).
 #include "device_types.h"
 #include "fused_common.h"
 #include "msgemm_internal.h"
@@ -850,7 +850,8 @@ matrix_small_tile_kernel(MatrixArgs a)
 //     the codes of the step after it, which come from memory and have a step more to arrive.
 //   * One meeting of the wavefronts a step, behind it.  Ahead of the last products of a step: level.
 // Measured, us: 49152 x 12288 x 64 fp16 77 to 82 = 0.94 to 1.0 Pflop/s (tiles of 16 rows with activations through registers 87 to 89), 28672 x 8192 x 64 bf16 with
-// scales 41 to 44 (51 to 52), 16384 x 4096 x 64 15.6 (21), 14336 x 4096 x 32 12.6 (14.3), 28672 x 4096 x 64 int8 18.6 (20.9).  Level or slower: wavefronts of
+// scales 41 to 44 (51 to 52), 16384 x 4096 x 64 15.6 (21), 14336 x 4096 x 32 12.6 (14.3), 28672 x 4096 x 64 int8 18.6 (20.9), 28672 x 8192 x 64 fp16 with
+// E4M3 codes 48 (passes of the streaming kernel 161), 25856 x 6144 x 24 29.5 (53).  Level or slower: wavefronts of
 // different priority, an interleaving of products and decoding laid down by hand.
 // 32 x 32 products, sixteen (int8: 32) columns of k at a time
 template <typename XT> struct Big {
@@ -873,7 +874,7 @@ template <> struct Big<int8_t> {
     }
 };
 
-template <typename XT, int R, int NT, bool kScaled, bool kDirect>
+template <typename XT, int F, int R, int NT, bool kScaled, bool kDirect>
 __global__ void __launch_bounds__(512)
 matrix_tile_kernel(MatrixArgs a)
 {
@@ -885,6 +886,7 @@ matrix_tile_kernel(MatrixArgs a)
     constexpr bool kInt = sizeof(XT) == 1;
     constexpr int Wr = kTileRowWaves, Wk = 8 / Wr;
     constexpr int T = G::kSteps;
+    constexpr int kVecs = F == kInt4 ? 2 : 4;          // loads of codes per row tile and run
     constexpr int kPiece = 16 / (int)sizeof(XT);       // elements of a 16-byte piece
     constexpr int kPieces = kRun / kPiece;             // pieces of a column's run
     constexpr int kColsPerLoad = 64 / kPieces;         // a wavefront's load: 1 KiB of LDS
@@ -910,6 +912,7 @@ matrix_tile_kernel(MatrixArgs a)
     uint32_t* partials = a.partials;
     int64_t ldy = a.ldy, m = a.m;
     float factor = a.factor;
+    const float times = a.times;
     asm volatile("" : "+s"(Y), "+s"(partials), "+s"(ldy), "+s"(m), "+s"(factor));
     // this segment's runs; a ragged one (the last of k) goes first, so that what it takes is part of the start
     const int run0 = blockIdx.y * a.seg_runs;
@@ -917,7 +920,7 @@ matrix_tile_kernel(MatrixArgs a)
     const int nruns = run1 - run0, ragged = run1 > a.full_runs ? 1 : 0;
     const int steps = (nruns + Wk - 1) / Wk;
 
-    constexpr uint32_t run_bytes = R * Wr * 2048u;
+    constexpr uint32_t run_bytes = R * Wr * kVecs * 1024u;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(a.codes + (int64_t)rg * a.runs * run_bytes), 0, (int)(a.runs * run_bytes), 0x00020000);
     constexpr int kScaleRow = Wr * 32 * Rp;
@@ -943,15 +946,15 @@ matrix_tile_kernel(MatrixArgs a)
     uint8_t* const mine = lds + g * kTileBytes;
 
     struct Codes {
-        v4u c[R][2];
+        v4u c[R][kVecs];
         uint32_t q[1];
     };
     v4u xr[kDirect ? 1 : kMine];
     const auto run_at = [&](int i) { return ragged ? (i == 0 ? run1 - 1 : run0 + i - 1) : run0 + i; };
     // (a step past the last run: the codes come from past the end of the buffer, the activations are those of the first run again)
     const auto load_code = [&](Codes& st, bool ok, int run, int j) {
-        const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + wr * R * 2048u + lane * 16u;
-        st.c[j / 2][j % 2] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + j * 1024u), 0, kAuxNt);
+        const uint32_t off = (ok ? (uint32_t)run * run_bytes : kPastEnd) + wr * R * kVecs * 1024u + lane * 16u;
+        st.c[j / kVecs][j % kVecs] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + j * 1024u), 0, kAuxNt);
     };
     const auto load_scales = [&](Codes& st, bool ok, int run) {
         if constexpr (kScaled) {
@@ -1002,7 +1005,7 @@ matrix_tile_kernel(MatrixArgs a)
             stage_ragged();
         }
 #pragma unroll
-        for (int j = 0; j < 2 * R; ++j) load_code(st, true, run, j);
+        for (int j = 0; j < kVecs * R; ++j) load_code(st, true, run, j);
         load_scales(st, true, run);
     };
     // The next step's activations are in LDS for every wavefront when this returns, its codes in registers; the codes of the one after it are
@@ -1024,7 +1027,11 @@ matrix_tile_kernel(MatrixArgs a)
     // have a step more to arrive.
     v4u w[2][R], x[2][NT];
     constexpr int kHalf = T / 2;
-    constexpr int kLater = 2 * R + (kScaled ? 1 : 0);
+    constexpr int kLater = kVecs * R + (kScaled ? 1 : 0);
+    const auto decode = [&](v4u& to, const v4u (&c)[kVecs], int t) {
+        if constexpr (F == kInt4) P::decode(c[t / G::kVecSteps], t % G::kVecSteps, to);
+        else to = convert<F, XT>(c[t / 2][2 * (t & 1)], c[t / 2][2 * (t & 1) + 1], times);
+    };
     const auto compute = [&](const Codes& st, const Codes& next, Codes& later, int s, uint32_t buf) {
         const bool ok1 = (s + 1) * Wk + g < nruns, ok2 = (s + 2) * Wk + g < nruns;
         const int run1 = ok1 ? run_at((s + 1) * Wk + g) : 0, run2 = ok2 ? run_at((s + 2) * Wk + g) : 0;
@@ -1040,7 +1047,7 @@ matrix_tile_kernel(MatrixArgs a)
                 for (int j = t * kMine / kHalf; j < (t + 1) * kMine / kHalf; ++j) load_x(buf ^ kStageBytes, run1, j);
             } else {
 #pragma unroll
-                for (int j = (t - kHalf) * 2 * R / kHalf; j < (t + 1 - kHalf) * 2 * R / kHalf; ++j) load_code(later, ok2, run2, j);
+                for (int j = (t - kHalf) * kVecs * R / kHalf; j < (t + 1 - kHalf) * kVecs * R / kHalf; ++j) load_code(later, ok2, run2, j);
                 if (t == kHalf) load_scales(later, ok2, run2);
             }
             if (t + 1 < T) {
@@ -1050,8 +1057,8 @@ matrix_tile_kernel(MatrixArgs a)
             }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if (t + 1 < T) P::decode(st.c[r][(t + 1) / G::kVecSteps], (t + 1) % G::kVecSteps, w[then][r]);
-                else P::decode(next.c[r][0], 0, w[then][r]);
+                if (t + 1 < T) decode(w[then][r], st.c[r], t + 1);
+                else decode(w[then][r], next.c[r], 0);
             }
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -1089,11 +1096,11 @@ matrix_tile_kernel(MatrixArgs a)
         const bool ok = Wk + g < nruns;
         const int run = ok ? run_at(Wk + g) : 0;
 #pragma unroll
-        for (int j = 0; j < 2 * R; ++j) load_code(ring[1], ok, run, j);
+        for (int j = 0; j < kVecs * R; ++j) load_code(ring[1], ok, run, j);
         load_scales(ring[1], ok, run);
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) P::decode(ring[0].c[r][0], 0, w[0][r]);
+    for (int r = 0; r < R; ++r) decode(w[0][r], ring[0].c[r], 0);
     arrive(std::integral_constant<int, kLater>{});
     uint32_t buf = 0;
     for (int s = 0; s < steps; s += 3) {
@@ -1157,7 +1164,7 @@ matrix_tile_kernel(MatrixArgs a)
                 YT* const to = Y + (int64_t)(col0 + col) * ldy + grow;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if constexpr (!kInt && !__is_same(XT, __half)) sum[e] *= factor;
+                    if constexpr (!kInt && !(F == kInt4 && __is_same(XT, __half))) sum[e] *= factor;
                     if (e < left) to[e * ldy] = to_output<YT, S>(sum[e]);
                 }
             }
@@ -1224,17 +1231,17 @@ matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, in
 struct Remap { uint8_t to[256]; };
 __global__ void __launch_bounds__(256)
 matrix_repack8_kernel(const uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs,
-                      int R, Remap remap, int64_t dwords)
+                      int R, Remap remap, int tall, int64_t dwords)
 {
     __shared__ uint8_t to[256];
     to[threadIdx.x] = remap.to[threadIdx.x];
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
-        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63, half = (int)(i >> 8) & 1;
-        const int64_t tile = i >> 9;                       // (row group, run, r)
+        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63, part = (int)(i >> 8) & (tall ? 3 : 1);
+        const int64_t tile = i >> (tall ? 10 : 9);         // (row group, run, r)
         const int64_t run = tile / R % runs, rg = tile / R / runs;
-        const int64_t row = (rg * R + tile % R) * 16 + (lane & 15);
-        const int64_t col = run * kRun + 32 * (lane >> 4) + 16 * half + 4 * w;
+        const int64_t row = tall ? (rg * R + tile % R) * 32 + (lane & 31) : (rg * R + tile % R) * 16 + (lane & 15);
+        const int64_t col = run * kRun + (tall ? 64 * (lane >> 5) : 32 * (lane >> 4)) + 16 * part + 4 * w;
         uint32_t v = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -1279,19 +1286,20 @@ int launch_stream(const Plan& p, const MatrixArgs& a, hipStream_t s)
     return reduce_segments<XT>(p, a, s);
 }
 
-template <typename XT, int R, int NT>
+template <typename XT, int F, int R, int NT>
 int launch_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
     const dim3 grid((unsigned)(kXcds * a.passes * ((a.row_groups + kXcds - 1) / kXcds)), (unsigned)p.mx_segments);
-    constexpr bool kCanScale = sizeof(XT) != 1 && R < 3;
+    // (scaled sums are held twice)
+    constexpr bool kCanScale = sizeof(XT) != 1 && (F == kInt4 ? R < 3 : R * NT < 4);
     if (sizeof(XT) != 1 && !kCanScale && a.scales) return MSGEMM_ERR_UNSUPPORTED;
     // straight into the LDS (at any alignment) where 32 bits reach every piece
     const bool direct = (32 * NT + 1) * a.ldx * (int64_t)sizeof(XT) < (1ll << 31);
     const bool scaled = kCanScale && a.scales;
-    if (scaled && direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale, true>), grid, dim3(512), 0, s, a);
-    else if (scaled) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, kCanScale, false>), grid, dim3(512), 0, s, a);
-    else if (direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false, true>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((matrix_tile_kernel<XT, R, NT, false, false>), grid, dim3(512), 0, s, a);
+    if (scaled && direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, F, R, NT, kCanScale, true>), grid, dim3(512), 0, s, a);
+    else if (scaled) hipLaunchKernelGGL((matrix_tile_kernel<XT, F, R, NT, kCanScale, false>), grid, dim3(512), 0, s, a);
+    else if (direct) hipLaunchKernelGGL((matrix_tile_kernel<XT, F, R, NT, false, true>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((matrix_tile_kernel<XT, F, R, NT, false, false>), grid, dim3(512), 0, s, a);
     MSGEMM_HIP_TRY(hipGetLastError());
     return reduce_segments<XT>(p, a, s);
 }
@@ -1300,7 +1308,7 @@ template <typename XT>
 int launch_tile_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
 #define MSGEMM_CASE(RR, NN) \
-    if (p.mx_r == RR && p.mx_cols == 2 * NN) return launch_tile<XT, RR, NN>(p, a, s);
+    if (p.mx_r == RR && p.mx_cols == 2 * NN) return launch_tile<XT, kInt4, RR, NN>(p, a, s);
     MSGEMM_CASE(1, 1) MSGEMM_CASE(2, 1) MSGEMM_CASE(3, 1)
     MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2)
 #undef MSGEMM_CASE
@@ -1321,6 +1329,16 @@ int launch_small_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
 #define MSGEMM_CASE(RR, NN) \
     if (p.mx_r == RR && p.mx_cols == NN) return launch_small<RR, NN>(p, a, s);
     MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2) MSGEMM_CASE(1, 3) MSGEMM_CASE(2, 3) MSGEMM_CASE(3, 3)
+#undef MSGEMM_CASE
+    return MSGEMM_ERR_UNSUPPORTED;
+}
+
+template <typename XT, int F>
+int launch_tile_for_codes8(const Plan& p, const MatrixArgs& a, hipStream_t s)
+{
+#define MSGEMM_CASE(RR, NN) \
+    if (p.mx_r == RR && p.mx_cols == 2 * NN) return launch_tile<XT, F, RR, NN>(p, a, s);
+    MSGEMM_CASE(1, 1) MSGEMM_CASE(2, 1) MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
@@ -1366,6 +1384,9 @@ int launch_for_codes8(const Plan& p, const MatrixArgs& a, hipStream_t s)
 
 template <typename XT> int launch_for_format(const Plan& p, const MatrixArgs& a, hipStream_t s)
 {
+    if constexpr (sizeof(XT) == 2) {
+        if (p.mx_tall) return p.mx_format == kE4M3 ? launch_tile_for_codes8<XT, kE4M3>(p, a, s) : launch_tile_for_codes8<XT, kE5M2>(p, a, s);
+    }
     return p.mx_format == kE4M3 ? launch_for_codes8<XT, kE4M3>(p, a, s) : launch_for_codes8<XT, kE5M2>(p, a, s);
 }
 
@@ -1483,10 +1504,10 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // where they do not, until the codes of all passes are many.  us, passes / tile.  Filling: 16384 x 128 x 20 fp16 3.9 / 3.9, x 64 5.8 / 4.6;
     // 11008 x 512 x 20 4.7 / 4.5, x 64 7.1 / 5.5; 14336 x 4096 x 17 13.7 / 12.6; 8192 x 4096 x 72 24.7 / 15.0; 28672 x 4096 x 64 45.9 / 22.1.  Not: 4096 x 4096 x
     // 64 (32 MiB) 8.0 / 13.7, 8192 x 4096 x 64 (64) 13.2 / 14.2, 4096 x 14336 x 48 (84) 19.1 / 18.0, 8192 x 8192 x 48 (96) 26.2 / 19.0; int8 4096 x 14336 x 64
-    // (112) 15.4 / 15.7, 8192 x 8192 x 64 (128) 17.9 / 16.9.
+    // (112) 15.4 / 15.7, 8192 x 8192 x 64 (128) 17.9 / 16.9; 8-bit codes 8192 x 4096 x 20 fp16 (64) 13.4 / 13.9, 8192 x 4096 x 48 (96) 19.7 / 16.2.
     // int8 up to 48 columns: a long k keeps the kernel of smaller tiles (28672 x 4096 x 24 14.6 / 15.6, 14000 x 3006 x 33 10.8 / 11.7; 20 runs and more were
     // compared) by its own lines; a short one under few rows does well with passes (16384 x 512 x 20 4.2 / 4.3, 16384 x 1024 x 20 5.3 / 5.1).
-    const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun && !bytes &&
+    const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun &&
                           !(p.x_dtype == MSGEMM_I8 && k > ((int64_t)1 << 17));  // (int8 sums are 16 x too large in 32 bits)
     const bool int8 = p.x_dtype == MSGEMM_I8, narrow8 = int8 && p.b <= 48;
     const int64_t pass_mib = ((p.b + 15) / 16 * code_bytes) >> 20, row_groups = (p.m + 63) / 64;
@@ -1549,13 +1570,14 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     if (p.x_dtype == MSGEMM_F32 && !bytes) cost[0][2] = 3.95, cost[2][2] = 3.8;
     double best = 0;
     int R = 1;
-    for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i) {
+    const int sizes = tile && bytes && scaled && tile_tiles > 2 ? 1 : (tile && scaled) || bytes ? 2 : 3;   // (what the registers hold)
+    for (int i = 0; i < sizes; ++i) {
         const int r = tiles[tile][i];
         const int64_t n = tile ? segments_of(r) : 1;
         const double c = (double)((groups(r) * passes * n + p.cus - 1) / p.cus) * cost[width][i] / (double)n;
         if (i == 0 || c < best) { best = c; R = r; }
     }
-    for (int i = 0; i < ((tile && scaled) || bytes ? 2 : 3); ++i)
+    for (int i = 0; i < sizes; ++i)
         if (asked && o.panels_per_workgroup == tiles[tile][i]) R = o.panels_per_workgroup;
     int64_t segments = segments_of(R);
     // (a single fp32 column whose chains stay long although they are cut: 2048 x 16084 10.2 us in two segments, tables 8.7;
@@ -1655,7 +1677,7 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         Remap remap;
         for (int i = 0; i < 256; ++i) remap.to[i] = p.mx_remap[i];
         hipLaunchKernelGGL(matrix_repack8_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const uint8_t*)W_codes,
-                           p.codes_tiled, p.m, p.k / 2, p.ktiles, p.mx_r, remap, dwords);
+                           p.codes_tiled, p.m, p.k / 2, p.ktiles, p.mx_r * (p.mx_tall ? p.mx_row_waves : 1), remap, p.mx_tall ? 1 : 0, dwords);
         MSGEMM_HIP_TRY(hipGetLastError());
         return MSGEMM_OK;
     }

@@ -123,3 +123,64 @@ def test_replays_of_a_graph():
             assert np.array_equal(torch_io.to_host(Y), first)
     finally:
         B.msgemm_destroy(plan)
+
+
+def _formats():
+    from test_matrix_form import e5m2_values
+    return {"e4m3": np.nan_to_num(inputs.fp8_e4m3_values(), nan=-0.5), "e5m2": e5m2_values()}
+
+
+# (values up to 448: a result of 1666 of them times N(0, 1) has a deviation of 6000, a tenth of the largest fp16; times 2^3 it would be past it)
+@pytest.mark.parametrize("table,power", [("e4m3", -4), ("e5m2", -12), ("e4m3", 0)])
+@pytest.mark.parametrize("m,k,b,xd,sg,options,pad", [
+    (m, k, b, xd, sg, {"panels_per_workgroup": r}, pad) for r in (1, 2) for m, k, b, xd, sg, pad in [
+        (1, 128, 17, "f16", 0, 0), (130, 4 * 128 + 66, 32, "bf16", 0, 1), (200, 13 * 128 + 2, 64, "f16", 0, 7), (129, 9 * 128, 20, "bf16", 128, 8),
+        (65, 10 * 128, 50, "f16", 256, 0), (70, 5 * 128, 90, "bf16", 128, 3)]] + [(131, 11 * 128 + 2, 33, "f16", 0, {"batched_segments": 5}, 0)])
+def test_8_bit_codes_against_oracle(m, k, b, xd, sg, options, pad, table, power):
+    values = _formats()[table] * 2.0 ** power
+    codes = np.random.default_rng(m + k + b).integers(0, 256, size=(m, k), dtype=np.uint8)
+    X = inputs.make_x(k, b, xd, seed=k + 1)
+    Xp = np.zeros((b, k + pad), dtype=X.dtype)
+    Xp[:, :k], Xp[:, k:] = X, 77 if xd == "f16" else 0x4300
+    scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
+    Xd = oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64)
+    ref = oracle.gemm_f64_codes8(codes, Xd, values, scales, sg)
+    plan = B.msgemm_plan_codes8(m, k, b, xd, Y_OF_X[xd], sg, torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"), values,
+                                options=dict(options, batched_form=3, rows_per_lane=4))
+    try:
+        Y = torch_io.empty_output(b, m, Y_OF_X[xd], ldy=m + 1)
+        Y.fill_(-3)
+        B.msgemm_run(plan, torch_io.to_device(Xp, xd), k + pad, Y, m + 1)
+        torch.cuda.synchronize()
+        out = torch_io.to_host(Y)
+    finally:
+        B.msgemm_destroy(plan)
+    check(np.ascontiguousarray(out[:, :m]), ref, xd, f"8-bit weights {table}", elem_bound(codes, X, xd, scales, sg, values256=values))
+
+
+@pytest.mark.parametrize("xd,magnitude", [("bf16", 1e35), ("bf16", 1e-36), ("f16", 1e2)])
+@pytest.mark.parametrize("power", [-20, -12])
+@pytest.mark.parametrize("b,sg", [(20, 0), (40, 128)])
+def test_8_bit_codes_at_the_ends_of_the_range(b, sg, power, xd, magnitude):
+    if power < 0 and magnitude < 1:
+        power = 0                                       # (results that stay normal numbers)
+    m, k = 64, 1280 if sg else 1282
+    values = _formats()["e5m2"] * 2.0 ** power
+    codes = np.random.default_rng(m + b).integers(0, 256, size=(m, k), dtype=np.uint8)
+    X = (inputs.make_x(k, b, "f32", seed=k + 1) * np.float32(magnitude)).astype(np.float32)
+    X = {"bf16": inputs.f32_to_bf16_bits(X), "f16": X.astype(np.float16)}[xd]
+    scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
+    Xd = oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64)
+    ref = oracle.gemm_f64_codes8(codes, Xd, values, scales, sg)
+    plan = B.msgemm_plan_codes8(m, k, b, xd, Y_OF_X[xd], sg, torch_io.to_device(codes, "codes"), torch_io.to_device(scales, "scales"), values,
+                                options={"batched_form": 3, "rows_per_lane": 4})
+    try:
+        Y = torch_io.empty_output(b, m, Y_OF_X[xd])
+        B.msgemm_run(plan, torch_io.to_device(X, xd), k, Y, m)
+        torch.cuda.synchronize()
+        out = torch_io.to_host(Y)
+    finally:
+        B.msgemm_destroy(plan)
+    if np.abs(ref).max() > {"f16": 6.5e4, "bf16": 3e38}[xd]:
+        pytest.skip("results outside the output's range")
+    check(out, ref, xd, f"E5M2 times 2^{power}", elem_bound(codes, X, xd, scales, sg, values256=values))
