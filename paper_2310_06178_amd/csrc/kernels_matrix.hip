@@ -1354,11 +1354,11 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
     if constexpr (sizeof(XT) != 4) {
         MSGEMM_CASE(2, 0, 8, 2) MSGEMM_CASE(1, 0, 4, 8)
     } else {
-        MSGEMM_CASE(4, 2, 4, 2) MSGEMM_CASE(2, 2, 4, 2) MSGEMM_CASE(1, 2, 4, 2)
+        MSGEMM_CASE(4, 2, 4, 2) MSGEMM_CASE(1, 2, 4, 2)
         MSGEMM_CASE(2, 4, 4, 2) MSGEMM_CASE(1, 4, 4, 2)
     }
     if constexpr (sizeof(XT) != 1) {  // (int8: the compact form holds eight columns)
-        MSGEMM_CASE(4, 2, 8, 2) MSGEMM_CASE(2, 2, 8, 2) MSGEMM_CASE(1, 2, 8, 2)
+        MSGEMM_CASE(4, 2, 8, 2) MSGEMM_CASE(2, 2, 8, 2) MSGEMM_CASE(1, 2, 8, 2) MSGEMM_CASE(2, 2, 4, 2)
     }
     MSGEMM_CASE(4, 4, 8, 2) MSGEMM_CASE(4, 4, 4, 2) MSGEMM_CASE(2, 4, 8, 2) MSGEMM_CASE(1, 4, 8, 2)
 #undef MSGEMM_CASE
@@ -1596,7 +1596,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 37725 x 3640 x 1 int8 4 x 4 14.9, 4 x 2 17.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
     // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15, but
-    // 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; fp32, whose operands of eight
+    // 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; 14336 x 4096 x 8 in
+    // two row tiles, two workgroups a compute unit, 9.0, 8.55; fp32, whose operands of eight
     // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
     const bool f32 = p.x_dtype == MSGEMM_F32;
@@ -1606,7 +1607,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     } else if (bytes) {
         D = compact ? 4 : width == 1 && R == 1 && !f32 ? 4 : 2;
     } else if (!compact) {
-        W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : width == 2 && R == 4 && seg_runs >= 16 && groups(R) * passes * 4 >= 3 * p.cus ? 4 : 8;
+        W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) :
+            (width == 2 ? R == 4 && seg_runs >= 16 && groups(R) * passes * 8 >= 7 * p.cus : R == 2 && per_cu > 1) ? 4 : 8;
     } else if (R == 2) {
         if (per_cu == 1 || (int8 && seg_runs < 48)) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
