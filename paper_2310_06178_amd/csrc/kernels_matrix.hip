@@ -102,7 +102,11 @@ struct Bf16Weights {
     {
         // two's-complement nibbles: v_cvt_off_f32_i4 gives value / 16 in fp32, whose upper half is its bf16; the factor
         // is a power of two and is put back with the sums
-        const uint32_t x = c[t], y = x >> 4;
+        const uint32_t x = c[t];
+        uint32_t y = x >> 4;
+        // (hidden, or the compiler takes bits 12 to 19 of x instead of byte 1 of y, which the conversion cannot select by itself: an instruction more for
+        // three of the eight)
+        asm("" : "+v"(y));
         const float f0 = __builtin_amdgcn_cvt_off_f32_i4((int)x), f1 = __builtin_amdgcn_cvt_off_f32_i4((int)((x >> 8) & 0xff));
         const float f2 = __builtin_amdgcn_cvt_off_f32_i4((int)((x >> 16) & 0xff)), f3 = __builtin_amdgcn_cvt_off_f32_i4((int)(x >> 24));
         const float f4 = __builtin_amdgcn_cvt_off_f32_i4((int)y), f5 = __builtin_amdgcn_cvt_off_f32_i4((int)((y >> 8) & 0xff));
