@@ -1200,20 +1200,20 @@ matrix_reduce_kernel(MatrixArgs a, int segments)
 
 // Row-major codes -> the order above (inverse: back again).  Once per plan; 32 MiB in 65 us, bound by the row-major side,
 // where neighbouring lanes are a row apart.
-template <bool kInverse>
+template <bool kInverse, bool kTall>
 __global__ void __launch_bounds__(256)
 matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs, int R,
-                     int enc, int tall, int64_t dwords)
+                     int enc, int64_t dwords)
 {
     const int64_t kbytes = k / 2;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
         const int w = (int)(i & 3), lane = (int)(i >> 2) & 63;
-        const int64_t tile = i >> (tall ? 9 : 8);          // (row group, run, r)
+        const int64_t tile = i >> (kTall ? 9 : 8);          // (row group, run, r)
         const int r = (int)(tile % R);
         const int64_t rest = tile / R;
         const int64_t run = rest % runs, rg = rest / runs;
-        const int64_t row = tall ? (rg * R + r) * 32 + (lane & 31) : (rg * R + r) * 16 + (lane & 15);
-        const int64_t byte0 = (run * kRun + (tall ? 64 * (lane >> 5) + 32 * ((int)(i >> 8) & 1) : 32 * (lane >> 4)) + 8 * w) / 2;
+        const int64_t row = kTall ? (rg * R + r) * 32 + (lane & 31) : (rg * R + r) * 16 + (lane & 15);
+        const int64_t byte0 = (run * kRun + (kTall ? 64 * (lane >> 5) + 32 * ((int)(i >> 8) & 1) : 32 * (lane >> 4)) + 8 * w) / 2;
         uint8_t* src = rows + row * kbytes + byte0;
         uint32_t v = kInverse ? ((const uint32_t*)tiled)[i] : 0;
 #pragma unroll
@@ -1233,19 +1233,20 @@ matrix_repack_kernel(uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, in
 
 // Row-major 8-bit codes -> the order above; a pattern that the format does not read as its value is replaced by one it does.
 struct Remap { uint8_t to[256]; };
+template <bool kTall>
 __global__ void __launch_bounds__(256)
 matrix_repack8_kernel(const uint8_t* __restrict__ rows, uint8_t* __restrict__ tiled, int64_t m, int64_t k, int64_t runs,
-                      int R, Remap remap, int tall, int64_t dwords)
+                      int R, Remap remap, int64_t dwords)
 {
     __shared__ uint8_t to[256];
     to[threadIdx.x] = remap.to[threadIdx.x];
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dwords; i += (int64_t)gridDim.x * blockDim.x) {
-        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63, part = (int)(i >> 8) & (tall ? 3 : 1);
-        const int64_t tile = i >> (tall ? 10 : 9);         // (row group, run, r)
+        const int w = (int)(i & 3), lane = (int)(i >> 2) & 63, part = (int)(i >> 8) & (kTall ? 3 : 1);
+        const int64_t tile = i >> (kTall ? 10 : 9);         // (row group, run, r)
         const int64_t run = tile / R % runs, rg = tile / R / runs;
-        const int64_t row = tall ? (rg * R + tile % R) * 32 + (lane & 31) : (rg * R + tile % R) * 16 + (lane & 15);
-        const int64_t col = run * kRun + (tall ? 64 * (lane >> 5) : 32 * (lane >> 4)) + 16 * part + 4 * w;
+        const int64_t row = kTall ? (rg * R + tile % R) * 32 + (lane & 31) : (rg * R + tile % R) * 16 + (lane & 15);
+        const int64_t col = run * kRun + (kTall ? 64 * (lane >> 5) : 32 * (lane >> 4)) + 16 * part + 4 * w;
         uint32_t v = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -1255,15 +1256,16 @@ matrix_repack8_kernel(const uint8_t* __restrict__ rows, uint8_t* __restrict__ ti
 }
 
 // scales [m][nblocks] -> [row group][scale block][row wavefront][n][its row tiles, padded to Rp]; rows past m get zero
+template <int kHeight>
 __global__ void __launch_bounds__(256)
 matrix_repack_scales_kernel(const __half* __restrict__ scales, __half* __restrict__ ordered, int64_t m, int64_t nblocks,
-                            int R, int Wr, int Rp, int height, int64_t total)
+                            int R, int Wr, int Rp, int64_t total)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int r = (int)(i % Rp), n = (int)(i / Rp) % height, wr = (int)(i / (height * Rp) % Wr);
-        const int64_t rest = i / (height * Rp * Wr);
+        const int r = (int)(i % Rp), n = (int)(i / Rp) % kHeight, wr = (int)(i / (kHeight * Rp) % Wr);
+        const int64_t rest = i / (kHeight * Rp * Wr);
         const int64_t block = rest % nblocks, rg = rest / nblocks;
-        const int64_t row = ((rg * Wr + wr) * R + r) * height + n;
+        const int64_t row = ((rg * Wr + wr) * R + r) * kHeight + n;
         ordered[i] = r < R && row < m ? scales[row * nblocks + block] : __float2half(0.0f);
     }
 }
@@ -1653,13 +1655,10 @@ static int matrix_repack(const Plan& p, uint8_t* row_major, bool inverse, hipStr
     const int64_t dwords = p.ktiles * p.m_pad * 16;
     int64_t blocks = (dwords + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    const int enc = encoding_of(p.x_dtype);
-    if (inverse)
-        hipLaunchKernelGGL((matrix_repack_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, p.mx_tall ? 1 : 0, dwords);
-    else
-        hipLaunchKernelGGL((matrix_repack_kernel<false>), dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled,
-                           p.m, p.k, p.ktiles, p.mx_r * p.mx_row_waves, enc, p.mx_tall ? 1 : 0, dwords);
+    const auto kernel = inverse ? (p.mx_tall ? matrix_repack_kernel<true, true> : matrix_repack_kernel<true, false>)
+                                : (p.mx_tall ? matrix_repack_kernel<false, true> : matrix_repack_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, row_major, p.codes_tiled, p.m, p.k, p.ktiles,
+                       p.mx_r * p.mx_row_waves, encoding_of(p.x_dtype), dwords);
     MSGEMM_HIP_TRY(hipGetLastError());
     return MSGEMM_OK;
 }
@@ -1672,8 +1671,8 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         const int64_t total = (int64_t)(matrix_scale_bytes(p) / 2);
         int64_t blocks = (total + 255) / 256;
         if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(matrix_repack_scales_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const __half*)p.scales,
-                           (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), p.mx_tall ? 32 : 16, total);
+        hipLaunchKernelGGL(p.mx_tall ? matrix_repack_scales_kernel<32> : matrix_repack_scales_kernel<16>, dim3((unsigned)blocks), dim3(256), 0, s,
+                           (const __half*)p.scales, (__half*)p.scales_ordered, p.m, p.nblocks, p.mx_r, p.mx_row_waves, scale_slots(p), total);
         MSGEMM_HIP_TRY(hipGetLastError());
     }
     if (p.codes8) {
@@ -1682,8 +1681,8 @@ int matrix_repack(const Plan& p, const void* W_codes, hipStream_t s)
         if (blocks > 65536) blocks = 65536;
         Remap remap;
         for (int i = 0; i < 256; ++i) remap.to[i] = p.mx_remap[i];
-        hipLaunchKernelGGL(matrix_repack8_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const uint8_t*)W_codes,
-                           p.codes_tiled, p.m, p.k / 2, p.ktiles, p.mx_r * (p.mx_tall ? p.mx_row_waves : 1), remap, p.mx_tall ? 1 : 0, dwords);
+        hipLaunchKernelGGL(p.mx_tall ? matrix_repack8_kernel<true> : matrix_repack8_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s,
+                           (const uint8_t*)W_codes, p.codes_tiled, p.m, p.k / 2, p.ktiles, p.mx_r * p.mx_row_waves, remap, dwords);
         MSGEMM_HIP_TRY(hipGetLastError());
         return MSGEMM_OK;
     }
