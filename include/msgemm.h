@@ -165,7 +165,7 @@ typedef struct {
     int no_xcd_map;              /* 1: workgroup ids in k-tile-major order instead of grouped per L2 */
     int batched_form;            /* batched kernel: 0 = library's choice, 1 = build phase per k-tile, 2 = pipelined;
                                     3 with AUTO = the matrix form wherever it can serve the problem (then
-                                    panels_per_workgroup = 1, 2 or 4 tiles of 16 rows per wavefront, 3 for the tile kernel;
+                                    panels_per_workgroup = 1, 2 or 4 tiles of rows per wavefront, tile kernel 1, 2 or 3;
                                     rows_per_lane = 4 the tile kernel, 8 the streaming kernel for more than 16 columns;
                                     batched_segments).  Any other request in this structure that names a form of the table
                                     kernels keeps AUTO from the matrix form */

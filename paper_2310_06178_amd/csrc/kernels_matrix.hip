@@ -277,10 +277,11 @@ __device__ __forceinline__ void lds_barrier()
 // that count.  They end up in the same lane: y(column q) is the sum over t of register t of accumulator t of lane group q.
 //
 // Measured (one launch in a graph, cold codes; in brackets the table kernels with their second launch where they have
-// one): 16384 x 4096 x 1 fp16 7.4 us = 4.5 TB/s (9.5; a launch that only reads the codes 6.7), 49152 x 12288 x 1 45.2 us =
-// 6.7 TB/s (51.7), 14336 x 4096 x 16 fp16 with scales 9.5 us (30), 8192 x 8192 x 16 int8 8.6 us (30), 4096 x 4096 x 4 fp32
-// 6.0 us (8.9), 8192 x 8192 E4M3 codes, one column, 13.0 us (18.0).  What is left at sixteen columns is the decoding: two
-// to three vector instructions per pair of weights against one MFMA for sixteen columns.
+// one): 16384 x 4096 x 1 fp16 7.4 us = 4.5 TB/s (9.5; a launch that only reads the codes 6.7), 49152 x 12288 x 1 44.7 us =
+// 6.8 TB/s (51.7), 14336 x 4096 x 16 fp16 with scales 8.9 us (30), 8192 x 8192 x 16 int8 8.0 us (30), 4096 x 4096 x 4 fp32
+// 5.3 us (8.9), 8192 x 8192 E4M3 codes, one column, 12.9 us (18.0).  Without decoding and products the first takes 7.1, without
+// its activations 7.5.  What is left at sixteen columns is the way of the activations through the LDS, as many bytes as of
+// codes, and the decoding: two to three vector instructions per pair of weights against one MFMA for sixteen columns.
 template <typename XT, int R, int kCols4, int W, int D, bool kScaled, int F>
 __global__ void __launch_bounds__(W * 64)
 matrix_stream_kernel(MatrixArgs a)
