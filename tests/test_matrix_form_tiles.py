@@ -168,7 +168,7 @@ def test_8_bit_codes_at_the_ends_of_the_range(b, sg, power, xd, magnitude):
     values = _formats()["e5m2"] * 2.0 ** power
     codes = np.random.default_rng(m + b).integers(0, 256, size=(m, k), dtype=np.uint8)
     X = (inputs.make_x(k, b, "f32", seed=k + 1) * np.float32(magnitude)).astype(np.float32)
-    X = {"bf16": inputs.f32_to_bf16_bits(X), "f16": X.astype(np.float16)}[xd]
+    X = inputs.f32_to_bf16_bits(X) if xd == "bf16" else X.astype(np.float16)
     scales = inputs.make_scales(m, k, sg, seed=10) if sg else None
     Xd = oracle.bf16_bits_to_f64(X) if xd == "bf16" else X.astype(np.float64)
     ref = oracle.gemm_f64_codes8(codes, Xd, values, scales, sg)
