@@ -1318,6 +1318,7 @@ int batched_phase_form_panels(int64_t panels, int64_t ktiles, int64_t scale_grou
 bool batched_pipelined_is_faster(int64_t m, int64_t k, int64_t b, int64_t scale_group, int cus)
 {
     const int col_passes = (int)((b + kBC - 1) / kBC);
+    if (scale_group > 0 && scale_group < 2 * kPG) return true;  // neither form has k-tiles that small: refused by the caller
     // pipelined form: 512-row panels, k-tiles of 32 columns
     int ppw;
     int64_t per;

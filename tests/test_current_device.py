@@ -116,3 +116,26 @@ for m, matrix in ((1 << 20, False), (1 << 22, True)):
 print("ok")
 """)
     assert out.strip().endswith("ok")
+
+
+@pytest.mark.parametrize("group", [2, 8, 16, 30])
+def test_scale_blocks_smaller_than_a_table_tile(runtime, group):
+    """Scale blocks under 32 columns fit no k-tile of the tables in LDS: AUTO keeps its tables in device memory, a request for the
+    batched kernel is refused, and so are 8-bit codes (whose tables are in LDS only)."""
+    out = run(runtime, f"""
+from paper_2310_06178_amd import inputs
+values = [0.0 if v != v else float(v) for v in inputs.fp8_e4m3_values()]
+for b in (3, 16, 48):
+    for x in ("f16", "bf16"):
+        plan = B.msgemm_plan(64, 4 * {group}, b, x, x, 2, {group}, ADDRESS, ADDRESS, stream=0)
+        assert B.msgemm_plan_get_info(plan)["variant"] == B.VARIANT_GLOBAL_LUT
+        for make in (lambda: B.msgemm_plan(64, 4 * {group}, b, x, x, 2, {group}, ADDRESS, ADDRESS, B.VARIANT_FUSED_LDS16, stream=0),
+                     lambda: B.msgemm_plan_codes8(64, 2 * {group}, b, x, x, {group} // 2, ADDRESS, ADDRESS, values, stream=0)):
+            try:
+                make()
+                raise SystemExit("accepted")
+            except B.MsgemmError as e:
+                assert e.status == B.ERR_UNSUPPORTED, e
+print("ok")
+""")
+    assert out.strip().endswith("ok")
