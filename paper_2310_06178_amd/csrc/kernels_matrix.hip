@@ -1600,7 +1600,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
     //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3
     // Two row tiles: 6144 x 6144 x 3 fp16 4 x 4 5.6; in more workgroups 42240 x 6912 x 4 fp16 4 x 4 27.9, 8 x 2 27.5, 13160 x 24704 x 1 bf16 31.7, 30.8, 33792 x
-    // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 37725 x 3640 x 1 int8 4 x 4 14.9, 4 x 2 17.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.
+    // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
+    // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
+    // 60.9 / 61.5; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
     // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15, but
     // 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; 14336 x 4096 x 8 in
@@ -1617,7 +1619,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) :
             (width == 2 ? R == 4 && seg_runs >= 16 && groups(R) * passes * 8 >= 7 * p.cus : R == 2 && per_cu > 1) ? 4 : 8;
     } else if (R == 2) {
-        if (per_cu == 1 || (int8 && seg_runs < 48)) D = 4;
+        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 72))) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
         if (per_cu == 1 && seg_runs >= 32) W = 16;

@@ -8,20 +8,24 @@
 enum { kAlloc = 1, kLaunch = 2, kWork = 3, kEvent = 4 };
 static int current_device, capturing, count;
 static uintptr_t next_address = 0x100000000ull;
-static struct { int kind, device, own_stream; } calls[65536];
+static struct { int kind, device, own_stream; const void* kernel; } calls[65536];
+static struct { const void* host; char name[320]; } kernels[8192];
+static int kernels_known;
 static char streams[64];
 static int streams_made;
 
-static int note(int kind, const void* stream)
+static int note_kernel(int kind, const void* stream, const void* kernel)
 {
     if (count < 65536) {
         calls[count].kind = kind;
         calls[count].device = current_device;
         calls[count].own_stream = (const char*)stream >= streams && (const char*)stream < streams + sizeof(streams);
+        calls[count].kernel = kernel;
         ++count;
     }
     return 0;
 }
+static int note(int kind, const void* stream) { return note_kernel(kind, stream, 0); }
 
 /* for the test */
 int rec_count(void) { return count; }
@@ -29,8 +33,26 @@ int rec_kind(int i) { return calls[i].kind; }
 int rec_device(int i) { return calls[i].device; }
 int rec_own_stream(int i) { return calls[i].own_stream; }
 void rec_capture(int on) { capturing = on; }
+const char* rec_kernel(int i)          /* name of the kernel that call i launches, as the compiler made it */
+{
+    for (int j = 0; j < kernels_known; ++j)
+        if (kernels[j].host == calls[i].kernel) return kernels[j].name;
+    return "";
+}
+int rec_kernels(void) { return kernels_known; }   /* the library's own */
+const char* rec_name(int j) { return kernels[j].name; }
+void rec_forget(void) { count = 0; }
 
 /* the runtime */
+void __hipRegisterFunction(void** module, const void* host, char* device, const char* name, unsigned limit, void* tid, void* bid,
+                           void* block, void* grid, int* size)
+{
+    (void)module; (void)device; (void)limit; (void)tid; (void)bid; (void)block; (void)grid; (void)size;
+    if (kernels_known == 8192) return;
+    kernels[kernels_known].host = host;
+    strncpy(kernels[kernels_known].name, name, sizeof(kernels[0].name) - 1);
+    ++kernels_known;
+}
 int hipGetDevice(int* d) { *d = current_device; return 0; }
 int hipSetDevice(int d) { current_device = d; return 0; }
 int hipDeviceGetAttribute(int* v, int attribute, int device) { (void)attribute; (void)device; *v = 256; return 0; }
@@ -93,6 +115,6 @@ int __hipPopCallConfiguration(struct dim* g, struct dim* b, size_t* lds, void** 
 }
 int hipLaunchKernel(const void* f, struct dim g, struct dim b, void** args, size_t lds, void* stream)
 {
-    (void)f; (void)g; (void)b; (void)args; (void)lds;
-    return note(kLaunch, stream);
+    (void)g; (void)b; (void)args; (void)lds;
+    return note_kernel(kLaunch, stream, f);
 }

@@ -1,0 +1,75 @@
+"""Which kernel of the matrix form a problem runs in, by the library's own choice, on the CPU: libmsgemm.so over a stand-in for the HIP runtime
+(recording_hip_runtime.c, 256 compute units) that notes the kernels launched.  Problems on both sides of the lines of its rule."""
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+BODY = """
+import ctypes, json, sys
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+rec.rec_kernel.restype = rec.rec_name.restype = ctypes.c_char_p
+from paper_2310_06178_amd import binding as B
+from paper_2310_06178_amd import inputs
+B.load()
+A, E4M3 = 0x10000, [0.0 if v != v else float(v) for v in inputs.fp8_e4m3_values()]
+launched = []
+for m, k, b, x, group, bits, options, ldx in json.load(sys.stdin):
+    scales, y = A if group else None, "i32" if x == "i8" else x
+    if bits == 8:
+        plan = B.msgemm_plan_codes8(m, k, b, x, y, group, A, scales, E4M3, options=options, stream=0)
+    else:
+        plan = B.msgemm_plan(m, k, b, x, y, 2, group, A, scales, options=options, stream=0)
+    rec.rec_forget()
+    B.msgemm_run(plan, A, ldx or k, A, m, stream=0)
+    launched.append([rec.rec_kernel(i).decode() for i in range(rec.rec_count())])
+    B.msgemm_destroy(plan)
+json.dump([launched, [rec.rec_name(i).decode() for i in range(rec.rec_kernels())]], sys.stdout)
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "librecording_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wall", "-Wextra", "-Werror", "-o", out,
+                    os.path.join(ROOT, "tests", "recording_hip_runtime.c")], check=True)
+    return out
+
+
+def launches(runtime, problems):
+    """Kernels that msgemm_run launches for each (m, k, b, x, scale group[, bits, options, ldx]), and all that the library has."""
+    full = [list(p) + [4, None, 0][len(p) - 5:] for p in problems]
+    p = subprocess.run([sys.executable, "-c", BODY, runtime], cwd=ROOT, input=json.dumps(full), capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr[-3000:]
+    return json.loads(p.stdout)
+
+
+def short(name):
+    """stream R/W x D, tile R/column tiles, small R/column tiles, or tables."""
+    ints = [int(i) for i in re.findall(r"L[ib](\d+)E", name)]
+    if "matrix_stream_kernel" in name:
+        return "stream %d/%dx%d" % (ints[0], ints[2], ints[3])
+    if "matrix_tile_kernel" in name:
+        return "tile %d/%d" % (ints[1], ints[2])
+    if "matrix_small_tile_kernel" in name:
+        return "small %d/%d" % (ints[0], ints[1])
+    return "tables"
+
+
+# m, k, b, type of X, scale block, kernel
+CHOICES = [
+    # int8, two row tiles: rings of four in four wavefronts, unless three workgroups and more have 72 runs and more each
+    (14848, 10240, 1, "i8", 0, "stream 2/4x4"), (14848, 40192, 1, "i8", 0, "stream 2/4x4"), (19847, 6744, 4, "i8", 0, "stream 2/4x4"),
+    (37725, 6744, 8, "i8", 0, "stream 2/4x4"), (26000, 9088, 1, "i8", 0, "stream 2/4x4"), (26000, 9216, 1, "i8", 0, "stream 2/8x2"),
+]
+
+
+def test_own_choice(runtime):
+    launched, _ = launches(runtime, [c[:5] for c in CHOICES])
+    got = [c[:5] + (short(names[0]),) for c, names in zip(CHOICES, launched)]
+    assert got == CHOICES
