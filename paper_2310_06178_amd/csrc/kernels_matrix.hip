@@ -1568,12 +1568,15 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // registers).
     const int tiles[2][3] = {{1, 2, 4}, {1, 2, 3}};
     double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
-    // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, a little more where two
-    // workgroups of one tile would do the work of one of two, or very many have theirs to start.  us, one tile / two: 28672 x 4096 x 1 fp16 with
-    // scales 12.1 / 12.4, 11008 x 4096 x 4 bf16 7.1 / 8.0, 20480 x 8192 x 1 fp16 15.7 / 16.9, 8192 x 8192 x 1 bf16 8.4 / 8.7, 8192 x 4096 x 1 5.1 / 5.0, 42240 x 6912 x
-    // 4 28.8 / 27.5, 16384 x 16384 x 1 23.7 / 23.1.  fp32, two tiles / four: 16384 x 8192 x 4 19.2 / 18.6, 33280 x 4096 x 16 38.0 / 34.3)
-    if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && !int8 && runs < 96)
-        cost[0][0] = runs < 64 && groups(1) <= 2 * p.cus ? 1.05 : runs >= 48 && groups(1) > 8 * p.cus ? 1.12 : 0.98;
+    // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, or is one column under four workgroups a
+    // compute unit, and more the longer it is and the more columns it has.  us, one tile / two; where two workgroups of one tile do the work of one of two:
+    // 16384 x 3840 x 1 fp16 9.4 / 9.6, 8192 x 8192 x 1 bf16 8.4 / 8.7, 24089 x 5888 x 1 with scales 14.7 / 14.0, 13160 x 8192 x 2 with scales 13.2 / 12.6, 24089 x 4860 x 4 bf16
+    // 15.0 / 13.8, 16384 x 8192 x 4 bf16 with scales 16.2 / 14.3; where they do not: 20480 x 8192 x 1 15.7 / 16.9, 11008 x 4096 x 4 bf16 7.1 / 8.0, 33280 x 8192 x 4 bf16
+    // 1.06 : 1.  Over 210 problems with 6056 to 33280 rows and 1, 2 and 4 columns the choice takes 0.6 percent more than the faster of
+    // the two in the mean, 9 at most.
+    // fp32, two tiles / four: 16384 x 8192 x 4 19.2 / 18.6, 33280 x 4096 x 16 38.0 / 34.3)
+    if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && !int8)
+        cost[0][0] = runs < 24 || (p.b == 1 && runs < 72 && groups(1) <= 4 * p.cus) ? 0.98 : runs >= (p.b > 2 ? 48 : 96) ? 1.25 : 1.05;
     if (p.x_dtype == MSGEMM_F32 && !bytes) cost[0][2] = 3.95, cost[2][2] = 3.8;
     double best = 0;
     int R = 1;

@@ -66,6 +66,13 @@ CHOICES = [
     # int8, two row tiles: rings of four in four wavefronts, unless three workgroups and more have 72 runs and more each
     (14848, 10240, 1, "i8", 0, "stream 2/4x4"), (14848, 40192, 1, "i8", 0, "stream 2/4x4"), (19847, 6744, 4, "i8", 0, "stream 2/4x4"),
     (37725, 6744, 8, "i8", 0, "stream 2/4x4"), (26000, 9088, 1, "i8", 0, "stream 2/4x4"), (26000, 9216, 1, "i8", 0, "stream 2/8x2"),
+    # 16 bits: one row tile where that takes the busiest compute unit fewer row tiles, and for one column under four workgroups a compute unit
+    # or a short stream also where it takes as many
+    (11008, 4860, 1, "f16", 0, "stream 1/4x2"), (18097, 8192, 2, "f16", 128, "stream 1/4x4"), (33280, 8192, 1, "bf16", 0, "stream 1/4x4"),
+    (33280, 8192, 4, "bf16", 0, "stream 2/8x2"), (20480, 12288, 1, "f16", 0, "stream 2/8x2"),
+    (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
+    (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
+    (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
 ]
 
 
