@@ -1597,8 +1597,11 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // Streaming kernel, wavefronts and depth of their rings: what keeps the memory busy is some 32 KiB of codes in flight per compute
     // unit (its share of 6.3 TB/s times a microsecond's trip); more only queues, and an unrolled loop that is gone through once or twice
     // is fetched for nothing.  us, "wavefronts x depth", one column or a few and one row tile:
-    //   a workgroup per compute unit: 4096 x 14336 x 1 fp16 4 x 8 7.1, 16 x 2 7.0, 4 x 4 7.9; 4096 x 4096 x 1 fp32 5.6, 5.0, 5.1; a short k
-    //   in fours, 2048 x 1024 x 1 fp16 4 x 8 2.8, 16 x 2 2.7, 4 x 2 2.5
+    //   a workgroup per compute unit, 4 x 8 / 16 x 2 / 4 x 4: 4096 x 14336 x 1 fp16 6.9 / 6.7 / 7.6, x 2 with scales 7.3 / 7.2 / 8.0, x 4 7.6 / 7.5 / 7.7, 3072 x 14336 x 1
+    //   with scales 6.8 / 6.4 / 7.7, 4096 x 4096 x 2 with scales 4.1 / 3.8 / 3.9; from 160 runs on sixteen wavefronts lose, 4096 x 20480 x 4 9.3 / 9.9, x 8 int8 9.7 / 10.0, 3072 x
+    //   40960 x 4 fp16 with scales 16.2 / 17.2, 1792 x 40960 x 1 (two segments) 9.6 / 9.9, but not one or two columns with scales, 3072 x 24576 x 1 fp16 9.6 / 9.2, 3072 x
+    //   22528 x 2 bf16 10.6 / 9.7; under it, 4096 x 18432 x 4 fp16 8.9 / 8.8.  fp32 has them at any length: 4096 x 4096 x 1 5.3 / 4.6 / 4.7, 3072 x 40960 x 4 27.0 / 22.8 / 25.5.
+    //   A short k in fours, 2048 x 1024 x 1 fp16 4 x 8 2.8, 16 x 2 2.7, 4 x 2 2.5
     //   two: 8192 x 8192 x 1 bf16 4 x 8 9.1, 4 x 4 8.4; 8192 x 14336 x 1 fp16 11.8, 11.4
     //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
     //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3
@@ -1625,8 +1628,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 72))) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
-        if (per_cu == 1 && seg_runs >= 32) W = 16;
-        else if (per_cu > 1 && seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
+        if (per_cu == 1 && seg_runs >= 32 && (f32 || seg_runs < 160 || (scaled && p.b <= 2))) W = 16;
+        else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
         else if (seg_runs >= (per_cu > 2 ? 48 : int8 ? 12 : 16)) D = 4;
     }
     p.mx_depth = D;

@@ -73,6 +73,10 @@ CHOICES = [
     (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
     (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
     (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
+    # a workgroup per compute unit: sixteen wavefronts from 32 runs up to 160, and beyond for fp32 and one or two columns with scales
+    (4096, 14336, 2, "f16", 128, "stream 1/16x2"), (4096, 20352, 4, "f16", 0, "stream 1/16x2"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"),
+    (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (4096, 20480, 8, "i8", 0, "stream 1/4x8"),
+    (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"), (4096, 4096, 1, "i8", 0, "stream 1/16x2"),
 ]
 
 
