@@ -77,6 +77,12 @@ CHOICES = [
     (4096, 14336, 2, "f16", 128, "stream 1/16x2"), (4096, 20352, 4, "f16", 0, "stream 1/16x2"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"),
     (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (4096, 20480, 8, "i8", 0, "stream 1/4x8"),
     (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"), (4096, 4096, 1, "i8", 0, "stream 1/16x2"),
+    # a short k: rings of two up to ten runs; int8 whose columns end inside a 16-byte piece keep more in flight
+    (3072, 1280, 1, "f16", 0, "stream 1/4x2"), (3072, 1290, 1, "f16", 0, "stream 1/4x4"), (3072, 1290, 8, "i8", 0, "stream 1/4x4"),
+    (3072, 1290, 1, "f32", 0, "stream 1/4x2"), (3072, 2580, 1, "i8", 0, "stream 1/4x8"), (3072, 2820, 4, "i8", 0, "stream 1/4x8"),
+    (3072, 3070, 1, "i8", 0, "stream 1/4x8"), (3072, 2178, 1, "i8", 0, "stream 1/4x4"), (3072, 2562, 4, "i8", 0, "stream 1/4x4"),
+    (3072, 2576, 1, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
+    (12288, 3648, 1, "i8", 0, "stream 1/4x2"), (12288, 4096, 1, "i8", 0, "stream 1/4x2"), (12288, 3640, 8, "i8", 0, "stream 1/4x2"),
 ]
 
 
