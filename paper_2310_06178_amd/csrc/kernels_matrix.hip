@@ -1570,13 +1570,13 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
     // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, or is one column under four workgroups a
     // compute unit, and more the longer it is and the more columns it has.  us, one tile / two; where two workgroups of one tile do the work of one of two:
-    // 16384 x 3840 x 1 fp16 9.4 / 9.6, 8192 x 8192 x 1 bf16 8.4 / 8.7, 24089 x 5888 x 1 with scales 14.7 / 14.0, 13160 x 8192 x 2 with scales 13.2 / 12.6, 24089 x 4860 x 4 bf16
+    // 16384 x 3840 x 1 fp16 9.4 / 9.6, 7043 x 2176 x 3 with scales (two, or one of two) 4.2 / 4.0, 8192 x 8192 x 1 bf16 8.4 / 8.7, 24089 x 5888 x 1 with scales 14.7 / 14.0, 13160 x 8192 x 2 with scales 13.2 / 12.6, 24089 x 4860 x 4 bf16
     // 15.0 / 13.8, 16384 x 8192 x 4 bf16 with scales 16.2 / 14.3; where they do not: 20480 x 8192 x 1 15.7 / 16.9, 11008 x 4096 x 4 bf16 7.1 / 8.0, 33280 x 8192 x 4 bf16
     // 1.06 : 1.  Over 210 problems with 6056 to 33280 rows and 1, 2 and 4 columns the choice takes 0.6 percent more than the faster of
     // the two in the mean, 9 at most.
     // fp32, two tiles / four: 16384 x 8192 x 4 19.2 / 18.6, 33280 x 4096 x 16 38.0 / 34.3)
     if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && !int8)
-        cost[0][0] = runs < 24 || (p.b == 1 && runs < 72 && groups(1) <= 4 * p.cus) ? 0.98 : runs >= (p.b > 2 ? 48 : 96) ? 1.25 : 1.05;
+        cost[0][0] = groups(1) <= 2 * p.cus && runs < 64 ? 1.05 : runs < 24 || (p.b == 1 && runs < 72 && groups(1) <= 4 * p.cus) ? 0.98 : runs >= (p.b > 2 ? 48 : 96) ? 1.25 : 1.05;
     if (p.x_dtype == MSGEMM_F32 && !bytes) cost[0][2] = 3.95, cost[2][2] = 3.8;
     double best = 0;
     int R = 1;
@@ -1602,11 +1602,11 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   40960 x 4 fp16 with scales 16.2 / 17.2, 1792 x 40960 x 1 (two segments) 9.6 / 9.9, but not one or two columns with scales, 3072 x 24576 x 1 fp16 9.6 / 9.2, 3072 x
     //   22528 x 2 bf16 10.6 / 9.7; under it, 4096 x 18432 x 4 fp16 8.9 / 8.8.  fp32 has them at any length: 4096 x 4096 x 1 5.3 / 4.6 / 4.7, 3072 x 40960 x 4 27.0 / 22.8 / 25.5.
     //   A short k, 4 x 8 / 4 x 4 / 4 x 2: 3072 x 1024 x 1 fp16 3.0 / 2.7 / 2.5, int8 2.8 / 2.6 / 2.5, 3072 x 1290 x 1 fp16 3.1 / 2.9 / 3.1, int8 3.6 / 3.3 / 3.7, 3072 x 2048 x 1 fp16
-    //   3.3 / 2.9 / 3.2; int8 with columns apart 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, but 3072 x 2178 x 1 3.2 / 3.1 / 3.5,
-    //   3072 x 3330 x 1 level, 3072 x 2562 x 4 (k no multiple of four) 4.2 / 4.0
+    //   3.3 / 2.9 / 3.2; int8 3072 x 2816 x 1 3.15 / 3.25 / 3.6, x 8 3.5 / 3.4 / 3.7, 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, but 3072 x
+    //   2178 x 1 3.2 / 3.1 / 3.5, 3072 x 3330 x 1 level, 3072 x 2562 x 4 (k no multiple of four) 4.2 / 4.0
     //   two: 8192 x 8192 x 1 bf16 4 x 8 9.1, 4 x 4 8.4; 8192 x 14336 x 1 fp16 11.8, 11.4
     //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
-    //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3; 12288 x 4096 x 1 int8 4 x 4 6.5, 4 x 2 6.0, with columns apart 12288 x 3640 x 1 6.7, 7.1, 9000 x 5900 x 2 8.0, 8.3
+    //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3; 12288 x 4096 x 1 int8 4 x 4 6.5, 4 x 2 6.0, with columns that end inside a 16-byte piece 12288 x 3640 x 1 6.7, 7.1, 9000 x 5900 x 2 8.0, 8.3
     // Two row tiles: 6144 x 6144 x 3 fp16 4 x 4 5.6; in more workgroups 42240 x 6912 x 4 fp16 4 x 4 27.9, 8 x 2 27.5, 13160 x 24704 x 1 bf16 31.7, 30.8, 33792 x
     // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
     // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
@@ -1618,9 +1618,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
     const bool f32 = p.x_dtype == MSGEMM_F32;
-    // (int8, columns of X that end in the middle of a 16-byte piece: loads of any alignment take longer to come.  One column, or several at
-    // addresses that are multiples of four; several others are bound by the loads themselves.)
-    const bool apart = int8 && p.b <= 4 && k % 16 != 0 && (p.b == 1 || k % 4 == 0);
+    // (int8, one column, or up to four at addresses that are multiples of four: others are bound by the loads of the activations themselves)
+    const bool few8 = int8 && p.b <= 4 && (p.b == 1 || k % 4 == 0);
     int W = 4, D = 2;
     if (tile) {
         W = 8;
@@ -1635,8 +1634,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     } else if (R == 1) {
         if (per_cu == 1 && seg_runs >= 32 && (f32 || seg_runs < 160 || (scaled && p.b <= 2))) W = 16;
         else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
-        else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 26 && apart) D = 8;
-        else if (seg_runs >= (per_cu > 2 ? (apart ? 28 : 48) : f32 ? 16 : 11)) D = 4;
+        else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 26 && few8) D = 8;
+        else if (seg_runs >= (per_cu > 2 ? (few8 && k % 16 != 0 ? 28 : 48) : f32 ? 16 : 11)) D = 4;
     }
     p.mx_depth = D;
     p.mx_tile_kernel = tile;

@@ -72,16 +72,17 @@ CHOICES = [
     (33280, 8192, 4, "bf16", 0, "stream 2/8x2"), (20480, 12288, 1, "f16", 0, "stream 2/8x2"),
     (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
     (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
-    (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
+    (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (7043, 2176, 3, "f16", 128, "stream 2/4x4"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
     # a workgroup per compute unit: sixteen wavefronts from 32 runs up to 160, and beyond for fp32 and one or two columns with scales
     (4096, 14336, 2, "f16", 128, "stream 1/16x2"), (4096, 20352, 4, "f16", 0, "stream 1/16x2"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"),
     (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (4096, 20480, 8, "i8", 0, "stream 1/4x8"),
     (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"), (4096, 4096, 1, "i8", 0, "stream 1/16x2"),
-    # a short k: rings of two up to ten runs; int8 whose columns end inside a 16-byte piece keep more in flight
+    # a short k: rings of two up to ten runs; int8 in few columns keeps more in flight from 20 to 25 runs, and under three workgroups where
+    # columns end inside a 16-byte piece
     (3072, 1280, 1, "f16", 0, "stream 1/4x2"), (3072, 1290, 1, "f16", 0, "stream 1/4x4"), (3072, 1290, 8, "i8", 0, "stream 1/4x4"),
     (3072, 1290, 1, "f32", 0, "stream 1/4x2"), (3072, 2580, 1, "i8", 0, "stream 1/4x8"), (3072, 2820, 4, "i8", 0, "stream 1/4x8"),
     (3072, 3070, 1, "i8", 0, "stream 1/4x8"), (3072, 2178, 1, "i8", 0, "stream 1/4x4"), (3072, 2562, 4, "i8", 0, "stream 1/4x4"),
-    (3072, 2576, 1, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
+    (3072, 2816, 2, "i8", 0, "stream 1/4x8"), (3072, 2816, 8, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
     (12288, 3648, 1, "i8", 0, "stream 1/4x2"), (12288, 4096, 1, "i8", 0, "stream 1/4x2"), (12288, 3640, 8, "i8", 0, "stream 1/4x2"),
 ]
 
