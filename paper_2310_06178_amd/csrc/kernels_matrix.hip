@@ -973,7 +973,7 @@ matrix_tile_kernel(MatrixArgs a)
             const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)mine + buf + (wr + j * Wr) * 1024u;
             // (the wait states are those behind a vector instruction that writes a scalar operand, which the compiler does not count into asm)
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                         :: "s"(to), "v"(xoff[j]), "s"(xrsrc), "s"(run * (int)(kRun * sizeof(XT))) : "m0");
+                         :: "s"(to), "v"(xoff[j]), "s"(xrsrc), "s"(run * (int)(kRun * sizeof(XT))) : "m0", "memory");
         } else {
             xr[j] = load_any16<sizeof(XT)>(xbase + xoff[j] + (int64_t)run * (int)(kRun * sizeof(XT)));
         }
