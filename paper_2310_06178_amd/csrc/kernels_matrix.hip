@@ -1356,8 +1356,11 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
 #define MSGEMM_CASE(RR, CC, WW, DD) \
     if (p.mx_r == RR && p.mx_cols == CC && p.mx_waves == WW && p.mx_depth == DD) return launch_stream<XT, RR, CC, WW, DD, kInt4>(p, a, s);
     MSGEMM_CASE(4, 0, 4, 2)
-    MSGEMM_CASE(2, 0, 4, 2) MSGEMM_CASE(2, 0, 4, 4)
+    MSGEMM_CASE(2, 0, 4, 4)
     MSGEMM_CASE(1, 0, 4, 2) MSGEMM_CASE(1, 0, 4, 4) MSGEMM_CASE(1, 0, 16, 2)
+    if constexpr (sizeof(XT) != 1) {
+        MSGEMM_CASE(2, 0, 4, 2)
+    }
     if constexpr (sizeof(XT) != 4) {
         MSGEMM_CASE(2, 0, 8, 2) MSGEMM_CASE(1, 0, 4, 8)
     } else {
@@ -1443,12 +1446,12 @@ namespace {
 // (near a line either may be ahead by a tenth or two: the table kernels' forms change in steps).  us, tables / matrix form: one fp16 column,
 // 49152 x 128 4.9 / 4.1, 65536 x 128 5.0 / 5.2, 300000 x 128 6.3 / 18; 65536 x 256 8.1 / 6.1, 100000 x 256 6.5 / 8.4; 180000 x
 // 640 level, 300000 x 640 25 / 29, 600000 x 1024 level, 1000003 x 1024 78 / 102.  Eight columns: 49152 x 128 6.5 / 5.3, 65536 x
-// 128 6.6 / 7.3; 180000 x 640 1.14 : 1, 600000 x 640 71 / 92.  More columns: 24576 x 128 x 33 1.9 : 1, 57000 x 128 x 48 12.9 / 22.6;
-// 49152 x 64 x 33 1.5 : 1, 57000 x 64 x 48 10.2 / 23.2; 40000 x 256 x 48 1.2 : 1, 80000 x 256 x 48 21.8 / 34.4; 100000 x 384 x 32 30 / 39.
+// 128 6.6 / 7.3; 180000 x 640 1.14 : 1, 600000 x 640 71 / 92.  More columns: 49152 x 64 x 33
+// 1.5 : 1, 57000 x 64 x 48 10.2 / 23.2 (a run and more of 16-bit and int8 activations goes to the tile kernel, which has a line of its own).
 // A k that is no whole number of runs adds loads of single elements and counts for more: 156556 x 754 15.8 / 17.3, int8
 // 180000 x 640 1.3 : 1 but 182415 x 692 19.2 / 23.0.
-enum { kHalf = 1, kFloat = 2, kBytes = 4, kAny = 7, kRagged = 8, kWhole = 16 };
-// (types of X: fp16 and bf16, fp32, int8; only where k is not a multiple of 128, only where it is one of 64)
+enum { kHalf = 1, kFloat = 2, kBytes = 4, kAny = 7, kRagged = 8 };
+// (types of X: fp16 and bf16, fp32, int8; only where k is not a multiple of 128)
 struct ShortLine { int k_from, k_to, b_from, b_to, types, rows, to_rows = 1 << 30; };
 constexpr int kAllColumns = 1 << 30;
 constexpr ShortLine kShort4[] = {
@@ -1459,9 +1462,7 @@ constexpr ShortLine kShort4[] = {
     {1, 128, 9, 16, kBytes, 400},         {1, 32, 9, 32, kFloat, 100},          {1, 64, 9, kAllColumns, kFloat, 184},
     {65, 128, 9, 16, kFloat, 192, 300},   {65, 128, 17, 32, kFloat, 150},       {1, 64, 17, 32, kBytes, 432},
     {1, 64, 17, kAllColumns, kAny, 600},  {65, 128, 17, kAllColumns, kHalf | kBytes, 352},
-    {129, 192, 17, kAllColumns, kHalf | kWhole, 432},  {129, 192, 17, 48, kBytes | kWhole, 432},  {193, 256, 17, 64, kHalf, 600},
     // up to eight
-    {257, 320, 17, 48, kHalf, 640},       {321, 384, 17, 32, kHalf, 640},       {385, 512, 17, 32, kHalf, 2048},
     {513, 768, 1, 1, kHalf | kRagged, 600},  {513, 768, 1, 1, kBytes | kRagged, 416},  {513, 768, 3, 8, kBytes | kRagged, 640},
     {513, 768, 1, 1, kHalf | kFloat, 1024},  {513, 768, 1, 1, kBytes, 3072},    {769, 1024, 1, 1, kHalf | kFloat, 3072},
     {513, 1024, 2, 2, kFloat, 3072},      {513, 640, 2, 4, kHalf, 3400},        {513, 768, 5, 8, kHalf, 900},
@@ -1480,7 +1481,7 @@ bool short_k(const Plan& p, int64_t k)
     const auto beyond = [&](const ShortLine& l) {
         return k >= l.k_from && k <= l.k_to && p.b >= l.b_from && p.b <= l.b_to && (type & l.types) && rows > (int64_t)l.rows * p.cus &&
                rows <= (int64_t)l.to_rows * p.cus &&
-               (!(l.types & kRagged) || k % kRun != 0) && (!(l.types & kWhole) || k % 64 == 0);
+               (!(l.types & kRagged) || k % kRun != 0);
     };
     if (p.codes8) return std::any_of(std::begin(kShort8), std::end(kShort8), beyond);
     return std::any_of(std::begin(kShort4), std::end(kShort4), beyond);
