@@ -8,6 +8,11 @@ import sys
 
 import pytest
 
+import test_matrix_form_depths
+import test_matrix_form_instances
+import test_matrix_form_tiles
+from test_matrix_form_instances import MAPS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 BODY = """
@@ -15,14 +20,13 @@ import ctypes, json, sys
 rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 rec.rec_kernel.restype = rec.rec_name.restype = ctypes.c_char_p
 from paper_2310_06178_amd import binding as B
-from paper_2310_06178_amd import inputs
 B.load()
-A, E4M3 = 0x10000, [0.0 if v != v else float(v) for v in inputs.fp8_e4m3_values()]
-launched = []
-for m, k, b, x, group, bits, options, ldx in json.load(sys.stdin):
+A, launched = 0x10000, []
+problems, maps = json.load(sys.stdin)
+for m, k, b, x, group, weights, options, ldx in problems:
     scales, y = A if group else None, "i32" if x == "i8" else x
-    if bits == 8:
-        plan = B.msgemm_plan_codes8(m, k, b, x, y, group, A, scales, E4M3, options=options, stream=0)
+    if weights in maps:
+        plan = B.msgemm_plan_codes8(m, k, b, x, y, group, A, scales, maps[weights], options=options, stream=0)
     else:
         plan = B.msgemm_plan(m, k, b, x, y, 2, group, A, scales, options=options, stream=0)
     rec.rec_forget()
@@ -42,8 +46,8 @@ def runtime(tmp_path_factory):
 
 
 def launches(runtime, problems):
-    """Kernels that msgemm_run launches for each (m, k, b, x, scale group[, bits, options, ldx]), and all that the library has."""
-    full = [list(p) + [4, None, 0][len(p) - 5:] for p in problems]
+    """Kernels that msgemm_run launches for each (m, k, b, x, scale group[, weights, options, ldx]), and all that the library has."""
+    full = [list(p) + ["int4", None, 0][len(p) - 5:] for p in problems], {name: values.tolist() for name, values in MAPS.items()}
     p = subprocess.run([sys.executable, "-c", BODY, runtime], cwd=ROOT, input=json.dumps(full), capture_output=True, text=True, timeout=300)
     assert p.returncode == 0, p.stderr[-3000:]
     return json.loads(p.stdout)
@@ -84,6 +88,11 @@ CHOICES = [
     (3072, 3070, 1, "i8", 0, "stream 1/4x8"), (3072, 2178, 1, "i8", 0, "stream 1/4x4"), (3072, 2562, 4, "i8", 0, "stream 1/4x4"),
     (3072, 2816, 2, "i8", 0, "stream 1/4x8"), (3072, 2816, 8, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
     (12288, 3648, 1, "i8", 0, "stream 1/4x2"), (12288, 4096, 1, "i8", 0, "stream 1/4x2"), (12288, 3640, 8, "i8", 0, "stream 1/4x2"),
+    # more than 16 columns: tiles where they fill five eighths of the device or the passes' codes are 80 MiB, tables beyond 2400 rows a compute
+    # unit of a single run; int8 up to 48 columns: the kernel of 16-row tiles from 20 runs on
+    (10304, 512, 20, "f16", 0, "tile 1/1"), (10240, 512, 20, "f16", 0, "stream 2/8x2"), (4200, 14338, 40, "f16", 0, "tile 2/2"), (4200, 10498, 40, "f16", 0, "stream 4/8x2"),
+    (2400 * 256, 128, 17, "bf16", 0, "tile 3/1"), (2400 * 256 + 1, 128, 17, "bf16", 0, "tables"), (2400 * 256 + 1, 256, 17, "f16", 0, "tile 3/1"),
+    (28672, 4096, 24, "i8", 0, "small 2/2"), (28672, 4096, 49, "i8", 0, "tile 2/2"), (28672, 2432, 24, "i8", 0, "tile 2/1"),
 ]
 
 
@@ -91,3 +100,26 @@ def test_own_choice(runtime):
     launched, _ = launches(runtime, [c[:5] for c in CHOICES])
     got = [c[:5] + (short(names[0]),) for c, names in zip(CHOICES, launched)]
     assert got == CHOICES
+
+
+def test_every_instance_is_run_by_a_gpu_test(runtime):
+    """All instances of the matrix form's kernels that the library holds are launched by a problem of test_matrix_form_instances.py."""
+    cases = test_matrix_form_instances.CASES + test_matrix_form_instances.SMALL
+    launched, names = launches(runtime, cases)
+    assert all(run for run in launched)
+    held = {n for n in names if re.search("matrix_(stream|tile|small_tile|reduce)_kernel", n)}
+    assert len(held) > 250
+    assert held - {n for run in launched for n in run} == set()
+
+
+def test_what_the_gpu_tests_of_a_kernel_run(runtime):
+    """The problems that are named after a kernel run in it."""
+    tiles = [(m, k, b, x, group, "int4", dict(o, batched_form=3, rows_per_lane=4), 0) for m, k, b, x, group, o, _ in test_matrix_form_tiles.CASES]
+    assert {short(run[0])[:4] for run in launches(runtime, tiles)[0]} == {"tile"}
+    small = test_matrix_form_instances.SMALL
+    got = [short(run[0]) for run in launches(runtime, small)[0]]
+    assert got[:-3] == ["small %d/%d" % (c[6]["panels_per_workgroup"], 2 if c[2] <= 32 else 3) for c in small[:-3]] and got[-3:] == ["small 2/3", "tile 3/1", "tile 3/1"]
+    assert {short(run[0])[:4] for run in launches(runtime, test_matrix_form_instances.OWN)[0]} == {"tile"}
+    depths = [(m, k, b, x, group, "int4", dict(o, batched_form=3), 0) for m, k, b, x, group, o in test_matrix_form_depths.CASES]
+    got = {short(run[0]) for run in launches(runtime, depths)[0]}
+    assert got >= {"stream 1/16x2", "stream 1/4x4", "stream 1/4x8", "stream 1/4x2", "stream 2/4x4", "stream 4/4x2", "stream 1/8x2"}, got
