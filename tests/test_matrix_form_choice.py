@@ -115,6 +115,7 @@ def test_every_instance_is_run_by_a_gpu_test(runtime):
 def test_what_the_gpu_tests_of_a_kernel_run(runtime):
     """The problems that are named after a kernel run in it."""
     tiles = [(m, k, b, x, group, "int4", dict(o, batched_form=3, rows_per_lane=4), 0) for m, k, b, x, group, o, _ in test_matrix_form_tiles.CASES]
+    tiles += [(m, k, b, "i8", 0) for m, k, b in test_matrix_form_tiles.SHORT8]
     assert {short(run[0])[:4] for run in launches(runtime, tiles)[0]} == {"tile"}
     small = test_matrix_form_instances.SMALL
     got = [short(run[0]) for run in launches(runtime, small)[0]]
