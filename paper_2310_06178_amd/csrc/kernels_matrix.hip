@@ -1514,7 +1514,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // where they do not, until the codes of all passes are many.  us, passes / tile.  Filling: 16384 x 128 x 20 fp16 3.9 / 3.9, x 64 5.8 / 4.6;
     // 11008 x 512 x 20 4.7 / 4.5, x 64 7.1 / 5.5; 14336 x 4096 x 17 13.7 / 12.6; 8192 x 4096 x 72 24.7 / 15.0; 28672 x 4096 x 64 45.9 / 22.1.  Not: 4096 x 4096 x
     // 64 (32 MiB) 8.0 / 13.7, 8192 x 4096 x 64 (64) 13.2 / 14.2, 4096 x 14336 x 48 (84) 19.1 / 18.0, 8192 x 8192 x 48 (96) 26.2 / 19.0; int8 4096 x 14336 x 64
-    // (112) 15.4 / 15.7, 8192 x 8192 x 64 (128) 17.9 / 16.9; 8-bit codes 8192 x 4096 x 20 fp16 (64) 13.4 / 13.9, 8192 x 4096 x 48 (96) 19.7 / 16.2.
+    // (112) 14.6 / 14.7, 8192 x 7168 x 64 (112) 16.0 / 14.8, 8192 x 8192 x 64 (128) 17.5 / 15.9; 8-bit codes 8192 x 4096 x 20 fp16 (64) 13.4 / 13.9, 8192 x 4096 x 48 (96) 19.7 / 16.2.
     // int8 up to 48 columns: a long k keeps the kernel of smaller tiles (28672 x 4096 x 24 14.6 / 15.6, 14000 x 3006 x 33 10.8 / 11.7; 20 runs and more were
     // compared) by its own lines; a short one under few rows does well with passes (16384 x 512 x 20 4.2 / 4.3, 16384 x 1024 x 20 5.3 / 5.1).
     const bool tile_can = p.b > 16 && p.x_dtype != MSGEMM_F32 && k >= kRun &&
@@ -1526,7 +1526,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         runs >= 20 && pass_mib >= (row_groups * 8 > (int64_t)5 * p.cus && p.b >= 10 * small_tiles ? 48 : 112));
     const int64_t tall_passes = p.b <= 32 ? 1 : (p.b + 63) / 64;
     const bool tall = tile_can && !small && (asked && o.rows_per_lane ? o.rows_per_lane == 4 :
-        row_groups * tall_passes * 8 > (int64_t)5 * p.cus ? !narrow8 || runs >= 8 || row_groups > 2 * p.cus : !narrow8 && pass_mib >= (int8 ? 113 : 80));
+        row_groups * tall_passes * 8 > (int64_t)5 * p.cus ? !narrow8 || runs >= 8 || row_groups > 2 * p.cus : !narrow8 && pass_mib >= (int8 ? 112 : 80));
     const bool tile = small || tall;
     const int tile_tiles = small ? small_tiles : p.b <= 32 ? 2 : 4;
     const int64_t tile_passes = (p.b + 16 * tile_tiles - 1) / (16 * tile_tiles);
@@ -1615,8 +1615,10 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
     // 60.9 / 61.5; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
-    // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.6, 4 x 2 9.15, but
-    // 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; 14336 x 4096 x 8 in
+    // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.5, 4 x 2 9.0, 11264 x 4096 x 16 9.1, 8.7, 8960 x 4096 x 16 (140 workgroups) 8.8, 8.5, 11264 x 8192 x 16
+    // 14.8, 14.6, 9216 x 8192 x 16 level, but 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; int8 10240 x 4096 x 16 7.2, 7.3, 13312 x
+    // 4096 x 16 7.6, 7.7, level at 14336; in passes 8192 x 4096 x 32 8.7, 8.3, 4096 x 4096 x 64 8.3, 8.2, but three and more over a long k 4096 x 5376 x 64 9.5, 9.8, 5120 x 8192 x 40
+    // 12.4, 12.7; 14336 x 4096 x 8 in
     // two row tiles, two workgroups a compute unit, 9.0, 8.55; fp32, whose operands of eight
     // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
@@ -1629,8 +1631,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     } else if (bytes) {
         D = compact ? 4 : width == 1 && R == 1 && !f32 ? 4 : 2;
     } else if (!compact) {
-        W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) :
-            (width == 2 ? R == 4 && seg_runs >= 16 && groups(R) * passes * 8 >= 7 * p.cus : R == 2 && per_cu > 1) ? 4 : 8;
+        const bool full = groups(R) * passes * 16 >= (int8 ? 14 : 9) * p.cus && (passes < 3 || seg_runs < 40);
+        W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : (width == 2 ? R == 4 && seg_runs >= 16 && full : R == 2 && per_cu > 1) ? 4 : 8;
     } else if (R == 2) {
         if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 72))) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;

@@ -93,6 +93,13 @@ CHOICES = [
     (10304, 512, 20, "f16", 0, "tile 1/1"), (10240, 512, 20, "f16", 0, "stream 2/8x2"), (4200, 14338, 40, "f16", 0, "tile 2/2"), (4200, 10498, 40, "f16", 0, "stream 4/8x2"),
     (2400 * 256, 128, 17, "bf16", 0, "tile 3/1"), (2400 * 256 + 1, 128, 17, "bf16", 0, "tables"), (2400 * 256 + 1, 256, 17, "f16", 0, "tile 3/1"),
     (28672, 4096, 24, "i8", 0, "small 2/2"), (28672, 4096, 49, "i8", 0, "tile 2/2"), (28672, 2432, 24, "i8", 0, "tile 2/1"),
+    # four row tiles and 16 columns: four wavefronts from nine sixteenths of the compute units on (int8: seven eighths), but not in
+    # three passes and more over a long k
+    (143 * 64, 4096, 16, "f16", 128, "stream 4/8x2"), (144 * 64, 4096, 16, "f16", 128, "stream 4/4x2"), (223 * 64, 4096, 16, "i8", 0, "stream 4/8x2"),
+    (224 * 64, 4096, 16, "i8", 0, "stream 4/4x2"),
+    (8192, 4096, 32, "bf16", 0, "stream 4/4x2"), (4096, 4096, 64, "f16", 128, "stream 4/4x2"), (4096, 5376, 64, "f16", 128, "stream 4/8x2"),
+    # int8, 49 columns and more under few rows: tiles from 112 MiB of codes in all passes on
+    (8192, 7168, 64, "i8", 0, "tile 1/2"), (8192, 7166, 64, "i8", 0, "stream 4/8x2"),
 ]
 
 
