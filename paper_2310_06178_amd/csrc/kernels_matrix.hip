@@ -1603,7 +1603,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   a workgroup per compute unit, 4 x 8 / 16 x 2 / 4 x 4: 4096 x 14336 x 1 fp16 6.9 / 6.7 / 7.6, x 2 with scales 7.3 / 7.2 / 8.0, x 4 7.6 / 7.5 / 7.7, 3072 x 14336 x 1
     //   with scales 6.8 / 6.4 / 7.7, 4096 x 4096 x 2 with scales 4.1 / 3.8 / 3.9; from 160 runs on sixteen wavefronts lose, 4096 x 20480 x 4 9.3 / 9.9, x 8 int8 9.7 / 10.0, 3072 x
     //   40960 x 4 fp16 with scales 16.2 / 17.2, 1792 x 40960 x 1 (two segments) 9.6 / 9.9, but not one or two columns with scales, 3072 x 24576 x 1 fp16 9.6 / 9.2, 3072 x
-    //   22528 x 2 bf16 10.6 / 9.7; under it, 4096 x 18432 x 4 fp16 8.9 / 8.8.  fp32 has them at any length: 4096 x 4096 x 1 5.3 / 4.6 / 4.7, 3072 x 40960 x 4 27.0 / 22.8 / 25.5.
+    //   22528 x 2 bf16 10.6 / 9.7; under it, 4096 x 18432 x 4 fp16 8.9 / 8.8.  Nor do five to eight int8 columns: 4096 x 4096 x 8 4.3 / 4.2 / 3.9, 2560 x 8192 x 8 5.2 / 5.2 / 5.0, 2560 x 14336
+    //   x 8 7.0 / 7.0 / 7.0, 2562 x 15402 x 8 10.2 / 10.9.  fp32 has them at any length: 4096 x 4096 x 1 5.3 / 4.6 / 4.7, 3072 x 40960 x 4 27.0 / 22.8 / 25.5.
     //   A short k, 4 x 8 / 4 x 4 / 4 x 2: 3072 x 1024 x 1 fp16 3.0 / 2.7 / 2.5, int8 2.8 / 2.6 / 2.5, 3072 x 1290 x 1 fp16 3.1 / 2.9 / 3.1, int8 3.6 / 3.3 / 3.7, 3072 x 2048 x 1 fp16
     //   3.3 / 2.9 / 3.2; int8 3072 x 2816 x 1 3.15 / 3.25 / 3.6, x 8 3.5 / 3.4 / 3.7, 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, but 3072 x
     //   2178 x 1 3.2 / 3.1 / 3.5, 3072 x 3330 x 1 level, 3072 x 2562 x 4 (k no multiple of four) 4.2 / 4.0
@@ -1612,7 +1613,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3; 12288 x 4096 x 1 int8 4 x 4 6.5, 4 x 2 6.0, with columns that end inside a 16-byte piece 12288 x 3640 x 1 6.7, 7.1, 9000 x 5900 x 2 8.0, 8.3
     // Two row tiles: 6144 x 6144 x 3 fp16 4 x 4 5.6; in more workgroups 42240 x 6912 x 4 fp16 4 x 4 27.9, 8 x 2 27.5, 13160 x 24704 x 1 bf16 31.7, 30.8, 33792 x
     // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
-    // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
+    // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 32760 x 9900 x 1 (78 runs) 27.1 / 28.4, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
     // 60.9 / 61.5; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
     // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.5, 4 x 2 9.0, 11264 x 4096 x 16 9.1, 8.7, 8960 x 4096 x 16 (140 workgroups) 8.8, 8.5, 11264 x 8192 x 16
@@ -1634,10 +1635,10 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         const bool full = groups(R) * passes * 16 >= (int8 ? 14 : 9) * p.cus && (passes < 3 || seg_runs < 40);
         W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : (width == 2 ? R == 4 && seg_runs >= 16 && full : R == 2 && per_cu > 1) ? 4 : 8;
     } else if (R == 2) {
-        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 72))) D = 4;
+        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80))) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
-        if (per_cu == 1 && seg_runs >= 32 && (f32 || seg_runs < 160 || (scaled && p.b <= 2))) W = 16;
+        if (per_cu == 1 && seg_runs >= 32 && (f32 || seg_runs < 160 || (scaled && p.b <= 2)) && p.b <= 4) W = 16;
         else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
         else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 26 && few8) D = 8;
         else if (seg_runs >= (per_cu > 2 ? (few8 && k % 16 != 0 ? 28 : 48) : f32 ? 16 : 11)) D = 4;

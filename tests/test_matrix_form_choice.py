@@ -67,9 +67,9 @@ def short(name):
 
 # m, k, b, type of X, scale block, kernel
 CHOICES = [
-    # int8, two row tiles: rings of four in four wavefronts, unless three workgroups and more have 72 runs and more each
+    # int8, two row tiles: rings of four in four wavefronts, unless three workgroups and more have 80 runs and more each
     (14848, 10240, 1, "i8", 0, "stream 2/4x4"), (14848, 40192, 1, "i8", 0, "stream 2/4x4"), (19847, 6744, 4, "i8", 0, "stream 2/4x4"),
-    (37725, 6744, 8, "i8", 0, "stream 2/4x4"), (26000, 9088, 1, "i8", 0, "stream 2/4x4"), (26000, 9216, 1, "i8", 0, "stream 2/8x2"),
+    (37725, 6744, 8, "i8", 0, "stream 2/4x4"), (32760, 9900, 1, "i8", 0, "stream 2/4x4"), (26000, 10240, 1, "i8", 0, "stream 2/8x2"),
     # 16 bits: one row tile where that takes the busiest compute unit fewer row tiles, and for one column under four workgroups a compute unit
     # or a short stream also where it takes as many
     (11008, 4860, 1, "f16", 0, "stream 1/4x2"), (18097, 8192, 2, "f16", 128, "stream 1/4x4"), (33280, 8192, 1, "bf16", 0, "stream 1/4x4"),
@@ -77,10 +77,12 @@ CHOICES = [
     (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
     (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
     (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (7043, 2176, 3, "f16", 128, "stream 2/4x4"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
-    # a workgroup per compute unit: sixteen wavefronts from 32 runs up to 160, and beyond for fp32 and one or two columns with scales
+    # a workgroup per compute unit: sixteen wavefronts from 32 runs up to 160, and beyond for fp32 and one or two columns with scales; not
+    # for five to eight int8 columns
     (4096, 14336, 2, "f16", 128, "stream 1/16x2"), (4096, 20352, 4, "f16", 0, "stream 1/16x2"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"),
     (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (4096, 20480, 8, "i8", 0, "stream 1/4x8"),
     (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"), (4096, 4096, 1, "i8", 0, "stream 1/16x2"),
+    (4096, 4096, 8, "i8", 0, "stream 1/4x4"), (2562, 15402, 8, "i8", 0, "stream 1/4x8"), (2562, 15402, 4, "i8", 0, "stream 1/16x2"),
     # a short k: rings of two up to ten runs; int8 in few columns keeps more in flight from 20 to 25 runs, and under three workgroups where
     # columns end inside a 16-byte piece
     (3072, 1280, 1, "f16", 0, "stream 1/4x2"), (3072, 1290, 1, "f16", 0, "stream 1/4x4"), (3072, 1290, 8, "i8", 0, "stream 1/4x4"),

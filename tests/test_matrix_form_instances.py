@@ -40,7 +40,7 @@ def _cases():
             # more than one workgroup a compute unit (256 of them): segments make them out of few rows
             segments = dict(panels_per_workgroup=2, batched_segments=8)
             if x == "i8":
-                add(2070, 8 * 72, 1, x, scaled, **segments)
+                add(2070, 8 * 80, 1, x, scaled, **segments)
             else:
                 add(1050, 8 * 6, 3, x, scaled, **segments)
                 if x != "f32":
