@@ -1364,7 +1364,7 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
         MSGEMM_CASE(2, 0, 4, 2)
     }
     if constexpr (sizeof(XT) != 4) {
-        MSGEMM_CASE(2, 0, 8, 2) MSGEMM_CASE(1, 0, 4, 8)
+        MSGEMM_CASE(2, 0, 8, 2) MSGEMM_CASE(1, 0, 4, 8) MSGEMM_CASE(1, 0, 8, 4)
     } else {
         MSGEMM_CASE(4, 2, 4, 2) MSGEMM_CASE(1, 2, 4, 2)
         MSGEMM_CASE(2, 4, 4, 2) MSGEMM_CASE(1, 4, 4, 2)
@@ -1597,14 +1597,17 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // level at 2048 x 12288, 12 runs a wavefront)
     if (p.x_dtype == MSGEMM_F32 && p.b == 1 && !bytes && segments > 1 && runs > segments * waves(R) * 12 && !asked && !anyway) return false;
     if (asked && o.batched_segments) segments = o.batched_segments < runs ? o.batched_segments : runs;
-    // Streaming kernel, wavefronts and depth of their rings: what keeps the memory busy is some 32 KiB of codes in flight per compute
-    // unit (its share of 6.3 TB/s times a microsecond's trip); more only queues, and an unrolled loop that is gone through once or twice
-    // is fetched for nothing.  us, "wavefronts x depth", one column or a few and one row tile:
-    //   a workgroup per compute unit, 4 x 8 / 16 x 2 / 4 x 4: 4096 x 14336 x 1 fp16 6.9 / 6.7 / 7.6, x 2 with scales 7.3 / 7.2 / 8.0, x 4 7.6 / 7.5 / 7.7, 3072 x 14336 x 1
-    //   with scales 6.8 / 6.4 / 7.7, 4096 x 4096 x 2 with scales 4.1 / 3.8 / 3.9; from 160 runs on sixteen wavefronts lose, 4096 x 20480 x 4 9.3 / 9.9, x 8 int8 9.7 / 10.0, 3072 x
-    //   40960 x 4 fp16 with scales 16.2 / 17.2, 1792 x 40960 x 1 (two segments) 9.6 / 9.9, but not one or two columns with scales, 3072 x 24576 x 1 fp16 9.6 / 9.2, 3072 x
-    //   22528 x 2 bf16 10.6 / 9.7; under it, 4096 x 18432 x 4 fp16 8.9 / 8.8.  Nor do five to eight int8 columns: 4096 x 4096 x 8 4.3 / 4.2 / 3.9, 2560 x 8192 x 8 5.2 / 5.2 / 5.0, 2560 x 14336
-    //   x 8 7.0 / 7.0 / 7.0, 2562 x 15402 x 8 10.2 / 10.9.  fp32 has them at any length: 4096 x 4096 x 1 5.3 / 4.6 / 4.7, 3072 x 40960 x 4 27.0 / 22.8 / 25.5.
+    // Streaming kernel, wavefronts and depth of their rings.  A compute unit's share of 6.3 TB/s over a trip of a microsecond is 24 KiB of codes; the forms
+    // chosen have 16 (a short k: an unrolled loop that is gone through once or twice is fetched for nothing) to 64 KiB in flight, 32 where there is one
+    // workgroup of one row tile and a long k.  us, "wavefronts x depth", one column or a few and one row tile:
+    //   a workgroup per compute unit, 4 x 8 / 8 x 4 / 16 x 2 (a wavefront short of a whole ring asks for less, so which is ahead changes with the
+    //   length: the lines follow 21 lengths of 32 to 158 runs and more beyond).  fp16 7.61 / 7.28 / 7.41 at 4096 x 14336 x 1, 8.74 / 8.48 / 8.67 at 18432; 4096 x 7168 x 1 5.22 / 4.92 /
+    //   4.94, 3072 x 7168 x 2 4.86 / 4.58 / 4.50; rings that come out even, 4096 x 8192 x 1 5.20 / 5.23 / 5.40, 3072 x 12288 x 2 6.07 / 6.13 / 6.22; 4096 x 24576 x 4 11.9 / 12.1 / 12.3.  fp16 with
+    //   scales: 4096 x 4096 x 1 4.11 / 3.98 / 3.82, 4096 x 14336 x 2 7.33 / 7.17 / 7.21, 4096 x 14336 x 1 7.92 / 7.52 / 7.65, x 4 8.45 / 8.52 / 8.58, 4096 x 18432 x 4 10.0 / 10.2 / 10.5, 3072 x 40960 x 2
+    //   16.6 / 16.2 / 16.3.  bf16 with scales: 3072 x 11264 x 2 6.79 / 6.38 / 6.05, 4096 x 40960 x 1 18.5 / 17.9 / 18.0.  int8, columns of whole 16-byte pieces: 4096 x 3328 x 1 3.54 / 3.39 / 3.58, 4096 x
+    //   5904 x 1 5.33 / 5.29 / 5.09, 4096 x
+    //   7168 x 1 4.80 / 4.72 / 4.86, 3864 x 14336 x 3 7.21 / 6.79 / 6.64; others: 3072 x 7382 x 2 6.62 / 6.78 / 7.43, 3864 x 11940 x 3 7.43 / 7.82 / 7.75, 4096 x 11942 x 4 9.2 / 9.6 / 10.8, 3072 x 4996 x 2 4.11 / 4.12 / 4.02.  Five to eight int8 columns: 4 x 8 / 4 x 4 4096 x
+    //   4096 x 8 4.3 / 3.9, 2560 x 14336 x 8 level.  fp32 4 x 8 / 4 x 4 / 16 x 2: 4096 x 4096 x 1 5.3 / 4.7 / 4.6, 3072 x 40960 x 4 27.0 / 25.5 / 22.8.
     //   A short k, 4 x 8 / 4 x 4 / 4 x 2: 3072 x 1024 x 1 fp16 3.0 / 2.7 / 2.5, int8 2.8 / 2.6 / 2.5, 3072 x 1290 x 1 fp16 3.1 / 2.9 / 3.1, int8 3.6 / 3.3 / 3.7, 3072 x 2048 x 1 fp16
     //   3.3 / 2.9 / 3.2; int8 3072 x 2816 x 1 3.15 / 3.25 / 3.6, x 8 3.5 / 3.4 / 3.7, 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, but 3072 x
     //   2178 x 1 3.2 / 3.1 / 3.5, 3072 x 3330 x 1 level, 3072 x 2562 x 4 (k no multiple of four) 4.2 / 4.0
@@ -1638,8 +1641,18 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80))) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
-        if (per_cu == 1 && seg_runs >= 32 && (f32 || seg_runs < 160 || (scaled && p.b <= 2)) && p.b <= 4) W = 16;
-        else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
+        const bool bf16 = p.x_dtype == MSGEMM_BF16, pieces = k % 16 == 0;
+        const int64_t end = f32 || (scaled && p.b <= 2) ? runs + 1 : 160;
+        if (per_cu == 1 && int8 && p.b <= 4 && seg_runs >= (pieces ? 26 : 32) && seg_runs < end) {
+            if (seg_runs > 32 && seg_runs < 50) W = 16;
+            else if (pieces) W = 8, D = 4;
+            else D = 8;
+        } else if (per_cu == 1 && !int8 && seg_runs >= 32 && seg_runs < end) {
+            const bool wide = bf16 && scaled ? p.b > 1 || seg_runs < 160 : seg_runs < 92 && (scaled || seg_runs % 32 != 0);
+            if (f32 || wide) W = 16;
+            else if (scaled && p.b > 2 && seg_runs >= 108) D = 8;
+            else W = 8, D = 4;
+        } else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
         else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 26 && few8) D = 8;
         else if (seg_runs >= (per_cu > 2 ? (few8 && k % 16 != 0 ? 28 : 48) : f32 ? 16 : 11)) D = 4;
     }

@@ -77,12 +77,20 @@ CHOICES = [
     (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
     (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
     (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (7043, 2176, 3, "f16", 128, "stream 2/4x4"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
-    # a workgroup per compute unit: sixteen wavefronts from 32 runs up to 160, and beyond for fp32 and one or two columns with scales; not
-    # for five to eight int8 columns
-    (4096, 14336, 2, "f16", 128, "stream 1/16x2"), (4096, 20352, 4, "f16", 0, "stream 1/16x2"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"),
-    (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (4096, 20480, 8, "i8", 0, "stream 1/4x8"),
-    (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"), (4096, 4096, 1, "i8", 0, "stream 1/16x2"),
-    (4096, 4096, 8, "i8", 0, "stream 1/4x4"), (2562, 15402, 8, "i8", 0, "stream 1/4x8"), (2562, 15402, 4, "i8", 0, "stream 1/16x2"),
+    # a workgroup per compute unit: sixteen wavefronts from 32 runs on, eight from 92 on and where an unscaled k is whole turns of their rings, four
+    # beyond 160 (fp16 with scales and more than two columns: 108); fp32, and bf16 with scales up to 160 or in two columns, sixteen
+    (4096, 14336, 2, "f16", 128, "stream 1/8x4"), (4096, 11520, 2, "f16", 128, "stream 1/16x2"), (4096, 11776, 1, "bf16", 0, "stream 1/8x4"), (4096, 11648, 1, "bf16", 0, "stream 1/16x2"),
+    (4096, 8192, 1, "f16", 0, "stream 1/8x4"), (4096, 8064, 1, "f16", 0, "stream 1/16x2"), (4096, 8192, 1, "f16", 128, "stream 1/16x2"), (4096, 3968, 1, "f16", 0, "stream 1/4x4"),
+    (4096, 13696, 4, "f16", 128, "stream 1/8x4"), (4096, 13824, 4, "f16", 128, "stream 1/4x8"), (4096, 16384, 4, "f16", 128, "stream 1/4x8"),
+    (4096, 20352, 4, "f16", 0, "stream 1/8x4"), (4096, 20480, 4, "f16", 0, "stream 1/4x8"), (3072, 40960, 3, "f16", 128, "stream 1/4x8"), (3072, 40960, 2, "f16", 128, "stream 1/8x4"),
+    (3072, 24576, 2, "bf16", 128, "stream 1/16x2"), (3072, 24576, 1, "bf16", 128, "stream 1/8x4"), (3072, 20352, 3, "bf16", 128, "stream 1/16x2"), (3072, 20480, 3, "bf16", 128, "stream 1/4x8"),
+    (4096, 40960, 4, "f32", 0, "stream 1/16x2"), (1792, 40960, 1, "f16", 0, "stream 1/4x8"),
+    # int8 in few columns: sixteen wavefronts from 33 runs to 49, else eight from 26 runs up to 160 where columns are whole 16-byte pieces, and four with
+    # rings of eight where they are not
+    (4096, 4096, 1, "i8", 0, "stream 1/8x4"), (4096, 3328, 1, "i8", 0, "stream 1/8x4"), (4096, 4352, 2, "i8", 0, "stream 1/16x2"), (4096, 6400, 2, "i8", 0, "stream 1/8x4"),
+    (4096, 20352, 4, "i8", 0, "stream 1/8x4"), (4096, 20480, 4, "i8", 0, "stream 1/4x8"), (2562, 15402, 4, "i8", 0, "stream 1/4x8"), (4096, 4100, 1, "i8", 0, "stream 1/16x2"),
+    (4096, 4092, 1, "i8", 0, "stream 1/4x8"), (4096, 3844, 2, "i8", 0, "stream 1/4x4"), (4096, 6276, 1, "i8", 0, "stream 1/4x8"),
+    (4096, 20480, 8, "i8", 0, "stream 1/4x8"), (4096, 4096, 8, "i8", 0, "stream 1/4x4"), (2562, 15402, 8, "i8", 0, "stream 1/4x8"),
     # a short k: rings of two up to ten runs; int8 in few columns keeps more in flight from 20 to 25 runs, and under three workgroups where
     # columns end inside a 16-byte piece
     (3072, 1280, 1, "f16", 0, "stream 1/4x2"), (3072, 1290, 1, "f16", 0, "stream 1/4x4"), (3072, 1290, 8, "i8", 0, "stream 1/4x4"),

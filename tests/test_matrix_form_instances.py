@@ -26,13 +26,15 @@ def _cases():
     def add(m, runs, b, x, scaled, weights="int4", ldx=0, **options):
         if scaled and x == "i8":
             return
-        k = runs * RUN if scaled else runs * RUN + 2     # (unscaled: a ragged run of two columns behind the full ones)
+        k = runs * RUN if scaled else runs * RUN + (16 if x == "i8" and runs == 97 else 2)   # (unscaled: a ragged run of a few columns behind the full ones)
         cases.append((m, k, b, x, RUN if scaled else 0, weights, dict(options, batched_form=3), ldx))
 
     for x in ("f16", "bf16", "f32", "i8"):
         for scaled in (False, True):
             for runs in (5, 17, 34):                     # one row tile: rings of two, of four, sixteen wavefronts
                 add(33, runs, 1, x, scaled, panels_per_workgroup=1)
+            if x != "f32":                               # ... eight wavefronts (int8: of whole 16-byte pieces)
+                add(33, 161 if x == "bf16" and scaled else 97, 1, x, scaled, panels_per_workgroup=1, batched_segments=1)
             if x != "f32":
                 add(33, 161, 3, x, scaled, panels_per_workgroup=1, batched_segments=1)      # ... rings of eight
             add(65, 9, 2, x, scaled, panels_per_workgroup=2)            # two and four row tiles
