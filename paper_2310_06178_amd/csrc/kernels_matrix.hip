@@ -639,8 +639,8 @@ matrix_stream_kernel(MatrixArgs a)
     }
 }
 
-// Tile kernel for int8 activations, a long k and up to 48 columns: the larger tiles of the kernel below have too little to do between its
-// meetings there (8 steps of a microsecond and a half, 28672 x 4096 x 24: 15.6 us against 14.6).  A workgroup owns 64 R rows (four wavefronts of
+// Tile kernel for int8 activations and a long k, up to 48 columns and, over a longer one, 64: the larger tiles of the kernel below have too little to do
+// between its meetings there (8 steps of a microsecond and a half, 28672 x 4096 x 24: 15.6 us against 14.6).  A workgroup owns 64 R rows (four wavefronts of
 // R row tiles) for all of k, or a segment of it, and up to 16 NT columns: two groups of four wavefronts take alternate runs, and the wavefronts
 // of a group share the run's activations, staged in LDS in the streaming kernel's operand slots.  Activations and codes are requested five
 // to six steps ahead (registers; three more steps in LDS): loads return in order, so a wait for activations is a wait for every code requested
@@ -1338,6 +1338,7 @@ int launch_small_tile(const Plan& p, const MatrixArgs& a, hipStream_t s)
 #define MSGEMM_CASE(RR, NN) \
     if (p.mx_r == RR && p.mx_cols == NN) return launch_small<RR, NN>(p, a, s);
     MSGEMM_CASE(1, 2) MSGEMM_CASE(2, 2) MSGEMM_CASE(3, 2) MSGEMM_CASE(1, 3) MSGEMM_CASE(2, 3) MSGEMM_CASE(3, 3)
+    MSGEMM_CASE(1, 4) MSGEMM_CASE(2, 4) MSGEMM_CASE(3, 4)
 #undef MSGEMM_CASE
     return MSGEMM_ERR_UNSUPPORTED;
 }
@@ -1659,7 +1660,11 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     p.mx_depth = D;
     p.mx_tile_kernel = tile;
     p.mx_r = R;
-    p.mx_tall = tall;
+    // (int8, more than 48 columns: from 66 runs a segment the kernel of smaller tiles is ahead, whose wavefronts along k are fewer; in passes only where the
+    // workgroups leave compute units idle in their last round.  us, smaller / larger: 27648 x 10752 x 50 36.2 / 40.7, x 64 38.8 / 40.4, 36864 x 9216 x 50 40.2 / 42.9, 49152 x 12288 x 64
+    // 60.8 / 62.6, 16384 x 20480 x 50 (two segments of 80) 42.4 / 44.1; 27648 x 8192 x 50 32.5 / 31.4, x 4096 19.3 / 17.9, 12288 x 20480 x 64 (four of 40) 38.7 / 36.8; two passes, 36864 x
+    // 10752 x 80 (384 workgroups) 74.1 / 79.9, 27648 x 10752 x 100 59.8 / 63.2, three, 28672 x 9216 x 150 (450) 66.5 / 69.8, 16384 x 14336 x 80 (256) 45.5 / 44.6, 49152 x 10752 x 80 (512) 93.8 / 90.8)
+    p.mx_tall = tall && !(int8 && p.b > 48 && seg_runs >= 66 && (passes == 1 || groups(R) * passes * segments * 16 <= 15 * p.cus * per_cu));
     p.mx_row_waves = p.mx_tall ? kTileRowWaves : Wr;
     p.mx_waves = W;
     p.mx_segments = (int)segments;

@@ -85,7 +85,7 @@ struct Plan {
     // matrix form (kernels_matrix.hip): codes_tiled and scales_ordered hold its own orders
     bool matrix;
     bool mx_tile_kernel;  // the tile kernel (more than 16 columns), else the streaming kernel
-    bool mx_tall;         // ... of tiles of 32 rows (else 16: int8, up to 48 columns, a long k)
+    bool mx_tall;         // ... of tiles of 32 rows (else 16: int8, up to 64 columns, a long k)
     int mx_r;             // row tiles per wavefront
     int mx_row_waves;     // wavefronts side by side in rows
     int mx_waves;         // wavefronts per workgroup

@@ -99,10 +99,13 @@ CHOICES = [
     (3072, 2816, 2, "i8", 0, "stream 1/4x8"), (3072, 2816, 8, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
     (12288, 3648, 1, "i8", 0, "stream 1/4x2"), (12288, 4096, 1, "i8", 0, "stream 1/4x2"), (12288, 3640, 8, "i8", 0, "stream 1/4x2"),
     # more than 16 columns: tiles where they fill five eighths of the device or the passes' codes are 80 MiB, tables beyond 2400 rows a compute
-    # unit of a single run; int8 up to 48 columns: the kernel of 16-row tiles from 20 runs on
+    # unit of a single run; int8 up to 48 columns: the kernel of 16-row tiles from 20 runs on, up to
+    # 64 from 66 on
     (10304, 512, 20, "f16", 0, "tile 1/1"), (10240, 512, 20, "f16", 0, "stream 2/8x2"), (4200, 14338, 40, "f16", 0, "tile 2/2"), (4200, 10498, 40, "f16", 0, "stream 4/8x2"),
     (2400 * 256, 128, 17, "bf16", 0, "tile 3/1"), (2400 * 256 + 1, 128, 17, "bf16", 0, "tables"), (2400 * 256 + 1, 256, 17, "f16", 0, "tile 3/1"),
-    (28672, 4096, 24, "i8", 0, "small 2/2"), (28672, 4096, 49, "i8", 0, "tile 2/2"), (28672, 2432, 24, "i8", 0, "tile 2/1"),
+    (28672, 4096, 24, "i8", 0, "small 2/2"), (28672, 4096, 49, "i8", 0, "tile 2/2"), (27648, 10752, 50, "i8", 0, "small 2/4"), (27648, 8450, 64, "i8", 0, "small 2/4"),
+    (27648, 8320, 64, "i8", 0, "tile 2/2"), (36864, 10752, 80, "i8", 0, "small 3/4"), (16384, 14336, 80, "i8", 0, "tile 2/2"), (49152, 10752, 100, "i8", 0, "tile 3/2"), (16384, 10752, 64, "i8", 0, "tile 2/2"), (16384, 20480, 64, "i8", 0, "small 2/4"),
+    (28672, 2432, 24, "i8", 0, "tile 2/1"),
     # four row tiles and 16 columns: four wavefronts from nine sixteenths of the compute units on (int8: seven eighths), but not in
     # three passes and more over a long k
     (143 * 64, 4096, 16, "f16", 128, "stream 4/8x2"), (144 * 64, 4096, 16, "f16", 128, "stream 4/4x2"), (223 * 64, 4096, 16, "i8", 0, "stream 4/8x2"),
@@ -136,7 +139,7 @@ def test_what_the_gpu_tests_of_a_kernel_run(runtime):
     assert {short(run[0])[:4] for run in launches(runtime, tiles)[0]} == {"tile"}
     small = test_matrix_form_instances.SMALL
     got = [short(run[0]) for run in launches(runtime, small)[0]]
-    assert got[:-3] == ["small %d/%d" % (c[6]["panels_per_workgroup"], 2 if c[2] <= 32 else 3) for c in small[:-3]] and got[-3:] == ["small 2/3", "tile 3/1", "tile 3/1"]
+    assert got[:-3] == ["small %d/%d" % (c[6]["panels_per_workgroup"], (c[2] + 15) // 16) for c in small[:-3]] and got[-3:] == ["small 2/3", "tile 3/1", "tile 3/1"]
     assert {short(run[0])[:4] for run in launches(runtime, test_matrix_form_instances.OWN)[0]} == {"tile"}
     depths = [(m, k, b, x, group, "int4", dict(o, batched_form=3), 0) for m, k, b, x, group, o in test_matrix_form_depths.CASES]
     got = {short(run[0]) for run in launches(runtime, depths)[0]}

@@ -84,9 +84,11 @@ def _cases():
 
 
 CASES = _cases()
-# int8, 17 to 48 columns: the tile kernel of 16-row tiles over the lengths it is chosen for, rings that wrap, segments; and its own choice of the larger one
+# int8, 17 to 64 columns: the tile kernel of 16-row tiles over the lengths it is chosen for, rings that wrap, segments; and its own choice of the larger one
 SMALL = [(m, runs * RUN + 2, b, "i8", 0, "int4", dict(o, batched_form=3, rows_per_lane=4, panels_per_workgroup=r), 0)
          for r in (1, 2, 3) for b in (17, 32, 33, 48) for m, runs, o in ((70, 27, {}), (200, 40, {"batched_segments": 2}))]
+SMALL += [(m, runs * RUN + 2, b, "i8", 0, "int4", dict(o, batched_form=3, rows_per_lane=4, panels_per_workgroup=r), 0)
+          for r in (1, 2, 3) for b in (49, 64) for m, runs, o in ((70, 67, {"batched_segments": 1}), (200, 133, {"batched_segments": 2}))]
 SMALL += [(11008, 5126, 40, "i8", 0, "int4", None, 0), (33000, 130, 32, "i8", 0, "int4", None, 0), (33000, 386, 20, "i8", 0, "int4", None, 0)]
 # the tile kernel by the library's own choice
 OWN = [(4200, 14338, 40, "f16", 0, "int4", None, 0), (11008, 512, 64, "bf16", 128, "int4", None, 0), (16384, 130, 20, "f16", 0, "int4", None, 0),
