@@ -59,6 +59,7 @@ def _cases():
                 if x == "f32":
                     add(70, 3, 12, x, scaled, panels_per_workgroup=r)
             if x != "f32":
+                add(70, 81, 20, x, scaled, panels_per_workgroup=2, rows_per_lane=8, batched_segments=1)     # two passes over a long k
                 add(3584, 17, 60, x, scaled, panels_per_workgroup=4, rows_per_lane=8)   # four passes that fill the compute units
     for weights in MAPS:
         for x in ("f16", "bf16", "f32"):
