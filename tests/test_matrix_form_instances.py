@@ -43,6 +43,7 @@ def _cases():
             segments = dict(panels_per_workgroup=2, batched_segments=8)
             if x == "i8":
                 add(2070, 8 * 80, 1, x, scaled, **segments)
+                add(1050, 8 * 3, 13, x, scaled, **segments)
             else:
                 add(1050, 8 * 6, 3, x, scaled, **segments)
                 if x != "f32":
