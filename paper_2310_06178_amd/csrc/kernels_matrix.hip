@@ -1616,8 +1616,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   7168 x 1 4.80 / 4.72 / 4.86, 3864 x 14336 x 3 7.21 / 6.79 / 6.64; others: 3072 x 7382 x 2 6.62 / 6.78 / 7.43, 3864 x 11940 x 3 7.43 / 7.82 / 7.75, 4096 x 11942 x 4 9.2 / 9.6 / 10.8, 3072 x 4996 x 2 4.11 / 4.12 / 4.02.  Five to eight int8 columns: 4 x 8 / 4 x 4 4096 x
     //   4096 x 8 4.3 / 3.9, 2560 x 14336 x 8 level.  fp32 4 x 8 / 4 x 4 / 16 x 2: 4096 x 4096 x 1 5.3 / 4.7 / 4.6, 3072 x 40960 x 4 27.0 / 25.5 / 22.8.
     //   A short k, 4 x 8 / 4 x 4 / 4 x 2: 3072 x 1024 x 1 fp16 3.0 / 2.7 / 2.5, int8 2.8 / 2.6 / 2.5, 3072 x 1290 x 1 fp16 3.1 / 2.9 / 3.1, int8 3.6 / 3.3 / 3.7, 3072 x 2048 x 1 fp16
-    //   3.3 / 2.9 / 3.2; int8 3072 x 2816 x 1 3.15 / 3.25 / 3.6, x 8 3.5 / 3.4 / 3.7, 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, but 3072 x
-    //   2178 x 1 3.2 / 3.1 / 3.5, 3072 x 3330 x 1 level, 3072 x 2562 x 4 (k no multiple of four) 4.2 / 4.0
+    //   3.3 / 2.9 / 3.2; int8 3072 x 2816 x 1 3.15 / 3.25 / 3.6, x 8 3.5 / 3.4 / 3.7, 3072 x 2580 x 1 3.9 / 4.3 / 5.0, 3072 x 3070 x 1 4.0 / 4.4 / 5.1, 3072 x 2820 x 4 3.6 / 3.8 / 4.2, 3072 x 3334 x
+    //   1 3.8 / 4.0, 3072 x 3596 x 2 4.2 / 4.6, 3072 x 3686 x 3 4.4 / 4.7, but 3072 x 2178 x 1 3.2 / 3.1 / 3.5, 3072 x 3334 x 4 (k no multiple of four) 4.3 / 4.2
     //   two: 8192 x 8192 x 1 bf16 4 x 8 9.1, 4 x 4 8.4; 8192 x 14336 x 1 fp16 11.8, 11.4
     //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
     //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3; 12288 x 4096 x 1 int8 4 x 4 6.5, 4 x 2 6.0, with columns that end inside a 16-byte piece 12288 x 3640 x 1 6.7, 7.1, 9000 x 5900 x 2 8.0, 8.3
@@ -1636,8 +1636,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
     const bool f32 = p.x_dtype == MSGEMM_F32;
-    // (int8, one column, or up to four at addresses that are multiples of four: others are bound by the loads of the activations themselves)
-    const bool few8 = int8 && p.b <= 4 && (p.b == 1 || k % 4 == 0);
+    // (int8, one or three columns, or up to four at addresses that are multiples of four: others are bound by the loads of the activations themselves)
+    const bool few8 = int8 && p.b <= 4 && (p.b % 2 == 1 || k % 4 == 0);
     int W = 4, D = 2;
     if (tile) {
         W = 8;
@@ -1664,7 +1664,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
             else if (scaled && p.b > 2 && seg_runs >= 108) D = 8;
             else W = 8, D = 4;
         } else if (seg_runs >= (int8 ? 80 : 128) && !f32) D = 8;
-        else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 26 && few8) D = 8;
+        else if (per_cu == 1 && seg_runs >= 20 && seg_runs < 32 && few8) D = 8;
         else if (seg_runs >= (per_cu > 2 ? (few8 && k % 16 != 0 ? 28 : 48) : f32 ? 16 : 11)) D = 4;
     }
     p.mx_depth = D;

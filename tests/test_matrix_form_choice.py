@@ -89,14 +89,15 @@ CHOICES = [
     # rings of eight where they are not
     (4096, 4096, 1, "i8", 0, "stream 1/8x4"), (4096, 3328, 1, "i8", 0, "stream 1/8x4"), (4096, 4352, 2, "i8", 0, "stream 1/16x2"), (4096, 6400, 2, "i8", 0, "stream 1/8x4"),
     (4096, 20352, 4, "i8", 0, "stream 1/8x4"), (4096, 20480, 4, "i8", 0, "stream 1/4x8"), (2562, 15402, 4, "i8", 0, "stream 1/4x8"), (4096, 4100, 1, "i8", 0, "stream 1/16x2"),
-    (4096, 4092, 1, "i8", 0, "stream 1/4x8"), (4096, 3844, 2, "i8", 0, "stream 1/4x4"), (4096, 6276, 1, "i8", 0, "stream 1/4x8"),
+    (4096, 4092, 1, "i8", 0, "stream 1/4x8"), (4096, 3844, 2, "i8", 0, "stream 1/4x8"), (4096, 6276, 1, "i8", 0, "stream 1/4x8"),
     (4096, 20480, 8, "i8", 0, "stream 1/4x8"), (4096, 4096, 8, "i8", 0, "stream 1/4x4"), (2562, 15402, 8, "i8", 0, "stream 1/4x8"),
-    # a short k: rings of two up to ten runs; int8 in few columns keeps more in flight from 20 to 25 runs, and under three workgroups where
+    # a short k: rings of two up to ten runs; int8 in few columns keeps more in flight from 20 to 31 runs (25 in whole pieces), and under three workgroups where
     # columns end inside a 16-byte piece
     (3072, 1280, 1, "f16", 0, "stream 1/4x2"), (3072, 1290, 1, "f16", 0, "stream 1/4x4"), (3072, 1290, 8, "i8", 0, "stream 1/4x4"),
     (3072, 1290, 1, "f32", 0, "stream 1/4x2"), (3072, 2580, 1, "i8", 0, "stream 1/4x8"), (3072, 2820, 4, "i8", 0, "stream 1/4x8"),
     (3072, 3070, 1, "i8", 0, "stream 1/4x8"), (3072, 2178, 1, "i8", 0, "stream 1/4x4"), (3072, 2562, 4, "i8", 0, "stream 1/4x4"),
-    (3072, 2816, 2, "i8", 0, "stream 1/4x8"), (3072, 2816, 8, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x4"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
+    (3072, 2816, 2, "i8", 0, "stream 1/4x8"), (3072, 2816, 8, "i8", 0, "stream 1/4x4"), (3072, 3330, 1, "i8", 0, "stream 1/4x8"), (512, 3686, 3, "i8", 0, "stream 1/4x8"), (3072, 3334, 4, "i8", 0, "stream 1/4x4"),
+    (3072, 3596, 2, "i8", 0, "stream 1/4x8"), (12288, 3640, 1, "i8", 0, "stream 1/4x4"),
     (12288, 3648, 1, "i8", 0, "stream 1/4x2"), (12288, 4096, 1, "i8", 0, "stream 1/4x2"), (12288, 3640, 8, "i8", 0, "stream 1/4x2"),
     # more than 16 columns: tiles where they fill five eighths of the device or the passes' codes are 80 MiB, tables beyond 2400 rows a compute
     # unit of a single run; int8 up to 48 columns: the kernel of 16-row tiles from 20 runs on, up to
