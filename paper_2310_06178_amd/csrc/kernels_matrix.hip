@@ -854,8 +854,8 @@ matrix_small_tile_kernel(MatrixArgs a)
 //     registers 91 us instead of 79), and no wavefront asks for much at once: the next step's activations in the first half of a step, then
 //     the codes of the step after it, which come from memory and have a step more to arrive.
 //   * One meeting of the wavefronts a step, behind it.  Ahead of the last products of a step: level.
-// Measured, us: 49152 x 12288 x 64 fp16 77 to 82 = 0.94 to 1.0 Pflop/s (tiles of 16 rows with activations through registers 87 to 89), 28672 x 8192 x 64 bf16 with
-// scales 41 to 44 (51 to 52), 16384 x 4096 x 64 15.6 (21), 14336 x 4096 x 32 12.6 (14.3), 28672 x 4096 x 64 int8 18.6 (20.9), 28672 x 8192 x 64 fp16 with
+// Measured, us: 49152 x 12288 x 64 fp16 77 to 86 on different cards = 0.9 to 1.0 Pflop/s (tiles of 16 rows with activations through registers 87 to 93), 28672 x 8192 x 64
+// bf16 with scales 41 to 45 (52 to 59), 16384 x 4096 x 64 15.6 to 16.2 (21), 14336 x 4096 x 32 12.6 (14.3), 28672 x 4096 x 64 int8 18.6 (20.9), 28672 x 8192 x 64 fp16 with
 // E4M3 codes 48 (passes of the streaming kernel 161), 25856 x 6144 x 24 29.5 (53).  Level or slower: wavefronts of
 // different priority, an interleaving of products and decoding laid down by hand.
 // 32 x 32 products, sixteen (int8: 32) columns of k at a time
@@ -1470,7 +1470,8 @@ constexpr ShortLine kShort4[] = {
     {1, 128, 5, 8, kHalf, 248},           {1, 64, 5, 8, kFloat, 240},           {1, 128, 9, 16, kHalf, 352},
     {1, 128, 9, 16, kBytes, 400},         {1, 32, 9, 32, kFloat, 100},          {1, 64, 9, kAllColumns, kFloat, 184},
     {65, 128, 9, 16, kFloat, 192, 300},   {65, 128, 17, 32, kFloat, 150},       {1, 64, 17, 32, kBytes, 432},
-    {1, 64, 17, kAllColumns, kAny, 600},  {65, 128, 17, kAllColumns, kHalf | kBytes, 352},
+    {1, 64, 17, kAllColumns, kAny, 600},  {65, 127, 17, kAllColumns, kHalf, 352},
+    {65, 128, 17, kAllColumns, kBytes, 352},
     // up to eight
     {513, 768, 1, 1, kHalf | kRagged, 600},  {513, 768, 1, 1, kBytes | kRagged, 416},  {513, 768, 3, 8, kBytes | kRagged, 640},
     {513, 768, 1, 1, kHalf | kFloat, 1024},  {513, 768, 1, 1, kBytes, 3072},    {769, 1024, 1, 1, kHalf | kFloat, 3072},
@@ -1531,6 +1532,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     const int small_tiles = p.b <= 32 ? 2 : 3;
     const bool small = tile_can && narrow8 && (asked && o.rows_per_lane ? o.rows_per_lane == 4 :
         runs >= 20 && pass_mib >= (row_groups * 8 > (int64_t)5 * p.cus && p.b >= 10 * small_tiles ? 48 : 112));
+    // (tiles of 32 columns or of 64, whatever is padding.  us, against tiles of 48 columns and 16 rows where those fitted better: 28672 x 8192 x 40 fp16 41.8 / 45.0, bf16 with
+    // scales 45.2 / 53.0, 14336 x 4096 x 33 14.8 / 18.0; 65 to 96 columns, two passes of 64 against two of 48: 28672 x 8192 x 80 69.7 / 92.2, 11008 x 2048 x 72 12.4 / 19.6,
+    // int8 28672 x 8192 x 72 50.2 / 58.0)
     const int64_t tall_passes = p.b <= 32 ? 1 : (p.b + 63) / 64;
     const bool tall = tile_can && !small && (asked && o.rows_per_lane ? o.rows_per_lane == 4 :
         row_groups * tall_passes * 8 > (int64_t)5 * p.cus ? !narrow8 || runs >= 8 || row_groups > 2 * p.cus : !narrow8 && pass_mib >= (int8 ? 112 : 80));
@@ -1559,9 +1563,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // (wavefronts that the rule for segments counts with; the streaming kernel's workgroups may have more)
     const auto waves = [&](int r) { return tile ? 8 : width == 2 && r == 4 ? 8 : 4; };
     // Few row groups and a long k: segments of it side by side, their sums added by a second launch, as long as a wavefront
-    // keeps 16 runs (tile kernel: a workgroup 20, since the second launch and the sums' trip to memory and back take 10 to
-    // 15 us; 12288 x 49152 x 64, 64 row groups: 228 us in one segment, 95 in four; 8192 x 10240 x 64 in segments of 20 runs
-    // 27 us, of 40 29; but 16384 x 4096 x 64 28 in segments of 16, 21 uncut, int8 21 against 14.5).  With fp32 activations a
+    // keeps 16 runs (tile kernel: a workgroup 20.  Uncut / two segments / four: 4096 x 14336 x 64 fp16 37.5 / 25.0 / 18.5 us, 8192 x 8192 x 64 24.3 / 19.9, bf16 with scales
+    // 26.4 / 20.3, 6144 x 6144 x 64 (24 runs each) 19.2 / 15.2, 8192 x 5120 x 64 (20) 16.7 / 15.3, 8192 x 4096 x 64 (16) 14.3 / 14.1, x 32 11.6 / 11.0; where there are
+    // more than half as many row groups as compute units 11008 x 4096 x 64 14.7 / 21.9).  With fp32 activations a
     // run takes three products and as much splitting, and fewer are enough: 448 x 12288 x 1 9.6 us uncut, 8.0 in two, 7.2 in four
     // segments of 6 runs a wavefront, 448 x 4096 x 1 4.9 uncut, 6.1 in two; 448 x 8192 x 16 16.0, 12.0 and 9.4, 448 x 4096 x 16 9.6,
     // 8.7 and 7.5, x 8 6.8, 7.1 and 6.6.
@@ -1573,9 +1577,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     };
     // Row tiles per wavefront: the work of the busiest compute unit, in row tiles for the streaming kernel, weighted by
     // what a row tile costs -- the fewer tiles share a load of activations, the more of it each carries (measured with
-    // 1, 4 / 8 and 16 columns) -- and in workgroups of 1, 2 and 3 tiles for the tile kernel (28672 x 8192 x 64 scaled: two
-    // rounds of one tile 73 us, one of two 53; 49152 x 12288 x 64: 135, 110 and 87; three scaled tiles do not fit the
-    // registers).
+    // 1, 4 / 8 and 16 columns) -- and in workgroups of 1, 2 and 3 tiles for the tile kernel (a round of one tile 15.2 us, of two 22, of three 32: 16384 x 4096 x 64 fp16 in one
+    // round of one tile 16.2, 28672 x 4096 x 64 in one, two and three tiles 29.5, 23.6 and 27.9, 40960 x 4096 x 64 45.3, 41.8 and 31.9, 49152 x 12288 x 64 127, 114 and 82, 28672 x 8192 x 64 bf16
+    // with scales 58.9 and 45.1; three scaled tiles do not fit the registers).
     const int tiles[2][3] = {{1, 2, 4}, {1, 2, 3}};
     double cost[4][3] = {{1.25, 2.0, 4.12}, {1.2, 2.0, 3.8}, {1.55, 2.4, 4.0}, {1.0, 1.35, 1.9}};
     // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, or is one column under four workgroups a
