@@ -1585,12 +1585,12 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // (a column or a few of 16 bits are a small load: one row tile costs its share of two where the stream is short, or is one column under four workgroups a
     // compute unit, and more the longer it is and the more columns it has.  us, one tile / two; where two workgroups of one tile do the work of one of two:
     // 16384 x 3840 x 1 fp16 9.4 / 9.6, 7043 x 2176 x 3 with scales (two, or one of two) 4.2 / 4.0, 8192 x 8192 x 1 bf16 8.4 / 8.7, 24089 x 5888 x 1 with scales 14.7 / 14.0, 13160 x 8192 x 2 with scales 13.2 / 12.6, 24089 x 4860 x 4 bf16
-    // 15.0 / 13.8, 24089 x 2944 x 4 fp16 with scales 9.9 / 8.8, 40720 x 1280 x 4 7.8 / 7.2, 23552 x 1280 x 3 5.7 / 5.3, but 12759 x 896 x 4 bf16 (3.1 tiles of one a compute unit) 3.6 / 3.9, 16384 x 8192 x 4 bf16 with scales 16.2 / 14.3; where they do not: 20480 x 8192 x 1 15.7 / 16.9, 11008 x 4096 x 4 bf16 7.1 / 8.0, 33280 x 8192 x 4 bf16
+    // 15.0 / 13.8, 24089 x 2944 x 4 fp16 with scales 9.9 / 8.8, 40720 x 1280 x 4 7.8 / 7.2, 23552 x 1280 x 3 5.7 / 5.3, 40720 x 2048 x 1 10.2 / 9.5, but 12759 x 896 x 4 bf16 (3.1 tiles of one a compute unit) 3.6 / 3.9, 16384 x 8192 x 4 bf16 with scales 16.2 / 14.3; where they do not: 20480 x 8192 x 1 15.7 / 16.9, 11008 x 4096 x 4 bf16 7.1 / 8.0, 33280 x 8192 x 4 bf16
     // 1.06 : 1.  Over 210 problems with 6056 to 33280 rows and 1, 2 and 4 columns the choice takes 0.6 percent more than the faster of
     // the two in the mean, 9 at most.
     // fp32, two tiles / four: 16384 x 8192 x 4 19.2 / 18.6, 33280 x 4096 x 16 38.0 / 34.3)
     if (width == 0 && !bytes && p.x_dtype != MSGEMM_F32 && !int8)
-        cost[0][0] = groups(1) <= 2 * p.cus && runs < 64 ? 1.05 : scaled && p.b > 1 && runs < 24 && groups(1) > 4 * p.cus ? 1.10 : runs < 24 || (p.b == 1 && runs < 72 && groups(1) <= 4 * p.cus) ? 0.98 : runs >= (p.b > 2 ? 48 : 96) ? 1.25 : 1.05;
+        cost[0][0] = groups(1) <= 2 * p.cus && runs < 64 ? 1.05 : scaled && runs < 24 && groups(1) > 4 * p.cus ? 1.10 : runs < 24 || (p.b == 1 && runs < 72 && groups(1) <= 4 * p.cus) ? 0.98 : runs >= (p.b > 2 ? 48 : 96) ? 1.25 : 1.05;
     if (p.x_dtype == MSGEMM_F32 && !bytes) cost[0][2] = 3.95, cost[2][2] = 3.8;
     double best = 0;
     int R = 1;
