@@ -1626,7 +1626,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     //   three and more: 11003 x 4098 x 1 fp16 4 x 8 7.5, 4 x 2 6.9; 11008 x 4096 x 4 bf16 8.4, 7.1; 20000 x 8192 x 4 int8 4 x 4 15.7, 4 x 2 16.9; 12093 x
     //   20842 x 1 int8 4 x 8 22.6, 4 x 4 23.3; 12288 x 4096 x 1 int8 4 x 4 6.5, 4 x 2 6.0, with columns that end inside a 16-byte piece 12288 x 3640 x 1 6.7, 7.1, 9000 x 5900 x 2 8.0, 8.3
     // Two row tiles: 6144 x 6144 x 3 fp16 4 x 4 5.6; in more workgroups 42240 x 6912 x 4 fp16 4 x 4 27.9, 8 x 2 27.5, 13160 x 24704 x 1 bf16 31.7, 30.8, 33792 x
-    // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
+    // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0; with scales, three runs a wavefront, 46335
+    // x 1408 x 1 fp16 4 x 4 7.9, 4 x 2 8.3, bf16 8.9, 8.9, but 46335 x 1024 x 1 7.3, 7.0, 24089 x 1792 x 1 6.5, 6.3.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
     // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 32760 x 9900 x 1 (78 runs) 27.1 / 28.4, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
     // 60.9 / 61.5; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
@@ -1656,7 +1657,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         if (p.x_dtype == MSGEMM_F16 && width == 2 && R == 2 && passes == 2 && per_cu == 1 && seg_runs >= 80) W = 4, D = 4;
         if (int8 && R == 2 && per_cu > 1 && seg_runs < 16) W = 4;
     } else if (R == 2) {
-        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80))) D = 4;
+        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80)) || (scaled && !f32 && seg_runs > 8 && seg_runs <= 12)) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
         const bool bf16 = p.x_dtype == MSGEMM_BF16, pieces = k % 16 == 0;

@@ -77,7 +77,7 @@ CHOICES = [
     (16384, 4096, 1, "f16", 0, "stream 1/4x2"), (8192, 8192, 1, "bf16", 128, "stream 1/4x4"), (16400, 4096, 1, "f16", 0, "stream 1/4x2"),
     (24089, 5888, 1, "f16", 128, "stream 2/8x2"), (13160, 8192, 2, "f16", 128, "stream 2/8x2"), (24089, 4860, 4, "bf16", 0, "stream 2/8x2"),
     (24089, 2944, 4, "bf16", 0, "stream 1/4x2"), (7043, 2176, 3, "f16", 128, "stream 2/4x4"), (24089, 2944, 4, "f16", 128, "stream 2/4x2"), (24089, 2944, 1, "f16", 128, "stream 2/4x2"), (24089, 2944, 1, "f16", 0, "stream 1/4x2"),
-    (33000, 2560, 2, "f16", 128, "stream 1/4x2"), (12759, 896, 4, "bf16", 128, "stream 1/4x2"), (40720, 1280, 4, "bf16", 256, "stream 2/4x2"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
+    (33000, 2560, 2, "f16", 128, "stream 1/4x2"), (12759, 896, 4, "bf16", 128, "stream 1/4x2"), (40720, 1280, 4, "bf16", 256, "stream 2/4x4"), (46335, 1024, 2, "f16", 128, "stream 2/4x2"), (46335, 1536, 2, "f16", 128, "stream 2/4x4"), (24089, 1664, 2, "f16", 128, "stream 2/4x2"), (6056, 8192, 2, "f16", 0, "stream 2/4x4"),
     # a workgroup per compute unit: sixteen wavefronts from 32 runs on, eight from 92 on and where an unscaled k is whole turns of their rings, four
     # beyond 160 (fp16 with scales and more than two columns: 108); fp32, and bf16 with scales up to 160 or in two columns, sixteen
     (4096, 14336, 2, "f16", 128, "stream 1/8x4"), (4096, 11520, 2, "f16", 128, "stream 1/16x2"), (4096, 11776, 1, "bf16", 0, "stream 1/8x4"), (4096, 11648, 1, "bf16", 0, "stream 1/16x2"),
