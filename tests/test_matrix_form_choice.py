@@ -111,7 +111,7 @@ CHOICES = [
     # four row tiles and 16 columns: four wavefronts from nine sixteenths of the compute units on (int8: seven eighths), but not in
     # three passes and more over a long k (bf16 with scales: two), nor for fewer columns with scales over a longer one
     (5120, 5120, 24, "bf16", 128, "stream 4/8x2"), (5120, 4992, 24, "bf16", 128, "stream 4/4x2"), (5120, 5120, 24, "bf16", 0, "stream 4/4x2"), (5120, 5120, 24, "f16", 128, "stream 4/4x2"),
-    (11776, 12800, 11, "f16", 128, "stream 4/8x2"), (11776, 12672, 11, "f16", 128, "stream 4/4x2"), (11776, 12800, 14, "f16", 128, "stream 4/4x2"), (11776, 12800, 11, "f16", 0, "stream 4/4x2"),
+    (11776, 7680, 11, "f16", 128, "stream 4/8x2"), (11776, 7552, 11, "f16", 128, "stream 4/4x2"), (11776, 12800, 12, "f16", 128, "stream 4/4x2"), (11776, 12800, 11, "f16", 0, "stream 4/4x2"),
     (143 * 64, 4096, 16, "f16", 128, "stream 4/8x2"), (144 * 64, 4096, 16, "f16", 128, "stream 4/4x2"), (223 * 64, 4096, 16, "i8", 0, "stream 4/8x2"),
     (224 * 64, 4096, 16, "i8", 0, "stream 4/4x2"),
     (8192, 4096, 32, "bf16", 0, "stream 4/4x2"), (4096, 4096, 64, "f16", 128, "stream 4/4x2"), (4096, 5376, 64, "f16", 128, "stream 4/8x2"),
