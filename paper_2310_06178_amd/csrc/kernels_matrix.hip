@@ -1377,7 +1377,7 @@ int launch_for_type(const Plan& p, const MatrixArgs& a, hipStream_t s)
         MSGEMM_CASE(2, 4, 4, 4)
     }
     if constexpr (sizeof(XT) == 1) {
-        MSGEMM_CASE(2, 4, 4, 2)
+        MSGEMM_CASE(2, 4, 4, 2) MSGEMM_CASE(2, 4, 4, 4) MSGEMM_CASE(1, 4, 4, 4)
     }
     MSGEMM_CASE(4, 4, 8, 2) MSGEMM_CASE(4, 4, 4, 2) MSGEMM_CASE(2, 4, 8, 2) MSGEMM_CASE(1, 4, 8, 2)
 #undef MSGEMM_CASE
@@ -1629,7 +1629,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // 1792 x 1 fp16 4 x 4 8.5, 8 x 2 8.4, 4 x 2 8.1, 33280 x 7424 x 3 fp32 4 x 4 35.9, 8 x 2 35.4, 4 x 2 35.0; with scales, three runs a wavefront, 46335
     // x 1408 x 1 fp16 4 x 4 7.9, 4 x 2 8.3, bf16 8.9, 8.9, but 46335 x 1024 x 1 7.3, 7.0, 24089 x 1792 x 1 6.5, 6.3.  int8, 4 x 4 / 8 x 2 / 4 x 2: 37725 x
     // 3640 x 1 14.3 / 19.0 / 16.3, 19847 x 6744 x 1 14.4 / 17.9 / 14.2, 37725 x 6744 x 4 23.9 / 26.9 / 26.2, 32760 x 9900 x 1 (78 runs) 27.1 / 28.4, 26000 x 10240 x 4 25.2 / 24.6 / 26.1, 26000 x 20842 x 8 62.2 /
-    // 60.9 / 61.5; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
+    // 60.9 / 61.5; a k that is no whole number of runs 22868 x 18240 x 4 36.3 / 38.2; two workgroups, 14848 x 10240 x 1 13.7 / 14.3 / 13.7, 14848 x 40192 x 1 48.0 / 50.4 / 48.1.
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
     // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.5, 4 x 2 9.0, 11264 x 4096 x 16 9.1, 8.7, 8960 x 4096 x 16 (140 workgroups) 8.8, 8.5, 11264 x 8192 x 16
     // 14.8, 14.6, 9216 x 8192 x 16 level, but 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; int8 10240 x 4096 x 16 7.2, 7.3, 13312 x
@@ -1638,7 +1638,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // 28.5, bf16 28.3, 29.9, 11008 x 9216 x 9 16.2, 17.4, 9472 x 7680 x 11
     // 14.8, 15.1, x 13 level, 15907 x 4608 x 11 level; fp16 in two passes of two row tiles 4 x 4 / 8 x 2: 4096 x 14336 x 20 14.2 / 14.9, 3584 x 18944 x 22 17.7 / 18.7, x 24 with scales 17.4 / 18.0, but 4096 x 6144 x 22 7.8 / 7.3, bf16
     // with scales 4096 x 14336 x 22 16.3 / 14.6; int8 in two row tiles over a short k 4 x 2 / 8 x 2: 9984 x
-    // 1536 x 24 5.5 / 6.5, 18176 x 1536 x 16 6.0 / 6.4, but 18176 x 3072 x 16 9.4 / 8.9; 14336 x 4096 x 8 in
+    // 1536 x 24 5.5 / 6.5, 18176 x 1536 x 16 6.0 / 6.4, but 18176 x 3072 x 16 9.4 / 8.9; int8 over a long k
+    // that is no whole number of runs (columns of X then start anywhere in a line of the caches) 4 x 4 / 8 x 2: 4000 x 11428 x 16 11.8 / 12.5, 5608 x 11426 x 9 13.7 / 14.3, 2000 x 17326 x 32 16.3 / 17.0, but 4000 x
+    // 5620 x 16 7.6 / 7.2, 5608 x 17408 x 16 16.7 / 16.5; 14336 x 4096 x 8 in
     // two row tiles, two workgroups a compute unit, 9.0, 8.55; fp32, whose operands of eight
     // wavefronts take 96 KiB of LDS, 4096 x 4096 x 8 4 x 2 7.2, 8 x 2 6.4, 38400 x 3840 x 6 29.9, 36.5.
     const int64_t per_cu = (groups(R) * passes * segments + p.cus - 1) / p.cus, seg_runs = runs / segments;
@@ -1657,8 +1659,9 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
         W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : (width == 2 ? R == 4 && seg_runs >= 16 && full : R == 2 && per_cu > 1) ? 4 : 8;
         if (p.x_dtype == MSGEMM_F16 && width == 2 && R == 2 && passes == 2 && per_cu == 1 && seg_runs >= 80) W = 4, D = 4;
         if (int8 && R == 2 && per_cu > 1 && seg_runs < 16) W = 4;
+        if (int8 && width == 2 && R < 4 && k % kRun != 0 && seg_runs >= 80) W = 4, D = 4;
     } else if (R == 2) {
-        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80)) || (scaled && !f32 && seg_runs > 8 && seg_runs <= 12)) D = 4;
+        if (per_cu == 1 || (int8 && (per_cu == 2 || seg_runs < 80 || k % kRun != 0)) || (scaled && !f32 && seg_runs > 8 && seg_runs <= 12)) D = 4;
         else if (!f32 && seg_runs >= 28) W = 8;
     } else if (R == 1) {
         const bool bf16 = p.x_dtype == MSGEMM_BF16, pieces = k % 16 == 0;

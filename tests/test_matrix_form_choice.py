@@ -117,6 +117,9 @@ CHOICES = [
     (8192, 4096, 32, "bf16", 0, "stream 4/4x2"), (4096, 4096, 64, "f16", 128, "stream 4/4x2"), (4096, 5376, 64, "f16", 128, "stream 4/8x2"),
     # fp16 in two passes of two row tiles: four wavefronts with rings of four from 80 runs on
     (4096, 14336, 20, "f16", 0, "stream 2/4x4"), (4096, 10240, 32, "f16", 128, "stream 2/4x4"), (4096, 10112, 32, "f16", 128, "stream 2/8x2"), (4096, 14336, 20, "bf16", 0, "stream 2/8x2"),
+    # int8 over a long k that is no whole number of runs: four wavefronts with rings of four
+    (4000, 11428, 16, "i8", 0, "stream 1/4x4"), (4000, 11392, 16, "i8", 0, "stream 1/8x2"), (4000, 10000, 16, "i8", 0, "stream 1/8x2"), (5608, 11426, 9, "i8", 0, "stream 2/4x4"),
+    (22868, 18240, 4, "i8", 0, "stream 2/4x4"), (22868, 18304, 4, "i8", 0, "stream 2/8x2"),
     # int8 in two row tiles, two workgroups a compute unit and more: four wavefronts under 16 runs
     (9984, 1536, 24, "i8", 0, "stream 2/4x2"), (18176, 1920, 16, "i8", 0, "stream 2/4x2"), (18176, 2048, 16, "i8", 0, "stream 2/8x2"),
     # int8, 49 columns and more under few rows: tiles from 112 MiB of codes in all passes on

@@ -42,7 +42,10 @@ def _cases():
             # more than one workgroup a compute unit (256 of them): segments make them out of few rows
             segments = dict(panels_per_workgroup=2, batched_segments=8)
             if x == "i8":
-                add(2070, 8 * 80, 1, x, scaled, **segments)
+                if not scaled:                           # ... a k of whole runs, and a long one that is none
+                    cases.append((2070, 8 * 80 * RUN, 1, x, 0, "int4", dict(segments, batched_form=3), 0))
+                for r in (1, 2):
+                    add(70, 81, 13, x, scaled, panels_per_workgroup=r, batched_segments=1)
                 add(1050, 8 * 3, 13, x, scaled, **segments)
             else:
                 add(1050, 8 * 6, 3, x, scaled, **segments)
