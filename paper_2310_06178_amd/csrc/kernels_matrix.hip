@@ -1633,7 +1633,8 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     // Wider operands: 8192 x 8192 x 16 int8 4 x 4 8.8, 8 x 2 8.3; 28672 x 4096 x 6 fp16 (four row tiles) 4 x 3 14.4, 8 x 2 13.2; four row tiles and 16
     // columns, whose operands fill the LDS ports, 14336 x 4096 x 16 8 x 2 9.5, 4 x 2 9.0, 11264 x 4096 x 16 9.1, 8.7, 8960 x 4096 x 16 (140 workgroups) 8.8, 8.5, 11264 x 8192 x 16
     // 14.8, 14.6, 9216 x 8192 x 16 level, but 4107 x 908 x 32 5.0, 5.3, and 8679 x 8064 x 16 bf16, for half the compute units, 14.5, 15.5; int8 10240 x 4096 x 16 7.2, 7.3, 13312 x
-    // 4096 x 16 7.6, 7.7, level at 14336; in passes 8192 x 4096 x 32 8.7, 8.3, 4096 x 4096 x 64 8.3, 8.2, but three and more over a long k 4096 x 5376 x 64 9.5, 9.8, 5120 x 8192 x 40
+    // 4096 x 16 7.6, 7.7, level at 14336, 26000 x 3072 x 16 12.3, 11.1, in passes 8192 x 8192 x 24 11.6, 10.3, but where k is no
+    // whole number of runs 7970 x 2720 x 32 8.3, 9.0, 16000 x 2720 x 16 8.4, 9.2, 8192 x 3000 x 20 7.35, 8.2 (two workgroups a compute unit, 26000 x 3000 x 16 15.1, 13.6); 16 bits in passes 8192 x 4096 x 32 8.7, 8.3, 4096 x 4096 x 64 8.3, 8.2, but three and more over a long k 4096 x 5376 x 64 9.5, 9.8, 5120 x 8192 x 40
     // 12.4, 12.7, two with bf16 and scales 5120 x 14336 x 24 20.0, 22.1, 6144 x 5120 x 24 10.0, 10.2 (but 8192 x 4096 x 32 9.3, 9.0), or fewer columns with scales over a long k 11776 x 17152 x 11 fp16 27.2,
     // 28.5, bf16 28.3, 29.9, 11008 x 9216 x 9 16.2, 17.4, 9472 x 7680 x 11
     // 14.8, 15.1, x 13 level, 15907 x 4608 x 11 level; fp16 in two passes of two row tiles 4 x 4 / 8 x 2: 4096 x 14336 x 20 14.2 / 14.9, 3584 x 18944 x 22 17.7 / 18.7, x 24 with scales 17.4 / 18.0, but 4096 x 6144 x 22 7.8 / 7.3, bf16
@@ -1655,7 +1656,7 @@ bool matrix_choose_shape(Plan& p, int requested_variant, bool anyway)
     } else if (!compact) {
         const bool bf16_scales = scaled && p.x_dtype == MSGEMM_BF16, part = scaled && p.b % 16 != 0 && p.b % 16 < 12;
         const int64_t end = passes > 2 || (passes == 2 && bf16_scales) ? 40 : part ? (passes == 1 ? 60 : 100) : runs + 1;
-        const bool full = groups(R) * passes * 16 >= (int8 ? 14 : 9) * p.cus && seg_runs < end;
+        const bool full = groups(R) * passes * 16 >= (int8 ? 14 : 9) * p.cus && seg_runs < end && !(int8 && k % kRun != 0 && per_cu == 1);
         W = f32 ? (per_cu == 1 && seg_runs >= 16 ? 8 : 4) : (width == 2 ? R == 4 && seg_runs >= 16 && full : R == 2 && per_cu > 1) ? 4 : 8;
         if (p.x_dtype == MSGEMM_F16 && width == 2 && R == 2 && passes == 2 && per_cu == 1 && seg_runs >= 80) W = 4, D = 4;
         if (int8 && R == 2 && per_cu > 1 && seg_runs < 16) W = 4;

@@ -108,12 +108,12 @@ CHOICES = [
     (28672, 4096, 24, "i8", 0, "small 2/2"), (28672, 4096, 49, "i8", 0, "tile 2/2"), (27648, 10752, 50, "i8", 0, "small 2/4"), (27648, 8450, 64, "i8", 0, "small 2/4"),
     (27648, 8320, 64, "i8", 0, "tile 2/2"), (36864, 10752, 80, "i8", 0, "small 3/4"), (16384, 14336, 80, "i8", 0, "tile 2/2"), (49152, 10752, 100, "i8", 0, "tile 3/2"), (16384, 10752, 64, "i8", 0, "tile 2/2"), (16384, 20480, 64, "i8", 0, "small 2/4"),
     (28672, 2432, 24, "i8", 0, "tile 2/1"),
-    # four row tiles and 16 columns: four wavefronts from nine sixteenths of the compute units on (int8: seven eighths), but not in
+    # four row tiles and 16 columns: four wavefronts from nine sixteenths of the compute units on (int8: seven eighths; two workgroups each where k is no whole number of runs), but not in
     # three passes and more over a long k (bf16 with scales: two), nor for fewer columns with scales over a longer one
     (5120, 5120, 24, "bf16", 128, "stream 4/8x2"), (5120, 4992, 24, "bf16", 128, "stream 4/4x2"), (5120, 5120, 24, "bf16", 0, "stream 4/4x2"), (5120, 5120, 24, "f16", 128, "stream 4/4x2"),
     (11776, 7680, 11, "f16", 128, "stream 4/8x2"), (11776, 7552, 11, "f16", 128, "stream 4/4x2"), (11776, 12800, 12, "f16", 128, "stream 4/4x2"), (11776, 12800, 11, "f16", 0, "stream 4/4x2"),
     (143 * 64, 4096, 16, "f16", 128, "stream 4/8x2"), (144 * 64, 4096, 16, "f16", 128, "stream 4/4x2"), (223 * 64, 4096, 16, "i8", 0, "stream 4/8x2"),
-    (224 * 64, 4096, 16, "i8", 0, "stream 4/4x2"),
+    (224 * 64, 4096, 16, "i8", 0, "stream 4/4x2"), (26000, 8192, 16, "i8", 0, "stream 4/4x2"), (26000, 3000, 16, "i8", 0, "stream 4/4x2"), (7970, 2720, 32, "i8", 0, "stream 4/8x2"),
     (8192, 4096, 32, "bf16", 0, "stream 4/4x2"), (4096, 4096, 64, "f16", 128, "stream 4/4x2"), (4096, 5376, 64, "f16", 128, "stream 4/8x2"),
     # fp16 in two passes of two row tiles: four wavefronts with rings of four from 80 runs on
     (4096, 14336, 20, "f16", 0, "stream 2/4x4"), (4096, 10240, 32, "f16", 128, "stream 2/4x4"), (4096, 10112, 32, "f16", 128, "stream 2/8x2"), (4096, 14336, 20, "bf16", 0, "stream 2/8x2"),

@@ -64,7 +64,11 @@ def _cases():
                     add(70, 3, 12, x, scaled, panels_per_workgroup=r)
             if x != "f32":
                 add(70, 81, 20, x, scaled, panels_per_workgroup=2, rows_per_lane=8, batched_segments=1)     # two passes over a long k
-                add(3584, 17, 60, x, scaled, panels_per_workgroup=4, rows_per_lane=8)   # four passes that fill the compute units
+                # four passes that fill the compute units (int8: of a k of whole runs)
+                if x == "i8" and not scaled:
+                    cases.append((3584, 17 * RUN, 60, x, 0, "int4", dict(panels_per_workgroup=4, rows_per_lane=8, batched_form=3), 0))
+                else:
+                    add(3584, 17, 60, x, scaled, panels_per_workgroup=4, rows_per_lane=8)
     for weights in MAPS:
         for x in ("f16", "bf16", "f32"):
             for scaled in (False, True):
